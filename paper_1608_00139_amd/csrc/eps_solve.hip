@@ -46,10 +46,10 @@ constexpr int NB = 128;  // block size of the elimination
 // 4-slot LDS ring (global_load_lds, three slices in flight).  With cmode 1
 // or 2 the accumulators start from C (negated for cmode 1, and the result
 // negated back on the way out: both exact), so C is read once at the start of
-// the tile and D written once at the end.  Row tiles at or after
-// skip_tile are shifted down by skip_count, which leaves out the row tiles
-// skip_tile .. skip_tile + skip_count - 1 (the pivot rows of an elimination
-// step; skip_tile -1 = none).  D may alias C
+// the tile and D written once at the end.  Rows at or after skip_row are
+// shifted down by skip_rows, which leaves out the rows skip_row ..
+// skip_row + skip_rows - 1 (the pivot rows of an elimination step; skip_row
+// -1 = none; both multiples of 128).  D may alias C
 // (every element is read and written by the same lane); D may also alias B
 // when M = K = 128 and cmode = 0 (each workgroup reads its whole B column panel
 // before writing it).  A must not overlap D.
@@ -58,10 +58,10 @@ struct GemmArgs {
   const double* B; int64_t ldb;
   const double* C; int64_t ldc;
   double* D; int64_t ldd;
-  int M, N, K;      // M counts the rows computed (without the skipped tiles)
+  int M, N, K;      // M counts the rows computed (without the skipped ones)
   int cmode;
-  int skip_tile;
-  int skip_count = 1;
+  int skip_row = -1;
+  int skip_rows = 0;
 };
 
 // Output coordinate of accumulator element `item` of lane `lane` for
@@ -71,14 +71,20 @@ __device__ inline void f64_acc_coord(int lane, int item, int& r, int& c) {
   c = lane & 15;
 }
 
-// LDS of one slice: the A slice (128 rows x 16 doubles, 128-byte rows; the
+// LDS of one slice: the A slice (BM rows x 16 doubles, 128-byte rows; the
 // 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)) then the B slice
-// (16 k-rows x 128 doubles, 1 KB rows; chunk c of k-row k at c ^ 8 (k & 1)).
-// Either way the 32 lanes that one ds_read_b64 pass serves (two k values x
-// 16 rows or columns) hit 64 distinct banks.
-constexpr int kDgemmStages = 4;
-constexpr int kDgemmSliceBytes = 2 * 128 * 16 * 8;
-constexpr unsigned kDgemmLds = kDgemmStages * kDgemmSliceBytes;  // 128 KB: one update workgroup per CU
+// (16 k-rows x BN doubles; chunk c of k-row k at c ^ 8 (k & 1)).  Either way
+// the 32 lanes that one ds_read_b64 pass serves (two k values x 16 rows or
+// columns) hit 64 distinct banks.
+template <int BM, int BN, int STAGES>
+struct Dgemm {
+  static constexpr int WM = BM / 2, WN = BN / 2;  // four waves, 2 x 2
+  static constexpr int FM = WM / 16, FN = WN / 16;
+  static constexpr int kSlice = (BM + BN) * 128;
+  static constexpr unsigned kLds = STAGES * kSlice;
+  static constexpr int kA = BM / 32, kB = BN / 32;  // one-KB instructions per wave and slice
+  static_assert(kLds <= 160 * 1024 && BM % 32 == 0 && (BN == 64 || BN == 128), "tile");
+};
 
 // s_waitcnt with vmcnt = N and no wait on the other counters
 template <int N>
@@ -87,44 +93,62 @@ __device__ inline void dgemm_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// Waits until slice kt of nk has landed: at most the later slices' PS
+// instructions each (S - 2 slices at most, fewer at the end) are outstanding.
+template <int PS, int S>
+__device__ inline void dgemm_wait_slice(int later) {
+  if constexpr (S <= 2) {
+    dgemm_wait_vmcnt<0>();
+  } else {
+    if (later >= S - 2) dgemm_wait_vmcnt<PS*(S - 2)>();
+    else dgemm_wait_slice<PS, S - 1>(later);
+  }
+}
+
+template <int BM, int BN, int STAGES>
 __global__ void __launch_bounds__(256) k_dgemm(GemmArgs g) {
+  typedef Dgemm<BM, BN, STAGES> T;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int tiles_m = g.M / 128;
+  const int tiles_m = g.M / BM;
   // column-major walk over tiles keeps one B column panel hot across rows
-  int tm = blockIdx.x % tiles_m;
+  const int tm = blockIdx.x % tiles_m;
   const int tn = blockIdx.x / tiles_m;
-  if (g.skip_tile >= 0 && tm >= g.skip_tile) tm += g.skip_count;
-  const int m0 = tm * 128, n0 = tn * 128;
+  int m0 = tm * BM;
+  const int n0 = tn * BN;
+  if (g.skip_row >= 0 && m0 >= g.skip_row) m0 += g.skip_rows;
 
-  // Each wave issues 8 of a slice's 32 one-KB direct-to-LDS instructions:
-  // A instruction a = wave + 4 jj covers rows 8a .. 8a + 7 (lane l: row
-  // 8a + l / 8, LDS chunk l % 8), B instruction b = wave + 4 jj is k-row b
-  // (lane l: LDS chunk l).
-  const double* asrc[4];
-  const double* bsrc[4];
+  // Each wave issues its share of a slice's one-KB direct-to-LDS
+  // instructions: A instruction a = wave + 4 jj covers rows 8a .. 8a + 7
+  // (lane l: row 8a + l / 8, LDS chunk l % 8), B instruction b = wave + 4 jj
+  // covers 128 / BN k-rows (lane l: LDS chunk l of that run).
+  const double* asrc[T::kA];
+  const double* bsrc[T::kB];
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
-    const int a = wave + 4 * jj;
-    const int row = 8 * a + (lane >> 3);
+  for (int jj = 0; jj < T::kA; ++jj) {
+    const int row = 8 * (wave + 4 * jj) + (lane >> 3);
     asrc[jj] = g.A + (int64_t)(m0 + row) * g.lda + 2 * ((lane & 7) ^ ((row >> 1) & 7));
-    bsrc[jj] = g.B + (int64_t)a * g.ldb + n0 + 2 * (lane ^ (8 * (a & 1)));
   }
-  auto issue = [&](int kt) {
-    uint8_t* stage = lds + (kt % kDgemmStages) * kDgemmSliceBytes;
+#pragma unroll
+  for (int jj = 0; jj < T::kB; ++jj) {
+    const int q = (wave + 4 * jj) * 64 + lane, k = q / (BN / 2), ch = q % (BN / 2);
+    bsrc[jj] = g.B + (int64_t)k * g.ldb + n0 + 2 * (ch ^ (8 * (k & 1)));
+  }
+  auto issue = [&](int kt, int slot) {
+    uint8_t* stage = lds + slot * T::kSlice;
     const int k0 = kt * 16;
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
+    for (int jj = 0; jj < T::kA; ++jj)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc[jj] + k0),
                                        (__attribute__((address_space(3))) void*)(stage + (wave + 4 * jj) * 1024),
                                        16, 0, 0);
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(bsrc[jj] + (int64_t)k0 * g.ldb),
-                                       (__attribute__((address_space(3))) void*)(stage + 16384 + (wave + 4 * jj) * 1024),
-                                       16, 0, 0);
+    for (int jj = 0; jj < T::kB; ++jj)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(bsrc[jj] + (int64_t)k0 * g.ldb),
+          (__attribute__((address_space(3))) void*)(stage + BM * 128 + (wave + 4 * jj) * 1024), 16, 0, 0);
   };
 
   // fragment reads: lane (g4, r16) = (lane / 16, lane % 16) supplies
@@ -133,208 +157,269 @@ __global__ void __launch_bounds__(256) k_dgemm(GemmArgs g) {
   auto frags = [&](const uint8_t* st, int kk, double* af, double* bf) {
     const int k = kk + g4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = wm * 64 + i * 16 + r16;
+    for (int i = 0; i < T::FM; ++i) {
+      const int r = wm * T::WM + i * 16 + r16;
       af[i] = *(const double*)(st + r * 128 + (((k >> 1) ^ ((r >> 1) & 7)) << 4) + ((k & 1) << 3));
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = wn * 64 + j * 16 + r16;
-      bf[j] = *(const double*)(st + 16384 + k * 1024 + (((n >> 1) ^ (8 * (k & 1))) << 4) + ((n & 1) << 3));
+    for (int j = 0; j < T::FN; ++j) {
+      const int n = wn * T::WN + j * 16 + r16;
+      bf[j] = *(const double*)(st + BM * 128 + k * (BN * 8) + (((n >> 1) ^ (8 * (k & 1))) << 4) + ((n & 1) << 3));
     }
   };
 
   const int nk = g.K / 16;
 #pragma unroll
-  for (int s0 = 0; s0 < kDgemmStages - 1; ++s0)
-    if (s0 < nk) issue(s0);
+  for (int s0 = 0; s0 < STAGES - 1; ++s0)
+    if (s0 < nk) issue(s0, s0);
 
   // the accumulators from C while the first slices are in flight
-  v4d acc[4][4];
+  v4d acc[T::FM][T::FN];
   const double csgn = g.cmode == 1 ? -1.0 : 1.0;
   if (g.cmode) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < T::FN; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           int r, c;
           f64_acc_coord(lane, v, r, c);
-          acc[i][j][v] = csgn * g.C[(int64_t)(m0 + wm * 64 + i * 16 + r) * g.ldc + n0 + wn * 64 + j * 16 + c];
+          acc[i][j][v] = csgn * g.C[(int64_t)(m0 + wm * T::WM + i * 16 + r) * g.ldc + n0 + wn * T::WN + j * 16 + c];
         }
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+      for (int j = 0; j < T::FN; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
   }
 
+  int slot = 0;
   for (int kt = 0; kt < nk; ++kt) {
-    // slice kt has landed once at most the later slices' instructions
-    // (8 per slice) are outstanding; the barrier extends that to every wave
-    // and retires every read of slot (kt - 1) % 4, refilled below
-    const int later = (kt + 2 < nk ? kt + 2 : nk - 1) - kt;
-    if (later >= 2) dgemm_wait_vmcnt<16>();
-    else if (later == 1) dgemm_wait_vmcnt<8>();
-    else dgemm_wait_vmcnt<0>();
+    // slice kt has landed once at most the later slices' instructions are
+    // outstanding; the barrier extends that to every wave and retires every
+    // read of the slot before it in the ring, refilled below
+    dgemm_wait_slice<T::kA + T::kB, STAGES>(nk - 1 - kt);
     __builtin_amdgcn_s_barrier();
-    if (kt + kDgemmStages - 1 < nk) issue(kt + kDgemmStages - 1);
-    const uint8_t* st = lds + (kt % kDgemmStages) * kDgemmSliceBytes;
-    double af[2][4], bf[2][4];
+    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
+    const uint8_t* st = lds + slot * T::kSlice;
+    slot = slot + 1 == STAGES ? 0 : slot + 1;
+    double af[2][T::FM], bf[2][T::FN];
     frags(st, 0, af[0], bf[0]);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (q < 3) frags(st, 4 * (q + 1), af[(q + 1) & 1], bf[(q + 1) & 1]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < T::FN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[q & 1][i], bf[q & 1][j], acc[i][j], 0, 0, 0);
     }
   }
 
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < T::FN; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         int r, c;
         f64_acc_coord(lane, v, r, c);
-        const int64_t row = m0 + wm * 64 + i * 16 + r, col = n0 + wn * 64 + j * 16 + c;
+        const int64_t row = m0 + wm * T::WM + i * 16 + r, col = n0 + wn * T::WN + j * 16 + c;
         g.D[row * g.ldd + col] = csgn * acc[i][j][v];
       }
+}
+
+template <int BM, int BN, int STAGES>
+static hipError_t dgemm_launch(const GemmArgs& g, hipStream_t s) {
+  const int grid = (g.M / BM) * (g.N / BN);
+  hipLaunchKernelGGL((k_dgemm<BM, BN, STAGES>), dim3(grid), dim3(256), (Dgemm<BM, BN, STAGES>::kLds), s, g);
+  return hipGetLastError();
 }
 
 static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.M % 128 || g.N % 128 || g.K % 16) return hipErrorInvalidValue;
-  const int grid = (g.M / 128) * (g.N / 128);
-  hipLaunchKernelGGL(k_dgemm, dim3(grid), dim3(256), kDgemmLds, s, g);
-  return hipGetLastError();
+  return dgemm_launch<128, 128, 4>(g, s);
 }
 
 // ----------------------------------------------------------------- diagonal block inverse
 // In-place Gauss-Jordan inversion of the NB x NB block at W (ld), written to
-// Dinv (ld NB), with pivot blocks of PB rows and columns S = p .. p + PB - 1
-// (NB / PB steps of one barrier each).  1024 threads; thread t owns row t / 8
-// and the 16 contiguous columns 16 (t % 8) + m.  A step broadcasts the rows
-// and columns of S through LDS (double buffered); every thread inverts the
-// PB x PB pivot block P = a[S][S] itself (Gauss-Jordan in registers) and
-// updates its 16 entries:
-//   rows of S:   a[S][j] = P^-1 a[S][j]  (j not in S),   a[S][S] = P^-1
-//   other rows:  f = a[i][S] P^-1;  a[i][j] -= f a[S][j]  (j not in S),
-//                a[i][S] = -f
-// which is PB single-pivot steps done at once.  Signs: the block is a
-// strictly diagonally dominant M-matrix, so P^-1 >= 0 entrywise and, as for
-// single pivots, every update adds terms of one sign to each off-diagonal
-// entry (columns already pivoted hold entries >= 0, the others <= 0), so
-// zeros stay exact and nothing cancels.  The kernel runs beside the
-// trailing update (another stream): PB = 2 keeps it within the registers
-// that one resident update workgroup leaves free on a compute unit.
-constexpr int PB = 2;
-__global__ void __launch_bounds__(1024) k_block_inverse(const double* W, int64_t ld, double* Dinv) {
+// Dinv (ld NB), in NB / 16 steps of 16 x 16 pivot blocks on the matrix cores.
+// Eight waves own a column of eight 16 x 16 tiles each, kept in MFMA
+// accumulators for the whole kernel; a ninth wave inverts the pivot blocks.
+// Step k, with Q = a[k][k]^-1 and C = a[.][k] in LDS (C negated):
+//   Y = Q a[k][j]                       (the wave's own tile: the accumulator
+//                                        layout is the layout of operand B)
+//   a[i][j] += (-C[i]) Y  (i != k),  a[k][j] = Y
+// and in the pivot column j = k the same with a[i][k] = 0 and Y = Q, which
+// leaves -C[i] Q and Q.  Every wave updates its tile of row k + 1 first; the
+// owner of the next pivot block hands it to the ninth wave, which inverts it
+// while the others finish step k, so the serial chain (16 pivots in a block)
+// runs beside the products.
+// Bound by one compute unit's fp64 matrix cores: 2 NB^3 operations at 128 per
+// clock are 13.7 us.  Measured per 128 x 128 block (MI355X): 30.5 us, against
+// 175 us of the version before it, which took 64 steps of 2 x 2 pivots, each a
+// barrier, two dependent divisions and a rank-2 update on the vector units.
+// Signs: the block is a strictly diagonally dominant M-matrix, so every
+// inverse is >= 0 entrywise and, as for single pivots, every update adds
+// terms of one sign to each off-diagonal entry (columns already pivoted hold
+// entries >= 0, the others <= 0), so zeros stay exact and nothing cancels.
+constexpr int kInvThreads = 9 * 64;
+constexpr int kInvPitch = 17;  // doubles per 16-wide LDS row: operand reads and tile writes hit distinct banks
+
+// Lane n of each row of 16 lanes, to all lanes of that row.
+template <int N>
+__device__ inline double row_lane(double v) {
+  const int2 x = __builtin_bit_cast(int2, v);
+  int2 r;
+  r.x = __builtin_amdgcn_update_dpp(0, x.x, 0x150 + N, 0xf, 0xf, true);  // row_newbcast:N
+  r.y = __builtin_amdgcn_update_dpp(0, x.y, 0x150 + N, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, r);
+}
+
+// Row G (lanes 16 G .. 16 G + 15) of v, to all four rows of lanes.
+template <int G>
+__device__ inline int lane_row(int v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 h = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  const unsigned w = G < 2 ? h[0] : h[1];  // the half that holds row G, twice
+  const u32x2 q = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  return (int)((G & 1) ? q[1] : q[0]);
+}
+
+// 1 / x for the pivots, which lie in (1 / 65537, 1]: the hardware estimate and
+// two Newton steps (each squares the relative error, and the second one's
+// rounding is that of its last multiply-add).
+__device__ inline double pivot_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+}
+
+// Gauss-Jordan step P of the 16 x 16 inverse held by one wave: lane (r, g) =
+// (lane % 16, lane / 16) has columns 4 g .. 4 g + 3 of row r.
+template <int P>
+__device__ inline void inv16_step(double (&a)[4], int r, int g) {
+  constexpr int G = P >> 2, J = P & 3;
+  const int2 x = __builtin_bit_cast(int2, a[J]);
+  int2 cx;
+  cx.x = lane_row<G>(x.x);
+  cx.y = lane_row<G>(x.y);
+  const double col = __builtin_bit_cast(double, cx);  // a[r][P]
+  const double inv = pivot_rcp(row_lane<P>(col));
+  const double m = r == P ? inv : -col * inv;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const double pr = row_lane<P>(a[j]);  // a[P][4 g + j]
+    a[j] = __builtin_fma(m, pr, r == P ? 0.0 : a[j]);
+  }
+  if (g == G) a[J] = m;
+}
+
+template <int P>
+__device__ inline void inv16_steps(double (&a)[4], int r, int g) {
+  inv16_step<P>(a, r, g);
+  if constexpr (P < 15) inv16_steps<P + 1>(a, r, g);
+}
+
+__global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, int64_t ld, double* Dinv) {
   // the next panel's inverse shares its compute unit with a trailing-update
   // workgroup and is the longer chain in the late panels: its waves issue
   // first (0.2-0.3 ms per N = 8192 solve)
   __builtin_amdgcn_s_setprio(3);
-  __shared__ __attribute__((aligned(16))) double rowbuf[2][PB][NB];
-  __shared__ double colbuf[2][PB][NB];
-  const int t = threadIdx.x;
-  const int i = t >> 3, j0 = (t & 7) * 16;
-  double a[16];
+  __shared__ double cbuf[2][NB * kInvPitch];  // -C of steps k and k + 1
+  __shared__ double dbuf[16 * kInvPitch];     // pivot block to invert
+  __shared__ double qbuf[2][16 * kInvPitch];  // its inverse, steps k and k + 1
+  constexpr int NT = NB / 16;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  if (wave == NT) {  // the inverting wave
+    for (int k = 0; k < NT; ++k) {
+      __syncthreads();  // pivot block k is in dbuf
+      double a[4];
 #pragma unroll
-  for (int m = 0; m < 16; m += 2) {
-    const double2 v = *(const double2*)(W + (int64_t)i * ld + j0 + m);
-    a[m] = v.x;
-    a[m + 1] = v.y;
+      for (int j = 0; j < 4; ++j) a[j] = dbuf[c * kInvPitch + 4 * g + j];
+      inv16_steps<0>(a, c, g);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qbuf[k & 1][c * kInvPitch + 4 * g + j] = a[j];
+      __syncthreads();  // Q and C of step k are in LDS
+    }
+    return;
   }
-  for (int p = 0; p < NB; p += PB) {
-    const int b = (p / PB) & 1;
-    const bool owns_cols = (p >> 4) == (t & 7);  // columns p .. p + PB - 1 are among this thread's 16
-    const int pc = p & 15;                       // their position in a[]
-    const int r_in = i - p;                      // row of S held by this thread, if 0 <= r_in < PB
-    const bool in_s = r_in >= 0 && r_in < PB;
-    if (in_s) {
+  // tile i of this wave: element v of a lane is row 16 i + g + 4 v, column 16 wave + c
+  v4d acc[NT];
 #pragma unroll
-      for (int m = 0; m < 16; m += 2) *(double2*)&rowbuf[b][r_in][j0 + m] = make_double2(a[m], a[m + 1]);
-    }
-    if (owns_cols) {
+  for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int k = 0; k < PB; ++k) {
-        double v = a[0];
+    for (int v = 0; v < 4; ++v) acc[i][v] = W[(int64_t)(16 * i + g + 4 * v) * ld + 16 * wave + c];
+  // this wave's column as the panel -C of step k (k = wave)
+  auto publish_c = [&]() {
 #pragma unroll
-        for (int m = 1; m < 16; ++m) v = (m == pc + k) ? a[m] : v;
-        colbuf[b][k][i] = v;
-      }
-    }
-    __syncthreads();
-    // P^-1 by Gauss-Jordan without pivoting (every thread, same result)
-    double q[PB][PB];
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int r = 0; r < PB; ++r)
+      for (int v = 0; v < 4; ++v) cbuf[wave & 1][(16 * i + g + 4 * v) * kInvPitch + c] = -acc[i][v];
+  };
+  if (wave == 0) {
 #pragma unroll
-      for (int c = 0; c < PB; ++c) q[r][c] = rowbuf[b][r][p + c];
+    for (int v = 0; v < 4; ++v) dbuf[(g + 4 * v) * kInvPitch + c] = acc[0][v];
+  }
+  __syncthreads();
+  if (wave == 0) publish_c();
+  __syncthreads();
+  for (int k = 0; k < NT; ++k) {
+    const double* q = qbuf[k & 1];
+    const double* cb = cbuf[k & 1];
+    v4d y;
+    if (wave == k) {
 #pragma unroll
-    for (int k = 0; k < PB; ++k) {
-      const double inv = 1.0 / q[k][k];
+      for (int v = 0; v < 4; ++v) y[v] = q[(g + 4 * v) * kInvPitch + c];
 #pragma unroll
-      for (int r = 0; r < PB; ++r) {
-        if (r == k) continue;
-        const double f = q[r][k] * inv;
-#pragma unroll
-        for (int c = 0; c < PB; ++c)
-          if (c != k) q[r][c] = __builtin_fma(-f, q[k][c], q[r][c]);
-        q[r][k] = -f;
-      }
-#pragma unroll
-      for (int c = 0; c < PB; ++c) q[k][c] = (c == k) ? inv : q[k][c] * inv;
-    }
-    // the multipliers of this thread's row: f = a[i][S] P^-1 (other rows),
-    // or row r_in of P^-1 (rows of S)
-    double f[PB];
-    if (!in_s) {
-#pragma unroll
-      for (int c = 0; c < PB; ++c) f[c] = 0.0;
-#pragma unroll
-      for (int k = 0; k < PB; ++k) {
-        const double ck = colbuf[b][k][i];
-#pragma unroll
-        for (int c = 0; c < PB; ++c) f[c] = __builtin_fma(ck, q[k][c], f[c]);
-      }
+      for (int i = 0; i < NT; ++i) acc[i] = v4d{0.0, 0.0, 0.0, 0.0};
     } else {
+      v4d t = acc[0];
 #pragma unroll
-      for (int c = 0; c < PB; ++c) {
-        f[c] = q[0][c];
+      for (int i = 1; i < NT; ++i)
+        if (i == k) t = acc[i];
+      y = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int r = 1; r < PB; ++r) f[c] = (r == r_in) ? q[r][c] : f[c];
-      }
+      for (int v = 0; v < 4; ++v)
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(q[c * kInvPitch + 4 * v + g], t[v], y, 0, 0, 0);
     }
-    // other rows: a -= f a[S][.];  rows of S: a = f a[S][.] (sign and start differ)
-    const double sg = in_s ? 1.0 : -1.0;
-#pragma unroll
-    for (int m = 0; m < 16; m += 2) {
-      double2 acc = in_s ? make_double2(0.0, 0.0) : make_double2(a[m], a[m + 1]);
-#pragma unroll
-      for (int c = 0; c < PB; ++c) {
-        const double2 r = *(const double2*)&rowbuf[b][c][j0 + m];
-        acc.x = __builtin_fma(sg * f[c], r.x, acc.x);
-        acc.y = __builtin_fma(sg * f[c], r.y, acc.y);
+    auto update = [&](int i) {
+      if (i == k) {
+        acc[i] = y;
+        return;
       }
-      a[m] = acc.x;
-      a[m + 1] = acc.y;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(cb[(16 * i + c) * kInvPitch + 4 * v + g], y[v], acc[i], 0, 0, 0);
+    };
+    if (k + 1 < NT) {
+#pragma unroll
+      for (int i = 1; i < NT; ++i)
+        if (i == k + 1) {
+          update(i);
+          if (wave == i) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dbuf[(g + 4 * v) * kInvPitch + c] = acc[i][v];
+          }
+        }
+      __syncthreads();  // the next pivot block is ready
     }
-    if (owns_cols) {  // the columns of S: -f (other rows) or P^-1 (rows of S)
 #pragma unroll
-      for (int m = 0; m < 16; ++m)
-#pragma unroll
-        for (int c = 0; c < PB; ++c)
-          if (m == pc + c) a[m] = sg * f[c];
+    for (int i = 0; i < NT; ++i)
+      if (i != k + 1) update(i);
+    if (k + 1 < NT) {
+      if (wave == k + 1) publish_c();
+      __syncthreads();
     }
   }
 #pragma unroll
-  for (int m = 0; m < 16; m += 2) *(double2*)&Dinv[i * NB + j0 + m] = make_double2(a[m], a[m + 1]);
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Dinv[(16 * i + g + 4 * v) * NB + 16 * wave + c] = acc[i][v];
 }
 
 // ----------------------------------------------------------------- setup / copy / emit
@@ -391,7 +476,8 @@ __global__ void k_set_word(unsigned long long* p, unsigned long long v) { *p = v
 
 // ----------------------------------------------------------------- driver
 hipError_t eps_kernels_init() {
-  return hipFuncSetAttribute((const void*)k_dgemm, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDgemmLds);
+  return hipFuncSetAttribute((const void*)k_dgemm<128, 128, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)Dgemm<128, 128, 4>::kLds);
 }
 
 int64_t eps_padded_size(int64_t n) { return n <= 0 ? 0 : ((n + NB - 1) / NB) * NB; }
@@ -449,13 +535,13 @@ static hipError_t gj_blocks(double* V, int64_t Ns, int64_t ldv, double* Dinv, hi
   for (int k = 0; k < nblk; ++k) {
     const int64_t K0 = (int64_t)k * NB;
     const int cols = (int)(ldv - K0 - NB);
-    hipLaunchKernelGGL(k_block_inverse, dim3(1), dim3(1024), 0, s, (const double*)(V + K0 * ldv + K0), ldv, Dinv);
+    hipLaunchKernelGGL(k_block_inverse, dim3(1), dim3(kInvThreads), 0, s, (const double*)(V + K0 * ldv + K0), ldv, Dinv);
     EPS_CK(hipGetLastError(), "block inverse");
-    GemmArgs rp{Dinv, NB, V + K0 * ldv + K0 + NB, ldv, nullptr, 0, V + K0 * ldv + K0 + NB, ldv, NB, cols, NB, 0, -1};
+    GemmArgs rp{Dinv, NB, V + K0 * ldv + K0 + NB, ldv, nullptr, 0, V + K0 * ldv + K0 + NB, ldv, NB, cols, NB, 0};
     EPS_CK(dgemm(rp, s), "row panel product");
     if (nblk > 1) {
       GemmArgs up{V + K0, ldv, V + K0 * ldv + K0 + NB, ldv, V + K0 + NB, ldv, V + K0 + NB, ldv,
-                  (int)(Ns - NB), cols, NB, 1, k};
+                  (int)(Ns - NB), cols, NB, 1, k * NB, NB};
       EPS_CK(dgemm(up, s), "elimination update");
     }
   }
@@ -540,14 +626,13 @@ static hipError_t gj_eliminate(EpsWorkspace* ws, double* W, int64_t Ns, int64_t 
     const int64_t T0 = K0 + P;
     const int nT = (int)(ldw - T0);
     // Y = D^-1 W[p, T]
-    GemmArgs gy{Dp, 2 * P, W + K0 * ldw + T0, ldw, nullptr, 0, Y, ldw, P, nT, P, 0, -1};
+    GemmArgs gy{Dp, 2 * P, W + K0 * ldw + T0, ldw, nullptr, 0, Y, ldw, P, nT, P, 0};
     EPS_CK(dgemm(gy, s), "panel row product");
     const bool ahead = T0 < Ns;
     const int Pn = ahead ? (int)std::min<int64_t>(kPanel, Ns - T0) : 0;
     const int first = ahead ? Pn : nT;
     if (Ns > P) {
-      GemmArgs ua{W + K0, ldw, Y, ldw, W + T0, ldw, W + T0, ldw, (int)(Ns - P), first, P, 1, (int)(K0 / 128)};
-      ua.skip_count = P / 128;
+      GemmArgs ua{W + K0, ldw, Y, ldw, W + T0, ldw, W + T0, ldw, (int)(Ns - P), first, P, 1, (int)K0, P};
       EPS_CK(timed(ua), "elimination update");
     }
     if (ahead) {
@@ -557,8 +642,7 @@ static hipError_t gj_eliminate(EpsWorkspace* ws, double* W, int64_t Ns, int64_t 
       EPS_CK(hipEventRecord(ws->ev[1], ws->side), "event");
       if (nT > Pn) {
         GemmArgs ub{W + K0, ldw, Y + Pn, ldw, W + T0 + Pn, ldw, W + T0 + Pn, ldw, (int)(Ns - P), nT - Pn, P, 1,
-                    (int)(K0 / 128)};
-        ub.skip_count = P / 128;
+                    (int)K0, P};
         EPS_CK(timed(ub), "elimination update");
       }
     }
@@ -816,15 +900,15 @@ static hipError_t stein_doubling(int64_t Np, double* X, double* B, double* C, do
   while (!done && j < max_doublings) {
     // Bn = B B;  Cn = C C;  T = B X;  I = T C (into B's buffer, free once T
     // is formed);  X += I;  B <- Bn, C <- Cn (or B^T).
-    GemmArgs g1{B, Np, B, Np, nullptr, 0, Bn, Np, (int)Np, (int)Np, (int)Np, 0, -1};
+    GemmArgs g1{B, Np, B, Np, nullptr, 0, Bn, Np, (int)Np, (int)Np, (int)Np, 0};
     EPS_CK(dgemm(g1, s), "B B");
     if (!c_is_bt) {
-      GemmArgs g1c{C, Np, C, Np, nullptr, 0, Cn, Np, (int)Np, (int)Np, (int)Np, 0, -1};
+      GemmArgs g1c{C, Np, C, Np, nullptr, 0, Cn, Np, (int)Np, (int)Np, (int)Np, 0};
       EPS_CK(dgemm(g1c, s), "C C");
     }
-    GemmArgs g2{B, Np, X, Np, nullptr, 0, T, Np, (int)Np, (int)Np, (int)Np, 0, -1};
+    GemmArgs g2{B, Np, X, Np, nullptr, 0, T, Np, (int)Np, (int)Np, (int)Np, 0};
     EPS_CK(dgemm(g2, s), "B X");
-    GemmArgs g3{T, Np, C, Np, nullptr, 0, B, Np, (int)Np, (int)Np, (int)Np, 0, -1};
+    GemmArgs g3{T, Np, C, Np, nullptr, 0, B, Np, (int)Np, (int)Np, (int)Np, 0};
     EPS_CK(dgemm(g3, s), "T C");
     EPS_CK(hipMemsetAsync(d_counter, 0, 2 * sizeof(unsigned long long), s), "counter clear");
     hipLaunchKernelGGL(k_stein_accumulate, dim3(kElemGrid), dim3(256), 0, s, X, (const double*)B, (int64_t)Np * Np,
