@@ -41,9 +41,9 @@ constexpr int NB = 128;  // block size of the elimination
 
 // ----------------------------------------------------------------- fp64 MFMA GEMM
 // D = A * B (cmode 0), D = C - A * B (cmode 1) or D = C + A * B (cmode 2);
-// A: M x K, B: K x N, C/D: M x N, row-major.  128 x 128 output tiles, 4 waves
-// of 64 x 64 (v_mfma_f64_16x16x4f64), K slices of 16 fetched straight into a
-// 4-slot LDS ring (global_load_lds, three slices in flight).  With cmode 1
+// A: M x K, B: K x N, C/D: M x N, row-major.  BM x BN output tiles, 2 x 2
+// waves (v_mfma_f64_16x16x4f64), K slices of 16 fetched straight into an LDS
+// ring of STAGES slices (global_load_lds).  With cmode 1
 // or 2 the accumulators start from C (negated for cmode 1, and the result
 // negated back on the way out: both exact), so C is read once at the start of
 // the tile and D written once at the end.  Rows at or after skip_row are
@@ -237,10 +237,33 @@ static hipError_t dgemm_launch(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, int STAGES>
+static hipError_t dgemm_attr() {
+  return hipFuncSetAttribute((const void*)k_dgemm<BM, BN, STAGES>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)Dgemm<BM, BN, STAGES>::kLds);
+}
+
+// Tile rule, from the number t of 128 x 128 tiles (MI355X, 256 compute units;
+// two-slice rings of 64 KB, so that two workgroups share a compute unit and
+// one's barriers and tile ends are covered by the other's products):
+//  - t fills whole passes over the 256 compute units to 85%: 128 x 128.
+//    M = N = 8192, K = 512: 64.7 TFLOP/s (four-slice ring, one workgroup per
+//    compute unit: 51.9; 64 x 64 tiles: 60.7); M = N = K = 4096: 69.1 (64.2).
+//  - otherwise smaller tiles, whose last pass is shorter: 64 x 64 while they
+//    number more than 256 (M = N = K = 2560: 55.9 against 53.4 TFLOP/s),
+//    else 32 x 64 (1024: 46.1 against 16.0; M = N = 512, K = 128: 7.6 against
+//    22.5 us).  A 64 x 64 tile moves 16 KB into LDS for 1024 clocks of
+//    products, so small tiles stay bound by the products.
+// D aliasing B needs one row of tiles (128 rows, each workgroup reads its
+// whole B panel before it writes): 128 x 64.
 static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.M % 128 || g.N % 128 || g.K % 16) return hipErrorInvalidValue;
-  return dgemm_launch<128, 128, 4>(g, s);
+  if (g.D == g.B && g.cmode == 0) return g.M == 128 && g.K == 128 ? dgemm_launch<128, 64, 3>(g, s) : hipErrorInvalidValue;
+  const int64_t t = (int64_t)(g.M / 128) * (g.N / 128);
+  const int64_t slots = (t + 255) / 256 * 256;
+  if (t * 100 >= slots * 85) return dgemm_launch<128, 128, 2>(g, s);
+  return 4 * t > 256 ? dgemm_launch<64, 64, 3>(g, s) : dgemm_launch<32, 64, 4>(g, s);
 }
 
 // ----------------------------------------------------------------- diagonal block inverse
@@ -476,8 +499,11 @@ __global__ void k_set_word(unsigned long long* p, unsigned long long v) { *p = v
 
 // ----------------------------------------------------------------- driver
 hipError_t eps_kernels_init() {
-  return hipFuncSetAttribute((const void*)k_dgemm<128, 128, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)Dgemm<128, 128, 4>::kLds);
+  hipError_t e = dgemm_attr<128, 128, 2>();
+  if (e == hipSuccess) e = dgemm_attr<128, 64, 3>();
+  if (e == hipSuccess) e = dgemm_attr<64, 64, 3>();
+  if (e == hipSuccess) e = dgemm_attr<32, 64, 4>();
+  return e;
 }
 
 int64_t eps_padded_size(int64_t n) { return n <= 0 ? 0 : ((n + NB - 1) / NB) * NB; }
