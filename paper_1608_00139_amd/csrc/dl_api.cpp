@@ -970,7 +970,7 @@ int dl_sg_eps(dl_ctx* ctx, int64_t n, const uint8_t* P, int64_t ldp, double eps,
   int32_t dbl = 0;
   int64_t pos = 0;
   hipError_t e = dl::sg_eps_solve(&ctx->eps, ctx->budget, n, P, ldp, eps, S, lds, X, ldx, 64, (hipStream_t)stream,
-                                  &dbl, &pos, (unsigned long long*)(ctx->dscratch + 8), ctx->h_ring, &err);
+                                  &dbl, &pos, ctx->ring, ctx->h_ring, ctx->h_ring_dev, &err);
   if (e == hipErrorOutOfMemory) return fail(DL_ENOMEM, err);
   if (e == hipErrorNotReady) return fail(DL_ENOCONV, "doubling cap reached");
   if (e != hipSuccess) return fail(DL_EHIP, err + ": " + hipGetErrorString(e));
@@ -1043,7 +1043,7 @@ int dl_solve_two_sided(dl_ctx* ctx, int64_t n, const uint8_t* Q, int64_t ldq, co
   std::string err;
   int32_t dbl = 0;
   hipError_t e = dl::two_sided_solve(&ctx->eps, ctx->budget, n, Q, ldq, B, ldb, C, ldc, eps, R, ldr, X, ldx, nullptr, 0,
-                                     nullptr, 64, s, &dbl, (unsigned long long*)(ctx->dscratch + 8), ctx->h_ring,
+                                     nullptr, 64, s, &dbl, ctx->ring, ctx->h_ring, ctx->h_ring_dev,
                                      &err);
   if (e == hipErrorOutOfMemory) return fail(DL_ENOMEM, err);
   if (e == hipErrorNotReady) return fail(DL_ENOCONV, "doubling cap reached");

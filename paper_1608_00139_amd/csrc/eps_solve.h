@@ -58,12 +58,13 @@ hipError_t stacked_solve(EpsWorkspace* ws, size_t budget_left, const StackDesc& 
 // fp64; writes S = [X > 0] and optionally X.  Stops when a doubling adds no
 // positive entry and, if X_out is given, also changes no value.  *doublings
 // receives the number of doublings run, the last one confirming the fixpoint;
-// hipErrorNotReady if max_doublings ran out first.  d_counter / h_counter: two
-// device and two pinned host 64-bit words.
+// hipErrorNotReady if max_doublings ran out first.  counts: 2 (max_doublings +
+// 1) device words; h_counts and h_counts_dev: as many pinned host words and
+// their device mapping.
 hipError_t sg_eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const uint8_t* P, int64_t ldp, double eps,
                         uint8_t* S, int64_t lds, double* X_out, int64_t ldx, int max_doublings, hipStream_t s,
-                        int32_t* doublings, int64_t* positives, unsigned long long* d_counter,
-                        unsigned long long* h_counter, std::string* err);
+                        int32_t* doublings, int64_t* positives, unsigned long long* counts,
+                        unsigned long long* h_counts, unsigned long long* h_counts_dev, std::string* err);
 
 // Two-sided equation X = eps (Q + B X C) (Q, B, C 0/1 bytes with leading
 // dimensions; n x n) by the same doubling with B and C each scaled by
@@ -74,7 +75,7 @@ hipError_t sg_eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const u
 hipError_t two_sided_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const uint8_t* Q, int64_t ldq,
                            const uint8_t* B, int64_t ldb, const uint8_t* C, int64_t ldc, double eps, uint8_t* R,
                            int64_t ldr, double* X_out, int64_t ldx, int8_t* R8, int64_t ld8,
-                           unsigned long long* r8_count, int max_doublings, hipStream_t s, int32_t* doublings, unsigned long long* d_counter,
-                           unsigned long long* h_counter, std::string* err);
+                           unsigned long long* r8_count, int max_doublings, hipStream_t s, int32_t* doublings, unsigned long long* counts,
+                           unsigned long long* h_counts, unsigned long long* h_counts_dev, std::string* err);
 
 }  // namespace dl

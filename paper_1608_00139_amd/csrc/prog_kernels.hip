@@ -72,18 +72,32 @@ hipError_t launch_bytes_op(const int8_t* a, const int8_t* b, int ident, int comp
   return hipGetLastError();
 }
 
-// Largest column sum: each thread walks one column (consecutive threads take
-// consecutive columns, so every row read is coalesced).
-__global__ void __launch_bounds__(256) k_col_max(const uint8_t* A, int64_t lda, int n, int* out_max) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
+// Largest column sum.  A workgroup takes 64 columns, its sixteen waves every
+// sixteenth row of them (one 64-byte read per row).  Bound by the latency of
+// each wave's chain of row reads: n = 1024 5.7 us; with one thread per
+// column walking every row it took 243 us.
+__global__ void __launch_bounds__(1024) k_col_max(const uint8_t* A, int64_t lda, int n, int* out_max) {
+  __shared__ int red[16][64];
+  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + c;
   int s = 0;
-  for (int i = 0; i < n; ++i) s += A[(int64_t)i * lda + j] != 0;
-  atomicMax(out_max, s);
+  if (j < n) {
+#pragma unroll 8
+    for (int i = q; i < n; i += 16) s += A[(int64_t)i * lda + j] != 0;
+  }
+  red[q][c] = s;
+  __syncthreads();
+  if (q == 0) {
+#pragma unroll
+    for (int w = 1; w < 16; ++w) s += red[w][c];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s = max(s, __shfl_xor(s, off, 64));
+    if (c == 0 && s) atomicMax(out_max, s);
+  }
 }
 
 hipError_t launch_col_max(const uint8_t* A, int64_t lda, int n, int* out_max, hipStream_t s) {
-  hipLaunchKernelGGL(k_col_max, dim3((n + 255) / 256), dim3(256), 0, s, A, lda, n, out_max);
+  hipLaunchKernelGGL(k_col_max, dim3((n + 63) / 64), dim3(1024), 0, s, A, lda, n, out_max);
   return hipGetLastError();
 }
 

@@ -685,7 +685,7 @@ int Runner::run_layer(int L, int method) {
   int32_t dbl = 0;
   hipError_t e = two_sided_solve(&g->ctx->eps, g->ctx->budget, n, (const uint8_t*)Q.M, Np, (const uint8_t*)Bm.M, Np,
                                  (const uint8_t*)Cm.M, Np, eps, nullptr, 0, nullptr, 0, R.M, Np, nullptr, 64, s, &dbl,
-                                 (unsigned long long*)(g->ctx->dscratch + 8), g->ctx->h_ring, &err);
+                                 g->ctx->ring, g->ctx->h_ring, g->ctx->h_ring_dev, &err);
   if (e == hipErrorOutOfMemory) return perr(DL_ENOMEM, err);
   if (e == hipErrorNotReady) return perr(DL_ENOCONV, "doubling cap reached");
   if (e != hipSuccess) return perr(DL_EHIP, err + ": " + hipGetErrorString(e));
