@@ -58,6 +58,25 @@ struct NTParams {
   int tiles_m, tiles_n; // grid in tiles
 };
 
+// Early exit of the element-wise kernels of a series: the test every product
+// launch makes (step_is_done).  done() is true when the fixpoint was reached
+// before step `step`; the first launch that sees the repeat records it.
+// conv null: never.
+struct StepGate {
+  const unsigned long long* ones = nullptr;
+  int* conv = nullptr;
+  int step = 0;
+  __device__ bool done() const {
+    if (!conv) return false;
+    if (*(volatile const int*)conv < step) return true;
+    if (step < 2 || *(volatile const unsigned long long*)(ones + (step - 1) % kRing) !=
+                        *(volatile const unsigned long long*)(ones + (step - 2) % kRing))
+      return false;
+    if (threadIdx.x == 0) atomicMin(conv, step - 1);
+    return true;
+  }
+};
+
 // One request's product in a grouped (serving) launch: T x T output tiles
 // of an Np x Np int8 product, Np a multiple of T.
 struct GroupDesc {
@@ -211,7 +230,7 @@ hipError_t launch_col_max(const uint8_t* A, int64_t lda, int n, int* out_max, hi
 // `complement` is set; int8 0/1 Np x Np operands (a, b, out, outT may be null;
 // out may alias a or b).  Adds the ones of the result to *cnt if cnt is set.
 hipError_t launch_bytes_op(const int8_t* a, const int8_t* b, int ident, int complement, int n, int Np, int8_t* out,
-                           int8_t* outT, unsigned long long* cnt, hipStream_t s);
+                           int8_t* outT, unsigned long long* cnt, hipStream_t s, const StepGate& gate = StepGate());
 // Sets byte (i, j) of M (and of M2, and byte (j, i) of MT, when not null) for
 // every edge (i, j) of the device list edges[2 m] with 0 <= i, j < n; adds
 // the number of distinct edges to *ones.  The matrices must be zeroed.

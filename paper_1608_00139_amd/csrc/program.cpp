@@ -211,7 +211,7 @@ struct dl_program {
   std::vector<Mat> val, comp;
   std::vector<void*> keep;  // allocations holding results
   size_t bytes = 0;
-  unsigned long long* dcnt = nullptr;  // device counters
+  unsigned long long* dcnt = nullptr;  // device counter of dl_program_fetch
   unsigned long long* hcnt = nullptr;  // pinned mirror
 };
 
@@ -366,6 +366,7 @@ struct Runner {
   TileCfg tc;
   std::vector<void*> temps;  // freed after each layer
   std::vector<EventPair> evs;  // product launches, when the context times kernels
+  std::vector<int64_t> ev_step;  // their steps (0: not of a series)
 
   int alloc(int8_t** p, bool keep) {
     const size_t b = (size_t)Np * Np;
@@ -403,8 +404,29 @@ struct Runner {
     }
   }
 
-  // out = [add + X Y^T != 0] (+ I), int8; counts into *cnt when set.
-  int nt(const int8_t* X, const int8_t* Y, const int8_t* add, int8_t* out, int8_t* outT, unsigned long long* cnt) {
+  // The context's ring of model sizes and convergence step (those of its
+  // first fixpoint slot): sizes are summed over a layer's heads.
+  unsigned long long* ring() const { return g->ctx->ring; }
+  int* conv() const { return (int*)(g->ctx->ring + kRing); }
+
+  // Waits for the first `words` words of the ring (polling: a blocking wait
+  // adds the thread's wake-up).
+  int read_ring(size_t words) {
+    hipEvent_t& ev = g->ctx->slot_ev[0];
+    if (!ev) P_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    P_HIP(launch_publish(ring(), g->ctx->h_ring_dev, (int)words, s));
+    P_HIP(hipEventRecord(ev, s));
+    hipError_t e;
+    while ((e = hipEventQuery(ev)) == hipErrorNotReady) {
+    }
+    P_HIP(e);
+    return DL_OK;
+  }
+
+  // out = [add + X Y^T != 0] (+ I), int8.  step > 0: a product of that step of
+  // the layer's series (it returns at once past the fixpoint), counting into
+  // the step's model size when `count` is set.
+  int nt(const int8_t* X, const int8_t* Y, const int8_t* add, int8_t* out, int8_t* outT, int64_t step, bool count) {
     NTParams p{};
     p.X = X;
     p.Y = Y;
@@ -415,11 +437,11 @@ struct Runner {
     p.n_valid = (int)n;
     p.out = out;
     p.outT = outT;
-    p.ones = cnt;
-    p.count = cnt ? 1 : 0;
-    p.conv = nullptr;
-    p.step = 0;
-    p.check = 0;
+    p.ones = ring();
+    p.count = count ? 1 : 0;
+    p.conv = step > 0 ? conv() : nullptr;
+    p.step = (int)step;
+    p.check = 1;
     p.tiles_m = (int)(Np / tc.bm);
     p.tiles_n = (int)(Np / tc.bn);
     EventPair ev{nullptr, nullptr};
@@ -429,8 +451,25 @@ struct Runner {
     if (ev.a && ev.b) {
       (void)hipEventRecord(ev.b, s);
       evs.push_back(ev);
+      ev_step.push_back(step);
     }
     return DL_OK;
+  }
+  // Drops the events of the current layer's products past step k (launches
+  // that returned at once).
+  void drop_events(size_t first, int64_t k) {
+    size_t w = first;
+    for (size_t i = first; i < evs.size(); ++i) {
+      if (ev_step[i] > k) {
+        (void)hipEventDestroy(evs[i].a);
+        (void)hipEventDestroy(evs[i].b);
+        continue;
+      }
+      evs[w] = evs[i];
+      ev_step[w++] = ev_step[i];
+    }
+    evs.resize(w);
+    ev_step.resize(w);
   }
   // Adds the recorded product launches to the context's class-0 statistics
   // (after the stream has been synchronised) and frees the events.
@@ -445,6 +484,7 @@ struct Runner {
       (void)hipEventDestroy(e.b);
     }
     evs.clear();
+    ev_step.clear();
   }
 
   Mat view(const Factor& f) {
@@ -475,7 +515,7 @@ struct Runner {
       return DL_OK;
     }
     P_RC(alloc_mat(out, false));
-    return nt(L.M, R.T, nullptr, out->M, out->T, nullptr);
+    return nt(L.M, R.T, nullptr, out->M, out->T, 0, false);
   }
 
   Mat transposed(const Mat& m) {
@@ -524,28 +564,29 @@ int Runner::run_layer(int L, int method) {
   const std::vector<int>& heads = g->layers[L];
   const int M = (int)heads.size();
   auto local = [&](int p) { return (int)(std::find(heads.begin(), heads.end(), p) - heads.begin()); };
-  // constant parts A_h (both orientations) and the recursive terms
+  // constant parts A_h (both orientations; their sizes summed into ring
+  // entry 1) and the recursive terms
+  P_HIP(launch_ring_clear(ring(), conv(), 0, kRing, 1, s));
   std::vector<Mat> A(M);
   std::vector<const Term*> rec;
-  for (int h = 0; h < M; ++h) {
-    P_RC(alloc_mat(&A[h], false));
-    P_HIP(hipMemsetAsync(A[h].M, 0, (size_t)Np * Np, s));
-  }
+  std::vector<std::vector<const Term*>> consts(M);
   for (const Term& t : g->terms) {
     if (g->layer_of[t.head] != L) continue;
-    if (t.rec >= 0) {
+    if (t.rec >= 0)
       rec.push_back(&t);
-      continue;
-    }
-    Mat c;
-    P_RC(product(t.factors, 0, t.factors.size(), &c));
-    const int h = local(t.head);
-    P_HIP(launch_bytes_op(A[h].M, c.ident ? nullptr : c.M, c.ident ? 1 : 0, 0, (int)n, (int)Np, A[h].M, nullptr,
-                          nullptr, s));
+    else
+      consts[local(t.head)].push_back(&t);
   }
-  P_HIP(hipMemsetAsync(g->dcnt, 0, (size_t)M * sizeof(unsigned long long), s));
-  for (int h = 0; h < M; ++h)
-    P_HIP(launch_bytes_op(A[h].M, nullptr, 0, 0, (int)n, (int)Np, nullptr, A[h].T, g->dcnt + h, s));
+  for (int h = 0; h < M; ++h) {
+    P_RC(alloc_mat(&A[h], false));
+    for (size_t i = 0; i < std::max<size_t>(1, consts[h].size()); ++i) {
+      Mat c;  // no constant term: the empty relation
+      if (i < consts[h].size()) P_RC(product(consts[h][i]->factors, 0, consts[h][i]->factors.size(), &c));
+      const bool last = i + 1 >= consts[h].size();
+      P_HIP(launch_bytes_op(i ? A[h].M : nullptr, c.ident ? nullptr : c.M, c.ident ? 1 : 0, 0, (int)n, (int)Np, A[h].M,
+                            last ? A[h].T : nullptr, last ? ring() + 1 : nullptr, s));
+    }
+  }
 
   // form of the layer
   int form = F_GENERAL;
@@ -575,12 +616,9 @@ int Runner::run_layer(int L, int method) {
     }
     // the series R^(1) = A, R^(2) = A: the confirming application is the
     // second one unless A is empty
-    P_HIP(hipMemcpyAsync(g->hcnt, g->dcnt, (size_t)M * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    P_HIP(hipStreamSynchronize(s));
-    unsigned long long ones = 0;
-    for (int h = 0; h < M; ++h) ones += g->hcnt[h];
+    P_RC(read_ring(2));
     g->method_used[L] = DL_EVAL_ITERATION;
-    g->iters[L] = ones ? 2 : 1;
+    g->iters[L] = g->ctx->h_ring[1] ? 2 : 1;
     return DL_OK;
   }
   if (method == DL_EVAL_ITERATION || form == F_GENERAL) {
@@ -715,74 +753,77 @@ int Runner::iterate(int L, const std::vector<int>& heads, const std::vector<Mat>
     o.trans = t->factors[t->rec].trans;
     ops[local(t->head)].push_back(o);
   }
-  std::vector<Mat> cur(M), nxt(M);
-  for (int h = 0; h < M; ++h) {
-    P_RC(alloc_mat(&cur[h], false));
-    P_RC(alloc_mat(&nxt[h], false));
-  }
+  // R^(k) in buf[h][k % 2]; R^(1) = A, whose size is in the ring already
+  std::vector<Mat> buf[2];
+  buf[0].resize(M);
+  buf[1] = A;
+  for (int h = 0; h < M; ++h) P_RC(alloc_mat(&buf[0][h], false));
   int8_t *acc[2], *tmp;
   P_RC(alloc(&acc[0], false));
   P_RC(alloc(&acc[1], false));
   P_RC(alloc(&tmp, false));
-  // R^(1) = A
-  P_HIP(hipMemsetAsync(g->dcnt, 0, (size_t)M * sizeof(unsigned long long), s));
-  for (int h = 0; h < M; ++h)
-    P_HIP(launch_bytes_op(A[h].M, nullptr, 0, 0, (int)n, (int)Np, cur[h].M, cur[h].T, g->dcnt + h, s));
-  auto total = [&](int64_t* t) -> int {
-    P_HIP(hipMemcpyAsync(g->hcnt, g->dcnt, (size_t)M * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    P_HIP(hipStreamSynchronize(s));
-    int64_t sum = 0;
-    for (int h = 0; h < M; ++h) sum += (int64_t)g->hcnt[h];
-    *t = sum;
-    return DL_OK;
-  };
-  int64_t prev = 0, now = 0;
-  P_RC(total(&now));
-  int k = 1;
-  // every step before the repeat adds at least one of the M n^2 facts
-  const int64_t cap = (int64_t)M * n * n + 2;
-  while (now != prev && k < cap) {
-    prev = now;
-    ++k;
-    P_HIP(hipMemsetAsync(g->dcnt, 0, (size_t)M * sizeof(unsigned long long), s));
-    for (int h = 0; h < M; ++h) {
-      // the head's current iterate stands in for its non-recursive part A[h]:
-      // R^(k) = A + F(R^(k-1)) lies inside A + F(R^(k)) (F monotone, the
-      // iterates grow) and contains A, so A + F(R^(k)) = R^(k) + F(R^(k));
-      // for self-recursive terms it is also the product's left operand
-      const int8_t* addp = cur[h].M;
-      const size_t q = ops[h].size();
-      for (size_t i = 0; i < q; ++i) {
-        const Op& o = ops[h][i];
-        const bool last = i + 1 == q;
-        int8_t* dM = last ? nxt[h].M : acc[i & 1];
-        int8_t* dT = last ? nxt[h].T : nullptr;
-        unsigned long long* cnt = last ? g->dcnt + h : nullptr;
-        Mat r = cur[o.j];
-        if (o.trans) r = transposed(r);
-        if (o.P.ident && o.S.ident) {
-          P_HIP(launch_bytes_op(addp, r.M, 0, 0, (int)n, (int)Np, dM, dT, cnt, s));
-        } else if (o.P.ident) {
-          P_RC(nt(r.M, o.S.T, addp, dM, dT, cnt));
-        } else if (o.S.ident) {
-          P_RC(nt(o.P.M, r.T, addp, dM, dT, cnt));
-        } else {
-          P_RC(nt(o.P.M, r.T, nullptr, tmp, nullptr, nullptr));
-          P_RC(nt(tmp, o.S.T, addp, dM, dT, cnt));
+  // Steps are enqueued in groups, each launch first checking on the device
+  // whether the series has repeated, and the sizes are read back once per
+  // group (a copy and a synchronisation per step left ~20 us between steps).
+  // Past the fixpoint nothing is written, and both buffers hold the model.
+  const size_t first_ev = evs.size();
+  const int64_t cap = (int64_t)M * n * n + 2;  // every step before the repeat adds at least one of the M n^2 facts
+  int64_t s0 = 2, k = -1;
+  int group = 4;
+  while (k < 0 && s0 <= cap) {
+    const int cnt = (int)std::min<int64_t>(group, cap - s0 + 1);
+    if (s0 + cnt > kRing) P_HIP(launch_ring_clear(ring(), conv(), (int)(s0 % kRing), cnt, 0, s));
+    for (int64_t t = s0; t < s0 + cnt; ++t) {
+      const std::vector<Mat>&cur = buf[(t - 1) & 1], &nxt = buf[t & 1];
+      for (int h = 0; h < M; ++h) {
+        // the head's current iterate stands in for its non-recursive part A[h]:
+        // R^(k) = A + F(R^(k-1)) lies inside A + F(R^(k)) (F monotone, the
+        // iterates grow) and contains A, so A + F(R^(k)) = R^(k) + F(R^(k));
+        // for self-recursive terms it is also the product's left operand
+        const int8_t* addp = cur[h].M;
+        const size_t q = ops[h].size();
+        for (size_t i = 0; i < q; ++i) {
+          const Op& o = ops[h][i];
+          const bool last = i + 1 == q;
+          int8_t* dM = last ? nxt[h].M : acc[i & 1];
+          int8_t* dT = last ? nxt[h].T : nullptr;
+          Mat r = cur[o.j];
+          if (o.trans) r = transposed(r);
+          if (o.P.ident && o.S.ident) {
+            StepGate gate{ring(), conv(), (int)t};
+            P_HIP(launch_bytes_op(addp, r.M, 0, 0, (int)n, (int)Np, dM, dT, last ? ring() + t % kRing : nullptr, s,
+                                  gate));
+          } else if (o.P.ident) {
+            P_RC(nt(r.M, o.S.T, addp, dM, dT, t, last));
+          } else if (o.S.ident) {
+            P_RC(nt(o.P.M, r.T, addp, dM, dT, t, last));
+          } else {
+            P_RC(nt(o.P.M, r.T, nullptr, tmp, nullptr, t, false));
+            P_RC(nt(tmp, o.S.T, addp, dM, dT, t, last));
+          }
+          addp = dM;
         }
-        addp = dM;
       }
     }
-    P_RC(total(&now));
-    std::swap(cur, nxt);
+    const int64_t upto = s0 + cnt - 1;
+    s0 += cnt;
+    group = std::min(group + group / 2, 64);
+    P_RC(read_ring(kSlotWords));
+    const int cv = *(const int*)(g->ctx->h_ring + kRing);
+    const unsigned long long* hr = g->ctx->h_ring;
+    if (cv != kNotConverged)
+      k = cv;
+    else if (hr[upto % kRing] == hr[(upto - 1) % kRing])
+      k = upto;
   }
-  if (now != prev) return perr(DL_ENOCONV, "layer iteration cap reached");
+  if (k < 0) return perr(DL_ENOCONV, "layer iteration cap reached");
+  drop_events(first_ev, k);
   for (int h = 0; h < M; ++h) {
-    g->val[heads[h]] = cur[h];
-    keep_ptr(cur[h].M);
-    keep_ptr(cur[h].T);
+    g->val[heads[h]] = buf[k & 1][h];
+    keep_ptr(buf[k & 1][h].M);
+    keep_ptr(buf[k & 1][h].T);
   }
-  g->iters[L] = k;
+  g->iters[L] = (int)k;
   return DL_OK;
 }
 
@@ -812,11 +853,8 @@ int dl_program_create(dl_ctx* ctx, const char* text, dl_program** out) {
     delete g;
     return rc;
   }
-  size_t widest = 1;
-  for (auto& l : g->layers) widest = std::max(widest, l.size());
-  if (hipSetDevice(ctx->device) != hipSuccess ||
-      hipMalloc(&g->dcnt, widest * sizeof(unsigned long long)) != hipSuccess ||
-      hipHostMalloc(&g->hcnt, widest * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
+  if (hipSetDevice(ctx->device) != hipSuccess || hipMalloc(&g->dcnt, sizeof(unsigned long long)) != hipSuccess ||
+      hipHostMalloc(&g->hcnt, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     if (g->dcnt) (void)hipFree(g->dcnt);
     delete g;
@@ -883,7 +921,7 @@ int dl_program_run(dl_program* g, int method, void* stream) {
   P_HIP(hipSetDevice(g->ctx->device));
   release(g);
   hipStream_t s = (hipStream_t)stream;
-  Runner r{g, s, g->n, 0, 0, {}, {}};
+  Runner r{g, s, g->n, 0, 0, {}, {}, {}, {}};
   g->val.assign(g->names.size(), Mat());
   g->comp.assign(g->names.size(), Mat());
   if (g->n == 0) {
