@@ -460,7 +460,10 @@ int dl_program_predicate(dl_program* prog, int32_t index, const char** name, int
 int dl_program_bind(dl_program* prog, const char* name, int64_t n, const uint8_t* M, int64_t ldm);
 /* Evaluates every layer (blocks until done).  Device memory: two int8
  * (n rounded up to 256)^2 matrices per predicate plus per-layer temporaries
- * and the fp64 workspace of the epsilon forms. */
+ * and the fp64 workspace of the epsilon forms.  A context without a budget
+ * keeps up to 1 GiB of matrices that its programs gave back for their next
+ * runs; they are freed when the context and its programs are destroyed, or
+ * when an allocation of the context would fail. */
 int dl_program_run(dl_program* prog, int method, void* stream);
 /* Layer `layer` of the last run: its heads (predicate indices, up to cap),
  * form (dl_layer_form), the method used and its count: iterations of the

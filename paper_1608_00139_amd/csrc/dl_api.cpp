@@ -72,6 +72,11 @@ int ensure_ws(dl_ctx* c, size_t need) {
   }
   hipError_t e = hipMalloc(&c->ws, need);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
+    c->mats->drop();
+    e = hipMalloc(&c->ws, need);
+  }
+  if (e != hipSuccess) {
     c->ws = nullptr;
     (void)hipGetLastError();
     return fail(DL_ENOMEM, "hipMalloc of " + std::to_string(need) + " bytes failed");
@@ -602,10 +607,15 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
   hipError_t e = hipGetDeviceCount(&ndev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDeviceCount");
   if (device < 0 || device >= ndev) return fail(DL_EINVAL, "no such device");
-  dl_ctx* c = new (std::nothrow) dl_ctx();
+  dl_ctx* c = nullptr;
+  try {
+    c = new dl_ctx();
+  } catch (const std::bad_alloc&) {
+  }
   if (!c) return fail(DL_ENOMEM, "host allocation failed");
   c->device = device;
   c->budget = budget;
+  c->eps.spare = [pool = c->mats] { pool->drop(); };
   auto cleanup = [&](int st) {
     dl_destroy(c);
     return st;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <functional>
 #include <string>
 
 namespace dl {
@@ -13,7 +14,7 @@ struct EpsWorkspace {
   size_t size = 0;
   hipStream_t side = nullptr;  // look-ahead stream of the elimination (default priority)
   hipStream_t work = nullptr;  // the elimination's main stream (default priority)
-  bool masked = false;         // work and side run on disjoint compute units
+  std::function<void()> spare;  // frees what can be spared before an allocation is given up
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 

@@ -708,6 +708,11 @@ static hipError_t ensure(EpsWorkspace* ws, size_t budget_left, size_t need, cons
   }
   eps_free(ws);
   hipError_t e = hipMalloc(&ws->buf, need);
+  if (e != hipSuccess && ws->spare) {
+    (void)hipGetLastError();
+    ws->spare();
+    e = hipMalloc(&ws->buf, need);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     ws->buf = nullptr;

@@ -209,8 +209,9 @@ struct dl_program {
   int64_t Np = 0;
   bool ran = false;
   std::vector<Mat> val, comp;
-  std::vector<void*> keep;  // allocations holding results
-  size_t bytes = 0;
+  std::shared_ptr<MatPool> mats;  // where the matrices come from (null: allocated and freed, with a budget)
+  std::vector<void*> keep;        // matrices holding results
+  size_t bytes = 0;               // in use: results and temporaries
   unsigned long long* dcnt = nullptr;  // device counter of dl_program_fetch
   unsigned long long* hcnt = nullptr;  // pinned mirror
 };
@@ -356,6 +357,14 @@ int analyse(dl_program* g, const std::vector<SClause>& cs) {
 }
 
 // ----------------------------------------------------------------- device evaluation
+// A matrix of the last run's size back to the pool, or freed.
+void give_back(dl_program* g, void* q) {
+  if (g->mats)
+    g->mats->put(q, (size_t)g->Np * g->Np);
+  else
+    (void)hipFree(q);
+}
+
 enum Form { F_NONREC = 0, F_RIGHT_TAIL = 1, F_LEFT_TAIL = 2, F_TWO_SIDED = 3, F_GENERAL = 4 };
 
 struct Runner {
@@ -373,7 +382,7 @@ struct Runner {
     if (g->ctx->budget && g->bytes + b > g->ctx->budget)
       return perr(DL_ENOMEM, "program matrices exceed the workspace budget");
     void* q = nullptr;
-    if (hipMalloc(&q, b) != hipSuccess) {
+    if ((g->mats ? g->mats->get(b, &q) : hipMalloc(&q, b)) != hipSuccess) {
       (void)hipGetLastError();
       return perr(DL_ENOMEM, "hipMalloc of a program matrix failed");
     }
@@ -387,10 +396,11 @@ struct Runner {
     return alloc(&m->T, keep);
   }
   void free_temps() {
+    // launches may still read them: only this stream takes them from the pool
+    // before the run ends, and hipFree waits
     const size_t b = (size_t)Np * Np;
-    if (!temps.empty()) (void)hipStreamSynchronize(s);  // launches may still read them
     for (void* q : temps) {
-      (void)hipFree(q);
+      give_back(g, q);
       g->bytes -= b;
     }
     temps.clear();
@@ -828,7 +838,7 @@ int Runner::iterate(int L, const std::vector<int>& heads, const std::vector<Mat>
 }
 
 void release(dl_program* g) {
-  for (void* q : g->keep) (void)hipFree(q);
+  for (void* q : g->keep) give_back(g, q);
   g->keep.clear();
   g->bytes = 0;
   g->val.clear();
@@ -848,6 +858,7 @@ int dl_program_create(dl_ctx* ctx, const char* text, dl_program** out) {
   dl_program* g = new (std::nothrow) dl_program();
   if (!g) return perr(DL_ENOMEM, "host allocation failed");
   g->ctx = ctx;
+  if (!ctx->budget) g->mats = ctx->mats;
   int rc = analyse(g, cs);
   if (rc) {
     delete g;
@@ -956,7 +967,7 @@ int dl_program_run(dl_program* g, int method, void* stream) {
     r.free_temps();
   }
   r.free_temps();
-  if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = perr(DL_EHIP, "stream synchronisation failed");
+  if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = perr(DL_EHIP, "stream synchronisation failed");
   r.collect_events(rc == DL_OK);
   if (rc) {
     release(g);

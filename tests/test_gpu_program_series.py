@@ -120,3 +120,35 @@ def test_rerun_and_two_programs_share_a_context(dl):
         a.close()
     b.close()
     ctx.close()
+
+
+def test_budget_and_destroy_order(dl):
+    """A context with a budget keeps nothing and still refuses past it; a
+    program may outlive the runs of others that share its matrices."""
+    n = 300  # Np = 512: 256 KB a matrix
+    e = dlgen.to_dense(n, dlgen.er_edges(n, 1.5 / n, 1))
+    ed = dev(e)
+    want, _ = oprog.evaluate(PATH, {"e": e}, n)
+    announce("program budget")
+    small = dl.Context(workspace_budget=5 << 18)
+    prog = dl.Program(PATH, ctx=small)
+    prog.bind("e", ed)
+    for _ in range(2):
+        with pytest.raises(dl.DLError):
+            prog.run(dl.DL_EVAL_ITERATION)
+    prog.close()
+    enough = dl.Context(workspace_budget=9 << 18)
+    prog = dl.Program(PATH, ctx=enough)
+    prog.bind("e", ed)
+    for _ in range(3):
+        prog.run(dl.DL_EVAL_ITERATION)
+        assert np.array_equal(host(prog.fetch("p", n=n)[0]), want["p"])
+    prog.close()
+    one, two = dl.Program(PATH), dl.Program(PATH)
+    for p in (one, two):
+        p.bind("e", ed)
+        p.run(dl.DL_EVAL_ITERATION)
+    one.close()
+    two.run(dl.DL_EVAL_ITERATION)
+    assert np.array_equal(host(two.fetch("p", n=n)[0]), want["p"])
+    two.close()
