@@ -35,6 +35,7 @@
 // device-side convergence state and returns at once if the fixpoint was
 // already reached, so chunks of steps can be enqueued ahead.
 #include "common.h"
+#include "device.h"
 
 namespace dl {
 
@@ -268,22 +269,6 @@ __device__ inline u32x4 with_diag(u32x4 v, int gr, int gc, int n) {
     v[b >> 2] |= 1u << (8 * (b & 3));
   }
   return v;
-}
-
-__device__ inline int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// Block index -> logical index.  The hardware deals workgroups round-robin
-// over the 8 XCDs (block b on XCD b % 8); the blocks of XCD x get the
-// contiguous run of logical indices [x q + min(x, r), ...), q = nblocks / 8,
-// r = nblocks % 8 (a bijection on [0, nblocks) for any nblocks).
-__device__ inline int xcd_logical(int b, int nblocks) {
-  const int q = nblocks >> 3, r = nblocks & 7;
-  const int x = b & 7, local = b >> 3;
-  return x * q + (x < r ? x : r) + local;
 }
 
 // Block index -> output tile: each XCD takes a contiguous run of logical
@@ -747,18 +732,6 @@ static hipError_t set_lds_attr_small() {
 // ring_out[0 .. K] and status_out = {K, 0}, then zeroes the counters for the
 // next launch.
 
-__device__ inline unsigned ld_agent(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline unsigned long long ld_agent64(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void st_agent(unsigned* p, unsigned v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Waits until this wave's stores and atomics have completed.
-__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // Polls *p until (*p & mask) >= target; returns the word, or ~0u on a time
 // limit (then the abort word is raised and status_out[1] set) or an abort
 // seen in the abort word.
@@ -776,22 +749,6 @@ __device__ inline unsigned wait_word(const unsigned* p, unsigned mask, unsigned 
     }
     __builtin_amdgcn_s_sleep(1);
   }
-}
-
-// Device-scope (write-through, sc1) stores of 16 and 8 bytes at byte offset
-// off of a buffer (buffer instructions: the compiler knows them as stores
-// and keeps the wait states their data registers need).
-constexpr int kCpolSc1 = 16;  // cache-policy bits of a device-scope access
-__device__ inline __amdgpu_buffer_rsrc_t buffer_of(void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
-}
-__device__ inline void st_agent_x4(__amdgpu_buffer_rsrc_t r, int off, u32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kCpolSc1);
-}
-__device__ inline void st_agent_x2(__amdgpu_buffer_rsrc_t r, int off, unsigned lo, unsigned hi) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  u32x2 v = {lo, hi};
-  __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kCpolSc1);
 }
 
 // 16 boolean bytes as 16 operand elements (the bytes store_bool16 writes),

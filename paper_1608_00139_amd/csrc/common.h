@@ -172,6 +172,32 @@ inline void fix_small_place(FixSmallParams& p, unsigned* words) {
   p.finished = p.krow + p.tiles;
 }
 
+// The squaring closure of n <= 64 kBitTiles constants in one cooperative
+// launch, on bits (k_fix_bits in bit_kernels.hip).
+constexpr int kBitTiles = 32;  // 64 x 64 tiles a side at most
+constexpr int kBitLine = 16;   // 64-bit words per arrival word: a 128-byte line
+constexpr int kBitSteps = 16;  // squaring repeats by step 2 + ceil(log2(2048))
+struct FixBitsParams {
+  const uint8_t* A;
+  int64_t lda;
+  uint8_t* R;
+  int64_t ldr;
+  void* S[2];               // iterates, tile by tile (T x T tiles of 64 words): S^(t) in S[t & 1]
+  void* ST[2];              // their transposes
+  unsigned long long* cnt;  // [kBitSteps + 1][kBitTiles][kBitLine] arrivals and ones per step and tile row (the
+                            // first word of each line), zero between launches
+  unsigned* finished;       // [0] workgroups done, [1] abort, zero between launches
+  unsigned long long* ring_out;  // model sizes of steps 0 .. K
+  unsigned* status_out;          // [0] K, [1] 1 after an abort
+  int n, T;                      // T = ceil(n / 64)
+  int max_steps;                 // 1 .. kBitSteps
+  long long wait_limit;          // ticks
+};
+// Bytes of the four iterate buffers; counter words (32-bit, 8-byte aligned).
+size_t fix_bits_bytes(int64_t n);
+constexpr int64_t kFixBitsWords = 2 * (kBitSteps + 1) * kBitTiles * kBitLine + 2;
+hipError_t launch_fix_bits(const FixBitsParams& p, bool clear_first, hipStream_t s);
+
 // Launch helpers implemented in bool_kernels.hip.
 struct TileCfg {
   int bm, bn, kb, threads;

@@ -114,8 +114,10 @@ struct dl_ctx {
   std::shared_ptr<MatPool> mats = std::make_shared<MatPool>();  // program matrices (not with a budget)
   dl::EpsWorkspace eps;  // workspace of the epsilon solve
   std::vector<TuneEntry> tuned;  // tile configurations that override the size rule
-  unsigned* fs_words = nullptr;  // counters of the one-launch plain fixpoint (zero between launches)
+  unsigned* fs_words = nullptr;  // counters of the one-launch plain fixpoint, then of the one on bits (zero
+                                 // between launches)
   bool fs_dirty = false;         // a launch ended abnormally: clear them before the next
+  bool fb_dirty = false;         // the same for the one on bits
 };
 
 namespace dl {

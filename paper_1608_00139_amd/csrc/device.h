@@ -1,0 +1,54 @@
+// device.h -- device functions shared by the fixpoint kernels: wave sums, the
+// block order over the XCDs, and the device-scope accesses that hand data from
+// one workgroup of a launch to another.
+#pragma once
+
+#include "common.h"
+
+namespace dl {
+
+__device__ inline int wave_sum(int v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Block index -> logical index.  The hardware deals workgroups round-robin
+// over the 8 XCDs (block b on XCD b % 8); the blocks of XCD x get the
+// contiguous run of logical indices [x q + min(x, r), ...), q = nblocks / 8,
+// r = nblocks % 8 (a bijection on [0, nblocks) for any nblocks).
+__device__ inline int xcd_logical(int b, int nblocks) {
+  const int q = nblocks >> 3, r = nblocks & 7;
+  const int x = b & 7, local = b >> 3;
+  return x * q + (x < r ? x : r) + local;
+}
+
+__device__ inline unsigned ld_agent(const unsigned* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned long long ld_agent64(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st_agent(unsigned* p, unsigned v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Waits until this wave's stores and atomics have completed.
+__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Device-scope (write-through, sc1) stores of 16 and 8 bytes at byte offset
+// off of a buffer (buffer instructions: the compiler knows them as stores
+// and keeps the wait states their data registers need).
+constexpr int kCpolSc1 = 16;  // cache-policy bits of a device-scope access
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
+}
+__device__ inline void st_agent_x4(__amdgpu_buffer_rsrc_t r, int off, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kCpolSc1);
+}
+__device__ inline void st_agent_x2(__amdgpu_buffer_rsrc_t r, int off, unsigned lo, unsigned hi) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 v = {lo, hi};
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kCpolSc1);
+}
+
+}  // namespace dl

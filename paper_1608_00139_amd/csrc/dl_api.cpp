@@ -415,33 +415,18 @@ class Fix {
 // kernel writes R itself.
 constexpr long long kFixSmallWaitTicks = 200000000;  // 2 s of s_memrealtime (100 MHz)
 
-int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
-                    int prec, int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out,
-                    hipStream_t s) {
-  const int64_t Np = padded_size_for(prec, n);
-  const size_t matT = (size_t)mat_bytes(prec, Np);
-  FixSmallParams p{};
-  p.A = A;
-  p.lda = lda;
-  p.R = R;
-  p.ldr = ldr;
-  p.S[0] = ws;
-  p.S[1] = ws + matT;
-  p.n = (int)n;
-  p.Np = (int)Np;
-  p.tiles = (int)(Np / 32);
-  p.max_steps = (int)std::min<int64_t>(max_steps, Np + 2);
-  p.wait_limit = kFixSmallWaitTicks;
-  fix_small_place(p, c->fs_words);
-  // results straight into the pinned host ring of slot 0 and the word after it
-  p.ring_out = c->h_ring_dev;
-  p.status_out = (unsigned*)(c->h_ring_dev + kRing);
+// A whole-fixpoint kernel's results go straight into the pinned host ring of
+// slot 0 (model sizes of steps 0 .. K) and the word after it (its status).
+void expect_status(dl_ctx* c, unsigned long long** ring_out, unsigned** status_out) {
+  *ring_out = c->h_ring_dev;
+  *status_out = (unsigned*)(c->h_ring_dev + kRing);
   volatile unsigned* st = (volatile unsigned*)(c->h_ring + kRing);
   st[0] = ~0u;
   st[1] = 0u;
-  const bool clear = c->fs_dirty;
-  c->fs_dirty = true;  // until the launch is known to have ended normally
-  DL_HIP(launch_fix_small(prec, p, clear, s));
+}
+
+int await_status(dl_ctx* c, int max_steps, hipStream_t s) {
+  volatile unsigned* st = (volatile unsigned*)(c->h_ring + kRing);
   // The kernel's last store is its status word in pinned host memory, made
   // after every other store of the launch (R, the model sizes, the cleared
   // counters) has completed: the host spins on it and returns as soon as it
@@ -460,10 +445,14 @@ int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
   }
   if (!seen) DL_HIP(hipStreamSynchronize(s));
   if (st[1]) return fail(DL_EHIP, "whole-fixpoint kernel: a wait for other workgroups ran past its time limit");
-  if (st[0] == ~0u || st[0] > (unsigned)p.max_steps) return fail(DL_EHIP, "whole-fixpoint kernel reported no result");
-  c->fs_dirty = false;
+  if (st[0] == ~0u || st[0] > (unsigned)max_steps) return fail(DL_EHIP, "whole-fixpoint kernel reported no result");
+  return DL_OK;
+}
+
+// Steps, model sizes and convergence from the ring of a finished launch.
+void take_whole(dl_ctx* c, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out) {
   const volatile unsigned long long* ring = c->h_ring;
-  const int64_t K = st[0];
+  const int64_t K = *(volatile unsigned*)(c->h_ring + kRing);
   // the first repeat of the whole matrix's model sizes (at K if it converged)
   int64_t k = 1, conv = 0;
   for (; k <= K; ++k) {
@@ -478,8 +467,72 @@ int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
     for (int64_t j = 0; j <= steps; ++j) ones_out[j] = (int64_t)ring[j];
   if (steps_out) *steps_out = (int32_t)steps;
   if (converged_out) *converged_out = (int32_t)conv;
+}
+
+
+int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+                    int prec, int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out,
+                    hipStream_t s) {
+  const int64_t Np = padded_size_for(prec, n);
+  const size_t matT = (size_t)mat_bytes(prec, Np);
+  FixSmallParams p{};
+  p.A = A;
+  p.lda = lda;
+  p.R = R;
+  p.ldr = ldr;
+  p.S[0] = ws;
+  p.S[1] = ws + matT;
+  p.n = (int)n;
+  p.Np = (int)Np;
+  p.tiles = (int)(Np / 32);
+  p.max_steps = (int)std::min<int64_t>(max_steps, Np + 2);
+  p.wait_limit = kFixSmallWaitTicks;
+  fix_small_place(p, c->fs_words);
+  expect_status(c, &p.ring_out, &p.status_out);
+  const bool clear = c->fs_dirty;
+  c->fs_dirty = true;  // until the launch is known to have ended normally
+  DL_HIP(launch_fix_small(prec, p, clear, s));
+  if (int rc = await_status(c, p.max_steps, s)) return rc;
+  c->fs_dirty = false;
+  take_whole(c, ones_out, steps_out, converged_out);
   return DL_OK;
 }
+
+// The squaring series of int8 relations of at most 64 kBitTiles constants as
+// one cooperative launch on bits (k_fix_bits), read back like run_plain_whole.
+int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+                    int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out,
+                    hipStream_t s) {
+  FixBitsParams p{};
+  p.A = A;
+  p.lda = lda;
+  p.R = R;
+  p.ldr = ldr;
+  p.n = (int)n;
+  p.T = (int)((n + 63) / 64);
+  const size_t quarter = fix_bits_bytes(n) / 4;
+  p.S[0] = ws;
+  p.S[1] = ws + quarter;
+  p.ST[0] = ws + 2 * quarter;
+  p.ST[1] = ws + 3 * quarter;
+  p.max_steps = (int)std::min<int64_t>(max_steps, kBitSteps);
+  p.wait_limit = kFixSmallWaitTicks;
+  p.cnt = (unsigned long long*)(c->fs_words + fix_small_words(512));
+  p.finished = (unsigned*)(p.cnt + (kBitSteps + 1) * kBitTiles * kBitLine);
+  expect_status(c, &p.ring_out, &p.status_out);
+  const bool clear = c->fb_dirty;
+  c->fb_dirty = true;  // until the launch is known to have ended normally
+  DL_HIP(launch_fix_bits(p, clear, s));
+  if (int rc = await_status(c, p.max_steps, s)) return rc;
+  c->fb_dirty = false;
+  take_whole(c, ones_out, steps_out, converged_out);
+  return DL_OK;
+}
+
+// The int8 squaring series goes to run_square_bits up to this size: 186
+// against 216 us for product launches at n = 2048 (four workgroups per compute
+// unit there; more tiles would not be resident at once).
+constexpr int64_t kBitSquareMax = 64 * kBitTiles;
 
 // Runs `count` fixpoints of one size, mode and precision on stream s, with
 // up to two in flight: while the host reads one's counters back, the device
@@ -524,6 +577,16 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
       if ((rc = run_plain_whole(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, prec, max_steps,
                                 g == 0 ? ones_out : nullptr, steps_out ? steps_out + g : nullptr,
                                 converged_out ? converged_out + g : nullptr, s)))
+        return rc;
+    return DL_OK;
+  }
+  // so does the int8 squaring series at small n (bits); not while product
+  // launches are timed, which only the chunked path has
+  if (mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax && !(te && te->ms == 0.0) && !c->timing) {
+    if ((rc = ensure_ws(c, need))) return rc;
+    for (int g = 0; g < count; ++g)
+      if ((rc = run_square_bits(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, max_steps, g == 0 ? ones_out : nullptr,
+                                steps_out ? steps_out + g : nullptr, converged_out ? converged_out + g : nullptr, s)))
         return rc;
     return DL_OK;
   }
@@ -640,7 +703,7 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
     return cleanup(hip_fail(e, "hipMemset(ring)"));
   if ((e = hipMemset(c->conv, 0, 64 * sizeof(int))) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(conv)"));
   {
-    const size_t fsb = (size_t)fix_small_words(512) * sizeof(unsigned);
+    const size_t fsb = (size_t)(fix_small_words(512) + kFixBitsWords) * sizeof(unsigned);
     if ((e = hipMalloc(&c->fs_words, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(fixpoint counters)"));
     if ((e = hipMemset(c->fs_words, 0, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(fixpoint counters)"));
   }
