@@ -48,14 +48,11 @@ namespace dl {
 typedef unsigned long long u64;
 
 __device__ inline unsigned bit16_of_bytes(u32x4 x) {
+  const u32x4 b = bytes01(x);
   unsigned m = 0u;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    unsigned v = x[w];  // each byte's bits folded into its bit 0
-    v |= v >> 4;
-    v |= v >> 2;
-    v |= v >> 1;
-    v &= 0x01010101u;
+    unsigned v = b[w];
     v |= v >> 7;
     v |= v >> 14;
     m |= (v & 15u) << (4 * w);
@@ -115,8 +112,8 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
     unsigned m = 0u;
     if (gi < p.n) {
       const uint8_t* src = p.A + (int64_t)gi * p.lda + gj;
-      if (gj + 16 <= p.n && ((uintptr_t)src & 15) == 0) {
-        m = bit16_of_bytes(*(const u32x4*)src);
+      if (gj + 16 <= p.n) {
+        m = bit16_of_bytes(load16_any(src));
       } else {
         for (int e = 0; e < 16; ++e)
           if (gj + e < p.n && src[e] != 0) m |= 1u << e;
@@ -249,8 +246,8 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
     if (gi < p.n && gj < p.n) {
       const u32x4 v = bytes_of_bit16(((const unsigned short*)rows)[4 * pr + (tid & 3)]);
       uint8_t* dst = p.R + (int64_t)gi * p.ldr + gj;
-      if (gj + 16 <= p.n && ((uintptr_t)dst & 15) == 0) {
-        *(u32x4*)dst = v;
+      if (gj + 16 <= p.n) {
+        store16_any(dst, v);
       } else {
         for (int e = 0; e < 16 && gj + e < p.n; ++e) dst[e] = (uint8_t)((v[e >> 2] >> (8 * (e & 3))) & 1u);
       }

@@ -2111,7 +2111,9 @@ int choose_nt_config(int prec, int64_t np) {
 // Np x Np, and write the layouts the chosen fixpoint needs: int8 A and A^T
 // and A, A^T in operand precision, the latter two optionally with the
 // identity on the first n constants (ident bits 0 and 1: the right operand
-// of a closure step).  Counts the ones of A.
+// of a closure step).  Counts the ones of A.  Rows are read 16 bytes at a time
+// at any alignment (n = 2500, fp8: byte reads of unaligned rows took 32 us,
+// now 16).
 template <int PREC>
 __global__ void __launch_bounds__(256)
 k_ingest(const uint8_t* __restrict__ A, int64_t lda, int n, int Np, int8_t* A8, int8_t* AT8,
@@ -2134,13 +2136,8 @@ k_ingest(const uint8_t* __restrict__ A, int64_t lda, int n, int Np, int8_t* A8, 
     u32x4 v = {0u, 0u, 0u, 0u};
     if (gi < n) {
       const uint8_t* src = A + (int64_t)gi * lda + gj0;
-      if (gj0 + 16 <= n && (((uintptr_t)src) & 15) == 0) {
-        // whole 16-byte segment: fold each byte's bits into its bit 0
-        u32x4 x = *(const u32x4*)src;
-        x |= x >> 4;
-        x |= x >> 2;
-        x |= x >> 1;
-        v = x & 0x01010101u;
+      if (gj0 + 16 <= n) {
+        v = bytes01(load16_any(src));
       } else {
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
@@ -2252,7 +2249,9 @@ hipError_t launch_identity(int prec, void* S, int Np, int n, hipStream_t s) {
 }
 
 // Emit: crop the padded iterate to n x n and write 0/1 bytes into the
-// caller's matrix, transposing when the fixpoint ran on R^T.
+// caller's matrix, transposing when the fixpoint ran on R^T.  Rows are written
+// 16 bytes at a time at any alignment (n = 2500, fp8: byte stores to unaligned
+// rows took 23.5 us, now 6.6).
 template <int PREC>
 __global__ void __launch_bounds__(256)
 k_emit(const uint8_t* __restrict__ S, int Np, int transpose, int n, uint8_t* R, int64_t ldr) {
@@ -2265,8 +2264,8 @@ k_emit(const uint8_t* __restrict__ S, int Np, int transpose, int n, uint8_t* R, 
     const int gi = bi * 64 + r, gj0 = bj * 64 + c0;
     if (gi < n) {
       uint8_t* dst = R + (int64_t)gi * ldr + gj0;
-      if (gj0 + 16 <= n && (((uintptr_t)dst) & 15) == 0) {
-        *(u32x4*)dst = bool16_of<PREC>(S + ((int64_t)gi * Np + gj0) * elem_nibbles(PREC) / 2);
+      if (gj0 + 16 <= n) {
+        store16_any(dst, bool16_of<PREC>(S + ((int64_t)gi * Np + gj0) * elem_nibbles(PREC) / 2));
       } else {
 #pragma unroll
         for (int t = 0; t < 16; ++t)
@@ -2334,9 +2333,10 @@ hipError_t launch_ring_set(unsigned long long* ones, int slot, unsigned long lon
 }
 
 // Largest row sum of the 0/1 relation (||A||_inf, Sec. 2): one wave per row
-// on a grid of at most 1024 workgroups, 16 bytes per lane where the row is
-// 16-byte aligned, one atomic per workgroup (a workgroup per row with byte
-// loads and an atomic each took 116 us at N = 8192).
+// on a grid of at most 1024 workgroups, 16 bytes per lane, one atomic per
+// workgroup (a workgroup per row with byte loads and an atomic each took 116
+// us at N = 8192; byte loads for rows that are not 16-byte aligned 18.6 us at
+// n = 2500, now 10.5).
 constexpr int kRowMaxGrid = 1024;
 
 __global__ void __launch_bounds__(256) k_row_max(const uint8_t* A, int64_t lda, int n, int* out_max) {
@@ -2344,19 +2344,10 @@ __global__ void __launch_bounds__(256) k_row_max(const uint8_t* A, int64_t lda, 
   int best = 0;
   for (int row = blockIdx.x * 4 + wave; row < n; row += gridDim.x * 4) {
     const uint8_t* r = A + (int64_t)row * lda;
-    int s = 0, j0 = 0;
-    if (((uintptr_t)r & 15) == 0) {
-      const int nv = n / 16;
-      for (int v = lane; v < nv; v += 64) {
-        u32x4 x = *(const u32x4*)(r + 16 * v);
-        x |= x >> 4;  // each byte's bits folded into its bit 0
-        x |= x >> 2;
-        x |= x >> 1;
-        s += popc16(x & 0x01010101u);
-      }
-      j0 = 16 * nv;
-    }
-    for (int j = j0 + lane; j < n; j += 64) s += r[j] != 0;
+    int s = 0;
+    const int nv = n / 16;
+    for (int v = lane; v < nv; v += 64) s += popc16(bytes01(load16_any(r + 16 * v)));
+    for (int j = 16 * nv + lane; j < n; j += 64) s += r[j] != 0;
     s = wave_sum(s);
     best = s > best ? s : best;
   }

@@ -7,6 +7,21 @@
 
 namespace dl {
 
+// 16 bytes at any address: one global access each (the compiler knows the
+// alignment; the memory system splits what crosses a line).  A caller's rows
+// are rarely aligned: their stride is often n itself.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+__device__ inline u32x4 load16_any(const uint8_t* p) { return *(const u32x4_any*)p; }
+__device__ inline void store16_any(uint8_t* p, u32x4 v) { *(u32x4_any*)p = v; }
+
+// Nonzero bytes as ones: each byte's bits folded into its bit 0.
+__device__ inline u32x4 bytes01(u32x4 x) {
+  x |= x >> 4;
+  x |= x >> 2;
+  x |= x >> 1;
+  return x & 0x01010101u;
+}
+
 __device__ inline int wave_sum(int v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -135,3 +135,29 @@ def test_many_calls_and_streams(dl):
         assert np.array_equal(host(r), want[k % 4])
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("off", [0, 1, 2, 7, 13])
+@pytest.mark.parametrize("prec", ["i8", "f32", "bf16", "fp8", "fp4"])
+def test_unaligned_rows_in_and_out(dl, off, prec):
+    """Ingest, emit and the row norm at every alignment of the caller's rows,
+    with sizes that end inside a 16-byte segment; bytes around are untouched."""
+    import torch
+
+    for n in (17, 250):
+        a = dlgen.to_dense(n, dlgen.er_edges(n, 2.0 / n, off)) * 255
+        big = torch.full((n + 1, n + 37), 3, dtype=torch.uint8, device="cuda")
+        big[:n, off:off + n] = dev(a)
+        out = torch.full((n + 1, n + 29), 6, dtype=torch.uint8, device="cuda")
+        view, want = big[:n, off:off + n], oracle.tc_seminaive(a)[0]
+        ctx = dl.Context()
+        ctx.set_tuning(prec, n, 2)  # the product kernels
+        announce("unaligned", n, off, prec)
+        r, _ = dl.dl_tc(view, prec=prec, out=out[:n, off:off + n], ctx=ctx)
+        got = host(out)
+        assert np.array_equal(got[:n, off:off + n], want)
+        got[:n, off:off + n] = 6
+        assert np.all(got == 6)
+        bound = dl.dl_eps_bound(view, ctx=ctx)
+        assert bound == 1.0 / (1.0 + int((a != 0).sum(axis=1).max()))
+        ctx.close()
