@@ -418,7 +418,7 @@ static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
 // while the others finish step k, so the serial chain (16 pivots in a block)
 // runs beside the products.
 // Bound by one compute unit's fp64 matrix cores: 2 NB^3 operations at 128 per
-// clock are 13.7 us.  Measured per 128 x 128 block (MI355X): 30.5 us, against
+// clock are 13.7 us.  Measured per 128 x 128 block (MI355X): 29 us, against
 // 175 us of the version before it, which took 64 steps of 2 x 2 pivots, each a
 // barrier, two dependent divisions and a rank-2 update on the vector units.
 // Signs: the block is a strictly diagonally dominant M-matrix, so every
@@ -468,13 +468,13 @@ __device__ inline void inv16_step(double (&a)[4], int r, int g) {
   cx.y = lane_row<G>(x.y);
   const double col = __builtin_bit_cast(double, cx);  // a[r][P]
   const double inv = pivot_rcp(row_lane<P>(col));
-  const double m = r == P ? inv : -col * inv;
+  const double f = -col * inv;
+  // row P becomes a inv = a + (inv - 1) a: the other rows' multiply-add (the
+  // difference is rounded once, and not at all for pivots in [1/2, 1])
+  const double m = r == P ? inv - 1.0 : f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const double pr = row_lane<P>(a[j]);  // a[P][4 g + j]
-    a[j] = __builtin_fma(m, pr, r == P ? 0.0 : a[j]);
-  }
-  if (g == G) a[J] = m;
+  for (int j = 0; j < 4; ++j) a[j] = __builtin_fma(m, row_lane<P>(a[j]), a[j]);  // a[P][4 g + j]
+  if (g == G) a[J] = r == P ? inv : f;
 }
 
 template <int P>
@@ -583,17 +583,47 @@ __global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, 
 }
 
 // ----------------------------------------------------------------- setup / copy / emit
+// Four consecutive doubles, two 16-byte accesses; 8-byte alignment for the
+// caller's matrices (their stride may be odd).
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef v2d v2d_8 __attribute__((aligned(8)));
+typedef unsigned u32_any __attribute__((aligned(1)));
+
+// The bytes j .. j + 3 of a row of n as flags, 0 past its end.
+__device__ inline unsigned bytes4(const uint8_t* row, int j, int n) {
+  if (j + 4 <= n) {
+    unsigned x = *(const u32_any*)(row + j);
+    x |= x >> 4;
+    x |= x >> 2;
+    x |= x >> 1;
+    return x & 0x01010101u;
+  }
+  unsigned x = 0u;
+  for (int e = 0; e < 4; ++e)
+    if (j + e < n && row[j + e] != 0) x |= 1u << (8 * e);
+  return x;
+}
+
 // W[i][j] = [i == j] - eps b_ij  and, with C, W[i][Np + j] = eps c_ij; padded
-// rows and columns carry the identity and zeros.
+// rows and columns carry the identity and zeros.  Four columns a thread.
 __global__ void __launch_bounds__(256) k_eps_init(const uint8_t* B, int64_t ldb, const uint8_t* C, int64_t ldc,
                                                   int n, int Np, double eps, double* W) {
   const int i = blockIdx.y;
   const int64_t ld = C ? 2 * (int64_t)Np : Np;
-  for (int j = blockIdx.x * 256 + threadIdx.x; j < Np; j += gridDim.x * 256) {
-    const bool in = i < n && j < n;
-    const double b = (in && B[(int64_t)i * ldb + j] != 0) ? 1.0 : 0.0;
-    W[i * ld + j] = (i == j ? 1.0 : 0.0) - eps * b;
-    if (C) W[i * ld + Np + j] = eps * ((in && C[(int64_t)i * ldc + j] != 0) ? 1.0 : 0.0);
+  for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < Np; j += 1024 * gridDim.x) {
+    const unsigned b = i < n ? bytes4(B + (int64_t)i * ldb, j, n) : 0u;
+    v2d w[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e >> 1][e & 1] = (i == j + e ? 1.0 : 0.0) - (((b >> (8 * e)) & 1u) ? eps : 0.0);
+    *(v2d*)(W + i * ld + j) = w[0];
+    *(v2d*)(W + i * ld + j + 2) = w[1];
+    if (C) {
+      const unsigned c = i < n ? bytes4(C + (int64_t)i * ldc, j, n) : 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e >> 1][e & 1] = ((c >> (8 * e)) & 1u) ? eps : 0.0;
+      *(v2d*)(W + i * ld + Np + j) = w[0];
+      *(v2d*)(W + i * ld + Np + j + 2) = w[1];
+    }
   }
 }
 
@@ -603,9 +633,9 @@ __global__ void __launch_bounds__(256) k_eps_init(const uint8_t* B, int64_t ldb,
 //   X_ii = eps (a_ii + sum_{k != i} a_ik X_ki) / (1 - eps a_ii).
 // part[chunk][i] receives the sum over the chunk's k (added up by k_eps_emit
 // in chunk order).  A workgroup takes 64 columns i and the rows k of one
-// chunk; W's rows are read 512 bytes at a time where some a_ik is set, A
-// 16 bytes at a time.
-constexpr int kDiagChunk = 512;
+// chunk; A is read 16 bytes at a time.
+// Chunks of 128: n = 1000 13 us (512, one load at a time: 30 us).
+constexpr int kDiagChunk = 128;
 __global__ void __launch_bounds__(256)
 k_eps_diag(const uint8_t* A, int64_t lda, const double* W, int n, int Np, double* part) {
   __shared__ double red[4][64];
@@ -620,9 +650,13 @@ k_eps_diag(const uint8_t* A, int64_t lda, const double* W, int n, int Np, double
       if (k0 + 16 <= k1) __builtin_memcpy(b, src, 16);
       else
         for (int e = 0; e < k1 - k0; ++e) b[e] = src[e];
+      // every lane loads (those without the edge W[0], unused), so that the
+      // sixteen loads are in flight together
+      double v[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (b[e] != 0 && k0 + e != i) sum += W[(int64_t)(k0 + e) * Np + i];
+      for (int e = 0; e < 16; ++e) v[e] = W[b[e] != 0 ? (int64_t)(k0 + e) * Np + i : 0];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sum += b[e] != 0 && k0 + e != i ? v[e] : 0.0;
     }
   }
   red[q][c] = sum;
@@ -632,30 +666,55 @@ k_eps_diag(const uint8_t* A, int64_t lda, const double* W, int n, int Np, double
 
 // R = [X > 0] (and X itself when asked for), plus the smallest positive
 // entry of X: its bits go into *minpos by an unsigned atomic minimum (positive
-// doubles order like their bit patterns), one per workgroup.  A fixed grid
-// walks the rows, so the atomics stay few.  X is n x n with row stride ldw;
-// with part set its diagonal comes from the sums of k_eps_diag.
-constexpr int kEmitBlocks = 1024;
-__global__ void __launch_bounds__(256)
+// doubles order like their bit patterns), one per workgroup.  A fixed grid of
+// 16-wave workgroups walks the rows, four columns a thread, so the atomics
+// stay few (1024 of them took most of 17 us at n = 1000, now 10; n = 8192,
+// X written: 292 us with one column a thread, now 254).  X is n x n with row
+// stride ldw (even); with part set its diagonal comes from the sums of
+// k_eps_diag.
+constexpr int kEmitBlocks = 512;
+__global__ void __launch_bounds__(1024)
 k_eps_emit(const double* Xw, int64_t ldw, int n, uint8_t* R, int64_t ldr, double* X, int64_t ldx,
            unsigned long long* minpos, const double* part, int Np, int nchunk, const uint8_t* A, int64_t lda,
            double eps) {
-  __shared__ unsigned long long red[4];
+  __shared__ unsigned long long red[16];
   unsigned long long m = ~0ull;
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    for (int j = threadIdx.x; j < n; j += 256) {
-      double x = Xw[i * ldw + j];
-      if (part && i == j) {
-        const double a = A[(int64_t)i * lda + i] != 0 ? 1.0 : 0.0;
-        x = a;
-        for (int ch = 0; ch < nchunk; ++ch) x += part[(int64_t)ch * Np + i];
-        x = eps * x / (1.0 - eps * a);
+  const int tpr = (n + 3) / 4 < 1024 ? ((n + 3) / 4 + 63) / 64 * 64 : 1024;  // threads per row
+  const int rpb = 1024 / tpr;                                               // rows at once
+  const int sub = (int)threadIdx.x / tpr, tj = (int)threadIdx.x % tpr;
+  for (int i = blockIdx.x * rpb + sub; i < n && sub < rpb; i += gridDim.x * rpb) {
+    for (int j = 4 * tj; j < n; j += 4 * tpr) {
+      // whole groups of four lie inside the padded row
+      const v2d a = *(const v2d*)(Xw + i * ldw + j), b = *(const v2d*)(Xw + i * ldw + j + 2);
+      double x[4] = {a.x, a.y, b.x, b.y};
+      if (part && i >= j && i < j + 4) {
+        const double aii = A[(int64_t)i * lda + i] != 0 ? 1.0 : 0.0;
+        double d = aii;
+        for (int ch = 0; ch < nchunk; ++ch) d += part[(int64_t)ch * Np + i];
+        d = eps * d / (1.0 - eps * aii);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i == j + e) x[e] = d;
       }
-      R[(int64_t)i * ldr + j] = x > 0.0 ? 1 : 0;
-      if (X) X[(int64_t)i * ldx + j] = x;
-      if (x > 0.0) {
-        const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-        m = b < m ? b : m;
+      unsigned r = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (x[e] > 0.0 && j + e < n) {
+          r |= 1u << (8 * e);
+          const unsigned long long v = (unsigned long long)__double_as_longlong(x[e]);
+          m = v < m ? v : m;
+        }
+      if (j + 4 <= n) {
+        *(u32_any*)(R + (int64_t)i * ldr + j) = r;
+        if (X) {
+          *(v2d_8*)(X + (int64_t)i * ldx + j) = v2d{x[0], x[1]};
+          *(v2d_8*)(X + (int64_t)i * ldx + j + 2) = v2d{x[2], x[3]};
+        }
+      } else {
+        for (int e = 0; e < 4 && j + e < n; ++e) {
+          R[(int64_t)i * ldr + j + e] = (uint8_t)((r >> (8 * e)) & 1u);
+          if (X) X[(int64_t)i * ldx + j + e] = x[e];
+        }
       }
     }
   }
@@ -666,7 +725,7 @@ k_eps_emit(const double* Xw, int64_t ldw, int n, uint8_t* R, int64_t ldr, double
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) m = red[w] < m ? red[w] : m;
+    for (int w = 1; w < 16; ++w) m = red[w] < m ? red[w] : m;
     if (m != ~0ull) atomicMin(minpos, m);
   }
 }
@@ -910,7 +969,7 @@ hipError_t eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const uint
   hipLaunchKernelGGL(k_set_word, dim3(1), dim3(1), 0, s, minpos, ~0ull);
   EPS_CK(hipGetLastError(), "epsilon init");
 
-  hipLaunchKernelGGL(k_eps_init, dim3((unsigned)((Np + 255) / 256), (unsigned)Np), dim3(256), 0, s, B, ldb,
+  hipLaunchKernelGGL(k_eps_init, dim3((unsigned)((Np + 1023) / 1024), (unsigned)Np), dim3(256), 0, s, B, ldb,
                      closure ? (const uint8_t*)nullptr : C, ldc, (int)n, (int)Np, eps, W);
   EPS_CK(hipGetLastError(), "epsilon init");
   std::vector<std::pair<hipEvent_t, hipEvent_t>> evs;
@@ -922,7 +981,7 @@ hipError_t eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const uint
     if (e != hipSuccess) *err = "diagonal";
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_eps_emit, dim3((unsigned)std::min<int64_t>(n, kEmitBlocks)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_eps_emit, dim3((unsigned)std::min<int64_t>((n + 3) / 4, kEmitBlocks)), dim3(1024), 0, s,
                        (const double*)(closure ? W : W + Np), ldw, (int)n, R, ldr, X_out, ldx, minpos,
                        (const double*)(closure ? part : nullptr), (int)Np, nchunk, B, ldb, eps);
     e = hipGetLastError();
@@ -1040,10 +1099,14 @@ hipError_t stacked_solve(EpsWorkspace* ws, size_t budget_left, const StackDesc& 
 __global__ void __launch_bounds__(256)
 k_f64_from_bytes(const uint8_t* src, int64_t ld, int n, int Np, double scale, int identity, double* dst) {
   const int i = blockIdx.y;
-  for (int j = blockIdx.x * 256 + threadIdx.x; j < Np; j += gridDim.x * 256) {
-    double v = 0.0;
-    if (i < n && j < n) v = identity ? (i == j ? scale : 0.0) : (src[(int64_t)i * ld + j] != 0 ? scale : 0.0);
-    dst[(int64_t)i * Np + j] = v;
+  for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < Np; j += 1024 * gridDim.x) {
+    unsigned b = 0u;
+    if (i < n) b = identity ? (i >= j && i < j + 4 ? 1u << (8 * (i - j)) : 0u) : bytes4(src + (int64_t)i * ld, j, n);
+    v2d w[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e >> 1][e & 1] = ((b >> (8 * e)) & 1u) ? scale : 0.0;
+    *(v2d*)(dst + (int64_t)i * Np + j) = w[0];
+    *(v2d*)(dst + (int64_t)i * Np + j + 2) = w[1];
   }
 }
 
@@ -1076,10 +1139,24 @@ __global__ void __launch_bounds__(256) k_stein_clear(unsigned long long* cnt, in
 __global__ void __launch_bounds__(256)
 k_f64_emit(const double* X, int Np, int n, uint8_t* S, int64_t lds, double* Xo, int64_t ldx) {
   const int i = blockIdx.y;
-  for (int j = blockIdx.x * 256 + threadIdx.x; j < n; j += gridDim.x * 256) {
-    const double x = X[(int64_t)i * Np + j];
-    S[(int64_t)i * lds + j] = x > 0.0 ? 1 : 0;
-    if (Xo) Xo[(int64_t)i * ldx + j] = x;
+  for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < n; j += 1024 * gridDim.x) {
+    const v2d a = *(const v2d*)(X + (int64_t)i * Np + j), b = *(const v2d*)(X + (int64_t)i * Np + j + 2);
+    const double x[4] = {a.x, a.y, b.x, b.y};
+    if (j + 4 <= n) {
+      unsigned r = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r |= (x[e] > 0.0 ? 1u : 0u) << (8 * e);
+      *(u32_any*)(S + (int64_t)i * lds + j) = r;
+      if (Xo) {
+        *(v2d_8*)(Xo + (int64_t)i * ldx + j) = a;
+        *(v2d_8*)(Xo + (int64_t)i * ldx + j + 2) = b;
+      }
+    } else {
+      for (int e = 0; e < 4 && j + e < n; ++e) {
+        S[(int64_t)i * lds + j + e] = x[e] > 0.0 ? 1 : 0;
+        if (Xo) Xo[(int64_t)i * ldx + j + e] = x[e];
+      }
+    }
   }
 }
 
@@ -1158,7 +1235,7 @@ hipError_t sg_eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const u
   double* A = X + mat;
   double* T = A + mat;
   double* An = T + mat;
-  const dim3 rows((unsigned)((Np + 255) / 256), (unsigned)Np);
+  const dim3 rows((unsigned)((Np + 1023) / 1024), (unsigned)Np);
   // X_0 = eps I, A_0 = sqrt(eps) P, T = A_0 X_0 (one product per entry)
   const double se = sqrt(eps);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, (const uint8_t*)nullptr, (int64_t)0, (int)n, (int)Np,
@@ -1171,7 +1248,7 @@ hipError_t sg_eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const u
   EPS_CK(stein_doubling(Np, X, A, nullptr, T, An, nullptr, true, X_out != nullptr, max_doublings, s, counts, h_counts,
                         h_counts_dev, positives, doublings, &done, err),
          *err);
-  hipLaunchKernelGGL(k_f64_emit, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0, s, (const double*)X,
+  hipLaunchKernelGGL(k_f64_emit, dim3((unsigned)((n + 1023) / 1024), (unsigned)n), dim3(256), 0, s, (const double*)X,
                      (int)Np, (int)n, S, lds, X_out, ldx);
   EPS_CK(hipGetLastError(), "threshold");
   EPS_CK(hipStreamSynchronize(s), "sync");
@@ -1192,7 +1269,7 @@ hipError_t two_sided_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, cons
   double* T = Cd + mat;
   double* Bn = T + mat;
   double* Cn = Bn + mat;
-  const dim3 rows((unsigned)((Np + 255) / 256), (unsigned)Np);
+  const dim3 rows((unsigned)((Np + 1023) / 1024), (unsigned)Np);
   // X = eps (Q + B X C): X_0 = eps Q, B_0 = sqrt(eps) B, C_0 = sqrt(eps) C
   const double se = sqrt(eps);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, Q, ldq, (int)n, (int)Np, eps, 0, X);
@@ -1207,7 +1284,7 @@ hipError_t two_sided_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, cons
                         h_counts_dev, &pos, doublings, &done, err),
          *err);
   if (R) {
-    hipLaunchKernelGGL(k_f64_emit, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0, s, (const double*)X,
+    hipLaunchKernelGGL(k_f64_emit, dim3((unsigned)((n + 1023) / 1024), (unsigned)n), dim3(256), 0, s, (const double*)X,
                        (int)Np, (int)n, R, ldr, X_out, ldx);
     EPS_CK(hipGetLastError(), "threshold");
   }
