@@ -158,12 +158,14 @@ __device__ inline void dgemm_wait_slice(int later) {
 }
 
 template <int BM, int BN, int STAGES, bool BT = false, int ACC = ACC_NONE>
-__global__ void __launch_bounds__(256) k_dgemm(GemmArgs g) {
+__global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(GemmArgs g) {
   typedef Dgemm<BM, BN, STAGES> T;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  // the variant that runs beside a trailing update (see gj_blocks) issues first
+  if constexpr (BM == 32 && STAGES == 2) __builtin_amdgcn_s_setprio(3);
   if (g.stop.done()) {
     if (ACC != ACC_NONE && blockIdx.x == 0 && tid == 0) g.stop.cnt[2 * g.stop.j] = g.stop.cnt[2 * (g.stop.j - 1)];
     return;
@@ -425,7 +427,6 @@ static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
 // inverse is >= 0 entrywise and, as for single pivots, every update adds
 // terms of one sign to each off-diagonal entry (columns already pivoted hold
 // entries >= 0, the others <= 0), so zeros stay exact and nothing cancels.
-constexpr int kInvThreads = 9 * 64;
 constexpr int kInvPitch = 17;  // doubles per 16-wide LDS row: operand reads and tile writes hit distinct banks
 
 // Lane n of each row of 16 lanes, to all lanes of that row.
@@ -483,27 +484,36 @@ __device__ inline void inv16_steps(double (&a)[4], int r, int g) {
   if constexpr (P < 15) inv16_steps<P + 1>(a, r, g);
 }
 
-__global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, int64_t ld, double* Dinv, int64_t ldd) {
-  // the next panel's inverse shares its compute unit with a trailing-update
-  // workgroup and is the longer chain in the late panels: its waves issue
-  // first (0.2-0.3 ms per N = 8192 solve)
+// NT = 8: blocks of 128, eight column waves and the inverting wave.  NT = 4:
+// blocks of 64 for a panel inverse that runs beside the trailing update: four
+// waves of at most 80 registers and 20 KB of LDS, which fit on a compute unit
+// beside two update workgroups (2 x 216 registers a SIMD lane, 2 x 64 KB); the
+// wave that owns the next pivot block inverts it itself.
+template <int NT>
+__global__ void __launch_bounds__(NT == 8 ? 576 : 256, NT == 8 ? 1 : 6)
+k_block_inverse(const double* W, int64_t ld, double* Dinv, int64_t ldd) {
+  // beside a trailing update its waves issue first: it is the longer chain
   __builtin_amdgcn_s_setprio(3);
-  __shared__ double cbuf[2][NB * kInvPitch];  // -C of steps k and k + 1
-  __shared__ double dbuf[16 * kInvPitch];     // pivot block to invert
-  __shared__ double qbuf[2][16 * kInvPitch];  // its inverse, steps k and k + 1
-  constexpr int NT = NB / 16;
+  constexpr bool kOwn = NT == 4;
+  __shared__ double cbuf[2][16 * NT * kInvPitch];  // -C of steps k and k + 1
+  __shared__ double dbuf[16 * kInvPitch];          // pivot block to invert
+  __shared__ double qbuf[2][16 * kInvPitch];       // its inverse, steps k and k + 1
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, c = lane & 15;
+  // Q of step k from the pivot block in dbuf, by one wave
+  auto invert = [&](int k) {
+    double a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = dbuf[c * kInvPitch + 4 * g + j];
+    inv16_steps<0>(a, c, g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qbuf[k & 1][c * kInvPitch + 4 * g + j] = a[j];
+  };
   if (wave == NT) {  // the inverting wave
     for (int k = 0; k < NT; ++k) {
       __syncthreads();  // pivot block k is in dbuf
-      double a[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = dbuf[c * kInvPitch + 4 * g + j];
-      inv16_steps<0>(a, c, g);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) qbuf[k & 1][c * kInvPitch + 4 * g + j] = a[j];
+      invert(k);
       __syncthreads();  // Q and C of step k are in LDS
     }
     return;
@@ -521,18 +531,28 @@ __global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, 
 #pragma unroll
       for (int v = 0; v < 4; ++v) cbuf[wave & 1][(16 * i + g + 4 * v) * kInvPitch + c] = -acc[i][v];
   };
-  if (wave == 0) {
+  // hands the pivot block of step k over (and inverts it, without a wave for that)
+  auto pivot = [&](const v4d& t, int k) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) dbuf[(g + 4 * v) * kInvPitch + c] = acc[0][v];
+    for (int v = 0; v < 4; ++v) dbuf[(g + 4 * v) * kInvPitch + c] = t[v];
+    if constexpr (kOwn) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      invert(k);
+    }
+  };
+  // the first pivot block (kOwn: as step -1, so that the inverse's code is there once)
+  if constexpr (!kOwn) {
+    if (wave == 0) pivot(acc[0], 0);
+    __syncthreads();
+    if (wave == 0) publish_c();
+    __syncthreads();
   }
-  __syncthreads();
-  if (wave == 0) publish_c();
-  __syncthreads();
-  for (int k = 0; k < NT; ++k) {
+  for (int k = kOwn ? -1 : 0; k < NT; ++k) {
     const double* q = qbuf[k & 1];
     const double* cb = cbuf[k & 1];
-    v4d y;
-    if (wave == k) {
+    v4d y = {0.0, 0.0, 0.0, 0.0};
+    if (kOwn && k < 0) {
+    } else if (wave == k) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) y[v] = q[(g + 4 * v) * kInvPitch + c];
 #pragma unroll
@@ -542,7 +562,6 @@ __global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, 
 #pragma unroll
       for (int i = 1; i < NT; ++i)
         if (i == k) t = acc[i];
-      y = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         y = __builtin_amdgcn_mfma_f64_16x16x4f64(q[c * kInvPitch + 4 * v + g], t[v], y, 0, 0, 0);
@@ -555,31 +574,37 @@ __global__ void __launch_bounds__(kInvThreads) k_block_inverse(const double* W, 
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(cb[(16 * i + c) * kInvPitch + 4 * v + g], y[v], acc[i], 0, 0, 0);
+      if constexpr (kOwn) __builtin_amdgcn_sched_barrier(0);  // operand reads of later tiles would cost registers
     };
     if (k + 1 < NT) {
+      v4d t = acc[0];
 #pragma unroll
-      for (int i = 1; i < NT; ++i)
+      for (int i = 0; i < NT; ++i)
         if (i == k + 1) {
-          update(i);
-          if (wave == i) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) dbuf[(g + 4 * v) * kInvPitch + c] = acc[i][v];
-          }
+          if (!kOwn || k >= 0) update(i);
+          if (!kOwn && wave == i) pivot(acc[i], i);
+          t = acc[i];
         }
-      __syncthreads();  // the next pivot block is ready
+      if (kOwn && wave == k + 1) pivot(t, k + 1);
+      if constexpr (!kOwn) __syncthreads();  // the next pivot block is ready
     }
+    if (!kOwn || k >= 0) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-      if (i != k + 1) update(i);
+      for (int i = 0; i < NT; ++i)
+        if (i != k + 1) update(i);
+    }
     if (k + 1 < NT) {
       if (wave == k + 1) publish_c();
       __syncthreads();
     }
   }
+  int lane2;  // re-derived: addresses computed from it are not kept live across the steps
+  asm volatile("v_mov_b32 %0, %1" : "=v"(lane2) : "v"(lane));
+  double* dst = Dinv + (lane2 >> 4) * ldd + 16 * wave + (lane2 & 15);
 #pragma unroll
   for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Dinv[(16 * i + g + 4 * v) * ldd + 16 * wave + c] = acc[i][v];
+    for (int v = 0; v < 4; ++v) dst[(int64_t)(16 * i + 4 * v) * ldd] = acc[i][v];
 }
 
 // ----------------------------------------------------------------- setup / copy / emit
@@ -800,8 +825,8 @@ static hipError_t ensure(EpsWorkspace* ws, size_t budget_left, size_t need, cons
 //    Cb (Ns x P) holds W[., p] meanwhile, which other workgroups overwrite.
 //  - otherwise only the columns T right of the panel change (right-hand
 //    sides stand there; the columns left of T would hold the identity).
-static hipError_t gj_panel(double* W, int64_t Ns, int64_t ldw, int64_t K0, int P, const double* Q, int64_t ldq,
-                           bool inplace, double* Y, double* Cb, hipStream_t s) {
+static GemmArgs gj_panel(double* W, int64_t Ns, int64_t ldw, int64_t K0, int P, const double* Q, int64_t ldq,
+                           bool inplace, double* Y, double* Cb) {
   const int64_t c0 = inplace ? 0 : K0 + P;
   const int64_t cols = inplace ? Ns : ldw - c0;
   GemmArgs y{Q, ldq, W + K0 * ldw + c0, ldw, nullptr, 0, Y + c0, ldw, P, (int)cols, P, 0};
@@ -816,7 +841,7 @@ static hipError_t gj_panel(double* W, int64_t Ns, int64_t ldw, int64_t K0, int P
     y.copy_rows = (int)Ns;
     y.copy_cols = P;
   }
-  return dgemm(y, s);
+  return y;
 }
 
 static GemmArgs gj_update(double* W, int64_t Ns, int64_t ldw, int64_t K0, int P, bool inplace, const double* Y,
@@ -836,18 +861,32 @@ static GemmArgs gj_update(double* W, int64_t Ns, int64_t ldw, int64_t K0, int P,
 // In-place inverse of the n x n matrix V (row stride ldv, n a multiple of
 // NB), pivot blocks of NB: three launches a block.  scratch: NB x NB, then
 // Y (NB x ldv) and the saved column block (n x NB).
+// beside: the inverse runs on another stream beside a trailing update, whose
+// workgroups fill the chip and take every slot that comes free (a 128-block
+// inverse waited up to 1.1 ms for a compute unit, 240 us on average): all its
+// launches then are of a size that fits beside two update workgroups, pivot
+// blocks of 64 and products of 32 x 64 tiles with a 24 KB ring.
+// N = 8192 21.7 -> 19.5 ms.
 static size_t gj_blocks_scratch(int64_t n, int64_t ldv) { return (size_t)NB * NB + (size_t)NB * ldv + (size_t)n * NB; }
-static hipError_t gj_blocks(double* V, int64_t n, int64_t ldv, double* scratch, hipStream_t s, std::string* err) {
+static hipError_t gj_blocks(double* V, int64_t n, int64_t ldv, double* scratch, bool beside, hipStream_t s,
+                            std::string* err) {
+  const int nb = beside ? 64 : NB;
   double* Dinv = scratch;
   double* Y = Dinv + (size_t)NB * NB;
   double* Cb = Y + (size_t)NB * ldv;
-  for (int64_t K0 = 0; K0 < n; K0 += NB) {
-    hipLaunchKernelGGL(k_block_inverse, dim3(1), dim3(kInvThreads), 0, s, (const double*)(V + K0 * ldv + K0), ldv,
-                       n == NB ? V : Dinv, n == NB ? ldv : (int64_t)NB);
+  for (int64_t K0 = 0; K0 < n; K0 += nb) {
+    const double* blk = V + K0 * ldv + K0;
+    const bool whole = n == nb;
+    if (beside)
+      hipLaunchKernelGGL(k_block_inverse<4>, dim3(1), dim3(256), 0, s, blk, ldv, Dinv, (int64_t)nb);
+    else
+      hipLaunchKernelGGL(k_block_inverse<8>, dim3(1), dim3(576), 0, s, blk, ldv, whole ? V : Dinv,
+                         whole ? ldv : (int64_t)nb);
     EPS_CK(hipGetLastError(), "block inverse");
-    if (n == NB) break;
-    EPS_CK(gj_panel(V, n, ldv, K0, NB, Dinv, NB, true, Y, Cb, s), "row panel product");
-    EPS_CK(dgemm(gj_update(V, n, ldv, K0, NB, true, Y, Cb), s), "elimination update");
+    if (whole) break;
+    const GemmArgs y = gj_panel(V, n, ldv, K0, nb, Dinv, nb, true, Y, Cb), u = gj_update(V, n, ldv, K0, nb, true, Y, Cb);
+    EPS_CK((beside ? dgemm_launch<32, 64, 2, false, ACC_NONE>(y, s) : dgemm(y, s)), "row panel product");
+    EPS_CK((beside ? dgemm_launch<32, 64, 2, false, ACC_NONE>(u, s) : dgemm(u, s)), "elimination update");
   }
   return hipSuccess;
 }
@@ -895,7 +934,7 @@ static size_t gj_inplace_scratch_doubles(int64_t Ns) {
 static hipError_t gj_eliminate(EpsWorkspace* ws, double* W, int64_t Ns, int64_t ldw, bool inplace, double* scratch,
                                hipStream_t s, bool timing, std::vector<std::pair<hipEvent_t, hipEvent_t>>* evs,
                                std::string* err) {
-  if (inplace && Ns <= kDirectMax) return gj_blocks(W, Ns, ldw, scratch, s, err);
+  if (inplace && Ns <= kDirectMax) return gj_blocks(W, Ns, ldw, scratch, false, s, err);
   // the caller's stream s hands over to the work stream and takes it back
   EPS_CK(ensure_streams(ws, err), *err);
   EPS_CK(hipEventRecord(ws->ev[2], s), "event");
@@ -921,12 +960,12 @@ static hipError_t gj_eliminate(EpsWorkspace* ws, double* W, int64_t Ns, int64_t 
   hipLaunchKernelGGL(k_panel_copy, dim3((unsigned)((P + 255) / 256), (unsigned)P), dim3(256), 0, s, (const double*)W,
                      ldw, (int64_t)0, P, V[0]);
   EPS_CK(hipGetLastError(), "panel copy");
-  EPS_CK(gj_blocks(V[0], P, P, inner, s, err), *err);
+  EPS_CK(gj_blocks(V[0], P, P, inner, false, s, err), *err);
   int t = 0;
   for (int64_t K0 = 0; K0 < Ns; K0 += P, ++t) {
     P = (int)std::min<int64_t>(kPanel, Ns - K0);
     const int64_t T0 = K0 + P;
-    EPS_CK(gj_panel(W, Ns, ldw, K0, P, V[t & 1], P, inplace, Y, Cb, s), "panel row product");
+    EPS_CK(dgemm(gj_panel(W, Ns, ldw, K0, P, V[t & 1], P, inplace, Y, Cb), s), "panel row product");
     const bool ahead = T0 < Ns;
     if (ahead) {
       // the next pivot block, W[p', p'] - W[p', p] Y[., p'], and its inverse
@@ -936,7 +975,7 @@ static hipError_t gj_eliminate(EpsWorkspace* ws, double* W, int64_t Ns, int64_t 
       EPS_CK(dgemm(nd, s), "next pivot block");
       EPS_CK(hipEventRecord(ws->ev[0], s), "event");
       EPS_CK(hipStreamWaitEvent(ws->side, ws->ev[0], 0), "wait");
-      EPS_CK(gj_blocks(Vn, Pn, Pn, inner, ws->side, err), *err);
+      EPS_CK(gj_blocks(Vn, Pn, Pn, inner, true, ws->side, err), *err);
       EPS_CK(hipEventRecord(ws->ev[1], ws->side), "event");
     }
     EPS_CK(timed(gj_update(W, Ns, ldw, K0, P, inplace, Y, Cb)), "elimination update");
