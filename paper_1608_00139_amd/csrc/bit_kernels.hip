@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
         if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > p.wait_limit) {
           if (lane == 0) {
             st_agent(p.finished + 1, 1u);
-            st_agent(p.status_out + 1, 1u);
+            st_system(p.status_out + 1, 1u);
           }
           go = -1;
           break;
@@ -259,15 +259,15 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
   __syncthreads();
   if (!s_go) return;
   // the last workgroup: model sizes, cleared words, then the status
-  if (wave == 0 && lane <= t) p.ring_out[lane] = sizes;
+  if (wave == 0 && lane <= t) st_system64(p.ring_out + lane, sizes);
   for (int i = tid; i < (t + 1) * T; i += 256)
     __hip_atomic_store(p.cnt + bit_word(i / T, i % T), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid == 0) st_agent(p.finished, 0u);
   wait_stores();
   __syncthreads();
   if (tid == 0) {
-    p.status_out[1] = 0u;
-    p.status_out[0] = (unsigned)t;
+    st_system(p.status_out + 1, 0u);
+    st_system(p.status_out, (unsigned)t);
   }
 }
 

@@ -744,7 +744,7 @@ __device__ inline unsigned wait_word(const unsigned* p, unsigned mask, unsigned 
     if (ld_agent(abort_word) != 0u) return ~0u;
     if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > limit) {
       st_agent(abort_word, 1u);
-      st_agent(status_out + 1, 1u);
+      st_system(status_out + 1, 1u);
       return ~0u;
     }
     __builtin_amdgcn_s_sleep(1);
@@ -974,7 +974,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
     if (tid > 0)
       for (int i = 0; i < p.tiles; ++i)
         sum += ld_agent64(p.ones_row + (int64_t)i * stride + (tid < s_k[i] ? tid : s_k[i]));
-    p.ring_out[tid] = sum;
+    st_system64(p.ring_out + tid, sum);
   }
   __syncthreads();
   // every other workgroup is done with the counters: zero them
@@ -990,8 +990,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
   wait_stores();
   __syncthreads();
   if (tid == 0) {
-    p.status_out[1] = 0u;
-    p.status_out[0] = (unsigned)K;
+    st_system(p.status_out + 1, 0u);
+    st_system(p.status_out, (unsigned)K);
   }
 }
 

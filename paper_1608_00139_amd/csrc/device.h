@@ -47,6 +47,16 @@ __device__ inline unsigned long long ld_agent64(const unsigned long long* p) {
 __device__ inline void st_agent(unsigned* p, unsigned v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Stores to host memory that the host polls: system scope, so that a wait for
+// them (wait_stores) means the host can see them.  Plain stores may still sit
+// in the L2 then, and the host saw a status word before the results it
+// announces (once in about 80 thousand calls).
+__device__ inline void st_system(unsigned* p, unsigned v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ inline void st_system64(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // Waits until this wave's stores and atomics have completed.
 __device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
