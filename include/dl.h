@@ -256,8 +256,9 @@ int dl_measure_peak(dl_ctx* ctx, int kind, double* ops_per_s, void* stream);
 /* Tile autotuner for the product step shared by every fixpoint (Sec. 3's
  * thresholded products).  Tile configurations:
  *   0  256 x 256 tile, 16 waves of 64 x 64, operands loaded straight to LDS
- *   1  128 x 128 tile, 4 waves of 64 x 64, register-staged loads
- *   2  64 x 64 tile, 4 waves of 32 x 32, register-staged loads
+ *   1  128 x 128 tile, 8 waves of 32 x 64 (DL_F32: 16 of 32 x 32), operands
+ *      loaded straight to LDS
+ *   2  64 x 64 tile, 4 waves of 32 x 32, operands loaded straight to LDS
  *   3  (DL_I8 only) configuration 0 on the 32 x 32 x 32 int8 MFMA
  *   4  32 x 32 tile, 4 waves of 16 x 16, the whole K extent of its rows in
  *      LDS (operand rows of at most 2 KB: Np <= 2048 / element bytes)
@@ -273,8 +274,9 @@ int dl_measure_peak(dl_ctx* ctx, int kind, double* ops_per_s, void* stream);
  *      seconds ends the launch with DL_EHIP.
  * Without an entry the library picks by size: 5 for the plain series when
  * Np <= 512 and its rows fit; otherwise 4 when Np = 256, or DL_F32 at
- * Np = 512; else 0 when (Np/256)^2 >= 256 tiles, 1 when (Np/128)^2 >= 128,
- * else 2 (Np = dl_padded_size).
+ * Np = 512; else 0 from Np = 3072 (DL_FP4: 3584), 1 above Np = 1024 (DL_BF16:
+ * 1536), else 2; DL_F32 the one of 0, 1 and 2 with the least passes over the
+ * compute units by tile area (Np = dl_padded_size).
  * dl_tune times squaring-step launches of every configuration on a
  * pseudo-random 0/1 relation of size n in precision prec (five interleaved
  * rounds of about 4 ms per configuration, median per configuration; on

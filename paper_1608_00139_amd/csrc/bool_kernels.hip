@@ -22,16 +22,16 @@
 // fp8 e4m3 or fp4 e2m1), so every product is exact: int32 accumulation, or
 // fp32 accumulation of counts below 2^24.
 //
-// Kernel structure (k_nt_step): one workgroup computes a BM x BN output
-// tile, staging BK-byte slices of its X and Y row panels through LDS with
-// double buffering.  LDS holds each slice as 16-byte chunks ordered
-// [chunk][row][16 B], so the 16 lanes that read one MFMA operand chunk read
-// 256 contiguous bytes (no bank conflicts).  The epilogue stages the 0/1
-// tile through LDS, ORs the addend with 16-byte loads, stores coalesced rows
-// (and, for squaring, the transposed tile), and counts the ones of the tile
-// with a wave reduction and a single atomic per workgroup.  The large-tile
-// kernel (k_nt_dma, below) fetches its slices straight into LDS and keeps
-// the tile in registers until the stores.  A launch first checks the
+// Kernel structure (k_nt_dma): one workgroup computes a BM x BN output tile
+// from slices of its X and Y row panels, fetched straight into an LDS ring.
+// The epilogue keeps the 0/1 tile in registers until the stores (64 x 64
+// tiles: stages it through LDS), ORs the addend with 16-byte loads, stores
+// coalesced rows (and, for squaring, the transposed tile), and counts the ones
+// of the tile with a wave reduction and a single atomic per workgroup.  The
+// grouped serving step for small requests (nt_tile) stages its slices through
+// registers instead, as 16-byte chunks ordered [chunk][row][16 B], so the 16
+// lanes that read one MFMA operand chunk read 256 contiguous bytes (no bank
+// conflicts).  A launch first checks the
 // device-side convergence state and returns at once if the fixpoint was
 // already reached, so chunks of steps can be enqueued ahead.
 #include "common.h"
@@ -528,17 +528,6 @@ __device__ __forceinline__ void nt_tile(const NTParams& p, int row0, int col0,
       if (t) atomicAdd(cnt_dst, p.count > 1 ? t * (unsigned long long)p.count : t);
     }
   }
-}
-
-template <int BM, int BN, int WM, int WN, int KB, class Op, int SWZ, int PREF = 1>
-__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
-k_nt_step(NTParams p) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  if (step_is_done(p)) return;
-  int tm, tn;
-  tile_coords(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
-  nt_tile<BM, BN, WM, WN, KB, Op, SWZ, PREF>(p, tm * BM, tn * BN, p.count ? p.ones + (p.step % kRing) : nullptr,
-                                             smem, (int)threadIdx.x);
 }
 
 // ----------------------------------------------------------------- small relations
@@ -1107,7 +1096,7 @@ hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int tota
 }
 
 // ----------------------------------------------------------------- direct-to-LDS variant
-// Same product and epilogue as k_nt_step, but the K slices are fetched with
+// The product step: out = [add + X Y^T != 0], its K slices fetched with
 // global_load_lds_dwordx4 (global memory straight into LDS, no staging
 // registers) into a ring of NSTAGE slices, so NSTAGE - 1 slices are in
 // flight while one is multiplied.  Slice layout: KB-byte rows, the 16-byte
@@ -1147,7 +1136,8 @@ struct DmaKernel {
   // register epilogue (operands swapped in the MFMA so that a lane holds four
   // consecutive columns of one output row); not fp8, whose 32-byte fragments
   // leave no registers for it at four waves per SIMD
-  static constexpr bool SWAPPED = ((FR == 16 && FN % 4 == 0) || FR == 32) && BN == 256 && Op::kPrec != P_FP8;
+  static constexpr bool SWAPPED =
+      ((FR == 16 && FN % 4 == 0) || FR == 32) && (BN == 128 || (BN == 256 && Op::kPrec != P_FP8));
   static_assert(KC == 4 || KC == 8, "64- or 128-byte slices");
   static_assert(KC % KSTEP_CHUNKS == 0, "slice must hold whole MFMA k-steps");
   static_assert(((BM + BN) / ROWS_PER_DMA) % NWAVES == 0, "DMA instructions must divide evenly");
@@ -1181,11 +1171,15 @@ __device__ inline void wait_vmcnt() {
 // 32 x 32 tiles need only one exchange of two dwords between lanes l and
 // l + 32 (32 rows x 32 bytes per instruction).  For the
 // transposed copy the segments also go to LDS (chunk m of row r at chunk
-// m ^ h(r), h(r) = (r ^ (r >> 4)) & 15: conflict-free for the 16-byte
-// writes and the dword reads below); each thread then reads a 16 x 4 byte
+// m ^ h(r), h(r) = (r ^ (r >> 4)) & 15 for 256-byte tile rows and ((r >> 1) ^
+// (r >> 4)) & 7 for 128-byte ones: conflict-free for the 16-byte writes and (at
+// most 2-way for 128-byte rows) the dword reads below); each thread then reads a 16 x 4 byte
 // block as 16 dwords, transposes it in registers with byte permutes and
 // stores four 16-byte segments of out^T.  Returns this thread's ones.
-__device__ inline int ep_swz(int r) { return (r ^ (r >> 4)) & 15; }
+template <int CHUNKS>
+__device__ inline int ep_swz(int r) {
+  return CHUNKS == 16 ? (r ^ (r >> 4)) & 15 : ((r >> 1) ^ (r >> 4)) & 7;
+}
 
 // The four 0/1 bytes of an accumulator fragment (element i of a lane ->
 // byte i): counts are non-negative, so an integer count becomes its byte by
@@ -1221,7 +1215,7 @@ __device__ inline int dma_epilogue_swapped(const NTParams& p, const typename Op:
   static_assert((K::FR == 16 && Op::NI == 4) || (K::FR == 32 && Op::NI == 16), "16 x 16 or 32 x 32 fragments");
   constexpr int BM = K::WAVES_M * K::FM * K::FR, BN = K::WAVES_N * K::FN * K::FR;
   constexpr int CHUNKS = BN / 16;
-  static_assert(CHUNKS == 16, "the LDS swizzle assumes 256-byte tile rows");
+  static_assert(CHUNKS == 16 || CHUNKS == 8, "256- or 128-byte tile rows");
   uint8_t* outb = (uint8_t*)p.out;
   int cnt = 0;
   // Output segment e of this lane: row lr, columns lc .. lc + 15 of the tile.
@@ -1255,7 +1249,7 @@ __device__ inline int dma_epilogue_swapped(const NTParams& p, const typename Op:
     if (add_id) v = with_diag(v, gr, gc, p.n_valid);
     cnt += popc16(v);
     store_bool16<Op::kPrec>(dst, v);
-    if (p.outT) *(u32x4*)(et + lr * BN + 16 * ((lc >> 4) ^ ep_swz(lr))) = outT_id ? with_diag(v, gr, gc, p.n_valid) : v;
+    if (p.outT) *(u32x4*)(et + lr * BN + 16 * ((lc >> 4) ^ ep_swz<CHUNKS>(lr))) = outT_id ? with_diag(v, gr, gc, p.n_valid) : v;
   };
   if constexpr (K::FR == 16) {
     // segment (i, q) lies 16 i rows and 64 q columns from segment (0, 0):
@@ -1316,7 +1310,7 @@ __device__ inline int dma_epilogue_swapped(const NTParams& p, const typename Op:
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int lr = 16 * rb + k;
-        d[k] = *(const unsigned*)(et + lr * BN + 16 * ((cb >> 2) ^ ep_swz(lr)) + 4 * x);
+        d[k] = *(const unsigned*)(et + lr * BN + 16 * ((cb >> 2) ^ ep_swz<CHUNKS>(lr)) + 4 * x);
       }
       // row 4 cb + qq of out^T, columns 16 rb .. 16 rb + 15 of the tile
       uint8_t* const trow = outt + ((int64_t)(col0 + 4 * cb) * p.ld + row0 + 16 * rb) * K::NIB / 2;
@@ -1569,7 +1563,7 @@ __device__ __forceinline__ bool nt_dma_tile(const NTParams& p, int tm, int tn, u
     cnt = p.add ? dma_epilogue_swapped<K, Op, true>(p, acc, et, row0, col0, wm, wn, lane, tid)
                 : dma_epilogue_swapped<K, Op, false>(p, acc, et, row0, col0, wm, wn, lane, tid);
   } else {
-    // ---- epilogue of k_nt_step: the 0/1 tile through LDS byte by byte
+    // ---- the 0/1 tile through LDS byte by byte
     constexpr int SEG_PER_ROW = BN / 16;
     constexpr int SEGS = BM * SEG_PER_ROW / K::NT;
     u32x4 addv[SEGS];  // addend segments, requested together as in nt_tile
@@ -1743,7 +1737,7 @@ __device__ int dma_epilogue_sk(const NTParams& p, const SkParams& q, const typen
     if (add_id) v = with_diag(v, row0 + lr, col0 + lc, p.n_valid);
     cnt += popc16(v);
     *(u32x4*)(outb + (int64_t)(row0 + lr) * p.ld + col0 + lc) = v;
-    if (!diag_tile) *(u32x4*)(et + lr * BN + 16 * ((lc >> 4) ^ ep_swz(lr))) = v;
+    if (!diag_tile) *(u32x4*)(et + lr * BN + 16 * ((lc >> 4) ^ ep_swz<BN / 16>(lr))) = v;
   }
   if (!diag_tile) {
     // the mirror image: element (row0 + r, col0 + c) also at (col0 + c, row0 + r)
@@ -1756,7 +1750,7 @@ __device__ int dma_epilogue_sk(const NTParams& p, const SkParams& q, const typen
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int lr = 16 * rb + k;
-        d[k] = *(const unsigned*)(et + lr * BN + 16 * ((cb >> 2) ^ ep_swz(lr)) + 4 * x);
+        d[k] = *(const unsigned*)(et + lr * BN + 16 * ((cb >> 2) ^ ep_swz<BN / 16>(lr)) + 4 * x);
       }
       uint8_t* const trow = outb + (int64_t)(col0 + 4 * cb) * p.ld + row0 + 16 * rb;
 #pragma unroll
@@ -1923,9 +1917,11 @@ k_group_dma(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const
 template <class Op, int BM, int BN, int WM, int WN, int KB, int NSTAGE>
 static hipError_t launch_dma(const NTParams& p, hipStream_t s) {
   typedef DmaKernel<BM, BN, WM, WN, KB, Op, NSTAGE> K;
-  // one workgroup per compute unit (a multiple of 8), or one per tile
+  // as many workgroups as fit on the compute units by LDS (a multiple of 8),
+  // or one per tile
   const int tiles = p.tiles_m * p.tiles_n;
-  const int grid = tiles > g_cus ? g_cus : tiles;
+  const int slots = g_cus * (K::LDS_BYTES <= 64 * 1024 ? 2 : 1);
+  const int grid = tiles > slots ? slots : tiles;
   hipLaunchKernelGGL((k_nt_dma<BM, BN, WM, WN, KB, Op, NSTAGE>), dim3(grid), dim3(K::NT), K::LDS_BYTES, s, p);
   return hipGetLastError();
 }
@@ -1938,75 +1934,70 @@ static hipError_t set_lds_attr_dma() {
 }
 
 // ----------------------------------------------------------------- configurations
-// cfg 0: 256x256 tile, 16 waves of 64x64, direct-to-LDS slices (large n)
-// cfg 1: 128x128 tile, 4 waves of 64x64, register-staged  (medium n)
-// cfg 2: 64x64 tile,   4 waves of 32x32, register-staged  (small n)
+// All direct-to-LDS (k_nt_dma) except 4:
+// cfg 0: 256x256 tile, 16 waves of 64x64, ring of two 128-byte slices (fp32:
+//        four of 64 bytes), one workgroup per compute unit
+// cfg 1: 128x128 tile, 8 waves of 32x64 (fp32: 16 of 32x32), two 128-byte
+//        slices, two workgroups per compute unit
+// cfg 2: 64x64 tile, 4 waves of 32x32, four 128-byte slices, two workgroups
+//        per compute unit
 // cfg 3: int8 only, cfg 0 with the 32 x 32 x 32 MFMA instead of 16 x 16 x 64
 // cfg 4: 32x32 tile, 4 waves of 16x16, whole K in LDS (rows of at most 2 KB)
-
-template <class Op, int BM, int BN, int WM, int WN, int KB, int SWZ = (KB == 64 ? 2 : 1), int PREF = 1>
-static hipError_t launch_cfg(const NTParams& p, hipStream_t s) {
-  typedef NTKernel<BM, BN, WM, WN, KB, Op, SWZ, PREF> K;
-  const int grid = p.tiles_m * p.tiles_n;
-  hipLaunchKernelGGL((k_nt_step<BM, BN, WM, WN, KB, Op, SWZ, PREF>), dim3(grid), dim3(K::NT), K::LDS_BYTES, s, p);
-  return hipGetLastError();
-}
-
-template <class Op, int BM, int BN, int WM, int WN, int KB, int SWZ = (KB == 64 ? 2 : 1), int PREF = 1>
-static hipError_t set_lds_attr() {
-  typedef NTKernel<BM, BN, WM, WN, KB, Op, SWZ, PREF> K;
-  return hipFuncSetAttribute((const void*)k_nt_step<BM, BN, WM, WN, KB, Op, SWZ, PREF>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)K::LDS_BYTES);
-}
-
-// Large tiles: 256x256 per workgroup, 16 waves of 64x64, 128-byte K slices
-// fetched straight into a 2-slice LDS ring (fp32: 64-byte slices, 4-slice
-// ring), picked by sweeping tile shapes, slice depths and ring sizes at
-// n = 8192.  Smaller problems use register-staged 128x128 or 64x64 tiles so
-// that enough workgroups exist to fill the 256 compute units.
+// cfg 0 was picked by sweeping tile shapes, slice depths and ring sizes at
+// n = 8192.  1 and 2 serve the sizes whose 256 x 256 tiles leave compute units
+// idle.  With register-staged slices (loads into registers one slice ahead,
+// stored to LDS after the products) every slice waited for its loads; straight
+// to LDS, and with a second workgroup on the compute unit to run meanwhile, a
+// product takes (us, int8, before -> after): Np = 512 5.7 -> 5.1, 1024 10.0 ->
+// 8.5, 1536 16.4 -> 11.9, 2048 21.7 -> 15.9, 2560 31.0 -> 23.0; fp32 1024 34.0
+// -> 28.7, 2048 165 -> 139; bf16 2048 41.9 -> 28.9.
 template <class Op>
 struct BigCfg {
   static constexpr int KB = (Op::kPrec == P_F32) ? 64 : 128;
   static constexpr int NS = (Op::kPrec == P_F32) ? 4 : 2;
   typedef DmaKernel<256, 256, 64, 64, KB, Op, NS> K;
 };
+// wave tile of cfg 1: 32 x 64 packs its result in registers; fp32's products
+// leave that unused, and 16 waves hide more of their latency
+template <class Op>
+struct MidCfg {
+  static constexpr int WN = (Op::kPrec == P_F32) ? 32 : 64;
+  typedef DmaKernel<128, 128, 32, WN, 128, Op, 2> K;
+};
 
 template <class Op>
 static hipError_t launch_op(int cfg, const NTParams& p, hipStream_t s) {
-  constexpr int KSMALL = (Op::CPL == 2) ? 128 : 64;
   switch (cfg) {
     case 0: return launch_dma<Op, 256, 256, 64, 64, BigCfg<Op>::KB, BigCfg<Op>::NS>(p, s);
     case 3:
       if constexpr (Op::kPrec == P_I8) return launch_dma<OpI8x32, 256, 256, 64, 64, 128, 2>(p, s);
       return hipErrorInvalidValue;
     case 4: return launch_small<Op>(p, s);
-    case 1: return launch_cfg<Op, 128, 128, 64, 64, KSMALL>(p, s);
-    default: return launch_cfg<Op, 64, 64, 32, 32, KSMALL>(p, s);
+    case 1: return launch_dma<Op, 128, 128, 32, MidCfg<Op>::WN, 128, 2>(p, s);
+    default: return launch_dma<Op, 64, 64, 32, 32, 128, 4>(p, s);
   }
 }
 
 template <class Op>
 static hipError_t init_op() {
-  constexpr int KSMALL = (Op::CPL == 2) ? 128 : 64;
   hipError_t e;
   if ((e = set_lds_attr_dma<Op, 256, 256, 64, 64, BigCfg<Op>::KB, BigCfg<Op>::NS>()) != hipSuccess) return e;
   if constexpr (Op::kPrec == P_I8)
     if ((e = set_lds_attr_dma<OpI8x32, 256, 256, 64, 64, 128, 2>()) != hipSuccess) return e;
   if ((e = set_lds_attr_small<Op>()) != hipSuccess) return e;
   if ((e = set_lds_attr_fix_small<Op>()) != hipSuccess) return e;
-  if ((e = set_lds_attr<Op, 128, 128, 64, 64, KSMALL>()) != hipSuccess) return e;
-  return set_lds_attr<Op, 64, 64, 32, 32, KSMALL>();
+  if ((e = set_lds_attr_dma<Op, 128, 128, 32, MidCfg<Op>::WN, 128, 2>()) != hipSuccess) return e;
+  return set_lds_attr_dma<Op, 64, 64, 32, 32, 128, 4>();
 }
 
 template <class Op>
 static TileCfg cfg_of(int cfg) {
-  constexpr int KSMALL = (Op::CPL == 2) ? 128 : 64;
   switch (cfg) {
     case 0: { typedef typename BigCfg<Op>::K K; return {256, 256, BigCfg<Op>::KB, K::NT, K::LDS_BYTES}; }
     case 3: { typedef DmaKernel<256, 256, 64, 64, 128, OpI8x32, 2> K; return {256, 256, 128, K::NT, K::LDS_BYTES}; }
     case 4: return {32, 32, kSmallMaxLdb, kSmallThreads, small_lds_bytes(kSmallMaxLdb)};
-    case 1: { typedef NTKernel<128, 128, 64, 64, KSMALL, Op, (KSMALL == 64 ? 2 : 1)> K; return {128, 128, KSMALL, K::NT, K::LDS_BYTES}; }
-    default: { typedef NTKernel<64, 64, 32, 32, KSMALL, Op, (KSMALL == 64 ? 2 : 1)> K; return {64, 64, KSMALL, K::NT, K::LDS_BYTES}; }
+    case 1: { typedef typename MidCfg<Op>::K K; return {128, 128, 128, K::NT, K::LDS_BYTES}; }
+    default: { typedef DmaKernel<64, 64, 32, 32, 128, Op, 4> K; return {64, 64, 128, K::NT, K::LDS_BYTES}; }
   }
 }
 
@@ -2098,12 +2089,24 @@ bool nt_config_valid(int prec, int cfg, int64_t np) {
 int choose_nt_config(int prec, int64_t np) {
   // whole-K 32 x 32 tiles at Np = 256 (and fp32 at 512, where each byte
   // carries the most MFMA work); beyond that they move twice the operand
-  // bytes of 64 x 64 tiles and lose.  Then enough workgroups to cover the 256
-  // CUs before choosing the larger tiles (measured on MI355X).
+  // bytes of 64 x 64 tiles and lose.
   if (np == 256 || (prec == P_F32 && np == 512)) return 4;
-  if ((np / 256) * (np / 256) >= 256) return 0;
-  if ((np / 128) * (np / 128) >= 128) return 1;
-  return 2;
+  const auto t = [np](int64_t side) { return (np / side) * (np / side); };
+  if (prec == P_F32) {
+    // bound by the products: the passes over 256 compute units times the
+    // tile's area, each tile at its own rate (cfg 0 : 1 : 2 as 95 : 100 : 108;
+    // measured, us, cfg 1 / 2: Np = 2048 139 / 150, 2560 329 / 320, 3072 583 /
+    // 487; cfg 0 at 3840 956, 1 there 963, 2 991)
+    const auto cost = [&](int64_t side, int64_t w) { return (t(side) + 255) / 256 * side * side * w; };
+    const int64_t c0 = cost(256, 95), c1 = cost(128, 100), c2 = cost(64, 108);
+    return c0 <= c1 && c0 <= c2 ? 0 : (c1 <= c2 ? 1 : 2);
+  }
+  // int8 (fp8 alike), us, cfg 0 / 1 / 2: Np = 1024 17.4 / 8.8 / 8.5, 1280 19.9 /
+  // 10.2 / 11.2, 2816 35.6 / 25.4 / 44.8, 3072 38.6 / 40.2 / 50.5, 3840 47.4 /
+  // 53.6 / 93.1.  bf16 (twice the slices): 1280 - / 16.9 / 14.2, 2048 52.8 / 28.9
+  // / 33.9.  fp4 (half): 3328 30.0 / 27.2, 3840 33.9 / 35.8.
+  if (np >= (prec == P_FP4 ? 3584 : 3072)) return 0;
+  return np > (prec == P_BF16 ? 1536 : 1024) ? 1 : 2;
 }
 
 // ----------------------------------------------------------------- ingest / emit
