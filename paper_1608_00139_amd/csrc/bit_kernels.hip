@@ -245,12 +245,7 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
     const int gi = 64 * ti + pr, gj = 64 * tj + pc;
     if (gi < p.n && gj < p.n) {
       const u32x4 v = bytes_of_bit16(((const unsigned short*)rows)[4 * pr + (tid & 3)]);
-      uint8_t* dst = p.R + (int64_t)gi * p.ldr + gj;
-      if (gj + 16 <= p.n) {
-        store16_any(dst, v);
-      } else {
-        for (int e = 0; e < 16 && gj + e < p.n; ++e) dst[e] = (uint8_t)((v[e >> 2] >> (8 * (e & 3))) & 1u);
-      }
+      store16_agent_any(p.R + (int64_t)gi * p.ldr + gj, v, p.n - gj);
     }
   }
   wait_stores();

@@ -934,10 +934,12 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
   }
   // the last iterate computed, S^(t-1), back to R = S^T, cropped; every
   // store of the tile completes before the workgroup counts itself finished
-  for (int q = tid; q < 1024; q += kSmallThreads) {
-    const int r = q & 31, c = q >> 5;
+  for (int q = tid; q < 256; q += kSmallThreads) {
+    const int r = 4 * (q & 7), c = q >> 3;
     const int gi = row0 + r, gj = col0 + c;
-    if (gi < p.n && gj < p.n) p.R[(int64_t)gj * p.ldr + gi] = et[r * kSmallEst + c];
+    const uint8_t* e = et + r * kSmallEst + c;
+    const unsigned v = e[0] | e[kSmallEst] << 8 | e[2 * kSmallEst] << 16 | (unsigned)e[3 * kSmallEst] << 24;
+    if (gi < p.n && gj < p.n) store4_agent_any(p.R + (int64_t)gj * p.ldr + gi, v, p.n - gi);
   }
   wait_stores();
   __syncthreads();

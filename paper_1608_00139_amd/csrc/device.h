@@ -76,4 +76,36 @@ __device__ inline void st_agent_x2(__amdgpu_buffer_rsrc_t r, int off, unsigned l
   __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kCpolSc1);
 }
 
+// The same for a caller's buffer, of any alignment: the first `count` bytes
+// of v at p.  A kernel whose status word ends the call stores its results so:
+// a plain store may sit in its XCD's L2 until the launch ends, where other
+// streams do not see it.
+__device__ inline void st_agent_u8(uint8_t* p, unsigned v) {
+  __hip_atomic_store(p, (uint8_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void store4_agent_any(uint8_t* p, unsigned v, int count) {
+  if (count >= 4 && ((uintptr_t)p & 3) == 0) {
+    st_agent((unsigned*)p, v);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < count) st_agent_u8(p + e, v >> (8 * e));
+  }
+}
+__device__ inline void store16_agent_any(uint8_t* p, u32x4 v, int count) {
+  const int head = (int)(-(uintptr_t)p & 3);
+  if (count >= 16 && head != 0) {  // bytes up to a word, three words, the bytes left
+#pragma unroll
+    for (int w = 0; w < 3; ++w) st_agent((unsigned*)(p + head + 4 * w), __builtin_amdgcn_alignbyte(v[w + 1], v[w], head));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e < head) st_agent_u8(p + e, v[0] >> (8 * e));
+      else st_agent_u8(p + 12 + e, v[3] >> (8 * e));
+    }
+  } else {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) store4_agent_any(p + 4 * w, v[w], count - 4 * w);
+  }
+}
+
 }  // namespace dl

@@ -161,3 +161,33 @@ def test_unaligned_rows_in_and_out(dl, off, prec):
         bound = dl.dl_eps_bound(view, ctx=ctx)
         assert bound == 1.0 / (1.0 + int((a != 0).sum(axis=1).max()))
         ctx.close()
+
+
+@pytest.mark.parametrize("n", [33, 300, 1001, 1024, 2047])
+def test_result_is_seen_by_other_streams(dl, n):
+    """The one-launch closures return once their result is stored: a copy on
+    a stream of its own, made right after the call, sees it, at every offset
+    of the rows within a word (squaring in int8; the plain series in fp32)."""
+    import torch
+
+    a = dlgen.to_dense(n, dlgen.er_edges(n, min(1.0, 2.0 / n), 7 * n, self_loops=True))
+    want = oracle.tc_seminaive(a)[0]
+    ad = dev(a)
+    side = torch.cuda.Stream()
+    calls = [lambda out: dl.dl_tc(ad, out=out)]
+    if n <= 512:
+        calls.append(lambda out: dl.dl_tc(ad, dl.DL_TC_PLAIN, dl.DL_F32, out=out))
+    for off in range(4):
+        for call in calls:
+            announce("streams", n, off)
+            flat = torch.full((n * (n + off) + 4,), 9, dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()
+            out = flat[off : off + n * (n + off)].view(n, n + off)[:, :n]
+            call(out)
+            with torch.cuda.stream(side):
+                got = out.clone()
+            side.synchronize()
+            assert np.array_equal(got.cpu().numpy(), want)
+            flat = flat.cpu().numpy()
+            pad = flat[off : off + n * (n + off)].reshape(n, n + off)[:, n:]
+            assert (pad == 9).all() and (flat[:off] == 9).all() and (flat[off + n * (n + off) :] == 9).all()
