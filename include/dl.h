@@ -304,7 +304,7 @@ int64_t dl_padded_size(int64_t n, int kind, int prec);
  * Many independent fixpoints over uneven n, resident in one device pool and
  * advanced together: every dl_batch_step is one round of grouped launches
  * (64 x 64 output tiles for requests with n <= 256, 128 x 128 up to 1024,
- * 256 x 256 above) that moves each unfinished request forward by one product (a
+ * 256 x 256 above, or 128 x 128 in rounds with few such requests) that moves each unfinished request forward by one product (a
  * closure request by one
  * repeated-squaring step R' = min1(A + R R), Sec. 8; a same-generation
  * request by one of the two products T = min1(P S), S' = min1(I + T P^T),

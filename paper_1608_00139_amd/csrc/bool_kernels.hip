@@ -1019,13 +1019,13 @@ static hipError_t launch_fix_small_op(FixSmallParams p, hipStream_t s) {
 // ceil(total / gridDim.x) tiles.  Each pass over gridDim.x consecutive tiles
 // gives every XCD a contiguous run of them (xcd_logical), so neighbouring
 // tiles of one request, which read the same operand panels, share an L2.
-// T x T tiles, four waves of (T/2) x (T/2): 64 for small requests, 128 for
-// the others (four times the work per tile, twice the operand reuse).
+// 64 x 64 tiles, four waves of 32 x 32, for small requests; larger ones run on
+// the direct-to-LDS tiles (k_group_dma).
 // dyn_total: the live tile count after k_group_upload skipped the products of
 // finished requests (their descriptors then hold no tiles), or null.
-template <int T>
 __global__ void __launch_bounds__(256)
 k_group_step(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const int* __restrict__ dyn_total) {
+  constexpr int T = 64;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   if (dyn_total) total_tiles = min(total_tiles, *dyn_total);
   for (int item = xcd_logical(blockIdx.x, gridDim.x); item < total_tiles; item += gridDim.x) {
@@ -1071,30 +1071,6 @@ k_group_step(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, cons
     asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
     nt_tile<T, T, T / 2, T / 2, 64, OpI8, 2, 1>(p, tm * T, tn * T, g.cnt, smem, tid);
   }
-}
-
-__global__ void k_group_dma(const GroupDesc* __restrict__ desc, int nreq, int total_tiles,
-                            const int* __restrict__ dyn_total);
-size_t group_dma_lds();
-
-hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int total_tiles, int grid, hipStream_t s,
-                             const int* dyn_total) {
-  if (nreq <= 0 || total_tiles <= 0) return hipSuccess;
-  if (nreq > kMaxGroupRequests) return hipErrorInvalidValue;
-  if (tile == 64) {
-    typedef NTKernel<64, 64, 32, 32, 64, OpI8, 2, 1> K;
-    hipLaunchKernelGGL(k_group_step<64>, dim3(grid), dim3(K::NT), K::LDS_BYTES, s, desc, nreq, total_tiles,
-                       dyn_total);
-  } else if (tile == 128) {
-    typedef NTKernel<128, 128, 64, 64, 64, OpI8, 2, 1> K;
-    hipLaunchKernelGGL(k_group_step<128>, dim3(grid), dim3(K::NT), K::LDS_BYTES, s, desc, nreq, total_tiles,
-                       dyn_total);
-  } else if (tile == 256) {
-    hipLaunchKernelGGL(k_group_dma, dim3(grid), dim3(1024), group_dma_lds(), s, desc, nreq, total_tiles, dyn_total);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------- direct-to-LDS variant
@@ -1834,17 +1810,34 @@ hipError_t launch_nt_sym_sk(const NTParams& p, const SkParams& q, hipStream_t s)
   return hipGetLastError();
 }
 
-// Grouped serving step with the direct-to-LDS 256 x 256 tiles (requests with
-// Np a multiple of 256): one workgroup per CU walks the concatenated tile
-// lists as k_group_step does, fetching each next tile's first K slice while
-// it finishes the current one.
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(1, 4)))
+// Grouped serving step with the direct-to-LDS tiles: 256 x 256 (one workgroup
+// per CU) or 128 x 128 (two), requests with Np a multiple of the tile.  The
+// workgroups walk the concatenated tile lists as k_group_step does, fetching
+// each next tile's first K slice while they finish the current one.  The 128
+// tiles are bound by their loads' latency like the products of one fixpoint;
+// register-staged they took, per round of 1, 8 and 32 requests of n = 1024,
+// 38.4, 46.2 and 92.5 us, and take 34.7, 39.9 and 72.8 (some 25 us of a round
+// are its uploads and read-back).
+template <int T>
+struct GroupTile;
+template <>
+struct GroupTile<256> {
+  static constexpr int WM = 64, WN = 64, PER_CU = 1;
+  typedef DmaKernel<256, 256, WM, WN, 128, OpI8, 2> K;
+};
+template <>
+struct GroupTile<128> {
+  static constexpr int WM = 32, WN = 64, PER_CU = 2;
+  typedef DmaKernel<128, 128, WM, WN, 128, OpI8, 2> K;
+};
+template <int T>
+__global__ void __launch_bounds__(GroupTile<T>::K::NT) __attribute__((amdgpu_waves_per_eu(1, 4)))
 k_group_dma(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const int* __restrict__ dyn_total) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   if (dyn_total) total_tiles = min(total_tiles, *dyn_total);  // see k_group_step
   // every request's first tile, in LDS: the search for a tile's request
   // takes LDS reads instead of a chain of dependent global loads
-  int* first = (int*)(smem + DmaKernel<256, 256, 64, 64, 128, OpI8, 2>::LDS_BYTES);
+  int* first = (int*)(smem + GroupTile<T>::K::LDS_BYTES);
   for (int i = threadIdx.x; i < nreq; i += blockDim.x) first[i] = desc[i].tile_start;
   __syncthreads();
   auto find = [&](int item, int lo) {  // last request whose first tile is <= item, at or after lo
@@ -1877,17 +1870,17 @@ k_group_dma(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const
   for (; item < total_tiles; item += gridDim.x) {
     const GroupDesc& g = desc[cur];
     int tm, tn;
-    coords(item - g.tile_start, g.Np / 256, g.sym, tm, tn);
+    coords(item - g.tile_start, g.Np / T, g.sym, tm, tn);
     DmaPanels next;
     int nxt = cur;
     if (item + (int)gridDim.x < total_tiles) {
       nxt = find(item + gridDim.x, cur);
       const GroupDesc& h = desc[nxt];
       int tm2, tn2;
-      coords(item + gridDim.x - h.tile_start, h.Np / 256, h.sym, tm2, tn2);
+      coords(item + gridDim.x - h.tile_start, h.Np / T, h.sym, tm2, tn2);
       next.ldb = h.Np;
-      next.X = (const uint8_t*)h.X + (int64_t)tm2 * 256 * h.Np;
-      next.Y = (const uint8_t*)h.Y + (int64_t)tn2 * 256 * h.Np;
+      next.X = (const uint8_t*)h.X + (int64_t)tm2 * T * h.Np;
+      next.Y = (const uint8_t*)h.Y + (int64_t)tn2 * T * h.Np;
     }
     NTParams p{};
     p.X = g.X;
@@ -1911,9 +1904,40 @@ k_group_dma(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const
     __syncthreads();  // the previous tile's epilogue is done with LDS
     int tid;
     asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
-    pre = nt_dma_tile<256, 256, 64, 64, 128, OpI8, 2>(p, tm, tn, smem, tid, pre, next);
+    pre = nt_dma_tile<T, T, GroupTile<T>::WM, GroupTile<T>::WN, 128, OpI8, 2>(p, tm, tn, smem, tid, pre, next);
     cur = nxt;
   }
+}
+
+// the operand ring and epilogue, then the first tile of each request
+template <int T>
+static size_t group_dma_lds(int nreq) {
+  return GroupTile<T>::K::LDS_BYTES + ((size_t)nreq * sizeof(int) + 255) / 256 * 256;
+}
+
+template <int T>
+static hipError_t launch_group_dma(const GroupDesc* desc, int nreq, int total_tiles, hipStream_t s,
+                                   const int* dyn_total) {
+  const int slots = g_cus * GroupTile<T>::PER_CU;
+  hipLaunchKernelGGL(k_group_dma<T>, dim3(total_tiles < slots ? total_tiles : slots), dim3(GroupTile<T>::K::NT),
+                     group_dma_lds<T>(nreq), s, desc, nreq, total_tiles, dyn_total);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int total_tiles, hipStream_t s,
+                             const int* dyn_total) {
+  if (nreq <= 0 || total_tiles <= 0) return hipSuccess;
+  if (nreq > kMaxGroupRequests) return hipErrorInvalidValue;
+  if (tile == 64) {
+    typedef NTKernel<64, 64, 32, 32, 64, OpI8, 2, 1> K;
+    const int slots = 4 * g_cus;
+    hipLaunchKernelGGL(k_group_step, dim3(total_tiles < slots ? total_tiles : slots), dim3(K::NT), K::LDS_BYTES, s,
+                       desc, nreq, total_tiles, dyn_total);
+    return hipGetLastError();
+  }
+  if (tile == 128) return launch_group_dma<128>(desc, nreq, total_tiles, s, dyn_total);
+  if (tile == 256) return launch_group_dma<256>(desc, nreq, total_tiles, s, dyn_total);
+  return hipErrorInvalidValue;
 }
 
 template <class Op, int BM, int BN, int WM, int WN, int KB, int NSTAGE>
@@ -2003,17 +2027,17 @@ static TileCfg cfg_of(int cfg) {
   }
 }
 
-// the operand ring and epilogue, then the first tile of each request (up to kMaxGroupRequests)
-size_t group_dma_lds() { return DmaKernel<256, 256, 64, 64, 128, OpI8, 2>::LDS_BYTES + kMaxGroupRequests * sizeof(int); }
-
 hipError_t bool_kernels_init() {
   hipError_t e;
   int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
   g_cus = cus >= 8 ? cus / 8 * 8 : 8;
-  if ((e = hipFuncSetAttribute((const void*)k_group_dma, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)group_dma_lds())) != hipSuccess)
+  if ((e = hipFuncSetAttribute((const void*)k_group_dma<256>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)group_dma_lds<256>(kMaxGroupRequests))) != hipSuccess)
+    return e;
+  if ((e = hipFuncSetAttribute((const void*)k_group_dma<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)group_dma_lds<128>(kMaxGroupRequests))) != hipSuccess)
     return e;
   if ((e = hipFuncSetAttribute((const void*)k_nt_dma_sk, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)DmaKernel<256, 256, 64, 64, 128, OpI8, 2>::LDS_BYTES)) != hipSuccess)

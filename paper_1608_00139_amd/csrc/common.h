@@ -274,7 +274,7 @@ hipError_t measure_peak(int kind, int* sink, double* ops_per_s, hipStream_t s, c
 constexpr int kMaxGroupRequests = kRing;
 // dyn_total (device int, may be null): the live tile count written by
 // k_group_upload; total_tiles is then the bound the grid was sized for.
-hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int total_tiles, int grid, hipStream_t s,
+hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int total_tiles, hipStream_t s,
                              const int* dyn_total = nullptr);
 // Copy a round's descriptors from src (a device mapping of host memory) to
 // dst and renumber the tiles of each segment over the products that are not

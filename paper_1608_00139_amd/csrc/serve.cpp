@@ -9,7 +9,7 @@
 // squaring step R' = [A + R R], a same-generation request by one of the two
 // products of its step (T = [P S], then S' = [I + T P^T]) -- in up to three
 // persistent launches over the concatenated tile lists of the requests of
-// each tile size (64 x 64, 128 x 128, and the 256 x 256 direct-to-LDS tiles).
+// each tile size (64 x 64, and the direct-to-LDS 128 x 128 and 256 x 256 tiles).
 // The round ends
 // with one read-back of the per-request model sizes; a request whose model
 // size repeats is finished (its iteration count follows the same convention
@@ -80,6 +80,7 @@ struct Req {
   std::vector<int64_t> ones;  // model sizes known on the host, ones[k] for k <= known
   int64_t iters = 0;
   int tile = 64;            // output tile of its products (Np is a multiple of it)
+  bool tile_set = false;    // the tile is from the batch's tile table
   bool admit_count = false; // ones[1] pending from the ingest counter
   uint64_t gen = 0;         // admission number
   int64_t icomp = 0;        // issue state: iterate the next product builds on ...
@@ -143,7 +144,6 @@ struct dl_batch {
   uint64_t next_gen = 1;
   std::vector<Retired> retire;  // pool regions waiting for the round that may still read them
   int max_active = 0;
-  int grid = 1024;  // persistent workgroups of the 64 and 128 tile launches
   int cus = 256;
   std::vector<int> finished;  // slots finished and not yet polled
   std::vector<int> order;     // issue_round's scratch: active slots, largest first
@@ -152,13 +152,16 @@ struct dl_batch {
 namespace {
 
 // Output tiles by request size: 64 x 64 up to n = 256, 128 x 128 up to
-// n = 1024, 256 x 256 (the direct-to-LDS kernel) above, unless the batch's
-// tile table (dl_batch_tune / dl_batch_set_tiles) says otherwise.
+// n = 1024, 256 x 256 above (128 x 128 in rounds with few such requests, see
+// issue_round), unless the batch's tile table (dl_batch_tune /
+// dl_batch_set_tiles) says otherwise.
 int default_tile(int64_t n) { return n <= 256 ? 64 : (n <= 1024 ? 128 : 256); }
 
-int tile_for(const dl_batch* b, int64_t n) {
+int tile_for(const dl_batch* b, int64_t n, bool* from_table) {
+  *from_table = true;
   for (size_t i = 0; i < b->tile_n.size(); ++i)
     if (n <= b->tile_n[i]) return b->tile_t[i];
+  *from_table = false;
   return default_tile(n);
 }
 
@@ -275,7 +278,6 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
   int cus = 256;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0) cus = prop.multiProcessorCount;
-  b->grid = cus * 4;
   b->cus = cus;
   *out = b;
   return DL_OK;
@@ -320,7 +322,8 @@ int admit(dl_batch* b, int kind, int64_t n, int64_t tag, int32_t* slot_out, hipS
       break;
     }
   if (slot < 0) return bfail(DL_EAGAIN, "no free request slot");
-  const int tile = tile_for(b, n);
+  bool tile_set = false;
+  const int tile = tile_for(b, n, &tile_set);
   const int64_t Np = pad_to(n, tile);
   const size_t bytes = request_bytes(kind, Np);
   size_t off = 0;
@@ -333,6 +336,7 @@ int admit(dl_batch* b, int kind, int64_t n, int64_t tag, int32_t* slot_out, hipS
   r.n = n;
   r.Np = Np;
   r.tile = tile;
+  r.tile_set = tile_set;
   r.tag = tag;
   r.off = off;
   r.bytes = bytes;
@@ -488,12 +492,27 @@ int issue_round(dl_batch* b, hipStream_t s, Round& rd) {
   // tiles of small requests fill the last pass (largest-first scheduling)
   std::vector<int>& order = b->order;
   order.clear();
+  auto sides = [](const Req& r, int tile) {
+    const int t = (int)(r.Np / tile);
+    return r.kind == 1 && r.iphase == 1 ? t * (t + 1) / 2 : t * t;  // S' lists its upper triangle
+  };
+  int tiles128 = 0;  // the 256-tile requests' products in 128 x 128 tiles
   for (int i = 0; i < M; ++i) {
     const Req& r = b->req[i];
     if (!r.used || r.done) continue;
-    ++na[list_of(r.tile)];
+    if (r.tile == 256 && !r.tile_set) tiles128 += sides(r, 128);
     order.push_back(i);
   }
+  // A round with few large requests leaves compute units idle on 256 x 256
+  // tiles.  While their 128 x 128 tiles are resident at once (two to a compute
+  // unit) the smaller tile is faster, and not beyond.  Round times, 256 against
+  // 128 x 128 tiles: one request of n = 2048 (256 tiles) 51.9, 40.3 us; one of
+  // 2816 (484) 59.7, 48.8; two of 2048 (512) 54.2, 45.4; four of 1536 (576)
+  // 51.4, 54.5; one of 3328 (676) 66.0, 73.4.  A tile from the batch's table
+  // is kept.
+  const bool split = tiles128 <= 2 * b->cus;
+  auto tile_now = [&](const Req& r) { return r.tile == 256 && !r.tile_set && split ? 128 : r.tile; };
+  for (const int i : order) ++na[list_of(tile_now(b->req[i]))];
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->req[x].Np > b->req[y].Np; });
   int first[kLists], fill[kLists] = {0, 0, 0};
   first[2] = 0;
@@ -501,7 +520,8 @@ int issue_round(dl_batch* b, hipStream_t s, Round& rd) {
   first[0] = na[2] + na[1];
   for (const int i : order) {
     Req& r = b->req[i];
-    const int li = list_of(r.tile);
+    const int tile = tile_now(r), li = list_of(tile);
+    const int ntiles = sides(r, tile);  // before the request's phase moves on
     GroupDesc& g = hset[first[li] + fill[li]];
     std::memset(&g, 0, sizeof g);
     g.Np = (int)r.Np;
@@ -544,8 +564,7 @@ int issue_round(dl_batch* b, hipStream_t s, Round& rd) {
       r.icomp = t;
       r.iphase = 0;
     }
-    const int tside = (int)(r.Np / r.tile);
-    tiles[li] += g.sym ? tside * (tside + 1) / 2 : tside * tside;
+    tiles[li] += ntiles;
     rd.items.push_back(it);
     ++fill[li];
   }
@@ -556,9 +575,7 @@ int issue_round(dl_batch* b, hipStream_t s, Round& rd) {
   BHIP(launch_group_upload(b->h_desc_dev + (size_t)set * M, dset, gl, tot, s));
   for (int li = kLists - 1; li >= 0; --li) {  // the largest tiles first
     if (!na[li]) continue;
-    const int grid = li == 2 ? b->cus : b->grid;  // the 256 tiles take a whole CU each
-    BHIP(launch_group_step(64 << li, dset + first[li], na[li], tiles[li], std::min(grid, tiles[li]), s,
-                           tot + (2 - li)));
+    BHIP(launch_group_step(64 << li, dset + first[li], na[li], tiles[li], s, tot + (2 - li)));
   }
   // round and admission counters of the set in one read-back
   BHIP(move_words(cnt, b->h_cnt_dev + (size_t)set * 2 * M, sizeof(unsigned long long) * 2 * M, s));
@@ -790,10 +807,9 @@ int dl_batch_tune(dl_batch* b, const int64_t* sizes_in, int32_t k, int32_t* tile
         }
         if (rc) break;
         hipError_t e = hipMemcpyAsync(ddesc, h.data(), sizeof(GroupDesc) * count, hipMemcpyHostToDevice, s);
-        const int grid = std::min(T == 256 ? b->cus : b->grid, tiles);
         const int reps = round == 0 ? 1 : 3;
         if (e == hipSuccess) e = hipEventRecord(ea, s);
-        for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_group_step(T, ddesc, count, tiles, grid, s);
+        for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_group_step(T, ddesc, count, tiles, s);
         if (e == hipSuccess) e = hipEventRecord(eb, s);
         if (e == hipSuccess) e = hipEventSynchronize(eb);
         float t = 0.f;

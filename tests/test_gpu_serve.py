@@ -476,3 +476,47 @@ def test_bulk_admission_and_release(dl, lookahead):
             assert np.array_equal(host(out), _oracle(r)), tag
             left.discard(tag)
     b.close()
+
+
+@pytest.mark.parametrize("sizes", [(1100,), (2048, 1500, 300), (1025, 1280, 2047), (1500, 1500, 1500, 1500, 900),
+                                   (3000, 64)])
+@pytest.mark.parametrize("lookahead", [0, 1])
+def test_large_requests_change_tiles(dl, sizes, lookahead):
+    """Large requests on 128 x 128 tiles while few of them run and on 256 x
+    256 tiles otherwise: the models and iteration counts of both kinds are
+    those of the request alone, with rounds of either tile within one
+    request's life (the others finish or are admitted later) and with the tile
+    set by the caller."""
+    for table in (None, [{"n": 16384, "tile": 256}], [{"n": 16384, "tile": 128}]):
+        b = dl.Batch(pool_bytes=sum(4 * ((n + 255) // 256 * 256) ** 2 for n in sizes) * 2, max_active=16,
+                     lookahead=lookahead)
+        if table:
+            b.set_tiles(table)
+        reqs = []
+        for i, n in enumerate(sizes):
+            for kind in (b.TC, b.SG):
+                edges = dlgen.er_edges(n, 2.0 / n, 50 + i) if kind == b.TC else dlgen.forest_edges(n, 60 + i)
+                reqs.append((kind, dev(dlgen.to_dense(n, edges))))
+        announce("serve tiles", sizes, lookahead, table)
+        late = list(range(1, len(reqs), 2))
+        for i in range(0, len(reqs), 2):
+            assert b.dl_batch_submit(*reqs[i], i) is not None
+        got = {}
+        rounds = 0
+        while len(got) < len(reqs):
+            if rounds == 2:
+                for i in late:
+                    assert b.dl_batch_submit(*reqs[i], i) is not None
+            b.dl_batch_step()
+            rounds += 1
+            assert rounds < 200
+            for tag, slot, iters in b.dl_batch_poll():
+                a = reqs[tag][1]
+                out = dev(np.empty(tuple(a.shape), dtype=np.uint8))
+                ones = b.dl_batch_fetch(slot, out)
+                got[tag] = (host(out), iters, ones)
+        for tag, (r, iters, ones) in got.items():
+            kind, a = reqs[tag]
+            want, it = dl.dl_tc(a, prec="i8") if kind == b.TC else dl.dl_sg(a, prec="i8")
+            assert np.array_equal(r, host(want)) and iters == it and ones == int(host(want).sum())
+        b.close()
