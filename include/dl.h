@@ -383,6 +383,16 @@ int dl_batch_poll(dl_batch* batch, int64_t* tags, int32_t* slots, int32_t* iters
  * before it is polled; dl_batch_poll then no longer reports it. */
 int dl_batch_fetch(dl_batch* batch, int32_t slot, uint8_t* R, int64_t ldr, int64_t* ones, void* stream);
 
+/* dl_batch_fetch for `count` finished requests with one launch, without
+ * waiting for it: the model of slots[i] is written into R[i] (device uint8
+ * [n x ldr[i]]; NULL to discard) in stream order, so work queued on `stream`
+ * afterwards sees it; elsewhere it is complete once the stream has reached
+ * this point.  ones[i] (host int64[count], may be NULL) receives its number of
+ * true entries.  Any invalid entry, or a slot listed twice, is DL_EINVAL, and
+ * then no slot has been freed. */
+int dl_batch_fetch_n(dl_batch* batch, int32_t count, const int32_t* slots, uint8_t* const* R, const int64_t* ldr,
+                     int64_t* ones, void* stream);
+
 /* dl_batch_fetch without the models for `count` finished requests: ones[i]
  * (host int64[count], may be NULL) receives the number of true entries of
  * slots[i]'s model, and every slot and its pool memory is freed.  A slot

@@ -93,6 +93,7 @@ def load() -> ctypes.CDLL:
         "dl_batch_submit_edges_n": ([vp, i32, pi32, pi64, ctypes.POINTER(vp), pi64, pi64, pi32, pi32, vp],
                                     ctypes.c_int),
         "dl_batch_release_n": ([vp, i32, pi32, pi64], ctypes.c_int),
+        "dl_batch_fetch_n": ([vp, i32, pi32, ctypes.POINTER(vp), pi64, pi64, vp], ctypes.c_int),
         "dl_batch_info": ([vp, pi32, pi32, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
         "dl_solve_linear": ([vp, i64, vp, i64, vp, i64, dbl, vp, i64, vp, i64, vp], ctypes.c_int),
         "dl_solve_two_sided": ([vp, i64, vp, i64, vp, i64, vp, i64, dbl, vp, i64, vp, i64, pi32, vp],
@@ -645,6 +646,28 @@ class Batch:
         self._bulk_edges.extend(edges[:got.value])
         _check(rc)
         return [int(slots[i]) for i in range(got.value)]
+
+    def dl_batch_fetch_n(self, slots, outs) -> list[int]:
+        """Write the models of finished requests into `outs` with one launch,
+        in stream order (the call does not wait for it); returns their numbers
+        of true entries and frees the slots."""
+        k = len(slots)
+        if len(outs) != k:
+            raise ValueError("one output per slot")
+        if k == 0:
+            return []
+        ss = (ctypes.c_int32 * k)(*[int(x) for x in slots])
+        ptrs = (ctypes.c_void_p * k)()
+        lds = (ctypes.c_int64 * k)()
+        for i, out in enumerate(outs):
+            _, lds[i] = _mat(out, "R")
+            ptrs[i] = out.data_ptr()
+        ones = (ctypes.c_int64 * k)()
+        _check(load().dl_batch_fetch_n(self._h, k, ss, ptrs, lds, ones, _stream_ptr(self.stream)))
+        if self.stream is not None:
+            for out in outs:  # not to be reused before the launch has written it
+                out.record_stream(self.stream)
+        return [int(ones[i]) for i in range(k)]
 
     def dl_batch_release_n(self, slots) -> list[int]:
         """Free finished requests without copying their models; returns their

@@ -2335,6 +2335,57 @@ hipError_t launch_emit(int prec, const void* S, int Np, int transpose, int n, ui
   return hipGetLastError();
 }
 
+// k_emit for int8 iterates of several requests at once, 64 rows x 256 columns
+// a workgroup (16 rows in flight at a time, 256 contiguous bytes of each).  The
+// descriptors travel as kernel arguments, so no buffer outlives the call.
+struct EmitGroup {
+  EmitDesc d[kEmitGroup];
+  int count;
+};
+
+__global__ void __launch_bounds__(256) k_emit_group(EmitGroup a) {
+  int lo = 0, hi = a.count - 1;  // the matrix of this tile: uniform over the workgroup
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.d[mid].tile_start <= (int)blockIdx.x) lo = mid;
+    else hi = mid - 1;
+  }
+  const EmitDesc& d = a.d[lo];
+  const int n = d.n, nt = (n + 255) / 256;
+  const int local = blockIdx.x - d.tile_start;
+  const int r0 = local / nt * 64 + (threadIdx.x >> 4), c = local % nt * 256 + (threadIdx.x & 15) * 16;
+  if (c >= n) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + 16 * q;
+    if (r >= n) break;
+    const uint8_t* src = d.S + (int64_t)r * d.Np + c;
+    uint8_t* dst = d.R + (int64_t)r * d.ldr + c;
+    if (c + 16 <= n) {
+      store16_any(dst, bool16_of<P_I8>(src));
+    } else {
+      for (int t = 0; c + t < n; ++t) dst[t] = src[t] != 0;
+    }
+  }
+}
+
+hipError_t launch_emit_group(const EmitDesc* d, int count, hipStream_t s) {
+  for (int first = 0; first < count; first += kEmitGroup) {
+    EmitGroup a{};
+    a.count = count - first < kEmitGroup ? count - first : kEmitGroup;
+    int tiles = 0;
+    for (int i = 0; i < a.count; ++i) {
+      a.d[i] = d[first + i];
+      a.d[i].tile_start = tiles;
+      tiles += ((a.d[i].n + 63) / 64) * ((a.d[i].n + 255) / 256);
+    }
+    if (tiles > 0) hipLaunchKernelGGL(k_emit_group, dim3(tiles), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Zero the ring slots of steps [s0, s0 + count) before they accumulate, and
 // optionally reset the convergence state.  A kernel, not a memset, so the
 // sequence stays valid under stream capture.

@@ -245,6 +245,17 @@ hipError_t launch_ingest(int prec, const uint8_t* A, int64_t lda, int n, int Np,
                          int8_t* AT8, void* Aop, void* ATop, int ident, unsigned long long* ones_slot,
                          hipStream_t s);
 hipError_t launch_identity(int prec, void* S, int Np, int n, hipStream_t s);
+// Models of several int8 iterates to callers' matrices in one launch.
+struct EmitDesc {
+  const uint8_t* S;  // Np x Np iterate
+  uint8_t* R;        // n x ldr
+  int64_t ldr;
+  int Np, n;
+  int tile_start;  // set by launch_emit_group
+  int pad;
+};
+constexpr int kEmitGroup = 64;  // matrices per launch: their descriptors are its arguments
+hipError_t launch_emit_group(const EmitDesc* d, int count, hipStream_t s);
 hipError_t launch_emit(int prec, const void* S, int Np, int transpose, int n, uint8_t* R,
                        int64_t ldr, hipStream_t s);
 hipError_t launch_ring_clear(unsigned long long* ones, int* conv, int s0, int count, int reset_conv,

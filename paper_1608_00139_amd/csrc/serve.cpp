@@ -147,6 +147,8 @@ struct dl_batch {
   int cus = 256;
   std::vector<int> finished;  // slots finished and not yet polled
   std::vector<int> order;     // issue_round's scratch: active slots, largest first
+  std::vector<EmitDesc> emit;  // dl_batch_fetch_n's scratch: matrices to write ...
+  std::vector<char> listed;    // ... and the slots listed so far
 };
 
 namespace {
@@ -275,6 +277,8 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
     if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess)
       return fail_destroy(bfail(DL_EHIP, "event creation failed"));
   b->pend.reserve(max_active);
+  b->emit.reserve(max_active);
+  b->listed.assign(max_active, 0);
   int cus = 256;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0) cus = prop.multiProcessorCount;
@@ -621,6 +625,31 @@ int complete_round(dl_batch* b, Round& rd, int* finished) {
   return DL_OK;
 }
 
+int fetchable(const dl_batch* b, int32_t slot, const uint8_t* R, int64_t ldr) {
+  if (!b || slot < 0 || slot >= b->max_active || !b->req[slot].used) return bfail(DL_EINVAL, "bad slot");
+  if (!b->req[slot].done) return bfail(DL_EINVAL, "request not finished");
+  if (R && ldr < b->req[slot].n) return bfail(DL_EINVAL, "ldr < n");
+  return DL_OK;
+}
+
+// The fixpoint iterate r.iters lives in buffer r.iters % 2 of its kind.
+const uint8_t* model_of(const Req& r) {
+  return r.kind == 0 ? r.b[2 * (int)(r.iters & 1)] : r.b[1 + (int)(r.iters & 1)];
+}
+
+// Frees a finished request's slot and pool memory.
+void release(dl_batch* b, int32_t slot, int64_t* ones_out) {
+  Req& r = b->req[slot];
+  if (ones_out) *ones_out = r.ones[r.iters];
+  // a request fetched before it was polled is no longer reported by dl_batch_poll
+  b->finished.erase(std::remove(b->finished.begin(), b->finished.end(), slot), b->finished.end());
+  if (b->inflight.live)
+    b->retire.push_back({r.off, r.bytes, b->inflight.seq});  // the round in flight may still read it
+  else
+    pool_free(b, r.off, r.bytes);
+  r = Req();
+}
+
 }  // namespace
 
 extern "C" {
@@ -684,26 +713,37 @@ int dl_batch_poll(dl_batch* b, int64_t* tags, int32_t* slots, int32_t* iters, in
 }
 
 int dl_batch_fetch(dl_batch* b, int32_t slot, uint8_t* R, int64_t ldr, int64_t* ones_out, void* stream) {
-  if (!b || slot < 0 || slot >= b->max_active || !b->req[slot].used) return bfail(DL_EINVAL, "bad slot");
-  Req& r = b->req[slot];
-  if (!r.done) return bfail(DL_EINVAL, "request not finished");
-  if (R && ldr < r.n) return bfail(DL_EINVAL, "ldr < n");
+  if (int rc = fetchable(b, slot, R, ldr)) return rc;
   hipStream_t s = (hipStream_t)stream;
   BHIP(hipSetDevice(b->device));
   if (R) {
-    // the fixpoint iterate r.iters lives in buffer r.iters % 2 of its kind
-    const uint8_t* src = r.kind == 0 ? r.b[2 * (int)(r.iters & 1)] : r.b[1 + (int)(r.iters & 1)];
-    BHIP(launch_emit(P_I8, src, (int)r.Np, 0, (int)r.n, R, ldr, s));
+    const Req& r = b->req[slot];
+    BHIP(launch_emit(P_I8, model_of(r), (int)r.Np, 0, (int)r.n, R, ldr, s));
     BHIP(hipStreamSynchronize(s));
   }
-  if (ones_out) *ones_out = r.ones[r.iters];
-  // a request fetched before it was polled is no longer reported by dl_batch_poll
-  b->finished.erase(std::remove(b->finished.begin(), b->finished.end(), slot), b->finished.end());
-  if (b->inflight.live)
-    b->retire.push_back({r.off, r.bytes, b->inflight.seq});  // the round in flight may still read it
-  else
-    pool_free(b, r.off, r.bytes);
-  r = Req();
+  release(b, slot, ones_out);
+  return DL_OK;
+}
+
+int dl_batch_fetch_n(dl_batch* b, int32_t count, const int32_t* slots, uint8_t* const* R, const int64_t* ldr,
+                     int64_t* ones, void* stream) {
+  if (!b || count < 0 || count > b->max_active || (count > 0 && (!slots || !R || !ldr)))
+    return bfail(DL_EINVAL, "bad fetch arguments");
+  std::vector<EmitDesc>& d = b->emit;
+  std::vector<char>& seen = b->listed;
+  d.clear();
+  std::fill(seen.begin(), seen.end(), 0);
+  for (int32_t i = 0; i < count; ++i) {
+    if (int rc = fetchable(b, slots[i], R[i], ldr[i])) return rc;
+    if (seen[slots[i]]) return bfail(DL_EINVAL, "a slot is listed twice");
+    seen[slots[i]] = 1;
+    const Req& r = b->req[slots[i]];
+    if (R[i]) d.push_back({model_of(r), R[i], ldr[i], (int)r.Np, (int)r.n, 0, 0});
+  }
+  BHIP(hipSetDevice(b->device));
+  BHIP(launch_emit_group(d.data(), (int)d.size(), (hipStream_t)stream));
+  // pool memory is reused by later launches of the same stream only
+  for (int32_t i = 0; i < count; ++i) release(b, slots[i], ones ? ones + i : nullptr);
   return DL_OK;
 }
 

@@ -76,6 +76,8 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
     if tiles is not None and batch is None:
         b.set_tiles(tiles)
     bulk = hasattr(b, "dl_batch_submit_edges_n") and hasattr(b, "dl_batch_release_n")
+    fetch_n = getattr(b, "dl_batch_fetch_n", None)
+    writing: deque = deque()  # (event, completions) of models being written on the batch's stream
     pending = deque(sorted(requests, key=lambda r: r.arrival))
     waiting: deque = deque()
     inflight = {}  # slot -> (req, admitted time)
@@ -83,6 +85,15 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
     stats = StreamStats()
     t0 = time.perf_counter()
     now = 0.0
+
+    def written(wait: bool = False) -> None:
+        """Time the completions whose models have been written."""
+        while writing and (wait or writing[0][0].query()):
+            ev, comps = writing.popleft()
+            ev.synchronize()
+            t = time.perf_counter() - t0
+            for c in comps:
+                c.finished = t
 
     def kind_of(req):
         return Batch.TC if req.kind == "tc" else Batch.SG
@@ -135,6 +146,7 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
         stats.max_active = max(stats.max_active, len(inflight))
         b.dl_batch_step()
         stats.rounds += 1
+        written()
         done = b.dl_batch_poll()
         if not done:
             continue
@@ -145,18 +157,34 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
             keep_of[slot] = (req.rid in keep_results) if isinstance(keep_results, set) else bool(keep_results)
         drop = [slot for _, slot, _ in done if not keep_of[slot]]
         ones_of = dict(zip(drop, b.dl_batch_release_n(drop))) if bulk else {}
+        keep = [slot for _, slot, _ in done if keep_of[slot]]
+        outs = {slot: torch.empty((inflight[slot][0].n,) * 2, dtype=torch.uint8, device="cuda") for slot in keep}
+        kept = []  # completions whose models the launch below writes
+        if keep and fetch_n is not None:
+            # one launch for all of them, and no wait: the next round is
+            # issued while the device still runs the one in flight
+            ones_of.update(zip(keep, fetch_n(keep, [outs[slot] for slot in keep])))
+            ev = torch.cuda.Event()
+            ev.record(b.stream if b.stream is not None else torch.cuda.current_stream())
+            writing.append((ev, kept))
         for tag, slot, iters in done:
             req, adm = inflight.pop(slot)
-            if keep_of[slot]:
-                out = torch.empty((req.n, req.n), dtype=torch.uint8, device="cuda")
-                ones = b.dl_batch_fetch(slot, out)
-                results[req.rid] = (out, iters)
-                t_fin = time.perf_counter() - t0
+            t_fin = fin
+            if slot in ones_of:
+                ones = ones_of[slot]
             else:
-                ones = ones_of[slot] if bulk else b.dl_batch_fetch(slot, None)
-                t_fin = fin
-            stats.completions.append(Completion(tag, 0 if req.kind == "tc" else 1, req.n, iters, ones,
-                                                req.arrival, adm, t_fin))
+                ones = b.dl_batch_fetch(slot, outs.get(slot))
+                if slot in outs:
+                    t_fin = time.perf_counter() - t0
+            if slot in outs:
+                results[req.rid] = (outs[slot], iters)
+            c = Completion(tag, 0 if req.kind == "tc" else 1, req.n, iters, ones, req.arrival, adm, t_fin)
+            stats.completions.append(c)
+            if slot in outs and fetch_n is not None:
+                kept.append(c)
+        if kept and not lookahead:
+            written(wait=True)  # nothing is in flight behind them
+    written(wait=True)
     if torch.cuda.is_available():
         torch.cuda.synchronize()
     stats.wall = time.perf_counter() - t0

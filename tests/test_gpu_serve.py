@@ -520,3 +520,63 @@ def test_large_requests_change_tiles(dl, sizes, lookahead):
             want, it = dl.dl_tc(a, prec="i8") if kind == b.TC else dl.dl_sg(a, prec="i8")
             assert np.array_equal(r, host(want)) and iters == it and ones == int(host(want).sum())
         b.close()
+
+
+@pytest.mark.parametrize("lookahead", [0, 1])
+@pytest.mark.parametrize("sizes", [(1, 15, 16, 17, 63, 64, 65), (255, 256, 257, 500, 1025), tuple(range(20, 90))])
+def test_fetch_many(dl, sizes, lookahead):
+    """dl_batch_fetch_n: the models of requests of both kinds, at the edges of
+    its 64 x 256 tiles and for more matrices than one launch takes, into
+    outputs of any stride and alignment with nothing written beside them; a
+    slot listed twice, an unfinished one and a short row are refused with
+    every slot kept; the memory it frees serves later requests."""
+    import torch
+
+    b = dl.Batch(pool_bytes=1 << 28, max_active=len(sizes) + 1, lookahead=lookahead)
+    rels = {}
+    announce("fetch many", sizes[0], len(sizes), lookahead)
+    for turn in range(2):
+        for i, n in enumerate(sizes):
+            kind = b.TC if (i + turn) % 3 else b.SG
+            e = dlgen.er_edges(n, min(1.0, 2.0 / n), 7 * n + turn) if kind == b.TC else dlgen.forest_edges(n, 8 * n + turn)
+            rels[i] = (kind, dlgen.to_dense(n, e))
+            assert b.dl_batch_submit(kind, dev(rels[i][1]), i) is not None
+        done = []
+        while b.dl_batch_step()[0]:
+            done += b.dl_batch_poll()
+        done += b.dl_batch_poll()
+        assert sorted(tag for tag, _, _ in done) == list(range(len(sizes)))
+        longest = 600
+        path = np.zeros((longest, longest), dtype=np.uint8)
+        path[np.arange(longest - 1), np.arange(1, longest)] = 1
+        running = b.dl_batch_submit(b.TC, dev(path), 999)
+        flats, outs, slots = [], [], []
+        for tag, slot, _ in done:
+            n, off = sizes[tag], 1 + tag % 5
+            flat = torch.full((off + n * (n + off) + 3,), 9, dtype=torch.uint8, device="cuda")
+            flats.append(flat)
+            outs.append(flat[off : off + n * (n + off)].view(n, n + off)[:, :n])
+            slots.append(slot)
+        with pytest.raises(dl.DLError):
+            b.dl_batch_fetch_n(slots + slots[:1], outs + outs[:1])
+        with pytest.raises(dl.DLError):
+            b.dl_batch_fetch_n(slots + [running], outs + [dev(path)])
+        if outs[-1].shape[0] > 1:
+            with pytest.raises(dl.DLError):
+                b.dl_batch_fetch_n(slots, outs[:-1] + [torch.empty((1, 1), dtype=torch.uint8, device="cuda")])
+        ones = b.dl_batch_fetch_n(slots, outs)
+        assert b.dl_batch_info()[0] <= 1
+        if turn == 0:
+            while b.dl_batch_step()[0]:
+                pass
+            b.dl_batch_poll()
+            b.dl_batch_release_n([running])
+        for (tag, _, iters), flat, out, count in zip(done, flats, outs, ones):
+            n, off = sizes[tag], 1 + tag % 5
+            kind, a = rels[tag]
+            want = oracle.tc_seminaive(a)[0] if kind == b.TC else oracle.sg_seminaive(a)[0]
+            f = host(flat)
+            rows = f[off : off + n * (n + off)].reshape(n, n + off)
+            assert np.array_equal(rows[:, :n], want) and count == int(want.sum()), (n, kind)
+            assert (rows[:, n:] == 9).all() and (f[:off] == 9).all() and (f[off + n * (n + off) :] == 9).all()
+    b.close()
