@@ -561,6 +561,7 @@ class Batch:
                                    ctypes.byref(self._h)))
         if lookahead:
             _check(lib.dl_batch_set_lookahead(self._h, int(lookahead)))
+        self.lookahead = int(lookahead)  # rounds, as set at creation
         self._cap = int(max_active)
         self._tags = (ctypes.c_int64 * self._cap)()
         self._slots = (ctypes.c_int32 * self._cap)()

@@ -182,8 +182,8 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
             stats.completions.append(c)
             if slot in outs and fetch_n is not None:
                 kept.append(c)
-        if kept and not lookahead:
-            written(wait=True)  # nothing is in flight behind them
+        if kept and not getattr(b, "lookahead", 0):
+            written(wait=True)  # the next round would be waited for as well
     written(wait=True)
     if torch.cuda.is_available():
         torch.cuda.synchronize()
