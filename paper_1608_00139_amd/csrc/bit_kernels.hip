@@ -47,29 +47,6 @@ namespace dl {
 
 typedef unsigned long long u64;
 
-__device__ inline unsigned bit16_of_bytes(u32x4 x) {
-  const u32x4 b = bytes01(x);
-  unsigned m = 0u;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    unsigned v = b[w];
-    v |= v >> 7;
-    v |= v >> 14;
-    m |= (v & 15u) << (4 * w);
-  }
-  return m;
-}
-
-__device__ inline u32x4 bytes_of_bit16(unsigned m) {
-  u32x4 x;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const unsigned v = (m >> (4 * w)) & 15u;
-    x[w] = (v * 0x00204081u) & 0x01010101u;
-  }
-  return x;
-}
-
 // Bits 16 q .. 16 q + 15 of w as 16 int8 operand elements, nonzero where the
 // bit is set: 1, 2, 4 or 8, which v_perm and one mask give (the product's sums
 // of at most 2048 terms <= 64 stay positive int32 numbers, and only their

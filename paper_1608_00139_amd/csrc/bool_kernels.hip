@@ -1650,9 +1650,10 @@ k_nt_dma(NTParams p) {
 
 // Epilogue of a stream-K part (k_nt_dma_sk).  The 0/1 segments are packed as
 // in dma_epilogue_swapped.  A tile with several contributors: every one
-// stores its segments in its scratch slot with write-through stores, waits
-// for them, and counts itself in tile_cnt[t]; the last to arrive ORs in the
-// other slots (device-scope loads), clears the counter and finishes the tile:
+// stores its elements as bits in its scratch slot (a thread's 64 in one word,
+// so all contributors use the same order) with write-through stores, waits
+// for them, and counts itself in tile_cnt[t]; the last to arrive ORs the
+// slots (device-scope loads), clears the counter and finishes the tile:
 // identity on the diagonal tile, count, stores of the tile and (off the
 // diagonal) of its mirror image.  Returns the ones it adds to the model
 // size (an off-diagonal tile counts for its mirror too).
@@ -1662,7 +1663,7 @@ __device__ int dma_epilogue_sk(const NTParams& p, const SkParams& q, const typen
                                bool diag_tile) {
   static_assert(K::FR == 16 && Op::NI == 4 && __is_same(typename Op::Acc, v4i), "int8 16 x 16 fragments");
   constexpr int BM = K::WAVES_M * K::FM * K::FR, BN = K::WAVES_N * K::FN * K::FR;
-  static_assert(BM == 256 && BN == 256, "65536-byte slots");
+  static_assert(BM * BN == 8 * (int)kSkSlot, "slots of one bit an element");
   constexpr int NSEG = K::FM * (K::FN / 4);
   auto seg_row = [&](int e) { return wm * (K::FM * 16) + 16 * (e / (K::FN / 4)) + (lane & 15); };
   auto seg_col = [&](int e) { return wn * (K::FN * 16) + 16 * (4 * (e % (K::FN / 4)) + (lane >> 4)); };
@@ -1682,11 +1683,11 @@ __device__ int dma_epilogue_sk(const NTParams& p, const SkParams& q, const typen
     }
   }
   if (sk.nc > 1) {
-    constexpr unsigned kSlot = BM * BN;
+    static_assert(NSEG == 4 && K::NT * 8 == (int)kSkSlot, "a thread's 64 elements are one word of bits");
     __shared__ int s_last;
-    const __amdgpu_buffer_rsrc_t mine = buffer_of(q.scratch + ((size_t)sk.t * q.maxc + sk.my) * kSlot, kSlot);
-#pragma unroll
-    for (int e = 0; e < NSEG; ++e) st_agent_x4(mine, seg_row(e) * BN + seg_col(e), vs[e]);
+    const __amdgpu_buffer_rsrc_t mine = buffer_of(q.scratch + ((size_t)sk.t * q.maxc + sk.my) * kSkSlot, kSkSlot);
+    st_agent_x2(mine, tid * 8, bit16_of_bytes(vs[0]) | bit16_of_bytes(vs[1]) << 16,
+                bit16_of_bytes(vs[2]) | bit16_of_bytes(vs[3]) << 16);
     wait_stores();
     __syncthreads();
     if (tid == 0) {
@@ -1696,13 +1697,17 @@ __device__ int dma_epilogue_sk(const NTParams& p, const SkParams& q, const typen
     }
     __syncthreads();
     if (!s_last) return 0;
+    const __amdgpu_buffer_rsrc_t tile = buffer_of(q.scratch + (size_t)sk.t * q.maxc * kSkSlot, q.maxc * kSkSlot);
+    unsigned lo = 0u, hi = 0u;  // all contributors' bits, this workgroup's among them
     for (int k = 0; k < sk.nc; ++k) {
-      if (k == sk.my) continue;
-      const __amdgpu_buffer_rsrc_t other = buffer_of(q.scratch + ((size_t)sk.t * q.maxc + k) * kSlot, kSlot);
-#pragma unroll
-      for (int e = 0; e < NSEG; ++e)
-        vs[e] |= __builtin_amdgcn_raw_buffer_load_b128(other, seg_row(e) * BN + seg_col(e), 0, kCpolSc1);
+      const auto w = __builtin_amdgcn_raw_buffer_load_b64(tile, k * (int)kSkSlot + tid * 8, 0, kCpolSc1);
+      lo |= w[0];
+      hi |= w[1];
     }
+    vs[0] = bytes_of_bit16(lo & 0xffffu);
+    vs[1] = bytes_of_bit16(lo >> 16);
+    vs[2] = bytes_of_bit16(hi & 0xffffu);
+    vs[3] = bytes_of_bit16(hi >> 16);
     if (tid == 0) st_agent(q.tile_cnt + sk.t, 0u);
   }
   uint8_t* outb = (uint8_t*)p.out;
@@ -1798,7 +1803,7 @@ void sk_plan(int64_t Np, SkParams& q) {
 }
 
 size_t sk_scratch_bytes(const SkParams& q) {
-  return (size_t)q.tiles * q.maxc * 65536 + ((size_t)q.tiles * sizeof(unsigned) + 255) / 256 * 256;
+  return (size_t)q.tiles * q.maxc * kSkSlot + ((size_t)q.tiles * sizeof(unsigned) + 255) / 256 * 256;
 }
 
 hipError_t launch_nt_sym_sk(const NTParams& p, const SkParams& q, hipStream_t s) {

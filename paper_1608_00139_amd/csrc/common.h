@@ -211,13 +211,14 @@ hipError_t launch_nt_step(int prec, int cfg_id, const NTParams& p, hipStream_t s
 // computed, their tiles x (Np / 128) K slices dealt to the workgroups in runs
 // of `share` slices, so that every compute unit gets the same number of
 // slices.  A tile split over several workgroups is finished by the last of
-// them to arrive: each stores its partial 0/1 tile in scratch slot
+// them to arrive: each stores its partial Boolean tile as bits in scratch slot
 // (t * maxc + contributor) with write-through stores and counts itself in
-// tile_cnt[t]; the last ORs the others' partials (device-scope loads), adds
+// tile_cnt[t]; the last ORs the partials (device-scope loads), adds
 // the identity, counts, writes the tile and its mirror image and clears
 // tile_cnt[t] for the next launch.  tile_cnt starts at zero.
+constexpr unsigned kSkSlot = 256 * 256 / 8;
 struct SkParams {
-  uint8_t* scratch;    // tiles * maxc slots of 65536 bytes
+  uint8_t* scratch;    // tiles * maxc slots of kSkSlot bytes
   unsigned* tile_cnt;  // [tiles] arrivals, zero between launches
   int side;            // tiles per side, Np / 256
   int tiles;           // side (side + 1) / 2

@@ -22,6 +22,30 @@ __device__ inline u32x4 bytes01(u32x4 x) {
   return x & 0x01010101u;
 }
 
+// 16 bytes as 16 bits (nonzero or not), and back to 0/1 bytes.
+__device__ inline unsigned bit16_of_bytes(u32x4 x) {
+  const u32x4 b = bytes01(x);
+  unsigned m = 0u;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    unsigned v = b[w];
+    v |= v >> 7;
+    v |= v >> 14;
+    m |= (v & 15u) << (4 * w);
+  }
+  return m;
+}
+
+__device__ inline u32x4 bytes_of_bit16(unsigned m) {
+  u32x4 x;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const unsigned v = (m >> (4 * w)) & 15u;
+    x[w] = (v * 0x00204081u) & 0x01010101u;
+  }
+  return x;
+}
+
 __device__ inline int wave_sum(int v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -238,7 +238,7 @@ class Fix {
       if (sk_supported(prec_, cfg_, Np_)) {
         sk_plan(Np_, skq_);
         skq_.scratch = sl_.ws + 4 * matT;
-        skq_.tile_cnt = (unsigned*)(skq_.scratch + (size_t)skq_.tiles * skq_.maxc * 65536);
+        skq_.tile_cnt = (unsigned*)(skq_.scratch + (size_t)skq_.tiles * skq_.maxc * kSkSlot);
         DL_HIP(hipMemsetAsync(skq_.tile_cnt, 0, (size_t)skq_.tiles * sizeof(unsigned), s_));
         use_sk_ = true;
       }
