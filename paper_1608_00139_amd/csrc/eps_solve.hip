@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "common.h"
+#include "device.h"
 #include "eps_solve.h"
 
 namespace dl {
@@ -78,6 +79,8 @@ struct SteinStop {
   }
 };
 
+typedef double v2d __attribute__((ext_vector_type(2)));
+
 struct GemmArgs {
   const double* A; int64_t lda;
   const double* B; int64_t ldb;
@@ -95,6 +98,11 @@ struct GemmArgs {
   const double* B2 = nullptr;
   double* D2 = nullptr;
   SteinStop stop;
+  // K split between the owner of a tile and a helper (template SPLIT)
+  double* part = nullptr;     // one partial tile per tile
+  unsigned* state = nullptr;  // per tile: arrivals, kPartReady; zero between launches
+  int full = 0;               // tiles before the split ones, each a workgroup's own
+  int helpers = 0;
 };
 
 // Copies rows x cols doubles (cols even, rows 16-byte aligned) with the 256
@@ -157,11 +165,33 @@ __device__ inline void dgemm_wait_slice(int later) {
   }
 }
 
-template <int BM, int BN, int STAGES, bool BT = false, int ACC = ACC_NONE>
-__global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(GemmArgs g) {
+// SPLIT: the tiles of a product's last pass, t of them, leave slots of the chip
+// (two workgroups to a compute unit) without a tile.  Those get helpers:
+// helper h takes the last K slices of the c tiles q with q helpers / t = h,
+// K / (c + 1) of each, and the owner of a tile the others, so that all
+// workgroups have about the same number of slices.  Whichever of the two
+// finishes second adds the other's partial tile to its own: the first arrival
+// stores its partial with write-through stores and then marks it ready, and
+// the second waits for that mark -- of a workgroup that is running and waits
+// for nobody -- so no workgroup ever waits for one that may not have started.
+// A sum of two is the same in either order, so results do not depend on who
+// was first.
+constexpr unsigned kPartReady = 1u << 16;
+struct SplitPlan {
+  int first, count;  // tiles of a helper
+  __host__ __device__ SplitPlan(int t, int helpers, int h) {
+    first = (int)(((int64_t)h * t + helpers - 1) / helpers);
+    count = (int)(((int64_t)(h + 1) * t + helpers - 1) / helpers) - first;
+  }
+  // K slices of nk that the owners of its tiles keep
+  __host__ __device__ int owner_slices(int nk) const { return nk - (nk + count / 2) / (count + 1); }
+};
+
+template <int BM, int BN, int STAGES, bool BT = false, int ACC = ACC_NONE, bool SPLIT = false>
+__global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : BN == 128 && (SPLIT || ACC == ACC_SYM) ? 2 : 1) k_dgemm(GemmArgs g) {
   typedef Dgemm<BM, BN, STAGES> T;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   // the variant that runs beside a trailing update (see gj_blocks) issues first
@@ -171,19 +201,41 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
     return;
   }
   const int tiles_m = g.M / BM;
+  // this workgroup's pieces: tiles first .. first + pieces - 1, slices kb .. ke - 1 of each
+  const int nk = g.K / 16;
+  int first = (int)blockIdx.x, pieces = 1, kb = 0, ke = nk;
+  if constexpr (SPLIT) {
+    const int t = (int)gridDim.x - g.full - g.helpers, q = first - g.full;
+    if (q >= 0) {
+      const SplitPlan plan(t, g.helpers, q < t ? (int)((int64_t)q * g.helpers / t) : q - t);
+      if (q < t) {
+        ke = plan.owner_slices(nk);
+      } else {
+        kb = plan.owner_slices(nk);
+        first = g.full + plan.first;
+        pieces = plan.count;
+      }
+    }
+  }
+  for (int piece = 0; piece < (SPLIT ? pieces : 1); ++piece) {
+  const int tile = first + piece;
+  // split: nothing derived from the lane stays in registers from piece to piece
+  if constexpr (SPLIT) asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
+  int lane = tid & 63;
+  if (SPLIT && piece > 0) __syncthreads();  // every wave is done with the ring
   int m0, n0;
   if constexpr (ACC == ACC_SYM) {
-    // block q of the upper triangle in column order, sub-tile blockIdx % (BN / BM)
-    const int q = (int)blockIdx.x / (BN / BM);
+    // block q of the upper triangle in column order, sub-tile tile % (BN / BM)
+    const int q = tile / (BN / BM);
     int tn = (int)((sqrtf(8.0f * (float)q + 1.0f) - 1.0f) * 0.5f);
     while (tn * (tn + 1) / 2 > q) --tn;
     while ((tn + 1) * (tn + 2) / 2 <= q) ++tn;
-    m0 = (q - tn * (tn + 1) / 2) * BN + ((int)blockIdx.x % (BN / BM)) * BM;
+    m0 = (q - tn * (tn + 1) / 2) * BN + (tile % (BN / BM)) * BM;
     n0 = tn * BN;
   } else {
     // column-major walk over tiles keeps one B column panel hot across rows
-    int b = (int)blockIdx.x;
-    if (g.A2) {
+    int b = tile;
+    if (!SPLIT && g.A2) {
       const int tiles = tiles_m * (g.N / BN);
       if (b >= tiles) {
         b -= tiles;
@@ -195,17 +247,17 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
     m0 = b % tiles_m * BM;
     n0 = b / tiles_m * BN;
   }
-  if (n0 >= g.N) {  // past the product: a copying workgroup
+  if (!SPLIT && n0 >= g.N) {  // past the product: a copying workgroup
     const int r0 = ((int)blockIdx.x - tiles_m * (g.N / BN)) * kCopyRows;
     copy_block(g.cs + (int64_t)r0 * g.csld, g.csld, g.cd + (int64_t)r0 * g.cdld, g.cdld,
                min(kCopyRows, g.copy_rows - r0), g.copy_cols);
     return;
   }
-  if (g.prow >= 0 && m0 >= g.prow && m0 < g.prow + g.np) {
+  if (!SPLIT && g.prow >= 0 && m0 >= g.prow && m0 < g.prow + g.np) {
     copy_block(g.B + (int64_t)(m0 - g.prow) * g.ldb + n0, g.ldb, g.D + (int64_t)m0 * g.ldd + n0, g.ldd, BM, BN);
     return;
   }
-  const bool in_pcol = g.pcol >= 0 && n0 >= g.pcol && n0 < g.pcol + g.np;
+  const bool in_pcol = !SPLIT && g.pcol >= 0 && n0 >= g.pcol && n0 < g.pcol + g.np;
   if (in_pcol && g.pmode == 2) {
     copy_block(g.A + (int64_t)m0 * g.lda + (n0 - g.pcol), g.lda, g.D + (int64_t)m0 * g.ldd + n0, g.ldd, BM, BN);
     return;
@@ -234,7 +286,7 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
   }
   auto issue = [&](int kt, int slot) {
     uint8_t* stage = lds + slot * T::kSlice;
-    const int k0 = kt * 16;
+    const int k0 = (kb + kt) * 16;
 #pragma unroll
     for (int jj = 0; jj < T::kA; ++jj)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc[jj] + k0),
@@ -265,15 +317,15 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
     }
   };
 
-  const int nk = g.K / 16;
+  const int nks = ke - kb;
 #pragma unroll
   for (int s0 = 0; s0 < STAGES - 1; ++s0)
-    if (s0 < nk) issue(s0, s0);
+    if (s0 < nks) issue(s0, s0);
 
   // the accumulators from C while the first slices are in flight
   v4d acc[T::FM][T::FN];
   const double csgn = g.cmode == 1 ? -1.0 : 1.0;
-  if (g.cmode && !in_pcol) {
+  if (!SPLIT && g.cmode && !in_pcol) {
 #pragma unroll
     for (int i = 0; i < T::FM; ++i)
 #pragma unroll
@@ -292,13 +344,13 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
   }
 
   int slot = 0;
-  for (int kt = 0; kt < nk; ++kt) {
+  for (int kt = 0; kt < nks; ++kt) {
     // slice kt has landed once at most the later slices' instructions are
     // outstanding; the barrier extends that to every wave and retires every
     // read of the slot before it in the ring, refilled below
-    dgemm_wait_slice<T::kA + T::kB, STAGES>(nk - 1 - kt);
+    dgemm_wait_slice<T::kA + T::kB, STAGES>(nks - 1 - kt);
     __builtin_amdgcn_s_barrier();
-    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
+    if (kt + STAGES - 1 < nks) issue(kt + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
     const uint8_t* st = lds + slot * T::kSlice;
     slot = slot + 1 == STAGES ? 0 : slot + 1;
     double af[2][T::FM], bf[2][T::FN];
@@ -314,6 +366,54 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
     }
   }
 
+  if constexpr (SPLIT || BM * BN == 128 * 128) {
+    // re-derived: addresses computed from it are not kept live across the products
+    asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
+    lane = tid & 63;
+  }
+  if (SPLIT && tile >= g.full) {
+    // element pair e of thread tid at 16 (256 e + tid): the same in either piece
+    constexpr int kPairs = T::FM * T::FN * 2;
+    constexpr unsigned kTile = BM * BN * 8;
+    static_assert(kPairs * 256 * 16 == (int)kTile, "the partial tile");
+    __shared__ unsigned s_before;
+    const __amdgpu_buffer_rsrc_t part = buffer_of((uint8_t*)g.part + (size_t)(tile - g.full) * kTile, kTile);
+    unsigned* state = g.state + (tile - g.full);
+    __syncthreads();
+    if (tid == 0) s_before = __hip_atomic_fetch_add(state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if ((s_before & (kPartReady - 1)) == 0u) {  // first: leave the partial tile to the other
+#pragma unroll
+      for (int e = 0; e < kPairs; ++e) {
+        const v4d& x = acc[e / 2 / T::FN][e / 2 % T::FN];
+        st_agent_x4(part, (256 * e + tid) * 16, __builtin_bit_cast(u32x4, v2d{x[2 * (e & 1)], x[2 * (e & 1) + 1]}));
+      }
+      wait_stores();
+      __syncthreads();
+      if (tid == 0) __hip_atomic_fetch_add(state, kPartReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      continue;
+    }
+    if (tid == 0) {
+      while (ld_agent(state) < kPartReady) __builtin_amdgcn_s_sleep(2);
+      st_agent(state, 0u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kPairs; e += 4) {
+      v2d w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        w[u] = __builtin_bit_cast(
+            v2d, __builtin_amdgcn_raw_buffer_load_b128(part, (256 * (e + u) + tid) * 16, 0, kCpolSc1));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v4d& x = acc[(e + u) / 2 / T::FN][(e + u) / 2 % T::FN];
+        x[2 * (u & 1)] += w[u][0];
+        x[2 * (u & 1) + 1] += w[u][1];
+      }
+      __builtin_amdgcn_sched_barrier(0);  // four loads in flight: more would spill accumulators
+    }
+  }
   int pos = 0, chg = 0;
   const bool mirror = ACC == ACC_SYM && m0 / BN < n0 / BN;
 #pragma unroll
@@ -334,6 +434,8 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
           chg += y != x;
           *d = y;
           if (mirror) g.D[col * g.ldd + row] = y;
+          if constexpr (BM * BN == 128 * 128)
+            if (v == 3) __builtin_amdgcn_sched_barrier(0);  // more loads in flight would spill accumulators
         }
       }
   if constexpr (ACC != ACC_NONE) {
@@ -352,6 +454,7 @@ __global__ void __launch_bounds__(256, BM == 32 && STAGES == 2 ? 6 : 1) k_dgemm(
       if (t) atomicAdd(g.stop.cnt + 2 * g.stop.j + tid, (unsigned long long)(mirror ? 2 * t : t));
     }
   }
+  }
 }
 
 template <int BM, int BN, int STAGES, bool BT, int ACC>
@@ -367,6 +470,13 @@ static hipError_t dgemm_launch(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, bool BT, int ACC>
+static hipError_t dgemm_launch_split(const GemmArgs& g, int tiles, hipStream_t s) {
+  hipLaunchKernelGGL((k_dgemm<BM, BN, 2, BT, ACC, true>), dim3((unsigned)(tiles + g.helpers)), dim3(256),
+                     (Dgemm<BM, BN, 2>::kLds), s, g);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int STAGES, bool BT, int ACC>
 static hipError_t dgemm_attr() {
   return hipFuncSetAttribute((const void*)k_dgemm<BM, BN, STAGES, BT, ACC>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -375,7 +485,7 @@ static hipError_t dgemm_attr() {
 
 template <bool BT, int ACC>
 static hipError_t dgemm_attrs() {
-  hipError_t e = dgemm_attr<128, 128, 2, BT, ACC>();
+  hipError_t e = dgemm_attr<ACC == ACC_SYM ? 64 : 128, 128, 2, BT, ACC>();
   if (e == hipSuccess) e = dgemm_attr<64, 64, 3, BT, ACC>();
   if (e == hipSuccess) e = dgemm_attr<32, 64, 4, BT, ACC>();
   return e;
@@ -394,14 +504,34 @@ static hipError_t dgemm_attrs() {
 //    products, so small tiles stay bound by the products.
 // D aliasing B needs one row of tiles (128 rows, each workgroup reads its
 // whole B panel before it writes): 128 x 64.
+//  - with room for partial tiles (g.part), a last pass of 257 to 460 of the 512
+//    slots is split (SPLIT).  M = N = K = 2304, 2560, 2688: 402, 540, 612 us;
+//    whole 128 x 128 tiles 573, 633, 668, 64 x 64 tiles 463, 594, 633.  From
+//    there on the slots left are too few (2816, 484 tiles: 753 against 695).
+// A symmetric product takes halves of the 128 x 128 tiles, since the whole
+// tile's epilogue does not fit in the registers of two workgroups to a compute
+// unit (2816: 382 against 406 us), and splits them where 64 x 64 tiles fill
+// their passes to less than 85% (2048, 2560: 199, 317 us against 210, 352;
+// 2432, filled to 96%: 261 against 252).
+constexpr int kSplitSlots = 512;
 template <bool BT = false, int ACC = ACC_NONE>
 static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.M % 128 || g.N % 128 || g.K % 16) return hipErrorInvalidValue;
+  constexpr int BM = ACC == ACC_SYM ? 64 : 128;
   const int64_t side = g.N / 128;
   const int64_t t = ACC == ACC_SYM ? side * (side + 1) / 2 : (g.A2 ? 2 : 1) * (int64_t)(g.M / 128) * side;
-  const int64_t slots = (t + 255) / 256 * 256;
-  if (t * 100 >= slots * 85) return dgemm_launch<128, 128, 2, BT, ACC>(g, s);
+  auto fills = [](int64_t tiles) { return tiles * 100 >= (tiles + 255) / 256 * 256 * 85; };
+  if (g.part && !g.A2 && !(ACC == ACC_SYM && fills(side * (2 * side + 1)))) {
+    const int64_t tiles = t * (128 / BM), last = tiles % kSplitSlots;
+    if (last > kSplitSlots / 2 && last <= 460) {
+      GemmArgs h = g;
+      h.full = (int)(tiles - last);
+      h.helpers = kSplitSlots - (int)last;
+      return dgemm_launch_split<BM, 128, BT, ACC>(h, (int)tiles, s);
+    }
+  }
+  if (fills(t)) return dgemm_launch<BM, 128, 2, BT, ACC>(g, s);
   return 4 * t > 256 ? dgemm_launch<64, 64, 3, BT, ACC>(g, s) : dgemm_launch<32, 64, 4, BT, ACC>(g, s);
 }
 
@@ -610,7 +740,6 @@ k_block_inverse(const double* W, int64_t ld, double* Dinv, int64_t ldd) {
 // ----------------------------------------------------------------- setup / copy / emit
 // Four consecutive doubles, two 16-byte accesses; 8-byte alignment for the
 // caller's matrices (their stride may be odd).
-typedef double v2d __attribute__((ext_vector_type(2)));
 typedef v2d v2d_8 __attribute__((aligned(8)));
 typedef unsigned u32_any __attribute__((aligned(1)));
 
@@ -762,6 +891,7 @@ hipError_t eps_kernels_init() {
   hipError_t e = dgemm_attrs<false, ACC_NONE>();
   if (e == hipSuccess) e = dgemm_attrs<false, ACC_ADD>();
   if (e == hipSuccess) e = dgemm_attrs<true, ACC_SYM>();
+  // the split products' rings are 64 KB or less: no attribute
   return e;
 }
 
@@ -1170,7 +1300,13 @@ __global__ void __launch_bounds__(256) k_count_positive(const double* X, int64_t
   }
 }
 
-// The counts of a doubling loop, zeroed; counts[0] starts at `first`.
+// The words of a doubling loop: its counts, counts[0] starting at `first`, and
+// behind those of kSteinDoublings doublings the states of the split products'
+// tiles; all zeroed.
+constexpr int kSteinDoublings = 127;
+constexpr int kSteinState = 2 * (kSteinDoublings + 1);
+constexpr int kSteinWords = kSteinState + kSplitSlots / 2;
+static_assert(kSteinWords <= kRing, "the ring of a slot");
 __global__ void __launch_bounds__(256) k_stein_clear(unsigned long long* cnt, int words, unsigned long long first) {
   for (int i = threadIdx.x; i < words; i += 256) cnt[i] = i == 0 ? first : 0ull;
 }
@@ -1211,7 +1347,7 @@ k_f64_emit(const double* X, int Np, int n, uint8_t* S, int64_t lds, double* Xo, 
 // per group: a doubling after the last one costs its empty launches only.
 // Against each product its own full launch, the squares before the check, a
 // read-back per doubling and separate passes for the transpose and the sum:
-// same generation, n = 2500, five doublings 9.4 -> 6.7 ms; two-sided, n =
+// same generation, n = 2500, five doublings 9.4 -> 6.7 ms (5.9 with split products); two-sided, n =
 // 1024, six doublings 1.65 -> 1.07 ms.
 static hipError_t stein_doubling(int64_t Np, double* X, double* B, double* C, double* T, double* Bn, double* Cn,
                                  bool t_ready, bool want_values, int max_doublings, hipStream_t s,
@@ -1225,6 +1361,9 @@ static hipError_t stein_doubling(int64_t Np, double* X, double* B, double* C, do
     const int group = std::min(issued == 0 ? 4 : 2, max_doublings - issued);
     for (int q = 0; q < group; ++q) {
       const int j = ++issued;
+      // partial tiles of the split products: the square's fit in T, which holds
+      // nothing then, the others' in Bn
+      unsigned* state = max_doublings <= kSteinDoublings ? (unsigned*)(counts + kSteinState) : nullptr;
       SteinStop stop;
       stop.cnt = counts;
       stop.j = j;
@@ -1232,6 +1371,8 @@ static hipError_t stein_doubling(int64_t Np, double* X, double* B, double* C, do
       if (j > 1) {
         GemmArgs sq{B, Np, B, Np, nullptr, 0, Bn, Np, N, N, N, 0};
         sq.stop = stop;
+        sq.part = state ? T : nullptr;
+        sq.state = state;
         if (C) {
           sq.A2 = C;
           sq.B2 = C;
@@ -1244,10 +1385,14 @@ static hipError_t stein_doubling(int64_t Np, double* X, double* B, double* C, do
       if (j > 1 || !t_ready) {
         GemmArgs tx{B, Np, X, Np, nullptr, 0, T, Np, N, N, N, 0};
         tx.stop = stop;
+        tx.part = state ? Bn : nullptr;
+        tx.state = state;
         EPS_CK(dgemm(tx, s), "B X");
       }
       GemmArgs ac{T, Np, C ? C : B, Np, nullptr, 0, X, Np, N, N, N, 0};
       ac.stop = stop;
+      ac.part = state ? Bn : nullptr;
+      ac.state = state;
       EPS_CK((C ? dgemm<false, ACC_ADD>(ac, s) : dgemm<true, ACC_SYM>(ac, s)), "T C");
     }
     EPS_CK(launch_publish(counts, h_counts_dev, 2 * (issued + 1), s), "readback");
@@ -1281,7 +1426,8 @@ hipError_t sg_eps_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, const u
                      eps, 1, X);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, P, ldp, (int)n, (int)Np, se, 0, A);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, P, ldp, (int)n, (int)Np, se * eps, 0, T);
-  hipLaunchKernelGGL(k_stein_clear, dim3(1), dim3(256), 0, s, counts, 2 * (max_doublings + 1), (unsigned long long)n);
+  hipLaunchKernelGGL(k_stein_clear, dim3(1), dim3(256), 0, s, counts, std::max(2 * (max_doublings + 1), kSteinWords),
+                     (unsigned long long)n);
   EPS_CK(hipGetLastError(), "init");
   bool done = false;
   EPS_CK(stein_doubling(Np, X, A, nullptr, T, An, nullptr, true, X_out != nullptr, max_doublings, s, counts, h_counts,
@@ -1314,7 +1460,7 @@ hipError_t two_sided_solve(EpsWorkspace* ws, size_t budget_left, int64_t n, cons
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, Q, ldq, (int)n, (int)Np, eps, 0, X);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, B, ldb, (int)n, (int)Np, se, 0, Bd);
   hipLaunchKernelGGL(k_f64_from_bytes, rows, dim3(256), 0, s, C, ldc, (int)n, (int)Np, se, 0, Cd);
-  hipLaunchKernelGGL(k_stein_clear, dim3(1), dim3(256), 0, s, counts, 2 * (max_doublings + 1), 0ull);
+  hipLaunchKernelGGL(k_stein_clear, dim3(1), dim3(256), 0, s, counts, std::max(2 * (max_doublings + 1), kSteinWords), 0ull);
   hipLaunchKernelGGL(k_count_positive, dim3(kElemGrid), dim3(256), 0, s, (const double*)X, (int64_t)mat, counts);
   EPS_CK(hipGetLastError(), "init");
   bool done = false;

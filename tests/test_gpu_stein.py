@@ -112,3 +112,36 @@ def test_column_norm_bound(dl, n):
     dl.dl_solve_two_sided(dev(z), dev(b), dev(c), 1.0 / (1 + n))
     with pytest.raises(dl.DLError):
         dl.dl_solve_two_sided(dev(z), dev(b), dev(c), 1.0 / (1 + n) * 1.001)
+
+
+@pytest.mark.parametrize("n", [1930, 2100, 2250, 2688, 3500])
+def test_split_products_same_generation(dl, n):
+    """Sizes whose last pass of tiles is shared between owners and helpers
+    (about half and nearly all of the slots in use; 3500 after a full pass):
+    the equation's solution, and bit for bit the same one every time."""
+    p = dlgen.to_dense(n, dlgen.forest_edges(n, 3 * n))
+    d = int(p.sum(axis=1).max())
+    eps = 1.0 / (1 + d * d)
+    announce("stein split sg", n)
+    s, x, k = dl.dl_sg_eps(dev(p), eps, want_x=True)
+    xs = host(x)
+    want = _fixpoint(np.eye(n), p, p.T, eps)
+    np_ = (n + 127) // 128 * 128
+    assert np.all(np.abs(xs - want) <= 8 * np_ * max(k, 1) * 2.0 ** -53 * want)
+    assert np.array_equal(xs, xs.T) and np.array_equal(host(s), (xs > 0).astype(np.uint8))
+    for _ in range(3):
+        assert np.array_equal(host(dl.dl_sg_eps(dev(p), eps, want_x=True)[1]), xs)
+
+
+@pytest.mark.parametrize("n", [2100, 2560, 2688])
+def test_split_products_two_sided(dl, n):
+    q, b, c = (dlgen.to_dense(n, dlgen.er_edges(n, 2.0 / n, 5 * n + i)) for i in range(3))
+    eps = 0.5 / (1 + int(b.sum(axis=1).max()) * int(c.sum(axis=0).max()))
+    announce("stein split two-sided", n)
+    r, x, k = dl.dl_solve_two_sided(dev(q), dev(b), dev(c), eps, want_x=True)
+    xs = host(x)
+    want = _fixpoint(q, b, c, eps)
+    np_ = (n + 127) // 128 * 128
+    assert np.all(np.abs(xs - want) <= 8 * np_ * max(k, 1) * 2.0 ** -53 * want)
+    assert np.array_equal(host(r), (xs > 0).astype(np.uint8))
+    assert np.array_equal(host(dl.dl_solve_two_sided(dev(q), dev(b), dev(c), eps, want_x=True)[1]), xs)
