@@ -556,14 +556,10 @@ size_t small_lds_bytes(int64_t ldb) { return (size_t)64 * ldb + kSmallPart + 32 
 // groups 1..3 handing their partial sums to group 0 through LDS, which
 // writes the 0/1 result into the epilogue tile et (32 rows of kSmallEst
 // bytes).  Called by all kSmallThreads threads; ends before the barrier
-// that publishes et.  With XBYTES (fp32 only) the 32 X rows are 0/1 bytes
-// instead, xrow bytes per row from the start of the LDS image with the
-// 16-byte chunk c of row r at c ^ (r & 15), and each lane turns the four
-// bytes behind its operand chunk into four floats.
-template <class Op, bool XBYTES = false>
+// that publishes et.
+template <class Op>
 __device__ inline void small_tile_product(uint8_t* smem, int64_t ldb, int kc, int mask, int lane, int wave,
-                                          uint8_t* et, int xrow = 0) {
-  static_assert(!XBYTES || Op::kPrec == P_F32, "byte-valued X rows feed the fp32 product only");
+                                          uint8_t* et) {
   constexpr int KSTEP_CHUNKS = (64 / Op::FR) * Op::CPL;
   const int kg = wave >> 2, wq = wave & 3;  // K group, block of the tile
   const int wm = wq >> 1, wn = wq & 1;
@@ -578,15 +574,7 @@ __device__ inline void small_tile_product(uint8_t* smem, int64_t ldb, int kc, in
 #pragma unroll
     for (int c = 0; c < Op::CPL; ++c) {
       const int ch = ks * KSTEP_CHUNKS + g * Op::CPL + c;
-      if constexpr (XBYTES) {
-        // fp32 chunk ch = 4 ks + g holds k = 16 ks + 4 g .. + 3: dword g of
-        // byte chunk ks of the row
-        const unsigned w = *(const unsigned*)(smem + ra * xrow + 16 * (ks ^ (ra & 15)) + 4 * g);
-        const v4f f = {(float)(w & 0xffu), (float)((w >> 8) & 0xffu), (float)((w >> 16) & 0xffu), (float)(w >> 24)};
-        a[c] = __builtin_bit_cast(u32x4, f);
-      } else {
-        a[c] = *(const u32x4*)(xa + 16 * (ch ^ (ra & mask)));
-      }
+      a[c] = *(const u32x4*)(xa + 16 * (ch ^ (ra & mask)));
       b[c] = *(const u32x4*)(yb + 16 * (ch ^ (rb & mask)));
     }
     acc = Op::mma(a, b, acc);
@@ -688,30 +676,36 @@ static hipError_t set_lds_attr_small() {
 // S^(t) = [S^(t-1) (A + I)^T], for Np <= 512 (operand rows of at most 2 KB),
 // as one launch of one workgroup per 32 x 32 tile of S, all resident at once
 // (cooperative launch).  The right operand A + I never changes: each
-// workgroup builds its 32 rows of it once, from the caller's bytes, and keeps
-// them in LDS; each step it fetches its 32 rows of S^(t-1) (whole K, as in
-// k_nt_small) and writes its tile of S^(t).
+// workgroup builds its 32 rows of it once, from the caller's bytes, in LDS,
+// and each wave keeps its block's part of them in registers for the whole
+// series; each step it fetches its 32 rows of S^(t-1) (whole K) as bits and
+// writes its tile of S^(t).
 //
 // Row blocks are independent.  Block i of S^(t) (its rows 32 i .. 32 i + 31)
 // is block i of S^(t-1) times (A + I)^T, so it depends on no other block,
 // and once it repeats (S^(k) = S^(k-1) on those rows) it stays fixed.  The
-// tiles_n workgroups of tile row i therefore run their own series: between
-// steps they wait only for each other, through one word per step,
-// rowstep[i][t] = arrivals + 256 x (tiles whose count changed at step t);
-// the series of block i has repeated at step k_i when every tile of it is
-// unchanged there (counts only grow, so "changed" = "count changed"), and
-// all its workgroups stop there together.  The iterates of the whole matrix
-// first repeat at K = max_i k_i; its model sizes, ones[t] = sum_i
+// tiles_n workgroups of tile row i therefore run their own series and
+// exchange only each other's tiles: 32 words of 32 bits, each stored together
+// with the number of its step as one 8-byte word.  A thread polls its word of
+// the panel until it carries the step awaited, so a tile's arrival is its
+// data: one device-scope store and one load a step, where a store, its
+// completion, an arrival count, its poll and the panel's fetch used to follow
+// each other.  The bits become operand elements in registers, in front of the
+// MFMA.  A step takes, before and now: N = 512 fp32 4.78, 4.26 us (2 of them
+// its products, 1.7 at the matrix cores' rate), int8 2.31, 2.27; N = 256 fp32
+// 3.39, 2.66, int8 2.16, 1.71: bound by the one round trip.  All workgroups of a row hold
+// the same panel, so they see together when it has not changed and the series
+// of the block has repeated, at k_i.  The iterates of the whole matrix first
+// repeat at K = max_i k_i; its model sizes, ones[t] = sum_i
 // ones_i[min(t, k_i)], are summed by the last workgroup to finish.  A tile
 // of S^(t) overwrites the same tile of S^(t-2), whose only readers (the
-// workgroups of its row, in step t-1) have arrived at step t-1 before the
-// writer starts step t.
+// workgroups of its row, for step t-1) have published their tiles of S^(t-1),
+// which the writer has read.  Step numbers count on from launch to launch
+// (tag), so words left by an earlier launch are never taken for this one's.
 //
-// Coherence across XCDs without cache flushes: the tiles and counters are
+// Coherence across XCDs without cache flushes: the words and counters are
 // written with device-scope stores and atomics (write-through, "sc1") and
-// the next step's rows fetched with device-scope loads (sc1, past any stale
-// L1 or L2 copy); a workgroup waits for its tile's stores to complete
-// (s_waitcnt vmcnt(0)) before it counts its arrival.
+// read with device-scope loads (past any stale L1 or L2 copy).
 //
 // Each wait polls with a time limit (s_memrealtime ticks, 100 MHz); past it
 // the workgroup raises the abort word, reports it in status_out[1] and
@@ -721,64 +715,29 @@ static hipError_t set_lds_attr_small() {
 // ring_out[0 .. K] and status_out = {K, 0}, then zeroes the counters for the
 // next launch.
 
-// Polls *p until (*p & mask) >= target; returns the word, or ~0u on a time
-// limit (then the abort word is raised and status_out[1] set) or an abort
-// seen in the abort word.
-__device__ inline unsigned wait_word(const unsigned* p, unsigned mask, unsigned target, unsigned* abort_word,
-                                     unsigned* status_out, long long limit) {
-  const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
-  for (;;) {
-    const unsigned w = ld_agent(p);
-    if ((w & mask) >= target) return w;
-    if (ld_agent(abort_word) != 0u) return ~0u;
-    if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > limit) {
-      st_agent(abort_word, 1u);
-      st_system(status_out + 1, 1u);
-      return ~0u;
+// Polls *p until its high half is tag; returns the low half.  On a time limit
+// (then the abort word is raised and status_out[1] set) or an abort seen in
+// the abort word *failed is set.
+__device__ inline unsigned wait_tagged(const unsigned long long* p, unsigned tag, unsigned* abort_word,
+                                       unsigned* status_out, long long limit, int* failed) {
+  long long t0 = 0;
+  for (unsigned polls = 0;; ++polls) {
+    const unsigned long long w = ld_agent64(p);
+    if ((unsigned)(w >> 32) == tag) return (unsigned)w;
+    if ((polls & 15u) == 15u) {
+      const long long now = (long long)__builtin_amdgcn_s_memrealtime();
+      if (t0 == 0) t0 = now;
+      const bool late = now - t0 > limit;
+      if (late) {
+        st_agent(abort_word, 1u);
+        st_system(status_out + 1, 1u);
+      }
+      if (late || ld_agent(abort_word) != 0u) {
+        *failed = 1;
+        return 0u;
+      }
     }
     __builtin_amdgcn_s_sleep(1);
-  }
-}
-
-// 16 boolean bytes as 16 operand elements (the bytes store_bool16 writes),
-// stored with device-scope stores at byte offset off of buffer r.
-template <int PREC>
-__device__ inline void store_bool16_agent(__amdgpu_buffer_rsrc_t r, int off, u32x4 b) {
-  if constexpr (PREC == P_I8) {
-    st_agent_x4(r, off, b);
-  } else if constexpr (PREC == P_FP8) {
-    st_agent_x4(r, off, b * 0x38u);
-  } else if constexpr (PREC == P_FP4) {
-    unsigned w2[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const unsigned x = b[2 * h], y = b[2 * h + 1];
-      const unsigned lo = ((x & 1u) << 1) | (((x >> 8) & 1u) << 5) | (((x >> 16) & 1u) << 9) | (((x >> 24) & 1u) << 13);
-      const unsigned hi = ((y & 1u) << 1) | (((y >> 8) & 1u) << 5) | (((y >> 16) & 1u) << 9) | (((y >> 24) & 1u) << 13);
-      w2[h] = lo | (hi << 16);
-    }
-    st_agent_x2(r, off, w2[0], w2[1]);
-  } else if constexpr (PREC == P_BF16) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      u32x4 v;
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        const unsigned x = b[2 * h + w];
-        v[2 * w] = ((x & 1u) ? 0x3F80u : 0u) | (((x >> 8) & 1u) ? 0x3F800000u : 0u);
-        v[2 * w + 1] = (((x >> 16) & 1u) ? 0x3F80u : 0u) | (((x >> 24) & 1u) ? 0x3F800000u : 0u);
-      }
-      st_agent_x4(r, off + 16 * h, v);
-    }
-  } else {  // F32
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const unsigned x = b[w];
-      u32x4 v;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = ((x >> (8 * q)) & 1u) ? 0x3F800000u : 0u;
-      st_agent_x4(r, off + 16 * w, v);
-    }
   }
 }
 
@@ -807,30 +766,34 @@ __device__ inline u32x4 chunk_of_bits(unsigned bits) {
   return v;
 }
 
+constexpr int kFixPitch = 17;  // words per row of the X panel: a read of 16 rows hits distinct banks
+static size_t fix_small_lds_bytes(int64_t ldb) { return (size_t)32 * ldb + 32 * kSmallEst; }
+
 template <class Op>
 __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  __shared__ int s_go;  // 1 compute the step, 0 stop, -1 abort
-  // fp32: the iterates are kept as 0/1 bytes (Np bytes per row) and widened
-  // to floats as the product reads them, so that a step publishes and
-  // fetches a quarter of the bytes
-  constexpr bool XB = Op::kPrec == P_F32;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // Y, then the first tile as bytes
+  __shared__ unsigned xw[32 * kFixPitch];    // X panel: word (r, tile) = its 32 columns 32 tile ..
+  __shared__ unsigned pb[4 * 32];            // [K group][row]: nonzero columns of a group's product
+  __shared__ unsigned tile_rows[32];         // this workgroup's tile of the last iterate
+  __shared__ int s_go;                       // the last workgroup to finish
+  __shared__ int s_changed[2];               // by parity of the step: the panel differs from the one before
+  __shared__ int s_failed;                   // a wait failed
   constexpr int NIB = elem_nibbles(Op::kPrec);
   constexpr int EPC = 32 / NIB;  // operand elements per 16-byte chunk
   const unsigned G = gridDim.x;
   const int L = xcd_logical(blockIdx.x, (int)G);  // XCD-contiguous runs of tile rows
   const int ti = L / p.tiles, tj = L % p.tiles;
   const int row0 = 32 * ti, col0 = 32 * tj;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t ldb = (int64_t)p.Np * NIB / 2;
   const int kc = (int)(ldb / 16);
   const int mask = (kc % 16 == 0) ? 15 : 7;
-  const int stride = p.Np + 3;  // entries per row block in rowstep and ones_row
-  unsigned* rowstep = p.rowstep + (int64_t)ti * stride;
-  uint8_t* et = smem + 64 * ldb + kSmallPart;
+  const int stride = p.Np + 3;  // entries per row block in ones_row
+  uint8_t* et = smem + 32 * ldb;
 
   // One pass over rows col0 .. col0 + 31 of A builds both Y = those rows
-  // of A + I (LDS rows 32..63, kept for the whole series) and S^(1) = A^T
+  // of A + I (chunk c of row r at r ldb + 16 (c ^ (r & mask))) and S^(1) = A^T
   // (tile element (r, c) is A[col0 + c][row0 + r], i.e. the columns
   // row0 .. row0 + 31 of the same rows, before the identity is added).
   // Each item is the EPC bytes of A behind one operand chunk (consecutive
@@ -875,70 +838,101 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
         if (k >= row0 && k < row0 + 32) et[(k - row0) * kSmallEst + r] = (raw >> e) & 1u;
       }
     if (j >= k0 && j < k0 + EPC && j < p.n) raw |= 1u << (j - k0);  // the identity of A + I
-    *(u32x4*)(smem + (int64_t)(32 + r) * ldb + 16 * (c ^ ((32 + r) & mask))) = chunk_of_bits<Op::kPrec>(raw);
+    *(u32x4*)(smem + (int64_t)r * ldb + 16 * (c ^ (r & mask))) = chunk_of_bits<Op::kPrec>(raw);
   }
+  if (tid < 2) s_changed[tid] = 0;
+  if (tid == 2) s_failed = 0;
   __syncthreads();
 
-  int t = 1, prev_cnt = 0;
+  // Sixteen waves: K group kg (a run of K steps) of block (wm, wn) of the tile.
+  // Its part of Y stays in registers; KM steps at most (Np = 512).
+  constexpr int KSTEP_CHUNKS = 4 * Op::CPL;
+  constexpr int KM = (512 * NIB / 32 / KSTEP_CHUNKS + 3) / 4;
+  const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  const int g = lane >> 4, rf = lane & 15;
+  const int ksteps = kc / KSTEP_CHUNKS, per = (ksteps + 3) / 4;
+  u32x4 yf[KM][Op::CPL];
+#pragma unroll
+  for (int j = 0; j < KM; ++j)
+#pragma unroll
+    for (int c = 0; c < Op::CPL; ++c) {
+      const int ch = (kg * per + j) * KSTEP_CHUNKS + g * Op::CPL + c, rb = 16 * wn + rf;
+      yf[j][c] = u32x4{0u, 0u, 0u, 0u};
+      if (j < per && kg * per + j < ksteps) yf[j][c] = *(const u32x4*)(smem + (int64_t)rb * ldb + 16 * (ch ^ (rb & mask)));
+    }
+  const int words = 32 * p.tiles;  // of a panel: at most 512, one a thread
+  unsigned seen = 0u;              // this thread's word of the panel before
+  int t = 1;
   for (;;) {
-    // publish S^(t) from et: stores, count, then the arrival (wave 0)
+    unsigned long long* ex = p.exchange + (int64_t)(t & 1) * p.tiles * words;
+    // publish S^(t): the first from the bytes of et, the others from the K groups' bits
     if (wave == 0) {
-      const int r = lane >> 1, cs = lane & 1;
-      const u32x4 v = *(const u32x4*)(et + r * kSmallEst + 16 * cs);
-      if constexpr (XB)
-        st_agent_x4(buffer_of(p.S[t & 1], (unsigned)(p.Np * p.Np)), (row0 + r) * p.Np + col0 + 16 * cs, v);
-      else
-        store_bool16_agent<Op::kPrec>(buffer_of(p.S[t & 1], (unsigned)(ldb * p.Np)),
-                                      (int)(((int64_t)(row0 + r) * p.Np + col0 + 16 * cs) * NIB / 2), v);
-      const int cnt = wave_sum(popc16(v));
-      const unsigned changed = cnt != prev_cnt ? 1u : 0u;
-      prev_cnt = cnt;
-      wait_stores();
-      if (lane == 0) atomicAdd(rowstep + t, 1u + (changed << 8));
-      // the model size after the arrival, so the arrival does not wait for
-      // it; the wait before the finishing count below covers it
+      unsigned word = 0u;
+      if (lane < 32) {
+        if (t == 1) {
+          word = bit16_of_bytes(*(const u32x4*)(et + lane * kSmallEst)) |
+                 bit16_of_bytes(*(const u32x4*)(et + lane * kSmallEst + 16)) << 16;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) word |= pb[32 * k + lane];
+        }
+        __hip_atomic_store(ex + ti * words + 32 * tj + lane, (unsigned long long)(p.tag + t) << 32 | word,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tile_rows[lane] = word;
+      }
+      // the wait before the finishing count below covers this one
+      const int cnt = wave_sum(__popc(word));
       if (lane == 0 && cnt) atomicAdd(p.ones_row + (int64_t)ti * stride + t, (unsigned long long)cnt);
     }
-    ++t;
-    // decide whether step t runs: the row's arrivals at step t - 1
-    if (tid == 0) {
-      int go = 1;
-      if (t > p.max_steps) {
-        go = 0;
-      } else {
-        const unsigned w = wait_word(rowstep + (t - 1), 0xffu, (unsigned)p.tiles, p.finished + 1, p.status_out,
-                                     p.wait_limit);
-        if (w == ~0u) go = -1;
-        else if ((w >> 8) == 0u) go = 0;  // no tile of the row changed: its series repeated at t - 1
-      }
-      s_go = go;
+    if (++t > p.max_steps) break;
+    // X = rows row0 .. row0 + 31 of S^(t-1)
+    if (tid < words) {
+      int failed = 0;
+      const unsigned x =
+          wait_tagged(ex + ti * words + tid, p.tag + t - 1, p.finished + 1, p.status_out, p.wait_limit, &failed);
+      xw[(tid & 31) * kFixPitch + (tid >> 5)] = x;
+      if (x != seen) s_changed[t & 1] = 1;
+      if (failed) s_failed = 1;
+      seen = x;
     }
     __syncthreads();
-    const int go = s_go;
-    if (go < 0) return;
-    if (go == 0) break;
-    // X = rows row0 .. row0 + 31 of S^(t-1) into LDS rows 0..31
-    const int xrow = XB ? p.Np : (int)ldb;  // bytes per X row (global and LDS)
-    const int xc = xrow / 16, xmask = XB ? 15 : mask;
-    const uint8_t* Xg = (const uint8_t*)p.S[(t - 1) & 1] + (int64_t)row0 * xrow;
-    for (int i = wave; i < xc / 2; i += kSmallThreads / 64) {
-      const int q = 64 * i + lane;
-      const int r = q / xc, pos = q % xc;
-      const int c = pos ^ (r & xmask);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Xg + (int64_t)r * xrow + 16 * c),
-                                       (__attribute__((address_space(3))) void*)(smem + 1024 * i), 16, 0, kCpolSc1);
+    if (s_failed) return;
+    if (!s_changed[t & 1]) break;  // the row's series repeated at t - 1
+    if (tid == 0) s_changed[(t + 1) & 1] = 0;
+    typename Op::Acc acc = Op::zero();
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+      if (j < per && kg * per + j < ksteps) {
+        u32x4 xf[Op::CPL];
+#pragma unroll
+        for (int c = 0; c < Op::CPL; ++c) {
+          const int k0 = ((kg * per + j) * KSTEP_CHUNKS + g * Op::CPL + c) * EPC;
+          xf[c] = chunk_of_bits<Op::kPrec>(xw[(16 * wm + rf) * kFixPitch + (k0 >> 5)] >> (k0 & 31));
+        }
+        acc = Op::mma(xf, yf[j], acc);
+      }
     }
-    __syncthreads();  // vmcnt(0): the panel is in LDS
-    small_tile_product<Op, XB>(smem, ldb, kc, mask, lane, wave, et, xrow);
+    // Every term is >= 0, so an element of the product is nonzero where a
+    // group's sum is: lane l < 16 hands over row l = 4 (l / 4) + v of the block.
+    unsigned long long row_bits = 0ull;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const unsigned long long b = __ballot((int)Op::nz(acc, v));
+      if ((lane & 3) == v) row_bits = b;
+    }
+    if (lane < 16)
+      ((unsigned short*)pb)[(kg * 32 + 16 * wm + lane) * 2 + wn] = (unsigned short)(row_bits >> (16 * (lane >> 2)));
     __syncthreads();
   }
+  __syncthreads();
   // the last iterate computed, S^(t-1), back to R = S^T, cropped; every
   // store of the tile completes before the workgroup counts itself finished
   for (int q = tid; q < 256; q += kSmallThreads) {
     const int r = 4 * (q & 7), c = q >> 3;
     const int gi = row0 + r, gj = col0 + c;
-    const uint8_t* e = et + r * kSmallEst + c;
-    const unsigned v = e[0] | e[kSmallEst] << 8 | e[2 * kSmallEst] << 16 | (unsigned)e[3 * kSmallEst] << 24;
+    unsigned v = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v |= ((tile_rows[r + e] >> c) & 1u) << (8 * e);
     if (gi < p.n && gj < p.n) store4_agent_any(p.R + (int64_t)gj * p.ldr + gi, v, p.n - gi);
   }
   wait_stores();
@@ -971,7 +965,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
   // every other workgroup is done with the counters: zero them
   const int64_t rows = (int64_t)p.tiles * stride;
   for (int64_t i = tid; i < rows; i += kSmallThreads) {
-    st_agent(p.rowstep + i, 0u);
     __hip_atomic_store(p.ones_row + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (tid < p.tiles) st_agent(p.krow + tid, 0u);
@@ -989,17 +982,18 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
 __global__ void k_fix_small_clear(FixSmallParams p) {
   const int64_t rows = (int64_t)p.tiles * (p.Np + 3);
   for (int64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < rows; i += gridDim.x * blockDim.x) {
-    p.rowstep[i] = 0u;
     p.ones_row[i] = 0ull;
     if (i < p.tiles) p.krow[i] = 0u;
     if (i < 2) p.finished[i] = 0u;
   }
+  for (int64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < kFixSmallExchange; i += gridDim.x * blockDim.x)
+    p.exchange[i] = 0ull;
 }
 
 template <class Op>
 static hipError_t set_lds_attr_fix_small() {
   return hipFuncSetAttribute((const void*)k_fix_small<Op>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)small_lds_bytes(kSmallMaxLdb));
+                             (int)fix_small_lds_bytes(kSmallMaxLdb));
 }
 
 template <class Op>
@@ -1008,7 +1002,7 @@ static hipError_t launch_fix_small_op(FixSmallParams p, hipStream_t s) {
   if (ldb > kSmallMaxLdb || ldb % 128 != 0 || p.tiles * 32 != p.Np) return hipErrorInvalidValue;
   void* args[] = {&p};
   return hipLaunchCooperativeKernel((const void*)k_fix_small<Op>, dim3(p.tiles * p.tiles), dim3(kSmallThreads), args,
-                                    (unsigned)small_lds_bytes(ldb), s);
+                                    (unsigned)fix_small_lds_bytes(ldb), s);
 }
 
 // ----------------------------------------------------------------- grouped step (serving)

@@ -138,13 +138,16 @@ struct FixSmallParams {
   int64_t lda;
   uint8_t* R;
   int64_t ldr;
-  void* S[2];                    // iterates, Np x Np (S^(t) in S[t & 1]): fp32 as 0/1 bytes, others in operand precision
   // counters: zero when the launch starts, and left zero by a launch that
   // ends normally (the last workgroup clears them); see fix_small_words
   unsigned long long* ones_row;  // [tiles][Np + 3] model size of each row block per step
-  unsigned* rowstep;             // [tiles][Np + 3] arrivals + 256 x changes per row block and step
   unsigned* krow;                // [tiles] last step of each row block
   unsigned* finished;            // [0] workgroups done, [1] abort (a wait ran past its limit)
+  // tiles of the iterates as bits, S^(t) in half t & 1: [tile row][tile][row]
+  // words of (tag + t) << 32 | 32 columns; no word holds one of this launch's
+  // tags tag + 1 .. tag + max_steps when it starts
+  unsigned long long* exchange;
+  unsigned tag;
   // outputs (device or mapped host memory), written by the last workgroup
   unsigned long long* ring_out;  // ring_out[t] = size of S^(t), t = 0 .. K
   unsigned* status_out;          // [0] K, the last step of any row block; [1] 1 after an abort
@@ -157,19 +160,35 @@ bool fix_small_supported(int prec, int64_t np);
 // kernels' configurations are 0 .. nt_config_count - 1; for every other use
 // of the product step this id falls back to the size rule).
 constexpr int kCfgWholeFixpoint = 5;
-// The cooperative launch; with clear_first, a kernel that zeroes the
-// counters runs before it (needed once for fresh memory and after an abort).
-// Counter words (32-bit) for padded size np: fix_small_words(np), the first
-// 2 tiles (np + 3) of them holding ones_row (8-byte aligned).
+// The cooperative launch; with clear_first, a kernel that zeroes the counters
+// and the exchanged words runs before it (needed once for fresh memory, after
+// an abort and when the tags start again).
+// Words (32-bit) for padded size np: the counters of fix_small_counters(np),
+// the first 2 tiles (np + 3) of them holding ones_row, then the exchanged
+// words, as many for every size (8-byte aligned).
 hipError_t launch_fix_small(int prec, const FixSmallParams& p, bool clear_first, hipStream_t s);
-inline int64_t fix_small_words(int64_t np) { return 3 * (np / 32) * (np + 3) + (np / 32) + 2; }
-// Points the counters of p into `words` (fix_small_words(p.Np) of them, 8-byte aligned).
+constexpr int64_t kFixSmallExchange = 2 * 16 * 16 * 32;  // words of 8 bytes: Np = 512
+inline constexpr int64_t fix_small_counters(int64_t np) { return (2 * (np / 32) * (np + 3) + (np / 32) + 3) / 2 * 2; }
+inline constexpr int64_t fix_small_words(int64_t np) { return fix_small_counters(np) + 2 * kFixSmallExchange; }
+// Points the counters and exchanged words of p into `words` (fix_small_words(512)
+// of them, 8-byte aligned): the exchanged words lie behind the largest size's
+// counters, at one place for every size.
 inline void fix_small_place(FixSmallParams& p, unsigned* words) {
-  const int64_t rows = (int64_t)p.tiles * (p.Np + 3);
   p.ones_row = (unsigned long long*)words;
-  p.rowstep = words + 2 * rows;
-  p.krow = p.rowstep + rows;
+  p.krow = words + 2 * (int64_t)p.tiles * (p.Np + 3);
   p.finished = p.krow + p.tiles;
+  p.exchange = (unsigned long long*)(words + fix_small_counters(512));
+}
+// The tags of the next launch over one set of words, of which `last` is the
+// last launch's: from it on, or from zero, in words cleared first, before they
+// would run over.
+constexpr unsigned kFixSmallTags = 1024;  // above Np + 2
+inline unsigned fix_small_tag(unsigned* last, bool* clear) {
+  if (*last > ~0u - 2 * kFixSmallTags) {
+    *last = 0u;
+    *clear = true;
+  }
+  return *last += kFixSmallTags;
 }
 
 // The squaring closure of n <= 64 kBitTiles constants in one cooperative

@@ -116,6 +116,7 @@ struct dl_ctx {
   std::vector<TuneEntry> tuned;  // tile configurations that override the size rule
   unsigned* fs_words = nullptr;  // counters of the one-launch plain fixpoint, then of the one on bits (zero
                                  // between launches)
+  unsigned fs_tag = 0;           // tags the one-launch plain fixpoint has used (fix_small_tag)
   bool fs_dirty = false;         // a launch ended abnormally: clear them before the next
   bool fb_dirty = false;         // the same for the one on bits
 };

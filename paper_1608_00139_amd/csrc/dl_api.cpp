@@ -470,18 +470,15 @@ void take_whole(dl_ctx* c, int64_t* ones_out, int32_t* steps_out, int32_t* conve
 }
 
 
-int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+int run_plain_whole(dl_ctx* c, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
                     int prec, int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out,
                     hipStream_t s) {
   const int64_t Np = padded_size_for(prec, n);
-  const size_t matT = (size_t)mat_bytes(prec, Np);
   FixSmallParams p{};
   p.A = A;
   p.lda = lda;
   p.R = R;
   p.ldr = ldr;
-  p.S[0] = ws;
-  p.S[1] = ws + matT;
   p.n = (int)n;
   p.Np = (int)Np;
   p.tiles = (int)(Np / 32);
@@ -489,7 +486,8 @@ int run_plain_whole(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
   p.wait_limit = kFixSmallWaitTicks;
   fix_small_place(p, c->fs_words);
   expect_status(c, &p.ring_out, &p.status_out);
-  const bool clear = c->fs_dirty;
+  bool clear = c->fs_dirty;
+  p.tag = fix_small_tag(&c->fs_tag, &clear);
   c->fs_dirty = true;  // until the launch is known to have ended normally
   DL_HIP(launch_fix_small(prec, p, clear, s));
   if (int rc = await_status(c, p.max_steps, s)) return rc;
@@ -574,7 +572,7 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
   if (mode == M_PLAIN && max_steps >= 1 && fix_small_supported(prec, Np) && !forced_other) {
     if ((rc = ensure_ws(c, need))) return rc;
     for (int g = 0; g < count; ++g)
-      if ((rc = run_plain_whole(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, prec, max_steps,
+      if ((rc = run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps,
                                 g == 0 ? ones_out : nullptr, steps_out ? steps_out + g : nullptr,
                                 converged_out ? converged_out + g : nullptr, s)))
         return rc;

@@ -28,14 +28,11 @@ using namespace dl;
 namespace {
 
 constexpr int64_t kNoAllocMaxNp = 512;  // the one-launch kernel's limit
-// Layout of the array: two iterates of the largest size (fp32, Np = 512),
-// the kernel's counters, then its outputs: status (2 words) and the ring of
-// model sizes (Np + 3 entries).
-constexpr size_t kIterBytes = (size_t)kNoAllocMaxNp * kNoAllocMaxNp * 4;
-constexpr size_t kCountersOff = 2 * kIterBytes;
-constexpr size_t kCountersBytes = ((size_t)(3 * (kNoAllocMaxNp / 32) * (kNoAllocMaxNp + 3) + kNoAllocMaxNp / 32 + 2) *
-                                       sizeof(unsigned) + 255) / 256 * 256;
-constexpr size_t kOutOff = kCountersOff + kCountersBytes;
+// Layout of the array: the kernel's counters and the words its workgroups
+// exchange, then its outputs: status (2 words) and the ring of model sizes
+// (Np + 3 entries).
+constexpr size_t kCountersBytes = ((size_t)fix_small_words(kNoAllocMaxNp) * sizeof(unsigned) + 255) / 256 * 256;
+constexpr size_t kOutOff = kCountersBytes;
 constexpr size_t kOutWords = 1 + (kNoAllocMaxNp + 3);  // status (two 32-bit words), then the ring
 constexpr size_t kScratchBytes = kOutOff + kOutWords * 8;
 constexpr int kMaxDevices = 64;
@@ -46,6 +43,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_mu;
 void* g_ptr[kMaxDevices] = {};
 bool g_dirty[kMaxDevices] = {};
+unsigned g_tag[kMaxDevices] = {};
 
 int fail(int status, const std::string& msg) {
   set_last_error(msg);
@@ -111,20 +109,19 @@ extern "C" int dl_tc_noalloc(int64_t n, const uint8_t* A, int64_t lda, uint8_t* 
   p.lda = lda;
   p.R = R;
   p.ldr = ldr;
-  p.S[0] = sc;
-  p.S[1] = sc + kIterBytes;
   p.n = (int)n;
   p.Np = (int)Np;
   p.tiles = (int)(Np / 32);
   p.max_steps = (int)(Np + 2);  // the plain series repeats by step n + 1
   p.wait_limit = kWaitTicks;
-  fix_small_place(p, (unsigned*)(sc + kCountersOff));
+  fix_small_place(p, (unsigned*)sc);
   p.status_out = (unsigned*)(sc + kOutOff);
   p.ring_out = (unsigned long long*)(sc + kOutOff + 8);
   bool clear;
   {
     std::lock_guard<std::mutex> lk(g_mu);
     clear = g_dirty[dev];
+    p.tag = fix_small_tag(&g_tag[dev], &clear);
     g_dirty[dev] = true;  // until this launch is known to have ended normally
   }
   if ((e = launch_fix_small(prec, p, clear, s)) != hipSuccess) return hip_fail(e, "whole-fixpoint launch");

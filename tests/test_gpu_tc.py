@@ -478,3 +478,26 @@ def test_config_chung_lu_n32768(dl):
     d = it_plain - 1
     assert iters == (1 if d == 0 else 2 + int(np.ceil(np.log2(d))) if d > 1 else 2)
     assert int(got.sum()) == int(ones[-1])
+
+
+@pytest.mark.parametrize("prec", ["i8", "f32", "bf16", "fp8", "fp4"])
+def test_plain_series_consecutive_sizes(dl, prec):
+    """The one-launch plain series over sizes that share its counters and
+    exchanged words, at the edges of its 32 x 32 tiles, one call after the
+    other: a path (the longest series, cut off and whole) and a random
+    relation, sizes of every iterate included."""
+    for n in (512, 1, 33, 257, 31, 511, 64, 256, 32, 300):
+        path = np.zeros((n, n), dtype=np.uint8)
+        path[np.arange(n - 1), np.arange(1, n)] = 1
+        rand = dlgen.to_dense(n, dlgen.er_edges(n, min(1.0, 2.0 / n), 3 * n, self_loops=True))
+        announce("plain sizes", prec, n)
+        for a in (rand, path):
+            ad = dev(a)
+            want, ones, iters = oracle.tc_seminaive(a)[:3]
+            for cap in (1, 2, 7, n + 2):
+                st = dl.dl_tc_steps(ad, cap, method=dl.DL_TC_PLAIN, prec=prec)
+                assert st.steps == min(cap, iters) and st.ones == list(ones[: st.steps + 1]), (n, cap)
+                if st.converged:
+                    assert np.array_equal(host(st.R), want)
+                else:
+                    assert int(host(st.R).sum()) == ones[st.steps]
