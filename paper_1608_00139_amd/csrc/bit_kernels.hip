@@ -9,7 +9,7 @@
 // the bits become int8 operands in registers, in front of the MFMA.
 //
 // k_fix_bits: one workgroup per 64 x 64 tile (ti, tj) of R, all resident at
-// once (cooperative launch), T = ceil(n / 64) <= 32 tiles a side.  Step 1
+// once (see kResidentTicks), T = ceil(n / 64) <= 32 tiles a side.  Step 1
 // packs the workgroup's tile of A; step t >= 2 computes its tile of
 //   R^(t) = R^(t-1) | [R^(t-1) R^(t-1) != 0]
 // (adding the previous iterate instead of A leaves the iterates unchanged)
@@ -35,7 +35,7 @@
 // of words, so the 16 rows one read touches hit distinct banks.
 //
 // Measured (MI355X, a call as the caller sees it, degree 2; before: product
-// launches): n = 300 107 -> 54 us, n = 1000 134 -> 70 us, n = 2048 216 -> 186
+// launches): n = 300 108 -> 48 us, n = 1000 140 -> 67 us, n = 2048 210 -> 180
 // us.  Of the 50 us in the kernel at n = 1000 (seven steps) the waits for
 // other workgroups take 24, the products 11 (AND and OR of the bits on the
 // vector units instead: 17), publishing 6, fetching 4: bound by the chain of
@@ -134,10 +134,10 @@ __global__ void __launch_bounds__(256, 4) k_fix_bits(FixBitsParams p) {
           go = -1;
           break;
         }
-        if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > p.wait_limit) {
+        if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > (t == 1 ? kResidentTicks : p.wait_limit)) {
           if (lane == 0) {
             st_agent(p.finished + 1, 1u);
-            st_system(p.status_out + 1, 1u);
+            st_system(p.status_out + 1, t == 1 ? kNotResident : 1u);
           }
           go = -1;
           break;
@@ -254,7 +254,7 @@ size_t fix_bits_bytes(int64_t n) {
 }
 
 hipError_t launch_fix_bits(const FixBitsParams& q, bool clear_first, hipStream_t s) {
-  FixBitsParams p = q;
+  const FixBitsParams& p = q;
   if (p.n <= 0 || p.T != (p.n + 63) / 64 || p.T > kBitTiles || p.max_steps < 1 || p.max_steps > kBitSteps)
     return hipErrorInvalidValue;
   if (clear_first) {
@@ -262,9 +262,9 @@ hipError_t launch_fix_bits(const FixBitsParams& q, bool clear_first, hipStream_t
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  void* args[] = {&p};
-  return hipLaunchCooperativeKernel((const void*)k_fix_bits, dim3(p.T * p.T), dim3(256), args,
-                                    (unsigned)(2 * 64 * (((p.T + 3) & ~3) + 1) * sizeof(u64)), s);
+  hipLaunchKernelGGL(k_fix_bits, dim3(p.T * p.T), dim3(256),
+                     (unsigned)(2 * 64 * (((p.T + 3) & ~3) + 1) * sizeof(u64)), s, p);
+  return hipGetLastError();
 }
 
 }  // namespace dl

@@ -674,8 +674,8 @@ static hipError_t set_lds_attr_small() {
 // ----------------------------------------------------------------- whole plain fixpoint in one launch
 // The plain series of Sec. 3, run transposed (S = R^T): S^(1) = A^T,
 // S^(t) = [S^(t-1) (A + I)^T], for Np <= 512 (operand rows of at most 2 KB),
-// as one launch of one workgroup per 32 x 32 tile of S, all resident at once
-// (cooperative launch).  The right operand A + I never changes: each
+// as one launch of one workgroup per 32 x 32 tile of S, those of a row all
+// resident at once (see kResidentTicks).  The right operand A + I never changes: each
 // workgroup builds its 32 rows of it once, from the caller's bytes, in LDS,
 // and each wave keeps its block's part of them in registers for the whole
 // series; each step it fetches its 32 rows of S^(t-1) (whole K) as bits and
@@ -716,10 +716,10 @@ static hipError_t set_lds_attr_small() {
 // next launch.
 
 // Polls *p until its high half is tag; returns the low half.  On a time limit
-// (then the abort word is raised and status_out[1] set) or an abort seen in
+// (then the abort word is raised and status_out[1] = code) or an abort seen in
 // the abort word *failed is set.
 __device__ inline unsigned wait_tagged(const unsigned long long* p, unsigned tag, unsigned* abort_word,
-                                       unsigned* status_out, long long limit, int* failed) {
+                                       unsigned* status_out, long long limit, unsigned code, int* failed) {
   long long t0 = 0;
   for (unsigned polls = 0;; ++polls) {
     const unsigned long long w = ld_agent64(p);
@@ -730,7 +730,7 @@ __device__ inline unsigned wait_tagged(const unsigned long long* p, unsigned tag
       const bool late = now - t0 > limit;
       if (late) {
         st_agent(abort_word, 1u);
-        st_system(status_out + 1, 1u);
+        st_system(status_out + 1, code);
       }
       if (late || ld_agent(abort_word) != 0u) {
         *failed = 1;
@@ -888,8 +888,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
     // X = rows row0 .. row0 + 31 of S^(t-1)
     if (tid < words) {
       int failed = 0;
-      const unsigned x =
-          wait_tagged(ex + ti * words + tid, p.tag + t - 1, p.finished + 1, p.status_out, p.wait_limit, &failed);
+      const bool first = t == 2;
+      const unsigned x = wait_tagged(ex + ti * words + tid, p.tag + t - 1, p.finished + 1, p.status_out,
+                                     first ? kResidentTicks : p.wait_limit, first ? kNotResident : 1u, &failed);
       xw[(tid & 31) * kFixPitch + (tid >> 5)] = x;
       if (x != seen) s_changed[t & 1] = 1;
       if (failed) s_failed = 1;
@@ -979,15 +980,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_fix_small(FixSmallParams p) {
   }
 }
 
-__global__ void k_fix_small_clear(FixSmallParams p) {
-  const int64_t rows = (int64_t)p.tiles * (p.Np + 3);
-  for (int64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < rows; i += gridDim.x * blockDim.x) {
-    p.ones_row[i] = 0ull;
-    if (i < p.tiles) p.krow[i] = 0u;
-    if (i < 2) p.finished[i] = 0u;
-  }
-  for (int64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < kFixSmallExchange; i += gridDim.x * blockDim.x)
-    p.exchange[i] = 0ull;
+// All words that fix_small_place hands out, whatever the size of the launch
+// that left them: sizes share them.
+__global__ void k_fix_small_clear(unsigned* words) {
+  for (int64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < fix_small_words(512); i += gridDim.x * blockDim.x)
+    words[i] = 0u;
 }
 
 template <class Op>
@@ -997,12 +994,12 @@ static hipError_t set_lds_attr_fix_small() {
 }
 
 template <class Op>
-static hipError_t launch_fix_small_op(FixSmallParams p, hipStream_t s) {
+static hipError_t launch_fix_small_op(const FixSmallParams& p, hipStream_t s) {
   const int64_t ldb = (int64_t)p.Np * elem_nibbles(Op::kPrec) / 2;
   if (ldb > kSmallMaxLdb || ldb % 128 != 0 || p.tiles * 32 != p.Np) return hipErrorInvalidValue;
-  void* args[] = {&p};
-  return hipLaunchCooperativeKernel((const void*)k_fix_small<Op>, dim3(p.tiles * p.tiles), dim3(kSmallThreads), args,
-                                    (unsigned)fix_small_lds_bytes(ldb), s);
+  hipLaunchKernelGGL(k_fix_small<Op>, dim3(p.tiles * p.tiles), dim3(kSmallThreads), (unsigned)fix_small_lds_bytes(ldb),
+                     s, p);
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------- grouped step (serving)
@@ -2076,7 +2073,7 @@ bool fix_small_supported(int prec, int64_t np) {
 hipError_t launch_fix_small(int prec, const FixSmallParams& p, bool clear_first, hipStream_t s) {
   if (!fix_small_supported(prec, p.Np) || p.max_steps < 1 || p.max_steps > p.Np + 2) return hipErrorInvalidValue;
   if (clear_first) {
-    hipLaunchKernelGGL(k_fix_small_clear, dim3(32), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_fix_small_clear, dim3(64), dim3(256), 0, s, (unsigned*)p.ones_row);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

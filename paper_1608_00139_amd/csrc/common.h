@@ -130,7 +130,21 @@ struct AdmitDesc {
 };
 hipError_t launch_admit(const AdmitDesc* d, int nreq, long long total_units, long long total_edges, hipStream_t s);
 
-// The whole plain closure fixpoint in one cooperative launch (k_fix_small in
+// The one-launch fixpoints need all their workgroups (k_fix_small: those of a
+// tile row) on the chip together.  A cooperative launch does not see to that
+// beside another one or beside other work (several threads' launches held
+// parts of the chip and waited for the rest until their time limit), and costs
+// 11.5 us more than an ordinary one (17.7 against 6.2 us from the call to a
+// status word in host memory).  So they are launched the ordinary way, and
+// each workgroup's first wait is for all the others' first tiles: once it is
+// over they are all running, and nothing can keep them from finishing.  If it
+// takes longer than kResidentTicks -- other work holds the chip -- the launch
+// ends with kNotResident in status_out[1], and the series is run by product
+// launches, which wait for nobody.
+constexpr long long kResidentTicks = 20000;  // 200 us of s_memrealtime (100 MHz)
+constexpr unsigned kNotResident = 2u;
+
+// The whole plain closure fixpoint in one launch (k_fix_small in
 // bool_kernels.hip): one workgroup per 32 x 32 tile of S = R^T, for
 // operand rows of at most 2 KB and Np <= 512.
 struct FixSmallParams {
@@ -150,7 +164,7 @@ struct FixSmallParams {
   unsigned tag;
   // outputs (device or mapped host memory), written by the last workgroup
   unsigned long long* ring_out;  // ring_out[t] = size of S^(t), t = 0 .. K
-  unsigned* status_out;          // [0] K, the last step of any row block; [1] 1 after an abort
+  unsigned* status_out;          // [0] K, the last step of any row block; [1] 1 after an abort, or kNotResident
   int n, Np, tiles;              // tiles = Np / 32 per side
   int max_steps;                 // at most Np + 2
   long long wait_limit;          // ticks
@@ -160,7 +174,7 @@ bool fix_small_supported(int prec, int64_t np);
 // kernels' configurations are 0 .. nt_config_count - 1; for every other use
 // of the product step this id falls back to the size rule).
 constexpr int kCfgWholeFixpoint = 5;
-// The cooperative launch; with clear_first, a kernel that zeroes the counters
+// The launch; with clear_first, a kernel that zeroes the counters of every size
 // and the exchanged words runs before it (needed once for fresh memory, after
 // an abort and when the tags start again).
 // Words (32-bit) for padded size np: the counters of fix_small_counters(np),
@@ -191,8 +205,7 @@ inline unsigned fix_small_tag(unsigned* last, bool* clear) {
   return *last += kFixSmallTags;
 }
 
-// The squaring closure of n <= 64 kBitTiles constants in one cooperative
-// launch, on bits (k_fix_bits in bit_kernels.hip).
+// The squaring closure of n <= 64 kBitTiles constants in one launch, on bits (k_fix_bits in bit_kernels.hip).
 constexpr int kBitTiles = 32;  // 64 x 64 tiles a side at most
 constexpr int kBitLine = 16;   // 64-bit words per arrival word: a 128-byte line
 constexpr int kBitSteps = 16;  // squaring repeats by step 2 + ceil(log2(2048))

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cfloat>
 #include <cmath>
 #include <climits>
@@ -409,10 +410,8 @@ class Fix {
   SkParams skq_{};
 };
 
-// The plain series at small Np as one cooperative launch (k_fix_small): the
-// iterates in the slot's workspace, its ring for the model sizes and its
-// convergence word for the kernel's status, read back once at the end.  The
-// kernel writes R itself.
+// The plain series at small Np as one launch (k_fix_small), which leaves its
+// model sizes and status in pinned host memory and writes R itself.
 constexpr long long kFixSmallWaitTicks = 200000000;  // 2 s of s_memrealtime (100 MHz)
 
 // A whole-fixpoint kernel's results go straight into the pinned host ring of
@@ -425,7 +424,7 @@ void expect_status(dl_ctx* c, unsigned long long** ring_out, unsigned** status_o
   st[1] = 0u;
 }
 
-int await_status(dl_ctx* c, int max_steps, hipStream_t s) {
+int await_status(dl_ctx* c, int max_steps, hipStream_t s, bool* not_resident) {
   volatile unsigned* st = (volatile unsigned*)(c->h_ring + kRing);
   // The kernel's last store is its status word in pinned host memory, made
   // after every other store of the launch (R, the model sizes, the cleared
@@ -444,8 +443,45 @@ int await_status(dl_ctx* c, int max_steps, hipStream_t s) {
     if ((polls & 4095u) == 0 && hipStreamQuery(s) != hipErrorNotReady) break;
   }
   if (!seen) DL_HIP(hipStreamSynchronize(s));
+  *not_resident = st[1] == kNotResident;
+  if (*not_resident) {
+    DL_HIP(hipStreamSynchronize(s));  // every workgroup has left, some after its own limit
+    return DL_OK;
+  }
   if (st[1]) return fail(DL_EHIP, "whole-fixpoint kernel: a wait for other workgroups ran past its time limit");
   if (st[0] == ~0u || st[0] > (unsigned)max_steps) return fail(DL_EHIP, "whole-fixpoint kernel reported no result");
+  return DL_OK;
+}
+
+// Compute units that whole-fixpoint launches of this process hold, per device
+// (an estimate).  A launch that would not fit beside the others is not
+// started: they would keep each other waiting.
+std::atomic<int> g_whole_units[64];
+constexpr int kWholeUnits = 256;
+constexpr int kNoRoom = -1;  // of run_whole: run the series by product launches
+
+// Runs a whole-fixpoint kernel, launch(clear), of `units` compute units;
+// kNoRoom if it is not started or its workgroups do not come to run together.
+// *dirty: its counters have to be cleared first.
+template <class Launch>
+int run_whole(dl_ctx* c, int units, bool* dirty, int max_steps, hipStream_t s,
+              unsigned long long** ring_out, unsigned** status_out, Launch launch) {
+  struct Hold {
+    std::atomic<int>& held;
+    int units;
+    const int before;
+    Hold(std::atomic<int>& h, int u) : held(h), units(u), before(h.fetch_add(u)) {}
+    ~Hold() { held.fetch_sub(units); }
+  } hold(g_whole_units[c->device & 63], units);
+  if (hold.before > 0 && hold.before + units > kWholeUnits) return kNoRoom;
+  expect_status(c, ring_out, status_out);
+  const bool clear = *dirty;
+  *dirty = true;  // until the launch is known to have ended normally
+  DL_HIP(launch(clear));
+  bool not_resident = false;
+  if (int rc = await_status(c, max_steps, s, &not_resident)) return rc;
+  if (not_resident) return kNoRoom;
+  *dirty = false;
   return DL_OK;
 }
 
@@ -485,19 +521,19 @@ int run_plain_whole(dl_ctx* c, int64_t n, const uint8_t* A, int64_t lda, uint8_t
   p.max_steps = (int)std::min<int64_t>(max_steps, Np + 2);
   p.wait_limit = kFixSmallWaitTicks;
   fix_small_place(p, c->fs_words);
-  expect_status(c, &p.ring_out, &p.status_out);
-  bool clear = c->fs_dirty;
-  p.tag = fix_small_tag(&c->fs_tag, &clear);
-  c->fs_dirty = true;  // until the launch is known to have ended normally
-  DL_HIP(launch_fix_small(prec, p, clear, s));
-  if (int rc = await_status(c, p.max_steps, s)) return rc;
-  c->fs_dirty = false;
+  bool wrapped = false;
+  p.tag = fix_small_tag(&c->fs_tag, &wrapped);
+  // (words whose tags start again are cleared even if this launch is not started)
+  c->fs_dirty = c->fs_dirty || wrapped;
+  if (int rc = run_whole(c, p.tiles * p.tiles, &c->fs_dirty, p.max_steps, s, &p.ring_out, &p.status_out,
+                         [&](bool clear) { return launch_fix_small(prec, p, clear, s); }))
+    return rc;
   take_whole(c, ones_out, steps_out, converged_out);
   return DL_OK;
 }
 
 // The squaring series of int8 relations of at most 64 kBitTiles constants as
-// one cooperative launch on bits (k_fix_bits), read back like run_plain_whole.
+// one launch on bits (k_fix_bits), read back like run_plain_whole.
 int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
                     int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out,
                     hipStream_t s) {
@@ -517,28 +553,26 @@ int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
   p.wait_limit = kFixSmallWaitTicks;
   p.cnt = (unsigned long long*)(c->fs_words + fix_small_words(512));
   p.finished = (unsigned*)(p.cnt + (kBitSteps + 1) * kBitTiles * kBitLine);
-  expect_status(c, &p.ring_out, &p.status_out);
-  const bool clear = c->fb_dirty;
-  c->fb_dirty = true;  // until the launch is known to have ended normally
-  DL_HIP(launch_fix_bits(p, clear, s));
-  if (int rc = await_status(c, p.max_steps, s)) return rc;
-  c->fb_dirty = false;
+  if (int rc = run_whole(c, (p.T * p.T + 3) / 4, &c->fb_dirty, p.max_steps, s, &p.ring_out, &p.status_out,
+                         [&](bool clear) { return launch_fix_bits(p, clear, s); }))
+    return rc;
   take_whole(c, ones_out, steps_out, converged_out);
   return DL_OK;
 }
 
-// The int8 squaring series goes to run_square_bits up to this size: 186
-// against 216 us for product launches at n = 2048 (four workgroups per compute
+// The int8 squaring series goes to run_square_bits up to this size: 180
+// against 210 us for product launches at n = 2048 (four workgroups per compute
 // unit there; more tiles would not be resident at once).
 constexpr int64_t kBitSquareMax = 64 * kBitTiles;
 
 // Runs `count` fixpoints of one size, mode and precision on stream s, with
 // up to two in flight: while the host reads one's counters back, the device
 // runs the other's products.  Per-fixpoint outputs are indexed by g;
-// ones_out (model sizes per step) is taken for count == 1 only.
+// ones_out (model sizes per step) is taken for count == 1 only.  whole: the
+// one-launch kernels may be used where they apply.
 int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* const* A, int64_t lda,
                   uint8_t* const* R, int64_t ldr, int prec, int32_t max_steps, int64_t* ones_out,
-                  int32_t* steps_out, int32_t* converged_out, hipStream_t s) {
+                  int32_t* steps_out, int32_t* converged_out, hipStream_t s, bool whole = true) {
   if (prec < P_I8 || prec > P_FP4) return fail(DL_EINVAL, "unknown precision");
   if (max_steps < 0) return fail(DL_EINVAL, "max_steps < 0");
   if (count <= 0) return DL_OK;
@@ -569,23 +603,26 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
   for (const auto& t : c->tuned)
     if (t.prec == prec && t.np == Np) te = &t;
   const bool forced_other = te && te->cfg != kCfgWholeFixpoint && te->ms == 0.0;
-  if (mode == M_PLAIN && max_steps >= 1 && fix_small_supported(prec, Np) && !forced_other) {
-    if ((rc = ensure_ws(c, need))) return rc;
-    for (int g = 0; g < count; ++g)
-      if ((rc = run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps,
-                                g == 0 ? ones_out : nullptr, steps_out ? steps_out + g : nullptr,
-                                converged_out ? converged_out + g : nullptr, s)))
-        return rc;
-    return DL_OK;
-  }
+  const bool plain_whole =
+      whole && mode == M_PLAIN && max_steps >= 1 && fix_small_supported(prec, Np) && !forced_other;
   // so does the int8 squaring series at small n (bits); not while product
   // launches are timed, which only the chunked path has
-  if (mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax && !(te && te->ms == 0.0) && !c->timing) {
+  const bool square_bits = whole && mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax &&
+                           !(te && te->ms == 0.0) && !c->timing;
+  if (plain_whole || square_bits) {
     if ((rc = ensure_ws(c, need))) return rc;
-    for (int g = 0; g < count; ++g)
-      if ((rc = run_square_bits(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, max_steps, g == 0 ? ones_out : nullptr,
-                                steps_out ? steps_out + g : nullptr, converged_out ? converged_out + g : nullptr, s)))
-        return rc;
+    for (int g = 0; g < count; ++g) {
+      int64_t* ones = g == 0 ? ones_out : nullptr;
+      int32_t* steps = steps_out ? steps_out + g : nullptr;
+      int32_t* converged = converged_out ? converged_out + g : nullptr;
+      rc = plain_whole
+               ? run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps, ones, steps, converged, s)
+               : run_square_bits(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s);
+      if (rc == kNoRoom)  // this one and the rest by product launches
+        return run_fixpoints(c, mode, count - g, n, A + g, lda, R + g, ldr, prec, max_steps, ones, steps, converged, s,
+                             false);
+      if (rc) return rc;
+    }
     return DL_OK;
   }
   int nslots = count >= 2 ? kFixSlots : 1;

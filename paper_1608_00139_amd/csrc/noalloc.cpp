@@ -12,6 +12,7 @@
 // first).
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -124,14 +125,20 @@ extern "C" int dl_tc_noalloc(int64_t n, const uint8_t* A, int64_t lda, uint8_t* 
     p.tag = fix_small_tag(&g_tag[dev], &clear);
     g_dirty[dev] = true;  // until this launch is known to have ended normally
   }
-  if ((e = launch_fix_small(prec, p, clear, s)) != hipSuccess) return hip_fail(e, "whole-fixpoint launch");
   unsigned long long out[kOutWords];
   const size_t out_bytes = 8 * (size_t)(1 + Np + 3);
-  if ((e = hipMemcpyAsync(out, sc + kOutOff, out_bytes, hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return hip_fail(e, "read-back of the model sizes");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   unsigned status[2];
-  memcpy(status, out, sizeof status);
+  // again while other work keeps the launch's workgroups from running together (kResidentTicks)
+  const auto until = std::chrono::steady_clock::now() + std::chrono::seconds(2);
+  for (;;) {
+    if ((e = launch_fix_small(prec, p, clear, s)) != hipSuccess) return hip_fail(e, "whole-fixpoint launch");
+    if ((e = hipMemcpyAsync(out, sc + kOutOff, out_bytes, hipMemcpyDeviceToHost, s)) != hipSuccess)
+      return hip_fail(e, "read-back of the model sizes");
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    memcpy(status, out, sizeof status);
+    if (status[1] != kNotResident || std::chrono::steady_clock::now() > until) break;
+    clear = true;
+  }
   if (status[1]) return fail(DL_EHIP, "whole-fixpoint kernel: a wait for other workgroups ran past its time limit");
   const int64_t K = status[0];
   if (K < 1 || K > p.max_steps) return fail(DL_EHIP, "whole-fixpoint kernel reported no result");

@@ -191,3 +191,56 @@ def test_result_is_seen_by_other_streams(dl, n):
             flat = flat.cpu().numpy()
             pad = flat[off : off + n * (n + off)].reshape(n, n + off)[:, n:]
             assert (pad == 9).all() and (flat[:off] == 9).all() and (flat[off + n * (n + off) :] == 9).all()
+
+
+def test_one_launch_closures_on_a_busy_chip(dl):
+    """Four threads with a context and a stream each run the one-launch
+    closures (both kinds) while products on a fifth stream keep the chip busy:
+    whether a launch finds its workgroups room together or the series is run
+    by product launches, every model and iteration count is right."""
+    import threading
+
+    import torch
+
+    cases = []
+    for n, method, prec in ((700, dl.DL_TC_SQUARE, dl.DL_I8), (400, dl.DL_TC_PLAIN, dl.DL_F32),
+                            (2000, dl.DL_TC_SQUARE, dl.DL_I8), (512, dl.DL_TC_PLAIN, dl.DL_I8)):
+        a = dlgen.to_dense(n, dlgen.er_edges(n, 2.0 / n, 9 * n))
+        ad = dev(a)
+        want, iters = dl.dl_tc(ad, method, prec)
+        assert np.array_equal(host(want), oracle.tc_seminaive(a)[0])
+        cases.append((ad, method, prec, host(want), iters))
+    wrong = []
+
+    def work(case):
+        ad, method, prec, want, iters = case
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            ctx = dl.Context()
+            out = torch.empty_like(ad)
+            for k in range(25):
+                announce("busy chip", ad.shape[0], k)
+                try:
+                    _, it = dl.dl_tc(ad, method, prec, out=out, ctx=ctx)
+                except dl.DLError as err:
+                    wrong.append((ad.shape[0], k, str(err)))
+                    continue
+                if it != iters or not np.array_equal(out.cpu().numpy(), want):
+                    wrong.append((ad.shape[0], k, it))
+            ctx.close()
+
+    torch.cuda.synchronize()
+    busy = torch.cuda.Stream()
+    threads = [threading.Thread(target=work, args=(c,)) for c in cases]
+    with torch.cuda.stream(busy):
+        x = torch.rand((4096, 4096), device="cuda")
+        y = torch.empty_like(x)
+        for t in threads:
+            t.start()
+        while any(t.is_alive() for t in threads):
+            for _ in range(4):
+                torch.mm(x, x, out=y)
+            busy.synchronize()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong[:5]
