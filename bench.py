@@ -374,18 +374,26 @@ def run_extras(dl, ctx, graphs, outs, np, torch):
     del a, o
     torch.cuda.empty_cache()
 
-    # same generation, N = 4096 random forests
-
+    # same generation, N = 4096 random forests: by lists of their entries, and
+    # by the two dense products a step (a configuration set for the size keeps
+    # those), whose operations eff_tops counts
     sg = []
     n = 4096
+    pctx = dl.Context(0)
+    pctx.set_tuning("i8", n, 0)
     for seed in SEEDS:
         p = torch.from_numpy(dlgen.to_dense(n, dlgen.forest_edges(n, seed))).cuda()
         s = torch.empty_like(p)
         dl.dl_sg(p, prec=dl.DL_I8, out=s, ctx=ctx)
         (_, it), t = timed(lambda: dl.dl_sg(p, prec=dl.DL_I8, out=s, ctx=ctx))
-        sg.append({"n": n, "seed": seed, "iters": it, "time_to_fixpoint_ms": round(t * 1e3, 2),
-                   "eff_tops": round(2 * 2.0 * n ** 3 * (it - 1) / t / 1e12, 1),
-                   "model_size": int(s.sum().item())})
+        q = torch.empty_like(p)
+        dl.dl_sg(p, prec=dl.DL_I8, out=q, ctx=pctx)
+        _, tp = timed(lambda: dl.dl_sg(p, prec=dl.DL_I8, out=q, ctx=pctx))
+        sg.append({"n": n, "seed": seed, "iters": it, "time_to_fixpoint_ms": round(t * 1e3, 3),
+                   "by_products_ms": round(tp * 1e3, 3),
+                   "by_products_eff_tops": round(2 * 2.0 * n ** 3 * (it - 1) / tp / 1e12, 1),
+                   "model_mismatches": int((q != s).sum().item()), "model_size": int(s.sum().item())})
+    pctx.close()
     res["sg_n4096"] = sg
 
     # same generation, epsilon form (fp64 Smith doubling), N = 4096 forests

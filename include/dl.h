@@ -127,7 +127,7 @@ int dl_tc_batch(dl_ctx* ctx, int32_t count, int64_t n, const uint8_t* const* A, 
  * capture, tight serving loops, harnesses that forbid hipMalloc): dl_tc with
  * method DL_TC_PLAIN for n <= 512 constants, any dl_prec, run by the same
  * one-launch kernel (tile configuration 5), with every device buffer it
- * needs (two iterates, counters, read-back words: 2.2 MB at most) in a
+ * needs (counters, exchanged words, read-back words: 0.2 MB) in a
  * static device array that each GPU holds from the first call on it until
  * the process ends.  Allocates nothing and takes no context.  The current device is the
  * one used.  Calls on one GPU share that array: calls that overlap on one
@@ -145,7 +145,11 @@ int dl_tc_noalloc(int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t 
  * large tiles (n rounded up to 256 at least 4096 by the size rule, or tile
  * configuration 0) only its upper-triangle tiles are computed and then
  * mirrored, and the context's workspace also holds that product's partial
- * tiles (3.4 MB at n = 4096). */
+ * tiles (3.4 MB at n = 4096).  With DL_I8, 512 <= n <= 8192, at most 32
+ * entries in every row of P, no configuration set for that size
+ * (dl_tune_set) and timing off, both products are taken by lists of P's
+ * entries on bits instead (the same iterates and sizes, in the same
+ * workspace). */
 int dl_sg(dl_ctx* ctx, int64_t n, const uint8_t* P, int64_t ldp, uint8_t* S, int64_t lds,
           int prec, int32_t* iters, void* stream);
 

@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "libdl.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["bool_kernels.hip", "bit_kernels.hip", "eps_solve.hip", "prog_kernels.hip", "peak.hip", "peak_agpr.hip", "dl_api.cpp",
+SOURCES = ["bool_kernels.hip", "bit_kernels.hip", "list_kernels.hip", "eps_solve.hip", "prog_kernels.hip", "peak.hip", "peak_agpr.hip", "dl_api.cpp",
            "serve.cpp", "program.cpp", "noalloc.cpp"]
 
 # fp64 MFMA accumulators in architectural VGPRs rather than AGPRs: measured

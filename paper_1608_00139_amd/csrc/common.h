@@ -230,6 +230,32 @@ size_t fix_bits_bytes(int64_t n);
 constexpr int64_t kFixBitsWords = 2 * (kBitSteps + 1) * kBitTiles * kBitLine + 2;
 hipError_t launch_fix_bits(const FixBitsParams& p, bool clear_first, hipStream_t s);
 
+// The same-generation series by lists of P's entries, on bits, in one launch
+// (list_kernels.hip), for n <= kListMaxN and at most kListMax entries a row.
+constexpr int kListMax = 32;
+constexpr int kListMaxN = 8192;   // a slice of 32 rows a compute unit
+constexpr int kListArrivals = 8;  // words that a step's arrivals are spread over, a line each
+struct ListParams {
+  uint8_t* R;
+  int64_t ldr;
+  unsigned* VT[2];      // slices of P S, step t in VT[t & 1] ...
+  unsigned short* idx;  // [kListMax][n] list entries, [k n + j] = entry k of row j ...
+  unsigned short* len;  // ... and [n] their numbers
+  unsigned long long* cnt;  // [4][kListArrivals][16] arrivals and ones of steps t % 4, zero between launches
+  unsigned* finished;       // [0] workgroups done, [1] abort, zero between launches
+  unsigned long long* ring_out;  // model sizes of steps 1 .. K
+  unsigned* status_out;          // [0] K, 0 if a row is too long; [1] 1 after an abort, or kNotResident
+  int n, nb, pitch;              // nb = ceil(n / 32) slices of pitch = 32 nb words
+  int max_steps;                 // 2 .. kRing - 1
+  long long wait_limit;          // ticks
+};
+size_t sg_lists_bytes(int64_t n);
+constexpr int kListWords = 4 * kListArrivals * 32 + 2;  // 32-bit, 8-byte aligned
+hipError_t sg_lists_init();
+// ws: sg_lists_bytes(n), 16-byte aligned; words: kListWords of them.
+hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t* ws, unsigned* words, bool clear_first,
+                           hipStream_t s);
+
 // Launch helpers implemented in bool_kernels.hip.
 struct TileCfg {
   int bm, bn, kb, threads;

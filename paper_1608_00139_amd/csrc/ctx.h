@@ -119,6 +119,7 @@ struct dl_ctx {
   unsigned fs_tag = 0;           // tags the one-launch plain fixpoint has used (fix_small_tag)
   bool fs_dirty = false;         // a launch ended abnormally: clear them before the next
   bool fb_dirty = false;         // the same for the one on bits
+  bool fl_dirty = false;         // and for the one by lists
 };
 
 namespace dl {

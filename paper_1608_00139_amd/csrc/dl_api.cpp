@@ -565,6 +565,40 @@ int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
 // unit there; more tiles would not be resident at once).
 constexpr int64_t kBitSquareMax = 64 * kBitTiles;
 
+// The same-generation series by lists (k_sg_lists), read back like
+// run_plain_whole; kNoRoom as well if a row of P is too long for a list or the
+// series for the ring of model sizes.
+int run_sg_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* P, int64_t ldp, uint8_t* R, int64_t ldr,
+                 int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out, hipStream_t s) {
+  ListParams p{};
+  p.R = R;
+  p.ldr = ldr;
+  p.n = (int)n;
+  p.max_steps = std::min(max_steps, kRing - 1);
+  p.wait_limit = kFixSmallWaitTicks;
+  unsigned* words = c->fs_words + fix_small_words(512) + kFixBitsWords;
+  if (int rc = run_whole(c, (int)((n + 31) / 32), &c->fl_dirty, p.max_steps, s, &p.ring_out, &p.status_out,
+                         [&](bool clear) { return launch_sg_lists(p, P, ldp, ws, words, clear, s); }))
+    return rc;
+  const volatile unsigned long long* ring = c->h_ring;
+  const int64_t K = *(volatile unsigned*)(c->h_ring + kRing);
+  if (K == 0) return kNoRoom;
+  const bool converged = K >= 2 && ring[K] == ring[K - 1];
+  if (!converged && K < max_steps) return kNoRoom;
+  if (ones_out) {
+    ones_out[0] = 0;
+    for (int64_t k = 1; k <= K; ++k) ones_out[k] = (int64_t)ring[k];
+  }
+  if (steps_out) *steps_out = (int32_t)K;
+  if (converged_out) *converged_out = converged ? 1 : 0;
+  return DL_OK;
+}
+
+// Same generation in int8 goes to run_sg_lists from this size on where P's
+// rows allow it (n = 512: 65 against 205 us for products).  Finding that they
+// do not costs a dense P some 7 us, which would show below (n = 300: of 115).
+constexpr int64_t kListMinN = 512;
+
 // Runs `count` fixpoints of one size, mode and precision on stream s, with
 // up to two in flight: while the host reads one's counters back, the device
 // runs the other's products.  Per-fixpoint outputs are indexed by g;
@@ -609,15 +643,18 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
   // launches are timed, which only the chunked path has
   const bool square_bits = whole && mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax &&
                            !(te && te->ms == 0.0) && !c->timing;
-  if (plain_whole || square_bits) {
+  const bool sg_lists = whole && mode == M_SG && prec == P_I8 && max_steps >= 2 && n >= kListMinN && n <= kListMaxN &&
+                        !(te && te->ms == 0.0) && !c->timing;
+  if (plain_whole || square_bits || sg_lists) {
     if ((rc = ensure_ws(c, need))) return rc;
     for (int g = 0; g < count; ++g) {
       int64_t* ones = g == 0 ? ones_out : nullptr;
       int32_t* steps = steps_out ? steps_out + g : nullptr;
       int32_t* converged = converged_out ? converged_out + g : nullptr;
-      rc = plain_whole
-               ? run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps, ones, steps, converged, s)
-               : run_square_bits(c, (uint8_t*)c->ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s);
+      uint8_t* ws = (uint8_t*)c->ws;
+      rc = plain_whole   ? run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps, ones, steps, converged, s)
+           : square_bits ? run_square_bits(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s)
+                         : run_sg_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s);
       if (rc == kNoRoom)  // this one and the rest by product launches
         return run_fixpoints(c, mode, count - g, n, A + g, lda, R + g, ldr, prec, max_steps, ones, steps, converged, s,
                              false);
@@ -721,6 +758,7 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
   if ((e = hipSetDevice(device)) != hipSuccess) return cleanup(hip_fail(e, "hipSetDevice"));
   if ((e = bool_kernels_init()) != hipSuccess) return cleanup(hip_fail(e, "kernel attributes"));
   if ((e = dl::eps_kernels_init()) != hipSuccess) return cleanup(hip_fail(e, "kernel attributes"));
+  if ((e = dl::sg_lists_init()) != hipSuccess) return cleanup(hip_fail(e, "kernel attributes"));
   if ((e = hipMalloc(&c->ring, kFixSlots * kSlotWords * sizeof(unsigned long long))) != hipSuccess)
     return cleanup(hip_fail(e, "hipMalloc(ring)"));
   if ((e = hipMalloc(&c->conv, 64 * sizeof(int))) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(conv)"));
@@ -738,7 +776,7 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
     return cleanup(hip_fail(e, "hipMemset(ring)"));
   if ((e = hipMemset(c->conv, 0, 64 * sizeof(int))) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(conv)"));
   {
-    const size_t fsb = (size_t)(fix_small_words(512) + kFixBitsWords) * sizeof(unsigned);
+    const size_t fsb = (size_t)(fix_small_words(512) + kFixBitsWords + kListWords) * sizeof(unsigned);
     if ((e = hipMalloc(&c->fs_words, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(fixpoint counters)"));
     if ((e = hipMemset(c->fs_words, 0, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(fixpoint counters)"));
   }

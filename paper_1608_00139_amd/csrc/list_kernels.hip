@@ -1,0 +1,306 @@
+// list_kernels.hip -- the same-generation series for a relation with few
+// entries a row: products with P as gathers over lists, on bits, the whole
+// series in one launch.
+//
+// S' = [I + P S P^T] (Sec. 7.2) multiplies by P twice a step, and P -- parents,
+// typically one or two of them -- never changes.  As dense products a step at
+// n = 4096 takes 90 us of matrix-core work whatever P holds.  With the columns
+// of the nonzero entries of each row of P as a list, (M P^T)[i][j] is the OR
+// of M[i][q] over the list of j, and with 32 rows of M in the bits of a word,
+// one word per column, a list of c entries costs c LDS reads for 32 entries
+// of the result, and a step moves n^2 / 8 bytes instead of reading and writing
+// n^2 four times.
+//
+// Layout ("slices"): word j of slice b of a matrix holds rows 32 b ..
+// 32 b + 31 of column j, bit r = row 32 b + r; pitch = 32 nb words, nb =
+// ceil(n / 32).  Rows and columns from n on are zero.
+//
+// k_sg_lists: workgroup b keeps slice b of S in LDS for the whole series.  A
+// step gathers V = S P^T and stores it transposed, in 32 x 32 blocks, to the
+// slices of V^T = P S (S is symmetric) that other workgroups
+// read; when all have arrived it fetches its slice, gathers V^T P^T = P S P^T
+// -- symmetric again -- and adds I.  An arrival carries the ones of the slice
+// of S^(t-1), so every workgroup learns the model size of step t - 1 while it
+// waits for step t's exchange, and all stop together at the first repeat; the
+// exchange of step t is then left unused.  V^T is double buffered: a slice of
+// step t + 2 is stored by workgroups that have seen all the others arrive at
+// t + 1, and so done with step t's.
+//
+// All workgroups have to run together: see kResidentTicks.  Coherence across
+// XCDs as in k_fix_bits: device-scope stores, loads and atomics.
+//
+// A step takes 5 us at n = 4096, bound by the round trips of the exchange (10
+// us with the blocks transposed by a ballot a row).  Measured, same generation
+// of random forests, by products and now: n = 1024 277, 68 us a call; n = 4096
+// 1212, 105; n = 8192 10560, 220.
+#include "common.h"
+#include "device.h"
+
+namespace dl {
+
+typedef unsigned long long u64;
+
+// Lists of the rows of P: entry k of row j at idx[k n + j], len[j] entries,
+// kListMax + 1 for a row with more.  A wave a row.  Where one of the first
+// rows is too long the host hears of it at once, so that a dense P's products
+// start 10 us earlier; of any other row it hears from k_sg_lists.  (One word
+// that all rows report to took 140 us of stores to one address.)
+__global__ void __launch_bounds__(256) k_row_lists(const uint8_t* P, int64_t ldp, int n, unsigned short* idx,
+                                                   unsigned short* len, unsigned* status_out) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  const uint8_t* src = P + (int64_t)row * ldp;
+  int base = 0;
+  for (int c0 = 0; c0 < n; c0 += 4096) {
+    unsigned m[4];  // four 1024-column pieces of the row, all loads in flight together
+    int own = 0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int j0 = c0 + 1024 * h + 16 * lane;
+      m[h] = 0u;
+      if (j0 + 16 <= n) {
+        m[h] = bit16_of_bytes(bytes01(load16_any(src + j0)));
+      } else {
+        for (int e = 0; j0 + e < n; ++e) m[h] |= (src[j0 + e] != 0 ? 1u : 0u) << e;
+      }
+      own += __popc(m[h]);
+    }
+    if (__ballot((int)(own != 0)) == 0ull) continue;
+    int upto = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(upto, off, 64);
+      if (lane >= off) upto += v;
+    }
+    const int total = __shfl(upto, 63, 64);
+    if (base + total > kListMax) {
+      base = kListMax + 1;
+      if (row < 8 && lane == 0) st_system(status_out, 0u);
+      break;
+    }
+    int k = base + upto - own;  // any order within the list
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+      for (unsigned rest = m[h]; rest != 0u; rest &= rest - 1, ++k)
+        idx[(int64_t)k * n + row] = (unsigned short)(c0 + 1024 * h + 16 * lane + __ffs((int)rest) - 1);
+    base += total;
+  }
+  if (lane == 0) len[row] = (unsigned short)base;
+}
+
+// The 32 x 32 bit matrix of lanes 0 .. 31 (row = lane, column = bit), and that
+// of lanes 32 .. 63, transposed: five exchanges with lane ^ s, each moving the
+// quarter whose row and column differ in bit s (a rotation, then a select by
+// mask; what the rotation carries round is outside the mask).
+template <int S>
+__device__ inline unsigned swap_quarters(unsigned v, int lane) {
+  constexpr unsigned M = S == 16 ? 0x0000ffffu : S == 8 ? 0x00ff00ffu : S == 4 ? 0x0f0f0f0fu : S == 2 ? 0x33333333u : 0x55555555u;
+  unsigned y;
+  if constexpr (S == 8) y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true);  // row_ror:8
+  else if constexpr (S == 2) y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true);  // quad_perm 2 3 0 1
+  else if constexpr (S == 1) y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);  // quad_perm 1 0 3 2
+  else y = (unsigned)__builtin_amdgcn_ds_swizzle((int)v, 0x1f | (S << 10));
+  const bool upper = (lane & S) != 0;
+  const unsigned x = __builtin_amdgcn_alignbit(y, y, upper ? S : 32 - S), k = upper ? M : ~M;
+  return (x & k) | (v & ~k);
+}
+__device__ inline unsigned transpose32(unsigned v, int lane) {
+  v = swap_quarters<16>(v, lane);
+  v = swap_quarters<8>(v, lane);
+  v = swap_quarters<4>(v, lane);
+  v = swap_quarters<2>(v, lane);
+  return swap_quarters<1>(v, lane);
+}
+
+constexpr u64 kArrived = 1ull << 40;  // above any sum of ones
+constexpr int kListThreads = 1024;
+
+__device__ inline u64* arrival(const ListParams& p, int t, int k) { return p.cnt + ((t & 3) * kListArrivals + k) * 16; }
+
+__global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned lds[];
+  __shared__ int red[kListThreads / 64];
+  __shared__ u64 s_total;
+  __shared__ int s_go;
+  unsigned* S = lds;            // slice b of S
+  unsigned* VT = lds + p.pitch;  // slice b of P S
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const unsigned bytes = (unsigned)((size_t)p.nb * p.pitch * 4);
+  // length and first entry of every column's list
+  unsigned* head = lds + 2 * p.pitch;
+  if (tid == 0) s_go = 1;
+  __syncthreads();
+  for (int j = tid; j < p.pitch; j += kListThreads) {
+    unsigned h = 0u;
+    if (j < p.n) {
+      const unsigned c = p.len[j];
+      if (c > (unsigned)kListMax) s_go = 0;
+      h = c << 16 | (c ? p.idx[j] : 0u);
+    }
+    head[j] = h;
+  }
+  auto gather = [&](const unsigned* m, int j) {
+    const unsigned h = head[j], c = h >> 16;
+    unsigned v = c ? m[h & 0xffffu] : 0u;
+    for (unsigned k = 1; k < c; ++k) v |= m[p.idx[(int64_t)k * p.n + j]];
+    return v;
+  };
+  __syncthreads();
+  if (s_go == 0) {  // some row is too long for a list: every workgroup sees that
+    if (b == 0 && tid == 0) st_system(p.status_out, 0u);
+    return;
+  }
+  // S^(1) = I
+  int ones = 0;
+  for (int j = tid; j < p.pitch; j += kListThreads) {
+    const unsigned v = j >> 5 == b && j < p.n ? 1u << (j & 31) : 0u;
+    S[j] = v;
+    ones += v != 0u;
+  }
+  u64 prev = 0ull;  // size of S^(t-2)
+  int t = 2, converged = 0;
+  for (;; ++t) {
+    ones = wave_sum(ones);
+    if (lane == 0) red[wave] = ones;
+    __syncthreads();  // S^(t-1) is complete
+    const __amdgpu_buffer_rsrc_t X = buffer_of(p.VT[t & 1], bytes);
+    for (int j0 = 64 * wave; j0 < p.pitch; j0 += kListThreads) {
+      const unsigned v = j0 + lane < p.pitch ? gather(S, j0 + lane) : 0u;
+      const unsigned w = transpose32(v, lane);  // row lane % 32 of the lane's 32 x 32 block
+      const int tile = (j0 >> 5) + (lane >> 5);
+      if (tile < p.nb)
+        __builtin_amdgcn_raw_buffer_store_b32(w, X, (tile * p.pitch + 32 * b + (lane & 31)) * 4, 0, kCpolSc1);
+    }
+    wait_stores();
+    __syncthreads();
+    if (wave == 0) {
+      u64 sum = lane < kListThreads / 64 ? (u64)red[lane] : 0ull;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      if (lane == 0) atomicAdd(arrival(p, t, b % kListArrivals), kArrived + sum);
+      const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+      int go = 1;
+      u64 v = 0ull;
+      for (;;) {
+        if (lane < kListArrivals) v = ld_agent64(arrival(p, t, lane));
+        int arrived = lane < kListArrivals ? (int)(v >> 40) : 0;
+        arrived = wave_sum(arrived);
+        if (arrived == p.nb) break;
+        if (ld_agent(p.finished + 1) != 0u) {
+          go = -1;
+          break;
+        }
+        if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > (t == 2 ? kResidentTicks : p.wait_limit)) {
+          if (lane == 0) {
+            st_agent(p.finished + 1, 1u);
+            st_system(p.status_out + 1, t == 2 ? kNotResident : 1u);
+          }
+          go = -1;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      u64 total = lane < kListArrivals ? v & (kArrived - 1) : 0ull;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+      if (b == 0) {
+        // everybody has left the words of step t - 2: they are step t + 2's
+        // (complete before this workgroup arrives at t + 1)
+        if (lane < kListArrivals)
+          __hip_atomic_store(arrival(p, t + 2, lane), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) st_system64(p.ring_out + (t - 1), total);
+        wait_stores();
+      }
+      if (lane == 0) {
+        s_total = total;
+        s_go = go;
+      }
+    }
+    __syncthreads();
+    if (s_go < 0) return;
+    const u64 now = s_total;
+    converged = now == prev ? 1 : 0;
+    if (converged || t > p.max_steps) break;
+    prev = now;
+    for (int q = 4 * tid; q < p.pitch; q += 4 * kListThreads)
+      *(u32x4*)(VT + q) = __builtin_amdgcn_raw_buffer_load_b128(X, (b * p.pitch + q) * 4, 0, kCpolSc1);
+    __syncthreads();
+    ones = 0;
+    for (int j = tid; j < p.pitch; j += kListThreads) {
+      unsigned v = gather(VT, j);
+      if (j >> 5 == b && j < p.n) v |= 1u << (j & 31);
+      S[j] = v;
+      ones += __popc(v);
+    }
+  }
+
+  // S^(t-1) as 0/1 bytes, a wave a row, 16 columns a lane; every store of the
+  // slice completes before the workgroup counts itself finished
+  for (int r = wave; r < 32; r += kListThreads / 64) {
+    const int row = 32 * b + r;
+    if (row >= p.n) break;
+    uint8_t* dst = p.R + (int64_t)row * p.ldr;
+    const __amdgpu_buffer_rsrc_t D = buffer_of(dst, (unsigned)p.n);
+    const bool aligned = ((uintptr_t)dst & 15) == 0;
+    for (int c = 16 * lane; c < p.n; c += 1024) {
+      u32x4 v;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const u32x4 s = *(const u32x4*)(S + c + 4 * x);
+        v[x] = ((s[0] >> r) & 1u) | ((s[1] >> r) & 1u) << 8 | ((s[2] >> r) & 1u) << 16 | ((s[3] >> r) & 1u) << 24;
+      }
+      if (aligned && c + 16 <= p.n) st_agent_x4(D, c, v);
+      else store16_agent_any(dst + c, v, p.n - c);
+    }
+  }
+  wait_stores();
+  __syncthreads();
+  if (tid == 0) s_go = atomicAdd(p.finished, 1u) == (unsigned)p.nb - 1u ? 1 : 0;
+  __syncthreads();
+  if (!s_go) return;
+  // the last workgroup: cleared words, then the status
+  if (tid < 4 * kListArrivals)
+    __hip_atomic_store(p.cnt + tid * 16, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) st_agent(p.finished, 0u);
+  wait_stores();
+  __syncthreads();
+  if (tid == 0) {
+    st_system(p.status_out + 1, 0u);
+    st_system(p.status_out, (unsigned)(t - 1));  // >= 1: the last step computed
+  }
+}
+
+__global__ void __launch_bounds__(256) k_lists_clear(ListParams p) {
+  for (int i = threadIdx.x; i < kListWords; i += 256) ((unsigned*)p.cnt)[i] = 0u;
+}
+
+size_t sg_lists_bytes(int64_t n) {
+  const size_t nb = (size_t)((n + 31) / 32);
+  return 2 * nb * 32 * nb * 4 + (size_t)(kListMax + 1) * n * 2;
+}
+
+hipError_t sg_lists_init() {
+  return hipFuncSetAttribute((const void*)k_sg_lists, hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kListMaxN * 4);
+}
+
+hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t* ws, unsigned* words, bool clear_first,
+                           hipStream_t s) {
+  if (p.n <= 0 || p.n > kListMaxN || p.max_steps < 2 || p.max_steps >= kRing) return hipErrorInvalidValue;
+  p.nb = (p.n + 31) / 32;
+  p.pitch = 32 * p.nb;
+  const size_t slices = (size_t)p.nb * p.pitch;
+  p.VT[0] = (unsigned*)ws;
+  p.VT[1] = p.VT[0] + slices;
+  p.idx = (unsigned short*)(p.VT[1] + slices);
+  p.len = p.idx + (size_t)kListMax * p.n;
+  p.cnt = (u64*)words;
+  p.finished = words + 4 * kListArrivals * 32;
+  if (clear_first) hipLaunchKernelGGL(k_lists_clear, dim3(1), dim3(256), 0, s, p);
+  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, P, ldp, p.n, p.idx, p.len,
+                     p.status_out);
+  hipLaunchKernelGGL(k_sg_lists, dim3(p.nb), dim3(kListThreads), 3 * p.pitch * 4, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace dl
