@@ -256,6 +256,21 @@ hipError_t sg_lists_init();
 hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t* ws, unsigned* words, bool clear_first,
                            hipStream_t s);
 
+// The series of a program's layer with one recursive term, R = A + P R, by
+// lists of P's entries (k_layer_lists), Np <= kListMaxN.
+struct LayerLists {
+  const int8_t* A;      // Np x Np, zero from row and column n on
+  int8_t *M, *T;        // the model and its transpose
+  unsigned short* idx;  // lists as in ListParams
+  unsigned short* len;
+  unsigned* words;       // [0] workgroups done, [1] their last steps; zero between launches
+  unsigned* status_out;  // host memory: K, the first step that repeats, or 0 if a row is too long
+  int n, Np;
+};
+constexpr int kLayerWords = 2;
+inline size_t layer_lists_bytes(int64_t n) { return (size_t)(kListMax + 1) * n * 2; }
+hipError_t launch_layer_lists(const LayerLists& p, const int8_t* P, hipStream_t s);
+
 // Launch helpers implemented in bool_kernels.hip.
 struct TileCfg {
   int bm, bn, kb, threads;

@@ -17,6 +17,12 @@
 // Fixpoints a batched call keeps in flight (each with its own workspace,
 // counters and read-back event).
 constexpr int kFixSlots = 2;
+// Series with a relation of few entries a row are run by lists of them from
+// this size on (same generation of n = 512: 65 against 205 us for products).
+// Finding that a row is too long costs a dense relation some 7 us, which would
+// show below (same generation of n = 300: of 115).
+constexpr int64_t kListMinN = 512;
+
 constexpr size_t kSlotWords = (size_t)dl::kRing + 1;  // a slot's ring and its convergence step
 
 struct EventPair {

@@ -594,11 +594,6 @@ int run_sg_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* P, int64_t ld
   return DL_OK;
 }
 
-// Same generation in int8 goes to run_sg_lists from this size on where P's
-// rows allow it (n = 512: 65 against 205 us for products).  Finding that they
-// do not costs a dense P some 7 us, which would show below (n = 300: of 115).
-constexpr int64_t kListMinN = 512;
-
 // Runs `count` fixpoints of one size, mode and precision on stream s, with
 // up to two in flight: while the host reads one's counters back, the device
 // runs the other's products.  Per-fixpoint outputs are indexed by g;
@@ -776,7 +771,7 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
     return cleanup(hip_fail(e, "hipMemset(ring)"));
   if ((e = hipMemset(c->conv, 0, 64 * sizeof(int))) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(conv)"));
   {
-    const size_t fsb = (size_t)(fix_small_words(512) + kFixBitsWords + kListWords) * sizeof(unsigned);
+    const size_t fsb = (size_t)(fix_small_words(512) + kFixBitsWords + kListWords + kLayerWords) * sizeof(unsigned);
     if ((e = hipMalloc(&c->fs_words, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(fixpoint counters)"));
     if ((e = hipMemset(c->fs_words, 0, fsb)) != hipSuccess) return cleanup(hip_fail(e, "hipMemset(fixpoint counters)"));
   }

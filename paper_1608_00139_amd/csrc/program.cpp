@@ -405,6 +405,14 @@ struct Runner {
     }
     temps.clear();
   }
+  // Gives a temporary allocation back before the layer ends.
+  void give(void* q) {
+    const auto it = std::find(temps.begin(), temps.end(), q);
+    if (it == temps.end()) return;
+    temps.erase(it);
+    give_back(g, q);
+    g->bytes -= (size_t)Np * Np;
+  }
   // Moves a temporary allocation into the kept set (a layer result).
   void keep_ptr(void* q) {
     auto it = std::find(temps.begin(), temps.end(), q);
@@ -430,6 +438,25 @@ struct Runner {
     while ((e = hipEventQuery(ev)) == hipErrorNotReady) {
     }
     P_HIP(e);
+    return DL_OK;
+  }
+
+  // Launches the series by lists and polls for its status, which the kernel
+  // stores in the pinned words of the context's second slot (programs use the
+  // first).
+  int run_lists(LayerLists& q, const int8_t* P, unsigned* K) {
+    volatile unsigned* st = (volatile unsigned*)(g->ctx->h_ring + kSlotWords + kRing);
+    q.status_out = (unsigned*)(g->ctx->h_ring_dev + kSlotWords + kRing);
+    *st = ~0u;
+    P_HIP(launch_layer_lists(q, P, s));
+    for (unsigned polls = 1; *st == ~0u; ++polls) {
+      if ((polls & 4095u) != 0) continue;
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) continue;
+      P_HIP(e);
+      if (*st == ~0u) return perr(DL_EHIP, "the series by lists reported no result");
+    }
+    *K = *st;
     return DL_OK;
   }
 
@@ -762,6 +789,40 @@ int Runner::iterate(int L, const std::vector<int>& heads, const std::vector<Mat>
     o.j = local(t->factors[t->rec].pred);
     o.trans = t->factors[t->rec].trans;
     ops[local(t->head)].push_back(o);
+  }
+  bool cfg_set = false;  // the caller chose a product configuration for this size
+  for (const auto& t : g->ctx->tuned) cfg_set = cfg_set || (t.prec == P_I8 && t.np == Np && t.ms == 0.0);
+  if (M == 1 && rec.size() == 1 && !ops[0][0].trans && ops[0][0].P.ident != ops[0][0].S.ident && n >= kListMinN &&
+      Np <= kListMaxN && !cfg_set && !g->ctx->timing) {
+    // R = A + P R, or R^T = A^T + S^T R^T, by lists where the relation's rows
+    // allow it
+    const Op& o = ops[0][0];
+    const bool left = o.P.ident;
+    Mat R;
+    int8_t* lists;
+    P_RC(alloc_mat(&R, false));
+    P_RC(alloc(&lists, false));
+    LayerLists q{};
+    q.A = left ? A[0].T : A[0].M;
+    q.M = left ? R.T : R.M;
+    q.T = left ? R.M : R.T;
+    q.idx = (unsigned short*)lists;
+    q.len = q.idx + (size_t)kListMax * n;
+    q.words = g->ctx->fs_words + fix_small_words(512) + kFixBitsWords + kListWords;
+    q.n = (int)n;
+    q.Np = (int)Np;
+    unsigned K = 0;
+    P_RC(run_lists(q, left ? o.S.T : o.P.M, &K));
+    if (K) {
+      g->val[heads[0]] = R;
+      keep_ptr(R.M);
+      keep_ptr(R.T);
+      g->iters[L] = (int)K;
+      return DL_OK;
+    }
+    give(R.M);
+    give(R.T);
+    give(lists);
   }
   // R^(k) in buf[h][k % 2]; R^(1) = A, whose size is in the ring already
   std::vector<Mat> buf[2];

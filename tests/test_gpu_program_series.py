@@ -152,3 +152,99 @@ def test_budget_and_destroy_order(dl):
     two.run(dl.DL_EVAL_ITERATION)
     assert np.array_equal(host(two.fetch("p", n=n)[0]), want["p"])
     two.close()
+
+
+LEFT = """
+p(X,Y) :- e(X,Y).
+p(X,Y) :- p(X,Z), f(Z,Y).
+"""
+CHAINED = """
+p(X,Y) :- e(X,Y).
+p(X,Y) :- e(X,Z), f(Z,W), p(W,Y).
+q(X,Y) :- f(X,Z), not p(Z,Y).
+q(X,Y) :- e(X,Z), q(Z,Y).
+"""
+NEGATED = """
+p(X,Y) :- e(X,Y).
+q(X,Y) :- f(X,Y).
+q(X,Y) :- not p(X,Z), q(Z,Y).
+"""
+
+
+@pytest.mark.parametrize("text", [PATH, LEFT, NO_BASE, CHAINED, NEGATED],
+                         ids=["right", "left", "no_base", "chained", "negated"])
+@pytest.mark.parametrize("n", [511, 512, 545, 1000])
+def test_series_by_lists_vs_oracle(dl, text, n):
+    """Layers with one recursive term, by lists of the relation's entries
+    (from n = 512, at most 32 a row) and, for a longer row or a complement, by
+    products: models and iteration counts."""
+    rng = np.random.default_rng(n)
+    for kind in ("sparse", "loops and longer lists", "long row", "empty base"):
+        loops = kind == "loops and longer lists"
+        rels = {k: dlgen.to_dense(n, dlgen.er_edges(n, (8 if loops else 1) * d / n, 5 * n + i, self_loops=loops))
+                for i, (k, d) in enumerate((("e", 1.0), ("f", 2.0)))}
+        if loops:  # lists on both sides of the entries kept at hand, each with its own row
+            for m in rels.values():
+                for row in range(0, n, 7):
+                    m[row] = 0
+                    m[row, rng.choice(n, row % 12, replace=False)] = 1
+                    m[row, row] = 1
+        if kind == "long row":
+            for m in rels.values():
+                m[n - 1] = 0
+                m[n - 1, rng.choice(n, 33, replace=False)] = 1
+                m[rng.choice(n, 33, replace=False), n - 2] = 1
+        if kind == "empty base":
+            rels["e"][:] = 0
+        announce("program lists", n, kind)
+        prog = dl.Program(text)
+        keep = {k: dev(v) for k, v in rels.items()}
+        for k, t in keep.items():
+            if f"{k}(" in text:
+                prog.bind(k, t)
+        prog.run(dl.DL_EVAL_ITERATION)
+        _check(dl, prog, text, {k: v for k, v in rels.items() if f"{k}(" in text}, n)
+        prog.close()
+
+
+def test_long_path_by_lists(dl):
+    """A path of 700 constants (the longest series), beside a run with the
+    product configuration set, which keeps the products."""
+    n = 700
+    e = np.zeros((n, n), dtype=np.uint8)
+    e[np.arange(n - 1), np.arange(1, n)] = 1
+    ed = dev(e)
+    announce("program long path")
+    for tuned in (False, True):
+        ctx = dl.Context()
+        if tuned:
+            ctx.set_tuning("i8", n, 1)
+        prog = dl.Program(PATH, ctx=ctx)
+        prog.bind("e", ed)
+        prog.run(dl.DL_EVAL_ITERATION)
+        _check(dl, prog, PATH, {"e": e}, n)
+        assert prog.layers()[0]["iters"] == n
+        prog.close()
+        ctx.close()
+
+
+def test_large_layer_by_lists_and_products(dl):
+    """n = 5200, where fewer entries of a list are kept at hand: the layers by
+    lists equal those by products (a configuration set by the caller)."""
+    n = 5200
+    e, f = (dev(dlgen.to_dense(n, dlgen.er_edges(n, 2.0 / n, 3 + i, self_loops=True))) for i in range(2))
+    announce("program large layer")
+    got = []
+    for tuned in (False, True):
+        ctx = dl.Context()
+        if tuned:
+            ctx.set_tuning("i8", n, 0)
+        prog = dl.Program(CHAINED, ctx=ctx)
+        prog.bind("e", e)
+        prog.bind("f", f)
+        prog.run(dl.DL_EVAL_ITERATION)
+        got.append(([host(prog.fetch(k, n=n)[0]) for k in "pq"], [layer["iters"] for layer in prog.layers()]))
+        prog.close()
+        ctx.close()
+    assert got[0][1] == got[1][1]
+    assert all(np.array_equal(a, b) for a, b in zip(got[0][0], got[1][0]))
