@@ -319,6 +319,10 @@ hipError_t launch_ingest(int prec, const uint8_t* A, int64_t lda, int n, int Np,
                          int8_t* AT8, void* Aop, void* ATop, int ident, unsigned long long* ones_slot,
                          hipStream_t s);
 hipError_t launch_identity(int prec, void* S, int Np, int n, hipStream_t s);
+// An int8 matrix cropped to n x n into R, its true entries counted into
+// *sum_out (mapped host memory).  words: two, zero between launches.
+hipError_t launch_emit_sum(const void* S, int Np, int n, uint8_t* R, int64_t ldr, unsigned long long* words,
+                           unsigned long long* sum_out, hipStream_t s);
 // Models of several int8 iterates to callers' matrices in one launch.
 struct EmitDesc {
   const uint8_t* S;  // Np x Np iterate

@@ -212,8 +212,9 @@ struct dl_program {
   std::shared_ptr<MatPool> mats;  // where the matrices come from (null: allocated and freed, with a budget)
   std::vector<void*> keep;        // matrices holding results
   size_t bytes = 0;               // in use: results and temporaries
-  unsigned long long* dcnt = nullptr;  // device counter of dl_program_fetch
-  unsigned long long* hcnt = nullptr;  // pinned mirror
+  unsigned long long* dcnt = nullptr;  // two device words of dl_program_fetch, zero between launches
+  unsigned long long* hcnt = nullptr;  // its count, pinned ...
+  unsigned long long* hcnt_dev = nullptr;  // ... and its device address
 };
 
 namespace {
@@ -925,10 +926,13 @@ int dl_program_create(dl_ctx* ctx, const char* text, dl_program** out) {
     delete g;
     return rc;
   }
-  if (hipSetDevice(ctx->device) != hipSuccess || hipMalloc(&g->dcnt, sizeof(unsigned long long)) != hipSuccess ||
-      hipHostMalloc(&g->hcnt, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
+  if (hipSetDevice(ctx->device) != hipSuccess || hipMalloc(&g->dcnt, 2 * sizeof(unsigned long long)) != hipSuccess ||
+      hipMemset(g->dcnt, 0, 2 * sizeof(unsigned long long)) != hipSuccess ||
+      hipHostMalloc(&g->hcnt, sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&g->hcnt_dev, g->hcnt, 0) != hipSuccess) {
     (void)hipGetLastError();
     if (g->dcnt) (void)hipFree(g->dcnt);
+    if (g->hcnt) (void)hipHostFree(g->hcnt);
     delete g;
     return perr(DL_ENOMEM, "counter allocation failed");
   }
@@ -1062,12 +1066,10 @@ int dl_program_fetch(dl_program* g, const char* name, uint8_t* out, int64_t ldo,
   }
   P_HIP(hipSetDevice(g->ctx->device));
   hipStream_t s = (hipStream_t)stream;
-  P_HIP(launch_emit(P_I8, g->val[p].M, (int)g->Np, 0, (int)g->n, out, ldo, s));
-  if (ones) {
-    P_HIP(hipMemsetAsync(g->dcnt, 0, sizeof(unsigned long long), s));
-    P_HIP(launch_bytes_op(g->val[p].M, nullptr, 0, 0, (int)g->n, (int)g->Np, nullptr, nullptr, g->dcnt, s));
-    P_HIP(hipMemcpyAsync(g->hcnt, g->dcnt, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-  }
+  if (ones)
+    P_HIP(launch_emit_sum(g->val[p].M, (int)g->Np, (int)g->n, out, ldo, g->dcnt, g->hcnt_dev, s));
+  else
+    P_HIP(launch_emit(P_I8, g->val[p].M, (int)g->Np, 0, (int)g->n, out, ldo, s));
   P_HIP(hipStreamSynchronize(s));
   if (ones) *ones = (int64_t)g->hcnt[0];
   return DL_OK;
