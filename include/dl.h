@@ -97,7 +97,11 @@ int dl_destroy(dl_ctx* ctx);
  *   R      device uint8 [n x ldr], receives the 0/1 least model of r2 (it
  *          may also hold intermediate iterates while the call runs)
  *   method dl_tc_method, prec dl_prec
- *   iters  host int32, see above. */
+ *   iters  host int32, see above.
+ * The plain series in DL_I8 with 512 < n <= 8192 and at most 32 entries in
+ * every row of A is run by lists of the entries on bits, with the same
+ * iterates (not while timing is on or a configuration is set for the size,
+ * dl_tune_set). */
 int dl_tc(dl_ctx* ctx, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
           int method, int prec, int32_t* iters, void* stream);
 

@@ -261,6 +261,7 @@ hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t*
 struct LayerLists {
   const int8_t* A;      // Np x Np, zero from row and column n on
   int8_t *M, *T;        // the model and its transpose
+  int64_t lda, ldm;     // set by the launch
   unsigned short* idx;  // lists as in ListParams
   unsigned short* len;
   unsigned* words;       // [0] workgroups done, [1] their last steps; zero between launches
@@ -270,6 +271,10 @@ struct LayerLists {
 constexpr int kLayerWords = 2;
 inline size_t layer_lists_bytes(int64_t n) { return (size_t)(kListMax + 1) * n * 2; }
 hipError_t launch_layer_lists(const LayerLists& p, const int8_t* P, hipStream_t s);
+// The plain closure R = A + A R of a caller's relation the same way (idx, len,
+// words, status_out and n of p are used).
+hipError_t launch_closure_lists(const LayerLists& p, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+                                hipStream_t s);
 
 // Launch helpers implemented in bool_kernels.hip.
 struct TileCfg {

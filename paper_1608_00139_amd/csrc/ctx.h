@@ -18,9 +18,11 @@
 // counters and read-back event).
 constexpr int kFixSlots = 2;
 // Series with a relation of few entries a row are run by lists of them from
-// this size on (same generation of n = 512: 65 against 205 us for products).
-// Finding that a row is too long costs a dense relation some 7 us, which would
-// show below (same generation of n = 300: of 115).
+// this size on: same generation of n = 512 65 against 205 us for products, the
+// plain closure of n = 600, 1000, 4096 (degree 2, 28 to 34 steps) 47, 56, 97
+// against 329, 407, 1739.  Finding that a row is too long costs a dense
+// relation some 10 us (plain closure of n = 1000 and 4096, degree 300, three
+// steps: 103, 182 to 109, 197), which would show more below.
 constexpr int64_t kListMinN = 512;
 
 constexpr size_t kSlotWords = (size_t)dl::kRing + 1;  // a slot's ring and its convergence step

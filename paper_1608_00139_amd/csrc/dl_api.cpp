@@ -594,6 +594,28 @@ int run_sg_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* P, int64_t ld
   return DL_OK;
 }
 
+// The plain closure by lists (k_layer_lists: the same iterates, in columns),
+// without its model sizes; kNoRoom if a row of A is too long for a list.
+int run_plain_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+                    int32_t max_steps, int32_t* steps_out, int32_t* converged_out, hipStream_t s) {
+  LayerLists p{};
+  p.idx = (unsigned short*)ws;
+  p.len = p.idx + (size_t)kListMax * n;
+  p.words = c->fs_words + fix_small_words(512) + kFixBitsWords + kListWords;
+  p.n = (int)n;
+  unsigned long long* ring_out = nullptr;
+  expect_status(c, &ring_out, &p.status_out);
+  DL_HIP(launch_closure_lists(p, A, lda, R, ldr, s));
+  bool not_resident = false;
+  if (int rc = await_status(c, max_steps, s, &not_resident)) return rc;
+  const unsigned K = *(volatile unsigned*)(c->h_ring + kRing);
+  if (K == 0) return kNoRoom;
+  DL_HIP(hipStreamSynchronize(s));  // R is in place for every stream
+  if (steps_out) *steps_out = (int32_t)K;
+  if (converged_out) *converged_out = 1;
+  return DL_OK;
+}
+
 // Runs `count` fixpoints of one size, mode and precision on stream s, with
 // up to two in flight: while the host reads one's counters back, the device
 // runs the other's products.  Per-fixpoint outputs are indexed by g;
@@ -640,7 +662,10 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
                            !(te && te->ms == 0.0) && !c->timing;
   const bool sg_lists = whole && mode == M_SG && prec == P_I8 && max_steps >= 2 && n >= kListMinN && n <= kListMaxN &&
                         !(te && te->ms == 0.0) && !c->timing;
-  if (plain_whole || square_bits || sg_lists) {
+  // the plain int8 series run to its end, where nobody asks for its sizes
+  const bool plain_lists = whole && !plain_whole && mode == M_PLAIN && prec == P_I8 && !ones_out && max_steps >= n + 2 &&
+                           n >= kListMinN && n <= kListMaxN && !(te && te->ms == 0.0) && !c->timing;
+  if (plain_whole || square_bits || sg_lists || plain_lists) {
     if ((rc = ensure_ws(c, need))) return rc;
     for (int g = 0; g < count; ++g) {
       int64_t* ones = g == 0 ? ones_out : nullptr;
@@ -649,7 +674,8 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
       uint8_t* ws = (uint8_t*)c->ws;
       rc = plain_whole   ? run_plain_whole(c, n, A[g], lda, R[g], ldr, prec, max_steps, ones, steps, converged, s)
            : square_bits ? run_square_bits(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s)
-                         : run_sg_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s);
+           : sg_lists    ? run_sg_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s)
+                         : run_plain_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, steps, converged, s);
       if (rc == kNoRoom)  // this one and the rest by product launches
         return run_fixpoints(c, mode, count - g, n, A + g, lda, R + g, ldr, prec, max_steps, ones, steps, converged, s,
                              false);

@@ -285,7 +285,9 @@ __global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
 // it does not have, so that a step reads them without a test; 8 where they fit
 // (90 us for 17 steps at n = 4000 with 4, since the longer lists of a wave's 64
 // rows then come from memory entry by entry).
-template <int E>
+// CALLER: A and R are a caller's matrices (n x n, any stride and alignment),
+// and no transpose is written.
+template <int E, bool CALLER>
 __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
   typedef unsigned short Entries __attribute__((ext_vector_type(E)));
   constexpr unsigned short kMore = 0x8000u;  // in the last entry: the list goes on
@@ -299,26 +301,36 @@ __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
   unsigned* cur = lds;
   unsigned* nxt = lds + p.Np;
   Entries* first = (Entries*)(lds + 2 * p.Np);
-  unsigned any = 0u;
-  for (int i = tid; i < p.Np; i += kListThreads) {
-    Entries e;
-    const int c = i < p.n ? p.len[i] : 0;
-    if (c > kListMax) s_go = 0;
-#pragma unroll
-    for (int k = 0; k < E; ++k) e[k] = k < c ? p.idx[(int64_t)k * p.n + i] : (unsigned short)i;
-    if (c > E) e[E - 1] |= kMore;
-    first[i] = e;
-    const u32x4* a = (const u32x4*)(p.A + (int64_t)i * p.Np + 32 * b);
-    const unsigned v = bit16_of_bytes(a[0]) | bit16_of_bytes(a[1]) << 16;
-    cur[i] = v;
-    any |= v;
-  }
-  if (any != 0u) s_changed[1] = 1;
+  for (int i = tid; i < p.n; i += kListThreads)
+    if (p.len[i] > kListMax) s_go = 0;
   __syncthreads();
   if (s_go == 0) {  // some row is too long for a list: every workgroup sees that
     if (blockIdx.x == 0 && tid == 0) st_system(p.status_out, 0u);
     return;
   }
+  unsigned any = 0u;
+  for (int i = tid; i < p.Np; i += kListThreads) {
+    Entries e;
+    const int c = i < p.n ? p.len[i] : 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) e[k] = k < c ? p.idx[(int64_t)k * p.n + i] : (unsigned short)i;
+    if (c > E) e[E - 1] |= kMore;
+    first[i] = e;
+    unsigned v = 0u;
+    const uint8_t* a = (const uint8_t*)p.A + (int64_t)i * p.lda + 32 * b;
+    if (!CALLER) {
+      v = bit16_of_bytes(((const u32x4*)a)[0]) | bit16_of_bytes(((const u32x4*)a)[1]) << 16;
+    } else if (i < p.n) {
+      if (32 * b + 32 <= p.n)
+        v = bit16_of_bytes(bytes01(load16_any(a))) | bit16_of_bytes(bytes01(load16_any(a + 16))) << 16;
+      else
+        for (int x = 0; 32 * b + x < p.n; ++x) v |= (a[x] != 0 ? 1u : 0u) << x;
+    }
+    cur[i] = v;
+    any |= v;
+  }
+  if (any != 0u) s_changed[1] = 1;
+  __syncthreads();
   int t = 1;  // cur is R^(t); s_changed[t % 3]: it differs from R^(t-1)
   while (s_changed[t % 3]) {
     if (tid == 0) s_changed[(t + 2) % 3] = 0;  // read by all before the last barrier
@@ -341,12 +353,20 @@ __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
     nxt = x;
     __syncthreads();
   }
-  for (int i = tid; i < p.Np; i += kListThreads) {
-    u32x4* m = (u32x4*)(p.M + (int64_t)i * p.Np + 32 * b);
-    m[0] = bytes_of_bit16(cur[i] & 0xffffu);
-    m[1] = bytes_of_bit16(cur[i] >> 16);
+  for (int i = tid; i < (CALLER ? p.n : p.Np); i += kListThreads) {
+    uint8_t* m = (uint8_t*)p.M + (int64_t)i * p.ldm + 32 * b;
+    const unsigned w = cur[i];
+    if (!CALLER) {
+      ((u32x4*)m)[0] = bytes_of_bit16(w & 0xffffu);
+      ((u32x4*)m)[1] = bytes_of_bit16(w >> 16);
+    } else if (32 * b + 32 <= p.n) {
+      store16_any(m, bytes_of_bit16(w & 0xffffu));
+      store16_any(m + 16, bytes_of_bit16(w >> 16));
+    } else {
+      for (int x = 0; 32 * b + x < p.n; ++x) m[x] = (uint8_t)((w >> x) & 1u);
+    }
   }
-  for (int r = wave; r < 32; r += kListThreads / 64)
+  for (int r = wave; !CALLER && r < 32; r += kListThreads / 64)
     for (int c = 16 * lane; c < p.Np; c += 1024) {
       u32x4 v;
 #pragma unroll
@@ -370,15 +390,36 @@ __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
   }
 }
 
-hipError_t launch_layer_lists(const LayerLists& p, const int8_t* P, hipStream_t s) {
-  if (p.n <= 0 || p.Np > kListMaxN || p.Np % 64 || p.Np < p.n) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, (const uint8_t*)P, (int64_t)p.Np, p.n, p.idx, p.len,
-                     p.status_out);
-  if (p.Np <= kListMaxN * 5 / 8)  // 24 bytes a row: 120 KB
-    hipLaunchKernelGGL(k_layer_lists<8>, dim3(p.Np / 32), dim3(kListThreads), 24 * p.Np, s, p);
+constexpr int kListsOf8 = kListMaxN * 5 / 8;  // up to here 8 entries a row fit: 24 bytes a row, 120 KB
+
+template <bool CALLER>
+static hipError_t launch_layer(const LayerLists& p, const uint8_t* P, int64_t ldp, hipStream_t s) {
+  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, P, ldp, p.n, p.idx, p.len, p.status_out);
+  const dim3 grid(p.Np / 32);
+  if (p.Np <= kListsOf8)
+    hipLaunchKernelGGL((k_layer_lists<8, CALLER>), grid, dim3(kListThreads), 24 * p.Np, s, p);
   else
-    hipLaunchKernelGGL(k_layer_lists<4>, dim3(p.Np / 32), dim3(kListThreads), 16 * p.Np, s, p);
+    hipLaunchKernelGGL((k_layer_lists<4, CALLER>), grid, dim3(kListThreads), 16 * p.Np, s, p);
   return hipGetLastError();
+}
+
+hipError_t launch_layer_lists(const LayerLists& q, const int8_t* P, hipStream_t s) {
+  if (q.n <= 0 || q.Np > kListMaxN || q.Np % 64 || q.Np < q.n) return hipErrorInvalidValue;
+  LayerLists p = q;
+  p.lda = p.ldm = p.Np;
+  return launch_layer<false>(p, (const uint8_t*)P, p.Np, s);
+}
+
+hipError_t launch_closure_lists(const LayerLists& q, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
+                                hipStream_t s) {
+  if (q.n <= 0 || q.n > kListMaxN) return hipErrorInvalidValue;
+  LayerLists p = q;
+  p.Np = (p.n + 31) / 32 * 32;
+  p.A = (const int8_t*)A;
+  p.lda = lda;
+  p.M = (int8_t*)R;
+  p.ldm = ldr;
+  return launch_layer<true>(p, A, lda, s);
 }
 
 __global__ void __launch_bounds__(256) k_lists_clear(ListParams p) {
@@ -390,12 +431,16 @@ size_t sg_lists_bytes(int64_t n) {
   return 2 * nb * 32 * nb * 4 + (size_t)(kListMax + 1) * n * 2;
 }
 
+template <int E, bool CALLER>
+static hipError_t layer_lists_attr(int bytes) {
+  return hipFuncSetAttribute((const void*)k_layer_lists<E, CALLER>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 hipError_t sg_lists_init() {
-  hipError_t e = hipFuncSetAttribute((const void*)k_layer_lists<4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     16 * kListMaxN);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_layer_lists<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          24 * (kListMaxN * 5 / 8));
+  hipError_t e = layer_lists_attr<8, false>(24 * kListsOf8);
+  if (e == hipSuccess) e = layer_lists_attr<8, true>(24 * kListsOf8);
+  if (e == hipSuccess) e = layer_lists_attr<4, false>(16 * kListMaxN);
+  if (e == hipSuccess) e = layer_lists_attr<4, true>(16 * kListMaxN);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute((const void*)k_sg_lists, hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kListMaxN * 4);
 }

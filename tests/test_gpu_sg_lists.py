@@ -109,3 +109,43 @@ def test_against_products(dl, n, cfg):
         assert a.converged and b.converged
         assert a.ones == b.ones and a.steps == b.steps and np.array_equal(host(a.R), host(b.R))
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [513, 543, 545, 1000, 1024, 2047, 5200])
+def test_plain_closure_by_lists(dl, n):
+    """dl_tc's plain int8 series, which takes the same lists (a word of 32
+    columns a row): models and iteration counts against the oracle, and against
+    the squaring series' model; a row of 33 entries, a path and an empty
+    relation too."""
+    import torch
+
+    rng = np.random.default_rng(n)
+    rels = {"er": dlgen.to_dense(n, dlgen.er_edges(n, 2.0 / n, 3 * n, self_loops=True))}
+    if n <= 2047:
+        rels["sparse"] = dlgen.to_dense(n, dlgen.er_edges(n, 0.8 / n, 4 * n))
+        rels["empty"] = np.zeros((n, n), dtype=np.uint8)
+        long_row = rels["sparse"].copy()
+        long_row[n - 1] = 0
+        long_row[n - 1, rng.choice(n, 33, replace=False)] = 1
+        rels["row of 33"] = long_row
+        several = rels["sparse"].copy()
+        for row in range(0, n, 5):
+            several[row] = 0
+            several[row, rng.choice(n, row % 33, replace=False)] = 1
+        rels["lists of 0 to 32"] = several
+    if n <= 600:
+        path = np.zeros((n, n), dtype=np.uint8)
+        path[np.arange(n - 1), np.arange(1, n)] = 1
+        rels["path"] = path
+    for tag, a in rels.items():
+        announce("plain lists", n, tag)
+        want, _, iters, _ = oracle.tc_seminaive(a)
+        off = n % 4
+        flat = torch.full((off + n * (n + off) + 8,), 9, dtype=torch.uint8, device="cuda")
+        out = flat[off : off + n * (n + off)].view(n, n + off)[:, :n]
+        _, it = dl.dl_tc(dev(a * np.uint8(5)), method=dl.DL_TC_PLAIN, prec="i8", out=out)
+        assert it == iters, (tag, it, iters)
+        h = host(flat)
+        rows = h[off : off + n * (n + off)].reshape(n, n + off)
+        assert np.array_equal(rows[:, :n], want), tag
+        assert (rows[:, n:] == 9).all() and (h[:off] == 9).all() and (h[off + n * (n + off) :] == 9).all()
