@@ -35,7 +35,7 @@
 // of words, so the 16 rows one read touches hit distinct banks.
 //
 // Measured (MI355X, a call as the caller sees it, degree 2; before: product
-// launches): n = 300 108 -> 48 us, n = 1000 140 -> 67 us, n = 2048 210 -> 180
+// launches): n = 300 108 -> 50 us, n = 1000 140 -> 63 us, n = 2048 210 -> 180
 // us.  Of the 50 us in the kernel at n = 1000 (seven steps) the waits for
 // other workgroups take 24, the products 11 (AND and OR of the bits on the
 // vector units instead: 17), publishing 6, fetching 4: bound by the chain of
