@@ -660,11 +660,11 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
   // launches are timed, which only the chunked path has
   const bool square_bits = whole && mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax &&
                            !(te && te->ms == 0.0) && !c->timing;
-  const bool sg_lists = whole && mode == M_SG && prec == P_I8 && max_steps >= 2 && n >= kListMinN && n <= kListMaxN &&
+  const bool sg_lists = whole && mode == M_SG && prec == P_I8 && max_steps >= 2 && n <= kListMaxN &&
                         !(te && te->ms == 0.0) && !c->timing;
   // the plain int8 series run to its end, where nobody asks for its sizes
   const bool plain_lists = whole && !plain_whole && mode == M_PLAIN && prec == P_I8 && !ones_out && max_steps >= n + 2 &&
-                           n >= kListMinN && n <= kListMaxN && !(te && te->ms == 0.0) && !c->timing;
+                           n <= kListMaxN && !(te && te->ms == 0.0) && !c->timing;
   if (plain_whole || square_bits || sg_lists || plain_lists) {
     if ((rc = ensure_ws(c, need))) return rc;
     for (int g = 0; g < count; ++g) {

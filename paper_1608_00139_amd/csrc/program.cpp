@@ -793,7 +793,7 @@ int Runner::iterate(int L, const std::vector<int>& heads, const std::vector<Mat>
   }
   bool cfg_set = false;  // the caller chose a product configuration for this size
   for (const auto& t : g->ctx->tuned) cfg_set = cfg_set || (t.prec == P_I8 && t.np == Np && t.ms == 0.0);
-  if (M == 1 && rec.size() == 1 && !ops[0][0].trans && ops[0][0].P.ident != ops[0][0].S.ident && n >= kListMinN &&
+  if (M == 1 && rec.size() == 1 && !ops[0][0].trans && ops[0][0].P.ident != ops[0][0].S.ident &&
       Np <= kListMaxN && !cfg_set && !g->ctx->timing) {
     // R = A + P R, or R^T = A^T + S^T R^T, by lists where the relation's rows
     // allow it

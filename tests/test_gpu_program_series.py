@@ -176,7 +176,7 @@ q(X,Y) :- not p(X,Z), q(Z,Y).
 @pytest.mark.parametrize("n", [511, 512, 545, 1000])
 def test_series_by_lists_vs_oracle(dl, text, n):
     """Layers with one recursive term, by lists of the relation's entries
-    (from n = 512, at most 32 a row) and, for a longer row or a complement, by
+    (at most 32 a row) and, for a longer row or a complement, by
     products: models and iteration counts."""
     rng = np.random.default_rng(n)
     for kind in ("sparse", "loops and longer lists", "long row", "empty base"):
@@ -204,6 +204,27 @@ def test_series_by_lists_vs_oracle(dl, text, n):
                 prog.bind(k, t)
         prog.run(dl.DL_EVAL_ITERATION)
         _check(dl, prog, text, {k: v for k, v in rels.items() if f"{k}(" in text}, n)
+        prog.close()
+
+
+@pytest.mark.parametrize("text", [PATH, LEFT], ids=["right", "left"])
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 64, 65, 200, 257])
+def test_small_series_by_lists(dl, text, n):
+    """The smallest sizes, where every row is short (n <= 32) or one in the
+    middle, beyond the first eight, is too long for a list (n > 33)."""
+    for long_row in (False, True):
+        rels = {k: dlgen.to_dense(n, dlgen.er_edges(n, min(0.5, 1.5 / n), n + i, self_loops=True)) for i, k in enumerate("ef")}
+        if long_row:
+            for m in rels.values():
+                m[n // 2] = 1
+                m[:, n // 2] = 1
+        announce("small program lists", n, long_row)
+        prog = dl.Program(text)
+        keep = {k: dev(v) for k, v in rels.items() if f"{k}(" in text}
+        for k, t in keep.items():
+            prog.bind(k, t)
+        prog.run(dl.DL_EVAL_ITERATION)
+        _check(dl, prog, text, {k: rels[k] for k in keep}, n)
         prog.close()
 
 

@@ -1,4 +1,4 @@
-"""Same generation by lists (int8, n >= 512, at most 32 entries a row): models,
+"""Same generation by lists (int8, at most 32 entries a row): models,
 per-step sizes and iteration counts against the oracle, exactly, at the edges
 of its 32-row slices and of its list length, and with the products' route
 beside it (another precision takes it)."""
@@ -38,6 +38,16 @@ def _check(dl, p, tag, caps=()):
 @pytest.mark.parametrize("n", [511, 512, 513, 543, 544, 545, 1000, 1024, 1025, 2047, 3000])
 def test_forests(dl, n):
     _check(dl, dlgen.to_dense(n, dlgen.forest_edges(n, n)), "forest", (0, 1, 2, 3))
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 65, 200, 257])
+def test_small(dl, n):
+    """One slice, two, an odd number of them; a row in the middle that is too
+    long for a list from n = 33 on."""
+    p = dlgen.to_dense(n, dlgen.forest_edges(n, n))
+    _check(dl, p, "small forest", (0, 1, 2, 3))
+    p[n // 2] = 1
+    _check(dl, p, "small, long row", (2,))
 
 
 @pytest.mark.parametrize("n", [600, 1100])
