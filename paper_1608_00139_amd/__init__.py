@@ -467,6 +467,7 @@ class Program:
         self.ctx = _ctx(ctx)
         self._h = ctypes.c_void_p()
         self._bound = {}
+        self._n = 0  # constants of the last run
         _check(lib.dl_program_create(self.ctx.handle, text.encode(), ctypes.byref(self._h)))
 
     def close(self) -> None:
@@ -498,6 +499,7 @@ class Program:
 
     def run(self, method: int = DL_EVAL_ITERATION, stream=None) -> None:
         _check(load().dl_program_run(self._h, int(method), _stream_ptr(stream)))
+        self._n = next(iter(self._bound.values())).shape[0] if self._bound else 0
 
     def layers(self) -> list[dict]:
         lib = load()
@@ -519,7 +521,7 @@ class Program:
         """Returns (model, ones)."""
         if out is None:
             if n is None:
-                n = next(iter(self._bound.values())).shape[0] if self._bound else 0
+                n = self._n
             out = torch.empty((n, n), dtype=torch.uint8, device=f"cuda:{self.ctx.device}")
         nn, ld = _mat(out, "out")
         ones = ctypes.c_int64()

@@ -206,7 +206,7 @@ struct dl_program {
   std::vector<const uint8_t*> bound;
   std::vector<int64_t> bound_ld;
   // device state
-  int64_t Np = 0;
+  int64_t Np = 0, ran_n = 0;  // sizes of the last run's matrices (n may be bound anew before the next)
   bool ran = false;
   std::vector<Mat> val, comp;
   std::shared_ptr<MatPool> mats;  // where the matrices come from (null: allocated and freed, with a budget)
@@ -996,6 +996,7 @@ int dl_program_run(dl_program* g, int method, void* stream) {
   if (g->n < 0) g->n = 0;
   P_HIP(hipSetDevice(g->ctx->device));
   release(g);
+  g->ran_n = g->n;
   hipStream_t s = (hipStream_t)stream;
   Runner r{g, s, g->n, 0, 0, {}, {}, {}, {}};
   g->val.assign(g->names.size(), Mat());
@@ -1059,17 +1060,18 @@ int dl_program_fetch(dl_program* g, const char* name, uint8_t* out, int64_t ldo,
   if (!g->ran) return perr(DL_EINVAL, "the program has not been run");
   const int p = pred_index(g, name);
   if (p < 0 || g->kind[p] != K_DEFINED) return perr(DL_EINVAL, std::string(name) + " is not defined by the program");
-  if (g->n > 0 && (!out || ldo < g->n)) return perr(DL_EINVAL, "bad output matrix");
-  if (g->n == 0) {
+  const int64_t n = g->ran_n;
+  if (n > 0 && (!out || ldo < n)) return perr(DL_EINVAL, "bad output matrix");
+  if (n == 0) {
     if (ones) *ones = 0;
     return DL_OK;
   }
   P_HIP(hipSetDevice(g->ctx->device));
   hipStream_t s = (hipStream_t)stream;
   if (ones)
-    P_HIP(launch_emit_sum(g->val[p].M, (int)g->Np, (int)g->n, out, ldo, g->dcnt, g->hcnt_dev, s));
+    P_HIP(launch_emit_sum(g->val[p].M, (int)g->Np, (int)n, out, ldo, g->dcnt, g->hcnt_dev, s));
   else
-    P_HIP(launch_emit(P_I8, g->val[p].M, (int)g->Np, 0, (int)g->n, out, ldo, s));
+    P_HIP(launch_emit(P_I8, g->val[p].M, (int)g->Np, 0, (int)n, out, ldo, s));
   P_HIP(hipStreamSynchronize(s));
   if (ones) *ones = (int64_t)g->hcnt[0];
   return DL_OK;

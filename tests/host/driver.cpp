@@ -1,0 +1,68 @@
+// The cases of tests/test_host_sources.py, one by name: prints "ok" or what
+// went wrong.
+#include <cstdio>
+#include <cstring>
+
+#include "../../include/dl.h"
+#include "runtime.h"
+
+namespace {
+
+int bad(const char* what, long long got) {
+  std::printf("%s: %lld (%s)\n", what, got, dl_last_error());
+  return 1;
+}
+
+const char* kClosure = "tc(X,Y) :- e(X,Y).\ntc(X,Y) :- e(X,Z), tc(Z,Y).\n";
+uint8_t* const kSome = (uint8_t*)64;  // a matrix that nothing reads here
+
+// A relation bound at another size after a run: the results of the last run
+// stay what they were until the next one.
+int fetch_after_rebind() {
+  dl_ctx* ctx = nullptr;
+  dl_program* p = nullptr;
+  if (int rc = dl_create(&ctx, 0, 0)) return bad("create", rc);
+  if (int rc = dl_program_create(ctx, kClosure, &p)) return bad("program", rc);
+  if (int rc = dl_program_bind(p, "e", 300, kSome, 300)) return bad("bind", rc);
+  if (int rc = dl_program_run(p, DL_EVAL_ITERATION, nullptr)) return bad("run", rc);
+  for (const int64_t n : {3000, 100, 0, 300}) {
+    if (int rc = dl_program_bind(p, "e", n, kSome, n)) return bad("bind again", rc);
+    int64_t ones = -1;
+    for (const bool count : {true, false}) {
+      fake::emits.clear();
+      if (int rc = dl_program_fetch(p, "tc", kSome, 3000, count ? &ones : nullptr, nullptr)) return bad("fetch", rc);
+      if (fake::emits.size() != 1) return bad("launches of a fetch", (long long)fake::emits.size());
+      const fake::Emit e = fake::emits[0];
+      if (e.n != 300 || e.Np != 512 || e.ld != 3000) return bad("constants fetched", e.n);
+    }
+    if (ones != 77) return bad("ones", ones);
+    if (dl_program_fetch(p, "tc", kSome, 299, &ones, nullptr) != DL_EINVAL) return bad("stride 299 taken", n);
+  }
+  if (int rc = dl_program_bind(p, "e", 600, kSome, 600)) return bad("bind", rc);
+  if (int rc = dl_program_run(p, DL_EVAL_ITERATION, nullptr)) return bad("run", rc);
+  fake::emits.clear();
+  if (int rc = dl_program_fetch(p, "tc", kSome, 600, nullptr, nullptr)) return bad("fetch", rc);
+  if (fake::emits[0].n != 600 || fake::emits[0].Np != 768) return bad("constants of the second run", fake::emits[0].n);
+  dl_program_destroy(p);
+  dl_destroy(ctx);
+  return fake::live ? bad("bytes left", (long long)fake::live) : 0;
+}
+
+struct Case {
+  const char* name;
+  int (*run)();
+};
+const Case kCases[] = {{"fetch_after_rebind", fetch_after_rebind}};
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  for (const Case& c : kCases)
+    if (argc > 1 && !std::strcmp(argv[1], c.name)) {
+      const int rc = c.run();
+      if (!rc) std::printf("ok\n");
+      return rc;
+    }
+  std::printf("no such case\n");
+  return 2;
+}
