@@ -230,12 +230,47 @@ size_t fix_bits_bytes(int64_t n);
 constexpr int64_t kFixBitsWords = 2 * (kBitSteps + 1) * kBitTiles * kBitLine + 2;
 hipError_t launch_fix_bits(const FixBitsParams& p, bool clear_first, hipStream_t s);
 
+// Where a row turns out too long for lists, the launch that would have run the
+// series writes the first operands of its products instead (int8, Np x Np, as
+// launch_ingest and launch_identity do): with the ring of model sizes reset by
+// the pass that makes the lists, finding out costs a dense relation no launch.
+// Calls in us, without lists and with: same generation, density 0.3, n = 64, 512,
+// 2048, 4096: 96, 100, 164, 265 and 94, 91, 136, 250; plain closure, 300 entries a
+// row, n = 600, 1000, 4096, 8192: 91, 98, 180, 1052 and 79, 83, 175, 1075 (with a
+// launch that only says no, then those of the product series: 116, 114, 158, 281
+// and 109, 114, 204, 1075).
+//   same generation: Y = P, S1 = I, ring[1] = n, `words` zeros at `zero`
+//   plain closure:   Y = A + I, S1 = A^T, ring[1] = the ones of A
+struct DenseStart {
+  int8_t* Y;
+  int8_t* S1;
+  int Np;
+  unsigned long long* ring;
+  int* conv;
+  unsigned* zero;
+  int words;
+};
+
 // The same-generation series by lists of P's entries, on bits, in one launch
 // (list_kernels.hip), for n <= kListMaxN and at most kListMax entries a row.
+//
+// Series with a relation of few entries a row go by lists at every size up to
+// kListMaxN (a slice of 32 rows a compute unit) and up to kListMax entries in
+// every row: at 32 they still win everywhere.  Calls in us, lists / products,
+// relations with exactly 4, 16 and 32 entries in every row (5 to 7, 4 or 5, 3 to
+// 5 steps):
+//   same generation  n = 64 54/102, 59/99, 64/94; 512 61/153, 64/100, 82/101;
+//                    4096 96/547, 145/428, 189/347; 8192 168/3795, 261/2544, 358/1946
+//   plain closure    n = 1024 45/168, 47/103, 55/98; 4096 73/624, 91/351, 126/270;
+//                    8192 111/3855, 172/1699, 238/1356
+//   program closure  n = 64 52/113, 51/77, 53/73; 512 50/123, 51/83, 59/78;
+//                    4096 106/706, 122/368, 155/291; 8192 208/4750, 270/2050, 334/1648
 constexpr int kListMax = 32;
-constexpr int kListMaxN = 8192;   // a slice of 32 rows a compute unit
+constexpr int kListMaxN = 8192;
 constexpr int kListArrivals = 8;  // words that a step's arrivals are spread over, a line each
 struct ListParams {
+  const uint8_t* P;
+  int64_t ldp;
   uint8_t* R;
   int64_t ldr;
   unsigned* VT[2];      // slices of P S, step t in VT[t & 1] ...
@@ -248,13 +283,13 @@ struct ListParams {
   int n, nb, pitch;              // nb = ceil(n / 32) slices of pitch = 32 nb words
   int max_steps;                 // 2 .. kRing - 1
   long long wait_limit;          // ticks
+  DenseStart dense;
 };
 size_t sg_lists_bytes(int64_t n);
 constexpr int kListWords = 4 * kListArrivals * 32 + 2;  // 32-bit, 8-byte aligned
 hipError_t sg_lists_init();
 // ws: sg_lists_bytes(n), 16-byte aligned; words: kListWords of them.
-hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t* ws, unsigned* words, bool clear_first,
-                           hipStream_t s);
+hipError_t launch_sg_lists(ListParams p, uint8_t* ws, unsigned* words, bool clear_first, hipStream_t s);
 
 // The series of a program's layer with one recursive term, R = A + P R, by
 // lists of P's entries (k_layer_lists), Np <= kListMaxN.
@@ -267,12 +302,13 @@ struct LayerLists {
   unsigned* words;       // [0] workgroups done, [1] their last steps; zero between launches
   unsigned* status_out;  // host memory: K, the first step that repeats, or 0 if a row is too long
   int n, Np;
+  DenseStart dense;  // the plain closure's (otherwise nothing is written for a row too long)
 };
 constexpr int kLayerWords = 2;
 inline size_t layer_lists_bytes(int64_t n) { return (size_t)(kListMax + 1) * n * 2; }
 hipError_t launch_layer_lists(const LayerLists& p, const int8_t* P, hipStream_t s);
 // The plain closure R = A + A R of a caller's relation the same way (idx, len,
-// words, status_out and n of p are used).
+// words, status_out, n and dense of p are used).
 hipError_t launch_closure_lists(const LayerLists& p, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
                                 hipStream_t s);
 

@@ -17,16 +17,6 @@
 // Fixpoints a batched call keeps in flight (each with its own workspace,
 // counters and read-back event).
 constexpr int kFixSlots = 2;
-// Series with a relation of few entries a row are run by lists of them, at
-// every size up to kListMaxN: same generation of forests of n = 40, 200, 512
-// 46, 62, 61 us against 172, 174, 179 for products, a program's closure (degree
-// 2) of the same sizes 51, 53, 51 against 180, 242, 250, the plain closure of
-// n = 600, 1000, 4096 (28 to 34 steps) 47, 56, 97 against 329, 407, 1739 (up to
-// Np = 512 it has k_fix_small).  Finding that a row is too long costs a
-// dense relation 10 to 15 us (same generation of n = 64 and 512 in three steps
-// 100, 92 to 109, 103; plain closure of n = 1000 and 4096, degree 300: 103, 182
-// to 109, 197; a program's closure nothing).
-
 constexpr size_t kSlotWords = (size_t)dl::kRing + 1;  // a slot's ring and its convergence step
 
 struct EventPair {

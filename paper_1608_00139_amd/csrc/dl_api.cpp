@@ -167,6 +167,13 @@ enum Mode { M_PLAIN = 0, M_SQUARE = 1, M_SG = 2 };
 // Workspace of one fixpoint: four operand-precision matrices.
 size_t fix_ws_bytes(int prec, int64_t Np) { return 4 * (size_t)mat_bytes(prec, Np) + 256; }
 
+// The stream-K plan of S', its scratch behind the operands.
+void plan_sk(uint8_t* ws, int prec, int64_t Np, SkParams* q) {
+  sk_plan(Np, *q);
+  q->scratch = ws + 4 * (size_t)mat_bytes(prec, Np);
+  q->tile_cnt = (unsigned*)(q->scratch + (size_t)q->tiles * q->maxc * kSkSlot);
+}
+
 // Device and pinned host state of one fixpoint in flight.
 struct FixSlot {
   uint8_t* ws = nullptr;
@@ -187,9 +194,9 @@ struct FixSlot {
 class Fix {
  public:
   Fix(dl_ctx* c, const FixSlot& sl, int mode, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
-      int prec, int32_t max_steps, hipStream_t s)
+      int prec, int32_t max_steps, hipStream_t s, bool ready)
       : c_(c), sl_(sl), mode_(mode), n_(n), A_(A), lda_(lda), R_(R), ldr_(ldr), prec_(prec),
-        max_steps_(max_steps), s_(s), tm_{c, s, {}} {}
+        max_steps_(max_steps), s_(s), ready_(ready), tm_{c, s, {}} {}
 
   bool done() const { return done_; }
   const FixSlot& slot() const { return sl_; }
@@ -203,7 +210,7 @@ class Fix {
     uint8_t* op[4];
     for (int i = 0; i < 4; ++i) op[i] = sl_.ws + i * matT;
     // the whole ring, so that chunks need no clear until the steps wrap
-    DL_HIP(launch_ring_clear(sl_.ring, sl_.conv, 0, kRing, 1, s_));
+    if (!ready_) DL_HIP(launch_ring_clear(sl_.ring, sl_.conv, 0, kRing, 1, s_));
     // The closure steps add the previous iterate instead of A (plain: A^T),
     // which gives the same iterates: R^(k) = A + f(R^(k-1)) lies inside
     // A + f(R^(k)) because f is monotone and R^(k-1) <= R^(k), and it
@@ -217,7 +224,8 @@ class Fix {
       Yop_ = op[0];
       S_[0] = op[1];
       S_[1] = op[2];
-      DL_HIP(launch_ingest(prec_, A_, lda_, (int)n_, (int)Np_, nullptr, nullptr, Yop_, S_[1], 1, sl_.ring + 1, s_));
+      if (!ready_)
+        DL_HIP(launch_ingest(prec_, A_, lda_, (int)n_, (int)Np_, nullptr, nullptr, Yop_, S_[1], 1, sl_.ring + 1, s_));
     } else if (mode_ == M_SQUARE) {
       // R^(1) = A and R^(1)T + I
       S_[0] = op[0];
@@ -231,16 +239,16 @@ class Fix {
       S_[0] = op[1];
       S_[1] = op[2];
       Tmp_ = op[3];
-      DL_HIP(launch_ingest(prec_, A_, lda_, (int)n_, (int)Np_, nullptr, nullptr, Yop_, nullptr, 0, nullptr, s_));
-      DL_HIP(launch_identity(prec_, S_[1], (int)Np_, (int)n_, s_));
-      DL_HIP(launch_ring_set(sl_.ring, 1, (unsigned long long)n_, s_));
+      if (!ready_) {
+        DL_HIP(launch_ingest(prec_, A_, lda_, (int)n_, (int)Np_, nullptr, nullptr, Yop_, nullptr, 0, nullptr, s_));
+        DL_HIP(launch_identity(prec_, S_[1], (int)Np_, (int)n_, s_));
+        DL_HIP(launch_ring_set(sl_.ring, 1, (unsigned long long)n_, s_));
+      }
       // S' is symmetric: its product runs on the upper-triangle tiles only,
       // split stream-K over the compute units (scratch after the operands)
       if (sk_supported(prec_, cfg_, Np_)) {
-        sk_plan(Np_, skq_);
-        skq_.scratch = sl_.ws + 4 * matT;
-        skq_.tile_cnt = (unsigned*)(skq_.scratch + (size_t)skq_.tiles * skq_.maxc * kSkSlot);
-        DL_HIP(hipMemsetAsync(skq_.tile_cnt, 0, (size_t)skq_.tiles * sizeof(unsigned), s_));
+        plan_sk(sl_.ws, prec_, Np_, &skq_);
+        if (!ready_) DL_HIP(hipMemsetAsync(skq_.tile_cnt, 0, (size_t)skq_.tiles * sizeof(unsigned), s_));
         use_sk_ = true;
       }
     }
@@ -308,9 +316,10 @@ class Fix {
   // after the fixpoint return at once but still cost a few microseconds
   // each.  The plain series starts at 4 and doubles; the same-generation
   // series (two launches a step, each ~3 us when it returns at once) starts
-  // at 4 and grows by half, so that fewer steps run past its fixpoint.
+  // at 4 and grows by half, so that fewer steps run past its fixpoint; at 3 for
+  // a relation with rows too long for lists, whose series is mostly 3 or 4 steps.
   int chunk() {
-    if (chunk_ == 0) chunk_ = mode_ == M_SQUARE ? 6 : 4;
+    if (chunk_ == 0) chunk_ = mode_ == M_SQUARE ? 6 : mode_ == M_SG && ready_ ? 3 : 4;
     const int cnt = (int)std::min<int64_t>(chunk_, (int64_t)max_steps_ - s0_ + 1);
     // entries of steps >= kRing still hold the counts of kRing steps before
     if (s0_ + cnt > kRing) DL_HIP(launch_ring_clear(sl_.ring, sl_.conv, (int)s0_, cnt, 0, s_));
@@ -393,6 +402,7 @@ class Fix {
   int prec_;
   int32_t max_steps_;
   hipStream_t s_;
+  const bool ready_;  // the list kernels have written the first operands and the ring (dense_start)
   Timer tm_;
   int64_t Np_ = 0;
   int cfg_ = 0;
@@ -459,6 +469,7 @@ int await_status(dl_ctx* c, int max_steps, hipStream_t s, bool* not_resident) {
 std::atomic<int> g_whole_units[64];
 constexpr int kWholeUnits = 256;
 constexpr int kNoRoom = -1;  // of run_whole: run the series by product launches
+constexpr int kDense = -2;   // the same, a row being too long for a list: their first operands are in place
 
 // Runs a whole-fixpoint kernel, launch(clear), of `units` compute units;
 // kNoRoom if it is not started or its workgroups do not come to run together.
@@ -565,24 +576,49 @@ int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
 // unit there; more tiles would not be resident at once).
 constexpr int64_t kBitSquareMax = 64 * kBitTiles;
 
+// Where the list kernels write a dense relation's first operands: those of a
+// Fix in the first slot, whose workspace begins at ws.  The lists themselves
+// lie in the fourth matrix, which holds nothing then.
+DenseStart dense_start(dl_ctx* c, uint8_t* ws, int mode, int64_t Np) {
+  const size_t mat = (size_t)mat_bytes(P_I8, Np);
+  DenseStart d{};
+  d.Y = (int8_t*)ws;
+  d.S1 = (int8_t*)(ws + 2 * mat);
+  d.Np = (int)Np;
+  d.ring = c->ring;
+  d.conv = (int*)(c->ring + kRing);
+  if (mode == M_SG && sk_supported(P_I8, pick_config(c, P_I8, Np), Np)) {
+    SkParams q{};
+    plan_sk(ws, P_I8, Np, &q);
+    d.zero = q.tile_cnt;
+    d.words = q.tiles;
+  }
+  return d;
+}
+
 // The same-generation series by lists (k_sg_lists), read back like
-// run_plain_whole; kNoRoom as well if a row of P is too long for a list or the
-// series for the ring of model sizes.
+// run_plain_whole; kDense if a row of P is too long for a list, kNoRoom as well
+// if the series is for the ring of model sizes.
 int run_sg_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* P, int64_t ldp, uint8_t* R, int64_t ldr,
                  int32_t max_steps, int64_t* ones_out, int32_t* steps_out, int32_t* converged_out, hipStream_t s) {
+  const int64_t Np = padded_size_for(P_I8, n);
   ListParams p{};
+  p.P = P;
+  p.ldp = ldp;
   p.R = R;
   p.ldr = ldr;
   p.n = (int)n;
   p.max_steps = std::min(max_steps, kRing - 1);
   p.wait_limit = kFixSmallWaitTicks;
+  p.dense = dense_start(c, ws, M_SG, Np);
+  uint8_t* lists = ws + 3 * (size_t)mat_bytes(P_I8, Np);
   unsigned* words = c->fs_words + fix_small_words(512) + kFixBitsWords;
   if (int rc = run_whole(c, (int)((n + 31) / 32), &c->fl_dirty, p.max_steps, s, &p.ring_out, &p.status_out,
-                         [&](bool clear) { return launch_sg_lists(p, P, ldp, ws, words, clear, s); }))
+                         [&](bool clear) { return launch_sg_lists(p, lists, words, clear, s); }))
     return rc;
   const volatile unsigned long long* ring = c->h_ring;
   const int64_t K = *(volatile unsigned*)(c->h_ring + kRing);
-  if (K == 0) return kNoRoom;
+  if (K == 0) return kDense;
   const bool converged = K >= 2 && ring[K] == ring[K - 1];
   if (!converged && K < max_steps) return kNoRoom;
   if (ones_out) {
@@ -595,21 +631,23 @@ int run_sg_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* P, int64_t ld
 }
 
 // The plain closure by lists (k_layer_lists: the same iterates, in columns),
-// without its model sizes; kNoRoom if a row of A is too long for a list.
+// without its model sizes; kDense if a row of A is too long for a list.
 int run_plain_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
                     int32_t max_steps, int32_t* steps_out, int32_t* converged_out, hipStream_t s) {
+  const int64_t Np = padded_size_for(P_I8, n);
   LayerLists p{};
-  p.idx = (unsigned short*)ws;
+  p.idx = (unsigned short*)(ws + 3 * (size_t)mat_bytes(P_I8, Np));
   p.len = p.idx + (size_t)kListMax * n;
   p.words = c->fs_words + fix_small_words(512) + kFixBitsWords + kListWords;
   p.n = (int)n;
+  p.dense = dense_start(c, ws, M_PLAIN, Np);
   unsigned long long* ring_out = nullptr;
   expect_status(c, &ring_out, &p.status_out);
   DL_HIP(launch_closure_lists(p, A, lda, R, ldr, s));
   bool not_resident = false;
   if (int rc = await_status(c, max_steps, s, &not_resident)) return rc;
   const unsigned K = *(volatile unsigned*)(c->h_ring + kRing);
-  if (K == 0) return kNoRoom;
+  if (K == 0) return kDense;
   DL_HIP(hipStreamSynchronize(s));  // R is in place for every stream
   if (steps_out) *steps_out = (int32_t)K;
   if (converged_out) *converged_out = 1;
@@ -620,10 +658,11 @@ int run_plain_lists(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
 // up to two in flight: while the host reads one's counters back, the device
 // runs the other's products.  Per-fixpoint outputs are indexed by g;
 // ones_out (model sizes per step) is taken for count == 1 only.  whole: the
-// one-launch kernels may be used where they apply.
+// one-launch kernels may be used where they apply; without, ready: the list
+// kernels have written the first relation's operands.
 int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* const* A, int64_t lda,
                   uint8_t* const* R, int64_t ldr, int prec, int32_t max_steps, int64_t* ones_out,
-                  int32_t* steps_out, int32_t* converged_out, hipStream_t s, bool whole = true) {
+                  int32_t* steps_out, int32_t* converged_out, hipStream_t s, bool whole = true, bool ready = false) {
   if (prec < P_I8 || prec > P_FP4) return fail(DL_EINVAL, "unknown precision");
   if (max_steps < 0) return fail(DL_EINVAL, "max_steps < 0");
   if (count <= 0) return DL_OK;
@@ -676,15 +715,16 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
            : square_bits ? run_square_bits(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s)
            : sg_lists    ? run_sg_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, ones, steps, converged, s)
                          : run_plain_lists(c, ws, n, A[g], lda, R[g], ldr, max_steps, steps, converged, s);
-      if (rc == kNoRoom)  // this one and the rest by product launches
+      if (rc == kNoRoom || rc == kDense)  // this one and the rest by product launches
         return run_fixpoints(c, mode, count - g, n, A + g, lda, R + g, ldr, prec, max_steps, ones, steps, converged, s,
-                             false);
+                             false, rc == kDense);
       if (rc) return rc;
     }
     return DL_OK;
   }
   int nslots = count >= 2 ? kFixSlots : 1;
   if (nslots > 1 && c->budget && need * nslots > c->budget) nslots = 1;  // one at a time within the budget
+  if (need * nslots > c->ws_size) ready = false;  // the workspace moves
   if ((rc = ensure_ws(c, need * nslots))) return rc;
   FixSlot slots[kFixSlots];
   for (int i = 0; i < nslots; ++i) {
@@ -704,7 +744,7 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
   int next = 0;
   auto launch = [&](const FixSlot& sl) -> int {
     const int g = next++;
-    jobs.emplace_back(c, sl, mode, n, A[g], lda, R[g], ldr, prec, max_steps, s);
+    jobs.emplace_back(c, sl, mode, n, A[g], lda, R[g], ldr, prec, max_steps, s, ready && g == 0);
     int r = jobs.back().start();
     if (r) return r;
     if (!jobs.back().done()) inflight.push_back(g);

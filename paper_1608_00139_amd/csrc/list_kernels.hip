@@ -44,9 +44,16 @@ typedef unsigned long long u64;
 // kListMax + 1 for a row with more.  A wave a row.  Where one of the first
 // rows is too long the host hears of it at once, so that a dense P's products
 // start 10 us earlier; of any other row it hears from k_sg_lists.  (One word
-// that all rows report to took 140 us of stores to one address.)
+// that all rows report to took 140 us of stores to one address.)  With ring, the
+// words of the product series start over as well (see DenseStart).
 __global__ void __launch_bounds__(256) k_row_lists(const uint8_t* P, int64_t ldp, int n, unsigned short* idx,
-                                                   unsigned short* len, unsigned* status_out) {
+                                                   unsigned short* len, unsigned* status_out,
+                                                   unsigned long long* ring, int* conv) {
+  if (ring) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    for (int q = t; q < kRing; q += gridDim.x * 256) ring[q] = 0ull;
+    if (t == 0) *conv = kNotConverged;
+  }
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= n) return;
   const uint8_t* src = P + (int64_t)row * ldp;
@@ -115,6 +122,47 @@ __device__ inline unsigned transpose32(unsigned v, int lane) {
 constexpr u64 kArrived = 1ull << 40;  // above any sum of ones
 constexpr int kListThreads = 1024;
 
+// Bytes c .. c + 15 of a caller's row of n as 0/1 bytes, 0 from n on.
+__device__ inline u32x4 row16(const uint8_t* row, int c, int n) {
+  if (c + 16 <= n) return bytes01(load16_any(row + c));
+  u32x4 v = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    if (c + e < n && row[c + e] != 0) v[e >> 2] |= 1u << (8 * (e & 3));
+  return v;
+}
+
+// Bit r of words c .. c + 15 as bytes: 16 elements of row r of a slice.
+__device__ inline u32x4 strip_row16(const unsigned* bits, int c, int r) {
+  u32x4 v;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const u32x4 w = *(const u32x4*)(bits + c + 4 * x);
+    v[x] = ((w[0] >> r) & 1u) | ((w[1] >> r) & 1u) << 8 | ((w[2] >> r) & 1u) << 16 | ((w[3] >> r) & 1u) << 24;
+  }
+  return v;
+}
+
+// DenseStart of the same generation, by all workgroups of k_sg_lists: a wave a row.
+__device__ inline void sg_dense_start(const ListParams& p) {
+  const DenseStart& d = p.dense;
+  const int wave = blockIdx.x * (kListThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  for (int row = wave; row < d.Np; row += gridDim.x * (kListThreads / 64))
+    for (int c = 16 * lane; c < d.Np; c += 1024) {
+      u32x4 v = {0u, 0u, 0u, 0u}, e = v;
+      if (row < p.n) {
+        v = row16(p.P + (int64_t)row * p.ldp, c, p.n);
+        if (row >= c && row < c + 16) e[(row - c) >> 2] = 1u << (8 * ((row - c) & 3));
+      }
+      *(u32x4*)(d.Y + (int64_t)row * d.Np + c) = v;
+      *(u32x4*)(d.S1 + (int64_t)row * d.Np + c) = e;
+    }
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < d.words; i += kListThreads) d.zero[i] = 0u;
+    if (threadIdx.x == 0) d.ring[1] = (u64)p.n;
+  }
+}
+
 __device__ inline u64* arrival(const ListParams& p, int t, int k) { return p.cnt + ((t & 3) * kListArrivals + k) * 16; }
 
 __global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
@@ -149,6 +197,7 @@ __global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
   __syncthreads();
   if (s_go == 0) {  // some row is too long for a list: every workgroup sees that
     if (b == 0 && tid == 0) st_system(p.status_out, 0u);
+    sg_dense_start(p);
     return;
   }
   // S^(1) = I
@@ -244,12 +293,7 @@ __global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
     const __amdgpu_buffer_rsrc_t D = buffer_of(dst, (unsigned)p.n);
     const bool aligned = ((uintptr_t)dst & 15) == 0;
     for (int c = 16 * lane; c < p.n; c += 1024) {
-      u32x4 v;
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const u32x4 s = *(const u32x4*)(S + c + 4 * x);
-        v[x] = ((s[0] >> r) & 1u) | ((s[1] >> r) & 1u) << 8 | ((s[2] >> r) & 1u) << 16 | ((s[3] >> r) & 1u) << 24;
-      }
+      const u32x4 v = strip_row16(S, c, r);
       if (aligned && c + 16 <= p.n) st_agent_x4(D, c, v);
       else store16_agent_any(dst + c, v, p.n - c);
     }
@@ -287,6 +331,65 @@ __global__ void __launch_bounds__(kListThreads) k_sg_lists(ListParams p) {
 // rows then come from memory entry by entry).
 // CALLER: A and R are a caller's matrices (n x n, any stride and alignment),
 // and no transpose is written.
+// DenseStart of the plain closure, by all workgroups of k_layer_lists, the b-th
+// of them: units of 128 columns (whole lines of A and Y) by a quarter of the
+// rows, as bits through LDS, word k of a row at k (Np / 4 + 16) + row (Np + 64
+// words; the pitch keeps four words of a row in different banks).  n = 8192,
+// 67 MB read and 134 MB written: 78 us in strips of 32 columns.
+__device__ inline void plain_dense_start(const LayerLists& p, int b, unsigned* bits) {
+  const DenseStart& d = p.dense;
+  __shared__ int s_ones;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int rows = d.Np / 4, pitch = rows + 16;
+  if (tid == 0) s_ones = 0;
+  int ones = 0;
+  for (int u = b; u < d.Np / 32; u += gridDim.x) {
+    const int c0 = u / 4 * 128, r0 = u % 4 * rows;
+    __syncthreads();
+    auto put = [&](int k, int r, u32x4 lo, u32x4 hi) {
+      const int i = r0 + r, c = c0 + 32 * k;
+      unsigned w = bit16_of_bytes(lo) | bit16_of_bytes(hi) << 16;
+      bits[k * pitch + r] = w;
+      ones += __popc(w);
+      if (i < p.n && i >= c && i < c + 32) w |= 1u << (i - c);
+      u32x4* y = (u32x4*)(d.Y + (int64_t)i * d.Np + c);
+      y[0] = bytes_of_bit16(w & 0xffffu);
+      y[1] = bytes_of_bit16(w >> 16);
+    };
+    const int k = tid & 3, left = p.n - r0 < rows ? p.n - r0 : rows;  // rows of the relation in this unit
+    const uint8_t* a = (const uint8_t*)p.A + (int64_t)(r0 + (tid >> 2)) * p.lda + c0 + 32 * k;
+    int r = tid >> 2;
+    if (c0 + 128 <= p.n)
+      for (; r + 3 * (kListThreads / 4) < left; r += kListThreads) {  // eight loads in flight
+        u32x4 x[4][2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e, a += (int64_t)(kListThreads / 4) * p.lda) {
+          x[e][0] = load16_any(a);
+          x[e][1] = load16_any(a + 16);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) put(k, r + e * (kListThreads / 4), x[e][0], x[e][1]);
+      }
+    for (; r < rows; r += kListThreads / 4) {
+      u32x4 x[2] = {};
+      if (r < left) {
+        const uint8_t* row = (const uint8_t*)p.A + (int64_t)(r0 + r) * p.lda;
+        x[0] = row16(row, c0 + 32 * k, p.n);
+        x[1] = row16(row, c0 + 32 * k + 16, p.n);
+      }
+      put(k, r, x[0], x[1]);
+    }
+    __syncthreads();
+    for (int col = wave; col < 128; col += kListThreads / 64)
+      for (int r = 16 * lane; r < rows; r += 1024)
+        *(u32x4*)(d.S1 + (int64_t)(c0 + col) * d.Np + r0 + r) = strip_row16(bits + (col >> 5) * pitch, r, col & 31);
+  }
+  ones = wave_sum(ones);
+  if (lane == 0 && ones) atomicAdd(&s_ones, ones);
+  __syncthreads();
+  if (tid == 0 && s_ones) atomicAdd(d.ring + 1, (u64)s_ones);
+}
+
 template <int E, bool CALLER>
 __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
   typedef unsigned short Entries __attribute__((ext_vector_type(E)));
@@ -306,6 +409,7 @@ __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
   __syncthreads();
   if (s_go == 0) {  // some row is too long for a list: every workgroup sees that
     if (blockIdx.x == 0 && tid == 0) st_system(p.status_out, 0u);
+    if constexpr (CALLER) plain_dense_start(p, b, lds);
     return;
   }
   unsigned any = 0u;
@@ -367,15 +471,8 @@ __global__ void __launch_bounds__(kListThreads) k_layer_lists(LayerLists p) {
     }
   }
   for (int r = wave; !CALLER && r < 32; r += kListThreads / 64)
-    for (int c = 16 * lane; c < p.Np; c += 1024) {
-      u32x4 v;
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const u32x4 w = *(const u32x4*)(cur + c + 4 * x);
-        v[x] = ((w[0] >> r) & 1u) | ((w[1] >> r) & 1u) << 8 | ((w[2] >> r) & 1u) << 16 | ((w[3] >> r) & 1u) << 24;
-      }
-      *(u32x4*)(p.T + (int64_t)(32 * b + r) * p.Np + c) = v;
-    }
+    for (int c = 16 * lane; c < p.Np; c += 1024)
+      *(u32x4*)(p.T + (int64_t)(32 * b + r) * p.Np + c) = strip_row16(cur, c, r);
   // the last workgroup reports K
   if (tid == 0) {
     atomicMax(p.words + 1, (unsigned)t);
@@ -394,7 +491,8 @@ constexpr int kListsOf8 = kListMaxN * 5 / 8;  // up to here 8 entries a row fit:
 
 template <bool CALLER>
 static hipError_t launch_layer(const LayerLists& p, const uint8_t* P, int64_t ldp, hipStream_t s) {
-  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, P, ldp, p.n, p.idx, p.len, p.status_out);
+  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, P, ldp, p.n, p.idx, p.len, p.status_out,
+                     CALLER ? p.dense.ring : nullptr, p.dense.conv);
   const dim3 grid(p.Np / 32);
   if (p.Np <= kListsOf8)
     hipLaunchKernelGGL((k_layer_lists<8, CALLER>), grid, dim3(kListThreads), 24 * p.Np, s, p);
@@ -412,9 +510,10 @@ hipError_t launch_layer_lists(const LayerLists& q, const int8_t* P, hipStream_t 
 
 hipError_t launch_closure_lists(const LayerLists& q, const uint8_t* A, int64_t lda, uint8_t* R, int64_t ldr,
                                 hipStream_t s) {
-  if (q.n <= 0 || q.n > kListMaxN) return hipErrorInvalidValue;
+  if (q.n <= 0 || q.n > kListMaxN || q.dense.Np < q.n || q.dense.Np % 128) return hipErrorInvalidValue;
   LayerLists p = q;
   p.Np = (p.n + 31) / 32 * 32;
+  if (p.dense.Np + 64 > 4 * p.Np) return hipErrorInvalidValue;  // the LDS that the lists' launch has
   p.A = (const int8_t*)A;
   p.lda = lda;
   p.M = (int8_t*)R;
@@ -445,8 +544,8 @@ hipError_t sg_lists_init() {
   return hipFuncSetAttribute((const void*)k_sg_lists, hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kListMaxN * 4);
 }
 
-hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t* ws, unsigned* words, bool clear_first,
-                           hipStream_t s) {
+hipError_t launch_sg_lists(ListParams p, uint8_t* ws, unsigned* words, bool clear_first, hipStream_t s) {
+  if (p.dense.Np < p.n || p.dense.Np % 16) return hipErrorInvalidValue;
   if (p.n <= 0 || p.n > kListMaxN || p.max_steps < 2 || p.max_steps >= kRing) return hipErrorInvalidValue;
   p.nb = (p.n + 31) / 32;
   p.pitch = 32 * p.nb;
@@ -458,8 +557,8 @@ hipError_t launch_sg_lists(ListParams p, const uint8_t* P, int64_t ldp, uint8_t*
   p.cnt = (u64*)words;
   p.finished = words + 4 * kListArrivals * 32;
   if (clear_first) hipLaunchKernelGGL(k_lists_clear, dim3(1), dim3(256), 0, s, p);
-  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, P, ldp, p.n, p.idx, p.len,
-                     p.status_out);
+  hipLaunchKernelGGL(k_row_lists, dim3((p.n + 3) / 4), dim3(256), 0, s, p.P, p.ldp, p.n, p.idx, p.len,
+                     p.status_out, p.dense.ring, p.dense.conv);
   hipLaunchKernelGGL(k_sg_lists, dim3(p.nb), dim3(kListThreads), 3 * p.pitch * 4, s, p);
   return hipGetLastError();
 }
