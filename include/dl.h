@@ -118,10 +118,13 @@ int dl_tc_steps(dl_ctx* ctx, int64_t n, const uint8_t* A, int64_t lda, uint8_t* 
 /* Transitive closure of `count` relations of one size (Sec. 3, as dl_tc):
  * A[g] and R[g] (g < count) are device uint8 matrices [n x lda] and
  * [n x ldr], passed as host arrays of `count` device pointers; iters[g]
- * (host int32) receives each fixpoint's iteration count.  The fixpoints run
- * two at a time on `stream`, so the host's counter read-back of one overlaps
- * the products of the other; the device workspace is twice that of dl_tc
- * (one at a time if the budget allows only one).  Results are identical to
+ * (host int32) receives each fixpoint's iteration count.  Fixpoints of
+ * product launches run two at a time on `stream`, so the host's counter
+ * read-back of one overlaps the products of the other; the device workspace is
+ * then twice that of dl_tc (one at a time if the budget allows only one).
+ * Series that take one launch (the plain series as in dl_tc; DL_I8 squaring up
+ * to n = 1728, and n = 1920 for a single relation, while timing is off and no
+ * configuration is set for the size) run one after the other.  Results are identical to
  * `count` dl_tc calls.  No R[g] may overlap any A[h] or another R[h]
  * (DL_EINVAL); count = 0 does nothing. */
 int dl_tc_batch(dl_ctx* ctx, int32_t count, int64_t n, const uint8_t* const* A, int64_t lda,

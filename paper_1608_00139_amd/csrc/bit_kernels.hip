@@ -1,7 +1,7 @@
 // bit_kernels.hip -- the int8 squaring closure of a small relation in one
 // launch, with bit-packed iterates.
 //
-// At n <= 2048 a fixpoint of product launches is bound by its launches, each
+// At n <= 1920 a fixpoint of product launches is bound by its launches, each
 // product's wait for its first loads, and the host's read-back (n = 300: 65 us
 // of kernels in a call of 107 us), not by arithmetic.  Here the whole series
 // runs in one launch; workgroups hand their tiles to each other as bits (an
@@ -9,7 +9,7 @@
 // the bits become int8 operands in registers, in front of the MFMA.
 //
 // k_fix_bits: one workgroup per 64 x 64 tile (ti, tj) of R, all resident at
-// once (see kResidentTicks), T = ceil(n / 64) <= 32 tiles a side.  Step 1
+// once (see kResidentTicks), T = ceil(n / 64) <= 30 tiles a side.  Step 1
 // packs the workgroup's tile of A; step t >= 2 computes its tile of
 //   R^(t) = R^(t-1) | [R^(t-1) R^(t-1) != 0]
 // (adding the previous iterate instead of A leaves the iterates unchanged)
@@ -34,12 +34,12 @@
 // 8-byte LDS read feeds four MFMA operands.  Rows are padded to an odd number
 // of words, so the 16 rows one read touches hit distinct banks.
 //
-// Measured (MI355X, a call as the caller sees it, degree 2; before: product
-// launches): n = 300 108 -> 50 us, n = 1000 140 -> 63 us, n = 2048 210 -> 180
+// Measured (MI355X, a call as the caller sees it, degree 2, product launches
+// and this one): n = 300 108, 50 us; n = 1000 116, 63 us; n = 1920 176, 174
 // us.  Of the 50 us in the kernel at n = 1000 (seven steps) the waits for
 // other workgroups take 24, the products 11 (AND and OR of the bits on the
 // vector units instead: 17), publishing 6, fetching 4: bound by the chain of
-// device-scope round trips.  At n = 2048 the products are 40% of it.
+// device-scope round trips.  At the top of the range the products are about 40% of it.
 #include "common.h"
 #include "device.h"
 

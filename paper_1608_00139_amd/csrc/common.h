@@ -206,9 +206,9 @@ inline unsigned fix_small_tag(unsigned* last, bool* clear) {
 }
 
 // The squaring closure of n <= 64 kBitTiles constants in one launch, on bits (k_fix_bits in bit_kernels.hip).
-constexpr int kBitTiles = 32;  // 64 x 64 tiles a side at most
+constexpr int kBitTiles = 30;  // 64 x 64 tiles a side at most
 constexpr int kBitLine = 16;   // 64-bit words per arrival word: a 128-byte line
-constexpr int kBitSteps = 16;  // squaring repeats by step 2 + ceil(log2(2048))
+constexpr int kBitSteps = 16;  // squaring repeats by step 2 + ceil(log2(1920))
 struct FixBitsParams {
   const uint8_t* A;
   int64_t lda;

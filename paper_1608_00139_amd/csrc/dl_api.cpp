@@ -571,10 +571,14 @@ int run_square_bits(dl_ctx* c, uint8_t* ws, int64_t n, const uint8_t* A, int64_t
   return DL_OK;
 }
 
-// The int8 squaring series goes to run_square_bits up to this size: 180
-// against 210 us for product launches at n = 2048 (four workgroups per compute
-// unit there; more tiles would not be resident at once).
-constexpr int64_t kBitSquareMax = 64 * kBitTiles;
+// The int8 squaring series goes to run_square_bits up to these sizes, alone and
+// in a batch, whose product series run two at a time.  Bits / products, us,
+// degree 1, 2, 4, 0.3 n: one relation of n = 1664 139/161, 138/161, 124/151,
+// 78/109; 1920 197/217, 174/176, 156/164, 93/113; 2048 213/215, 190/175, 168/162,
+// 100/110.  Two relations of n = 1728 294/316, 278/283, 245/258, 148/174; 1920
+// 384/370, 341/306, 301/280, 178/184; four of 1728 594/616, 544/528, 479/476,
+// 284/311; 1920 732/676, 671/573, 588/521, 340/331.
+constexpr int64_t kBitSquareMax = 64 * kBitTiles, kBitBatchMax = 64 * 27;
 
 // Where the list kernels write a dense relation's first operands: those of a
 // Fix in the first slot, whose workspace begins at ws.  The lists themselves
@@ -697,7 +701,8 @@ int run_fixpoints(dl_ctx* c, int mode, int count, int64_t n, const uint8_t* cons
       whole && mode == M_PLAIN && max_steps >= 1 && fix_small_supported(prec, Np) && !forced_other;
   // so does the int8 squaring series at small n (bits); not while product
   // launches are timed, which only the chunked path has
-  const bool square_bits = whole && mode == M_SQUARE && prec == P_I8 && max_steps >= 1 && n <= kBitSquareMax &&
+  const bool square_bits = whole && mode == M_SQUARE && prec == P_I8 && max_steps >= 1 &&
+                           n <= (count > 1 ? kBitBatchMax : kBitSquareMax) &&
                            !(te && te->ms == 0.0) && !c->timing;
   const bool sg_lists = whole && mode == M_SG && prec == P_I8 && max_steps >= 2 && n <= kListMaxN &&
                         !(te && te->ms == 0.0) && !c->timing;
