@@ -92,6 +92,21 @@ class MatPool {
   size_t total_ = 0;
 };
 
+// hipMalloc, once more after `kept` (if any) has given up its matrices; *p is
+// null on failure.
+inline hipError_t device_alloc(MatPool* kept, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && kept) {
+    (void)hipGetLastError();
+    kept->drop();
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+  }
+  return e;
+}
 struct dl_ctx {
   int device = 0;
   size_t budget = 0;

@@ -71,17 +71,8 @@ int ensure_ws(dl_ctx* c, size_t need) {
     c->ws_size = 0;
     if (e != hipSuccess) return hip_fail(e, "hipFree(workspace)");
   }
-  hipError_t e = hipMalloc(&c->ws, need);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    c->mats->drop();
-    e = hipMalloc(&c->ws, need);
-  }
-  if (e != hipSuccess) {
-    c->ws = nullptr;
-    (void)hipGetLastError();
+  if (device_alloc(c->mats.get(), &c->ws, need) != hipSuccess)
     return fail(DL_ENOMEM, "hipMalloc of " + std::to_string(need) + " bytes failed");
-  }
   c->ws_size = need;
   return DL_OK;
 }

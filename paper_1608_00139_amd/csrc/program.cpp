@@ -926,7 +926,8 @@ int dl_program_create(dl_ctx* ctx, const char* text, dl_program** out) {
     delete g;
     return rc;
   }
-  if (hipSetDevice(ctx->device) != hipSuccess || hipMalloc(&g->dcnt, 2 * sizeof(unsigned long long)) != hipSuccess ||
+  if (hipSetDevice(ctx->device) != hipSuccess ||
+      device_alloc(ctx->mats.get(), (void**)&g->dcnt, 2 * sizeof(unsigned long long)) != hipSuccess ||
       hipMemset(g->dcnt, 0, 2 * sizeof(unsigned long long)) != hipSuccess ||
       hipHostMalloc(&g->hcnt, sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void**)&g->hcnt_dev, g->hcnt, 0) != hipSuccess) {

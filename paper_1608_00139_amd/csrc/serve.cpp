@@ -48,6 +48,7 @@
 
 #include "../../include/dl.h"
 #include "common.h"
+#include "ctx.h"
 
 using namespace dl;
 
@@ -114,7 +115,7 @@ struct Retired {
 }  // namespace
 
 struct dl_batch {
-  dl_ctx* ctx = nullptr;
+  std::shared_ptr<MatPool> kept;  // the context's matrices, given up before an allocation fails
   int device = 0;
   uint8_t* pool = nullptr;
   size_t pool_bytes = 0;
@@ -232,7 +233,7 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
   *out = nullptr;
   dl_batch* b = new (std::nothrow) dl_batch();
   if (!b) return bfail(DL_ENOMEM, "host allocation failed");
-  b->ctx = ctx;
+  if (ctx) b->kept = ctx->mats;
   b->device = device;
   b->max_active = max_active;
   b->req.resize(max_active);
@@ -243,29 +244,27 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
   hipError_t e;
   if ((e = hipSetDevice(device)) != hipSuccess) return fail_destroy(bfail(DL_EHIP, "hipSetDevice"));
   if ((e = bool_kernels_init()) != hipSuccess) return fail_destroy(bfail(DL_EHIP, "kernel attributes"));
-  if ((e = hipMalloc(&b->pool, pool_bytes)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (device_alloc(b->kept.get(), (void**)&b->pool, pool_bytes) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "pool allocation failed"));
-  }
   b->pool_bytes = pool_bytes;
   b->free_list[0] = pool_bytes;
-  if ((e = hipMalloc(&b->d_desc, sizeof(GroupDesc) * 2 * max_active)) != hipSuccess)
+  if (device_alloc(b->kept.get(), (void**)&b->d_desc, sizeof(GroupDesc) * 2 * max_active) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "descriptor allocation failed"));
-  if ((e = hipMalloc(&b->d_tot, sizeof(int) * 8)) != hipSuccess)
+  if (device_alloc(b->kept.get(), (void**)&b->d_tot, sizeof(int) * 8) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "descriptor allocation failed"));
   // host buffers the device reads or writes directly (k_publish moves them;
   // runtime copies left a gap of ~10 us before each in the kernel trace)
   constexpr unsigned kMapped = hipHostMallocMapped | hipHostMallocCoherent;
   if ((e = hipHostMalloc(&b->h_desc, sizeof(GroupDesc) * 2 * max_active, kMapped)) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "pinned descriptor allocation failed"));
-  if ((e = hipMalloc(&b->d_cnt, sizeof(unsigned long long) * 4 * max_active)) != hipSuccess)
+  if (device_alloc(b->kept.get(), (void**)&b->d_cnt, sizeof(unsigned long long) * 4 * max_active) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "counter allocation failed"));
   if ((e = hipHostMalloc(&b->h_cnt, sizeof(unsigned long long) * 4 * max_active, kMapped)) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "pinned counter allocation failed"));
   if ((e = hipMemset(b->d_cnt, 0, sizeof(unsigned long long) * 4 * max_active)) != hipSuccess)
     return fail_destroy(bfail(DL_EHIP, "counter clear"));
   b->last.assign((size_t)2 * max_active, 0ull);
-  if ((e = hipMalloc(&b->d_adm, sizeof(AdmitDesc) * 2 * max_active)) != hipSuccess)
+  if (device_alloc(b->kept.get(), (void**)&b->d_adm, sizeof(AdmitDesc) * 2 * max_active) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "admission descriptor allocation failed"));
   if ((e = hipHostMalloc(&b->h_adm, sizeof(AdmitDesc) * 2 * max_active, kMapped)) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "pinned admission descriptor allocation failed"));
@@ -804,8 +803,7 @@ int dl_batch_tune(dl_batch* b, const int64_t* sizes_in, int32_t k, int32_t* tile
       if (buf) (void)hipFree(buf);
       buf = nullptr;
       buf_bytes = 0;
-      if (hipMalloc(&buf, need) != hipSuccess) {
-        (void)hipGetLastError();
+      if (device_alloc(b->kept.get(), (void**)&buf, need) != hipSuccess) {
         rc = bfail(DL_ENOMEM, "temporary memory for the tile autotuner");
         break;
       }

@@ -48,11 +48,47 @@ int fetch_after_rebind() {
   return fake::live ? bad("bytes left", (long long)fake::live) : 0;
 }
 
+// Memory that a program's matrices are kept in is given back before another
+// allocation of the context is refused: a batch's pool and the temporary
+// memory of its tuner.
+int kept_matrices_given_up() {
+  dl_ctx* ctx = nullptr;
+  dl_program* p = nullptr;
+  dl_batch* b = nullptr;
+  if (int rc = dl_create(&ctx, 0, 0)) return bad("create", rc);
+  const size_t before = fake::live;
+  if (int rc = dl_program_create(ctx, kClosure, &p)) return bad("program", rc);
+  auto fill = [&]() -> int {
+    if (int rc = dl_program_bind(p, "e", 2000, kSome, 2000)) return rc;
+    if (int rc = dl_program_run(p, DL_EVAL_ITERATION, nullptr)) return rc;
+    if (int rc = dl_program_bind(p, "e", 0, nullptr, 0)) return rc;
+    return dl_program_run(p, DL_EVAL_ITERATION, nullptr);  // gives its matrices back
+  };
+  if (int rc = fill()) return bad("run", rc);
+  const size_t kept = fake::live - before;
+  if (kept < (size_t)8 << 20) return bad("nothing was kept", (long long)kept);
+  fake::limit = fake::live + ((size_t)4 << 20);
+  if (int rc = dl_batch_create(ctx, 0, (size_t)8 << 20, 4, &b)) return bad("batch", rc);
+  fake::limit = ~(size_t)0;
+  if (int rc = fill()) return bad("run", rc);
+  const int64_t sizes[] = {2048};  // eight requests of 16 MB and their descriptors
+  fake::limit = fake::live + ((size_t)126 << 20);
+  if (int rc = dl_batch_tune(b, sizes, 1, nullptr, nullptr, nullptr)) return bad("tune", rc);
+  fake::limit = fake::live;  // and nothing left to give
+  dl_batch* c = nullptr;
+  if (dl_batch_create(ctx, 0, (size_t)8 << 20, 4, &c) != DL_ENOMEM || c) return bad("batch without memory", 0);
+  dl_batch_destroy(b);
+  dl_program_destroy(p);
+  dl_destroy(ctx);
+  return fake::live ? bad("bytes left", (long long)fake::live) : 0;
+}
+
 struct Case {
   const char* name;
   int (*run)();
 };
-const Case kCases[] = {{"fetch_after_rebind", fetch_after_rebind}};
+const Case kCases[] = {{"fetch_after_rebind", fetch_after_rebind},
+                        {"kept_matrices_given_up", kept_matrices_given_up}};
 
 }  // namespace
 

@@ -69,6 +69,10 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = 1.f;
+  return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
 }
@@ -98,6 +102,8 @@ hipError_t launch_layer_lists(const LayerLists& q, const int8_t*, hipStream_t) {
   *q.status_out = 2u;  // the series has repeated at step 2
   return noted("layer_lists");
 }
+hipError_t launch_hash_bool(uint8_t*, int64_t, int, int, unsigned, hipStream_t) { return noted("hash_bool"); }
+hipError_t launch_group_step(int, const GroupDesc*, int, int, hipStream_t, const int*) { return noted("group_step"); }
 hipError_t launch_emit(int, const void*, int Np, int, int n, uint8_t*, int64_t ldr, hipStream_t) {
   fake::emits.push_back({Np, n, ldr});
   return noted("emit");
