@@ -7,6 +7,7 @@
 
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -62,18 +63,26 @@ class MatPool {
     return e;
   }
   void put(void* p, size_t bytes) {
-    std::vector<void*> out;
-    {
+    bool is_kept = false;
+    try {
       std::lock_guard<std::mutex> l(m_);
       kept_.push_back({bytes, p});
       total_ += bytes;
-      while (total_ > kMaxKept) {
+      is_kept = true;
+    } catch (const std::bad_alloc&) {  // no host memory for the entry
+    }
+    if (!is_kept) (void)hipFree(p);
+    for (;;) {
+      void* oldest = nullptr;
+      {
+        std::lock_guard<std::mutex> l(m_);
+        if (total_ <= kMaxKept) return;
         total_ -= kept_.front().first;
-        out.push_back(kept_.front().second);
+        oldest = kept_.front().second;
         kept_.erase(kept_.begin());
       }
+      (void)hipFree(oldest);
     }
-    for (void* q : out) (void)hipFree(q);
   }
   // Frees what is kept (before an allocation elsewhere is given up).
   void drop() {

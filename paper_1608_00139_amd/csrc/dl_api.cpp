@@ -802,12 +802,14 @@ int dl_create(dl_ctx** out, int device, size_t budget) {
   dl_ctx* c = nullptr;
   try {
     c = new dl_ctx();
+    c->eps.spare = [pool = c->mats] { pool->drop(); };
   } catch (const std::bad_alloc&) {
+    delete c;
+    c = nullptr;
   }
   if (!c) return fail(DL_ENOMEM, "host allocation failed");
   c->device = device;
   c->budget = budget;
-  c->eps.spare = [pool = c->mats] { pool->drop(); };
   auto cleanup = [&](int st) {
     dl_destroy(c);
     return st;

@@ -236,18 +236,26 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
   if (ctx) b->kept = ctx->mats;
   b->device = device;
   b->max_active = max_active;
-  b->req.resize(max_active);
   auto fail_destroy = [&](int st) {
     dl_batch_destroy(b);
     return st;
   };
+  try {
+    b->req.resize(max_active);
+    b->free_list[0] = pool_bytes;
+    b->last.assign((size_t)2 * max_active, 0ull);
+    b->pend.reserve(max_active);
+    b->emit.reserve(max_active);
+    b->listed.assign(max_active, 0);
+  } catch (const std::bad_alloc&) {
+    return fail_destroy(bfail(DL_ENOMEM, "host allocation failed"));
+  }
   hipError_t e;
   if ((e = hipSetDevice(device)) != hipSuccess) return fail_destroy(bfail(DL_EHIP, "hipSetDevice"));
   if ((e = bool_kernels_init()) != hipSuccess) return fail_destroy(bfail(DL_EHIP, "kernel attributes"));
   if (device_alloc(b->kept.get(), (void**)&b->pool, pool_bytes) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "pool allocation failed"));
   b->pool_bytes = pool_bytes;
-  b->free_list[0] = pool_bytes;
   if (device_alloc(b->kept.get(), (void**)&b->d_desc, sizeof(GroupDesc) * 2 * max_active) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "descriptor allocation failed"));
   if (device_alloc(b->kept.get(), (void**)&b->d_tot, sizeof(int) * 8) != hipSuccess)
@@ -263,7 +271,6 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
     return fail_destroy(bfail(DL_ENOMEM, "pinned counter allocation failed"));
   if ((e = hipMemset(b->d_cnt, 0, sizeof(unsigned long long) * 4 * max_active)) != hipSuccess)
     return fail_destroy(bfail(DL_EHIP, "counter clear"));
-  b->last.assign((size_t)2 * max_active, 0ull);
   if (device_alloc(b->kept.get(), (void**)&b->d_adm, sizeof(AdmitDesc) * 2 * max_active) != hipSuccess)
     return fail_destroy(bfail(DL_ENOMEM, "admission descriptor allocation failed"));
   if ((e = hipHostMalloc(&b->h_adm, sizeof(AdmitDesc) * 2 * max_active, kMapped)) != hipSuccess)
@@ -275,9 +282,6 @@ int dl_batch_create(dl_ctx* ctx, int device, size_t pool_bytes, int max_active, 
   for (auto& ev : b->ev)
     if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess)
       return fail_destroy(bfail(DL_EHIP, "event creation failed"));
-  b->pend.reserve(max_active);
-  b->emit.reserve(max_active);
-  b->listed.assign(max_active, 0);
   int cus = 256;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0) cus = prop.multiProcessorCount;

@@ -1,10 +1,22 @@
 // The cases of tests/test_host_sources.py, one by name: prints "ok" or what
 // went wrong.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 
 #include "../../include/dl.h"
+#include "../../paper_1608_00139_amd/csrc/ctx.h"
 #include "runtime.h"
+
+static long g_fail_new = 0;  // the how manyth allocation from now fails (0: none)
+void* operator new(size_t bytes) {
+  if (g_fail_new > 0 && --g_fail_new == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(bytes ? bytes : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -83,12 +95,59 @@ int kept_matrices_given_up() {
   return fake::live ? bad("bytes left", (long long)fake::live) : 0;
 }
 
+// Host memory that runs out is DL_ENOMEM, not an exception: one allocation
+// after the other refused, in the calls that create and where matrices are
+// given back to be kept.
+int host_memory_runs_out() {
+  for (long k = 1; k < 40; ++k) {
+    dl_ctx* ctx = nullptr;
+    dl_batch* b = nullptr;
+    const char* at = "create";
+    try {
+      g_fail_new = k;
+      int rc = dl_create(&ctx, 0, 0);
+      g_fail_new = 0;
+      if (rc != DL_OK && rc != DL_ENOMEM) return bad("create", rc);
+      if (rc == DL_OK) {
+        at = "batch";
+        g_fail_new = k;
+        rc = dl_batch_create(ctx, 0, 1 << 20, 4, &b);
+        g_fail_new = 0;
+        if (rc != DL_OK && rc != DL_ENOMEM) return bad("batch", rc);
+        if ((rc == DL_OK) != (b != nullptr)) return bad("batch after", rc);
+      }
+      at = "put";
+      MatPool pool;
+      void* m = nullptr;
+      if (pool.get(4096, &m) != hipSuccess) return bad("get", k);
+      g_fail_new = k;
+      pool.put(m, 4096);
+      g_fail_new = 0;
+    } catch (const std::bad_alloc&) {
+      g_fail_new = 0;
+      return bad(at, k);
+    }
+    dl_batch_destroy(b);
+    dl_destroy(ctx);
+    if (fake::live) return bad("bytes left", (long long)fake::live);
+  }
+  // what is kept stays under its limit, the oldest given back first
+  MatPool pool;
+  void* m[3];
+  for (void*& q : m) pool.get(MatPool::kMaxKept / 2, &q);
+  for (void* q : m) pool.put(q, MatPool::kMaxKept / 2);
+  if (fake::live != MatPool::kMaxKept) return bad("kept", (long long)fake::live);
+  pool.drop();
+  return fake::live ? bad("bytes left", (long long)fake::live) : 0;
+}
+
 struct Case {
   const char* name;
   int (*run)();
 };
 const Case kCases[] = {{"fetch_after_rebind", fetch_after_rebind},
-                        {"kept_matrices_given_up", kept_matrices_given_up}};
+                        {"kept_matrices_given_up", kept_matrices_given_up},
+                        {"host_memory_runs_out", host_memory_runs_out}};
 
 }  // namespace
 

@@ -2,6 +2,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 
 #include "../../paper_1608_00139_amd/csrc/common.h"
@@ -11,13 +12,26 @@ namespace fake {
 size_t limit = ~(size_t)0, live = 0;
 std::vector<Emit> emits;
 std::vector<std::string> launches;
-static std::map<void*, size_t> blocks;
+template <class T>
+struct Plain {  // memory that the refused allocations of the tests do not reach
+  typedef T value_type;
+  Plain() = default;
+  template <class U>
+  Plain(const Plain<U>&) {}
+  T* allocate(size_t n) { return (T*)std::malloc(n * sizeof(T)); }
+  void deallocate(T* p, size_t) { std::free(p); }
+  template <class U>
+  bool operator==(const Plain<U>&) const { return true; }
+  template <class U>
+  bool operator!=(const Plain<U>&) const { return false; }
+};
+static std::map<void*, size_t, std::less<void*>, Plain<std::pair<void* const, size_t>>> blocks;
 }  // namespace fake
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t bytes) {
   if (bytes > fake::limit || fake::live > fake::limit - bytes) return hipErrorOutOfMemory;
-  *p = std::calloc(1, bytes);
+  *p = std::calloc(1, bytes);  // (untouched pages stay unbacked)
   fake::blocks[*p] = bytes;
   fake::live += bytes;
   return hipSuccess;
