@@ -115,6 +115,7 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
         return slots
 
     while pending or waiting or inflight:
+        written()  # before admissions or an idle gap take time
         now = time.perf_counter() - t0
         while pending and pending[0].arrival <= now:
             waiting.append(pending.popleft())
@@ -141,7 +142,7 @@ def run_stream(requests, make_input, pool_bytes: int, max_active: int = 256, kee
         if not inflight:
             if pending:  # idle until the next arrival
                 while time.perf_counter() - t0 < pending[0].arrival:
-                    pass
+                    written()
             continue
         stats.max_active = max(stats.max_active, len(inflight))
         b.dl_batch_step()
