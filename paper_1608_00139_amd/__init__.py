@@ -667,9 +667,8 @@ class Batch:
             ptrs[i] = out.data_ptr()
         ones = (ctypes.c_int64 * k)()
         _check(load().dl_batch_fetch_n(self._h, k, ss, ptrs, lds, ones, _stream_ptr(self.stream)))
-        if self.stream is not None:
-            for out in outs:  # not to be reused before the launch has written it
-                out.record_stream(self.stream)
+        for out in outs:  # not to be reused before the launch has written it
+            out.record_stream(self.stream if self.stream is not None else torch.cuda.current_stream(out.device))
         return [int(ones[i]) for i in range(k)]
 
     def dl_batch_release_n(self, slots) -> list[int]:
