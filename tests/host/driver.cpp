@@ -141,13 +141,38 @@ int host_memory_runs_out() {
   return fake::live ? bad("bytes left", (long long)fake::live) : 0;
 }
 
+// The step numbers of the one-launch plain series' exchanged words: no launch
+// uses one that an earlier launch has used since the words were cleared, none
+// is zero, none runs over.
+int launch_tags() {
+  const uint64_t top = (uint64_t)~0u;
+  unsigned last = 0u;
+  bool clear = false;
+  if (dl::fix_small_tag(&last, &clear) != dl::kFixSmallTags || clear) return bad("first tag", last);
+  for (unsigned from : {~0u - 4 * dl::kFixSmallTags, ~0u - 3 * dl::kFixSmallTags + 1, ~0u - 2 * dl::kFixSmallTags,
+                        ~0u - 2 * dl::kFixSmallTags + 1, ~0u}) {
+    last = from;
+    uint64_t used = from + (uint64_t)512 + 2;  // the last launch's highest
+    for (int k = 0; k < 4; ++k) {
+      clear = false;
+      const unsigned tag = dl::fix_small_tag(&last, &clear);
+      if (clear) used = 0;
+      if (tag != last || tag + (uint64_t)1 <= used || tag == 0u) return bad("tag in use", tag);
+      used = tag + (uint64_t)512 + 2;
+      if (used > top) return bad("tag runs over", tag);
+    }
+  }
+  return 0;
+}
+
 struct Case {
   const char* name;
   int (*run)();
 };
 const Case kCases[] = {{"fetch_after_rebind", fetch_after_rebind},
                         {"kept_matrices_given_up", kept_matrices_given_up},
-                        {"host_memory_runs_out", host_memory_runs_out}};
+                        {"host_memory_runs_out", host_memory_runs_out},
+                        {"launch_tags", launch_tags}};
 
 }  // namespace
 

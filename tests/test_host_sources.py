@@ -38,7 +38,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["fetch_after_rebind", "kept_matrices_given_up", "host_memory_runs_out"])
+@pytest.mark.parametrize("case", ["fetch_after_rebind", "kept_matrices_given_up", "host_memory_runs_out",
+                                  "launch_tags"])
 def test_case(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=60)
     assert (r.returncode, r.stdout) == (0, "ok\n"), (case, r.returncode, r.stdout, r.stderr)
