@@ -28,7 +28,7 @@
 // tiles: stages it through LDS), ORs the addend with 16-byte loads, stores
 // coalesced rows (and, for squaring, the transposed tile), and counts the ones
 // of the tile with a wave reduction and a single atomic per workgroup.  The
-// grouped serving step for small requests (nt_tile) stages its slices through
+// grouped serving step for small requests (nt_tile64) stages its slices through
 // registers instead, as 16-byte chunks ordered [chunk][row][16 B], so the 16
 // lanes that read one MFMA operand chunk read 256 contiguous bytes (no bank
 // conflicts).  A launch first checks the
@@ -303,67 +303,48 @@ __device__ inline bool step_is_done(const NTParams& p) {
   return false;
 }
 
-// LDS row swizzle: the 16-byte chunk c of row r of a staged slice is stored
-// at unit  c * rows + (r ^ swz(c)).  Lanes that store one global row (its KC
-// chunks) then land in different banks, and the lanes that read one MFMA
-// operand (consecutive rows of one chunk) still read a permutation of one
-// aligned 8-row block.  swz < 8 keeps every row inside its aligned block.
-template <int SWZ>
-__device__ __host__ constexpr int swz(int c) {
-  return SWZ ? ((c * SWZ) & 7) : 0;
-}
-
-template <int BM, int BN, int WM, int WN, int KB, class Op, int SWZ, int PREF = 1>
-struct NTKernel {
-  static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
-  static constexpr int NWAVES = WAVES_M * WAVES_N;
-  static constexpr int NT = NWAVES * 64;
-  static constexpr int KC = KB / 16;                 // chunks per row per stage
-  static constexpr int FR = Op::FR;
-  static constexpr int GROUPS = 64 / FR;             // lane groups along K
-  static constexpr int FM = WM / FR, FN = WN / FR;   // fragments per wave
-  static constexpr int CPL = Op::CPL;
-  static constexpr int KSTEP_CHUNKS = GROUPS * CPL;  // chunks consumed by one MFMA k-step
-  static constexpr int KSTEPS = KC / KSTEP_CHUNKS;
-  static constexpr int STAGE_CHUNKS = (BM + BN) * KC;
+// The 64 x 64 int8 tile of the grouped serving step: four waves of 32 x 32,
+// 64-byte K slices staged through registers.
+struct Tile64 {
+  static constexpr int B = 64, W = 32, FR = OpI8::FR, F = W / FR;  // tile, wave tile, fragments per wave side
+  static constexpr int NT = 256;
+  static constexpr int KB = 64, KC = KB / 16;         // bytes and 16-byte chunks of a row per slice: one MFMA k-step
+  static constexpr int STAGE_CHUNKS = 2 * B * KC;     // X rows, then Y rows
   static constexpr int LOADS = STAGE_CHUNKS / NT;
-  static constexpr int EPAD = 16;
-  static constexpr int EST = BN + EPAD;              // epilogue LDS row stride (bytes)
-  static constexpr size_t OPER_BYTES = 2ull * STAGE_CHUNKS * 16;
-  static constexpr size_t EPI_BYTES = (size_t)BM * EST;
-  static constexpr size_t LDS_BYTES = OPER_BYTES > EPI_BYTES ? OPER_BYTES : EPI_BYTES;
-  static constexpr int NIB = elem_nibbles(Op::kPrec);  // 4-bit units per element
-  static_assert(KC % KSTEP_CHUNKS == 0, "stage must hold whole MFMA k-steps");
-  static_assert(STAGE_CHUNKS % NT == 0, "loads must divide evenly");
-  static_assert((BM * BN / 16) % NT == 0, "epilogue segments must divide evenly");
-  static_assert(WM % FR == 0 && WN % FR == 0, "wave tile must hold whole fragments");
+  static constexpr int EST = B + 16;                  // epilogue LDS row stride (bytes)
+  static constexpr size_t LDS_BYTES = 2ull * STAGE_CHUNKS * 16;
+  static_assert(KC == 64 / FR * OpI8::CPL && (size_t)B * EST <= LDS_BYTES, "one k-step a slice, the tile in its ring");
+  // LDS row swizzle: the 16-byte chunk c of row r of a staged slice is stored
+  // at unit  c * rows + (r ^ swz(c)).  Lanes that store one global row (its KC
+  // chunks) then land in different banks, and the lanes that read one MFMA
+  // operand (consecutive rows of one chunk) still read a permutation of one
+  // aligned 8-row block.
+  __device__ static constexpr int swz(int c) { return (2 * c) & 7; }
 };
 
-// One BM x BN output tile at (row0, col0) of out = [add + X Y^T != 0];
-// its number of ones is added to *cnt_dst when cnt_dst is not null.  The
-// whole workgroup must call it (it synchronises through LDS).
-template <int BM, int BN, int WM, int WN, int KB, class Op, int SWZ, int PREF>
-__device__ __forceinline__ void nt_tile(const NTParams& p, int row0, int col0,
-                                        unsigned long long* cnt_dst, uint8_t* smem, int tid) {
-  typedef NTKernel<BM, BN, WM, WN, KB, Op, SWZ, PREF> K;
+// One tile at (row0, col0) of out = [add + X Y^T != 0]; its number of ones is
+// added to *cnt_dst when cnt_dst is not null.  The whole workgroup must call it
+// (it synchronises through LDS).
+__device__ __forceinline__ void nt_tile64(const NTParams& p, int row0, int col0, unsigned long long* cnt_dst,
+                                          uint8_t* smem, int tid) {
+  typedef Tile64 K;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / K::WAVES_N, wn = wave % K::WAVES_N;
-  const int64_t ldb = p.ld * K::NIB / 2;  // row pitch in bytes
-  const uint8_t* Xg = (const uint8_t*)p.X + (int64_t)row0 * ldb;
-  const uint8_t* Yg = (const uint8_t*)p.Y + (int64_t)col0 * ldb;
-  const int nk = (int)(ldb / KB);
+  const int wm = wave / 2, wn = wave % 2;
+  const uint8_t* Xg = (const uint8_t*)p.X + (int64_t)row0 * p.ld;
+  const uint8_t* Yg = (const uint8_t*)p.Y + (int64_t)col0 * p.ld;
+  const int nk = (int)(p.ld / K::KB);
 
   u32x4* lds = (u32x4*)smem;
-  // chunk q of a stage: rows [0, BM) of X then rows [0, BN) of Y; the KC
+  // chunk q of a slice: rows [0, 64) of X then rows [0, 64) of Y; the KC
   // chunks of one row are adjacent in global memory and in q
   auto gload = [&](u32x4 (&regs)[K::LOADS], int kt) {
 #pragma unroll
     for (int i = 0; i < K::LOADS; ++i) {
       const int q = tid + i * K::NT;
       const int row = q / K::KC, c = q % K::KC;
-      const uint8_t* src = (row < BM) ? (Xg + (int64_t)row * ldb) : (Yg + (int64_t)(row - BM) * ldb);
-      regs[i] = *(const u32x4*)(src + (int64_t)kt * KB + c * 16);
+      const uint8_t* src = (row < K::B) ? (Xg + (int64_t)row * p.ld) : (Yg + (int64_t)(row - K::B) * p.ld);
+      regs[i] = *(const u32x4*)(src + (int64_t)kt * K::KB + c * 16);
     }
   };
   auto sstore = [&](const u32x4 (&regs)[K::LOADS], int buf) {
@@ -372,158 +353,92 @@ __device__ __forceinline__ void nt_tile(const NTParams& p, int row0, int col0,
     for (int i = 0; i < K::LOADS; ++i) {
       const int q = tid + i * K::NT;
       const int row = q / K::KC, c = q % K::KC;
-      // X region: [KC][BM]; Y region after it: [KC][BN]
-      const int off = (row < BM) ? (c * BM + (row ^ swz<SWZ>(c)))
-                                 : (BM * K::KC + c * BN + ((row - BM) ^ swz<SWZ>(c)));
+      // X region: [KC][64]; Y region after it: [KC][64]
+      const int off = (row < K::B) ? (c * K::B + (row ^ K::swz(c)))
+                                   : (K::B * K::KC + c * K::B + ((row - K::B) ^ K::swz(c)));
       base[off] = regs[i];
     }
   };
 
-  typename Op::Acc acc[K::FM][K::FN];
+  v4i acc[K::F][K::F];
 #pragma unroll
-  for (int i = 0; i < K::FM; ++i)
+  for (int i = 0; i < K::F; ++i)
 #pragma unroll
-    for (int j = 0; j < K::FN; ++j) acc[i][j] = Op::zero();
+    for (int j = 0; j < K::F; ++j) acc[i][j] = OpI8::zero();
 
-  const int g = lane / K::FR, rf = lane % K::FR;
+  const int g = lane / K::FR, rf = lane % K::FR;  // this lane's chunk and row of a fragment
   auto compute = [&](int buf) {
     const u32x4* xs = lds + buf * K::STAGE_CHUNKS;
-    const u32x4* ys = xs + BM * K::KC;
+    const u32x4* ys = xs + K::B * K::KC;
+    u32x4 af[K::F], bf[K::F];
 #pragma unroll
-    for (int ks = 0; ks < K::KSTEPS; ++ks) {
-      u32x4 af[K::FM][K::CPL], bf[K::FN][K::CPL];
-#pragma unroll
-      for (int i = 0; i < K::FM; ++i)
-#pragma unroll
-        for (int c = 0; c < K::CPL; ++c) {
-          const int ch = ks * K::KSTEP_CHUNKS + g * K::CPL + c;
-          af[i][c] = xs[ch * BM + ((wm * WM + i * K::FR + rf) ^ swz<SWZ>(ch))];
-        }
-#pragma unroll
-      for (int j = 0; j < K::FN; ++j)
-#pragma unroll
-        for (int c = 0; c < K::CPL; ++c) {
-          const int ch = ks * K::KSTEP_CHUNKS + g * K::CPL + c;
-          bf[j][c] = ys[ch * BN + ((wn * WN + j * K::FR + rf) ^ swz<SWZ>(ch))];
-        }
-#pragma unroll
-      for (int i = 0; i < K::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < K::FN; ++j) acc[i][j] = Op::mma(af[i], bf[j], acc[i][j]);
+    for (int i = 0; i < K::F; ++i) {
+      af[i] = xs[g * K::B + ((wm * K::W + i * K::FR + rf) ^ K::swz(g))];
+      bf[i] = ys[g * K::B + ((wn * K::W + i * K::FR + rf) ^ K::swz(g))];
     }
+#pragma unroll
+    for (int i = 0; i < K::F; ++i)
+#pragma unroll
+      for (int j = 0; j < K::F; ++j) acc[i][j] = OpI8::mma(&af[i], &bf[j], acc[i][j]);
   };
 
-  if constexpr (PREF == 1) {
-    // one slice in flight: load k+1 into registers while computing k
-    u32x4 ra[K::LOADS];
-    gload(ra, 0);
-    sstore(ra, 0);
+  // one slice in flight: load k+1 into registers while computing k
+  u32x4 ra[K::LOADS];
+  gload(ra, 0);
+  sstore(ra, 0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt + 1 < nk) gload(ra, kt + 1);
+    compute(kt & 1);
+    if (kt + 1 < nk) sstore(ra, (kt + 1) & 1);
     __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 1 < nk) gload(ra, kt + 1);
-      compute(kt & 1);
-      if (kt + 1 < nk) sstore(ra, (kt + 1) & 1);
-      __syncthreads();
-    }
-  } else {
-    // two slices in flight: the loads of slice k+1 had a whole compute phase
-    // to land before they are stored to LDS at the end of iteration k
-    u32x4 ra[K::LOADS], rb[K::LOADS];
-    gload(ra, 0);
-    if (nk > 1) gload(rb, 1);
-    sstore(ra, 0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt += 2) {
-      // even iteration: rb holds slice kt+1, ra is free
-      if (kt + 2 < nk) gload(ra, kt + 2);
-      compute(0);
-      if (kt + 1 < nk) sstore(rb, 1);
-      __syncthreads();
-      if (kt + 1 >= nk) break;
-      // odd iteration: ra holds slice kt+2, rb is free
-      if (kt + 3 < nk) gload(rb, kt + 3);
-      compute(1);
-      if (kt + 2 < nk) sstore(ra, 0);
-      __syncthreads();
-    }
   }
 
-  // ---- epilogue: 0/1 tile in LDS, [BM][EST] bytes
-  constexpr int SEG_PER_ROW = BN / 16;
-  constexpr int SEGS = BM * SEG_PER_ROW / K::NT;
-  // int8 addend segments of this thread (segment i: tile row q / SEG_PER_ROW,
-  // 16-byte column q % SEG_PER_ROW, q = tid + i NT), all requested before
-  // the first is needed, so the tile waits on one memory round trip (wider
-  // operand-precision addends are read per segment: held together they
-  // would cost occupancy)
-  constexpr bool BATCH = Op::kPrec == P_I8;
-  u32x4 addv[SEGS];
-#pragma unroll
-  for (int i = 0; i < SEGS; ++i) {
-    const int q = tid + i * K::NT;
-    addv[i] = u32x4{0u, 0u, 0u, 0u};
-    if (BATCH && p.add) addv[i] = load_add16<Op::kPrec>(p, row0 + q / SEG_PER_ROW, col0 + (q % SEG_PER_ROW) * 16);
-  }
+  // ---- epilogue: 0/1 tile in LDS, [64][EST] bytes; thread's segment: 16
+  // columns of row tid / 4, its addend requested before the tile is staged
+  const int er = tid >> 2, ec = (tid & 3) * 16;
+  u32x4 addv = {0u, 0u, 0u, 0u};
+  if (p.add) addv = *(const u32x4*)(p.add + (int64_t)(row0 + er) * p.Np + col0 + ec);
   uint8_t* et = smem;
 #pragma unroll
-  for (int i = 0; i < K::FM; ++i)
+  for (int i = 0; i < K::F; ++i)
 #pragma unroll
-    for (int j = 0; j < K::FN; ++j)
+    for (int j = 0; j < K::F; ++j)
 #pragma unroll
-      for (int v = 0; v < Op::NI; ++v) {
+      for (int v = 0; v < OpI8::NI; ++v) {
         int r, c;
-        Op::coord(lane, v, r, c);
-        et[(wm * WM + i * K::FR + r) * K::EST + wn * WN + j * K::FR + c] = Op::nz(acc[i][j], v) ? 1 : 0;
+        OpI8::coord(lane, v, r, c);
+        et[(wm * K::W + i * K::FR + r) * K::EST + wn * K::W + j * K::FR + c] = OpI8::nz(acc[i][j], v) ? 1 : 0;
       }
   __syncthreads();
 
-  int cnt = 0;
-  uint8_t* outb = (uint8_t*)p.out;
-#pragma unroll
-  for (int i = 0; i < SEGS; ++i) {
-    const int q = tid + i * K::NT;
-    const int r = q / SEG_PER_ROW, cs = q % SEG_PER_ROW;
-    u32x4 v = *(const u32x4*)(et + r * K::EST + cs * 16);
-    const int gr = row0 + r, gc = col0 + cs * 16;
-    if (BATCH) v |= addv[i];
-    else if (p.add) v |= load_add16<Op::kPrec>(p, gr, gc);
-    if (p.add_identity) v = with_diag(v, gr, gc, p.n_valid);
-    cnt += popc16(v);
-    store_bool16<Op::kPrec>(outb + ((int64_t)gr * p.ld + gc) * K::NIB / 2, v);
-    if (p.outT) *(u32x4*)(et + r * K::EST + cs * 16) = p.outT_ident ? with_diag(v, gr, gc, p.n_valid) : v;
-  }
-
+  u32x4 v = *(const u32x4*)(et + er * K::EST + ec) | addv;
+  if (p.add_identity) v = with_diag(v, row0 + er, col0 + ec, p.n_valid);
+  int cnt = popc16(v);
+  *(u32x4*)((uint8_t*)p.out + (int64_t)(row0 + er) * p.ld + col0 + ec) = v;
   if (p.outT) {
+    *(u32x4*)(et + er * K::EST + ec) = p.outT_ident ? with_diag(v, row0 + er, col0 + ec, p.n_valid) : v;
     __syncthreads();
-    constexpr int SEG_PER_COL = BM / 16;
-    constexpr int TSEGS = BN * SEG_PER_COL / K::NT;
-    uint8_t* outt = (uint8_t*)p.outT;
-#pragma unroll 2
-    for (int i = 0; i < TSEGS; ++i) {
-      // consecutive lanes take consecutive columns of the same 16 rows, so
-      // each byte read of a wave touches one 64-byte run of one LDS row
-      const int q = tid + i * K::NT;
-      const int c = q % BN, rs = q / BN;
-      u32x4 v;
+    // consecutive lanes take consecutive columns of the same 16 rows, so each
+    // byte read of a wave touches one 64-byte run of one LDS row
+    const int c = tid % K::B, rs = tid / K::B;
+    u32x4 t;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint8_t* e = et + (rs * 16 + 4 * w) * K::EST + c;
-        v[w] = (unsigned)e[0] | ((unsigned)e[K::EST] << 8) | ((unsigned)e[2 * K::EST] << 16) |
-               ((unsigned)e[3 * K::EST] << 24);
-      }
-      store_bool16<Op::kPrec>(outt + ((int64_t)(col0 + c) * p.ld + row0 + rs * 16) * K::NIB / 2, v);
+    for (int w = 0; w < 4; ++w) {
+      const uint8_t* e = et + (rs * 16 + 4 * w) * K::EST + c;
+      t[w] = (unsigned)e[0] | ((unsigned)e[K::EST] << 8) | ((unsigned)e[2 * K::EST] << 16) |
+             ((unsigned)e[3 * K::EST] << 24);
     }
+    *(u32x4*)((uint8_t*)p.outT + (int64_t)(col0 + c) * p.ld + row0 + rs * 16) = t;
   }
 
   if (cnt_dst) {
-    __shared__ int red[K::NWAVES];
+    __shared__ int red[4];
     cnt = wave_sum(cnt);
     if (lane == 0) red[wave] = cnt;
     __syncthreads();
     if (tid == 0) {
-      unsigned long long t = 0;
-#pragma unroll
-      for (int w = 0; w < K::NWAVES; ++w) t += (unsigned long long)red[w];
+      const unsigned long long t = (unsigned long long)(red[0] + red[1] + red[2] + red[3]);
       // count 2: a tile of a symmetric product stands for its mirror image too
       if (t) atomicAdd(cnt_dst, p.count > 1 ? t * (unsigned long long)p.count : t);
     }
@@ -1016,7 +931,7 @@ static hipError_t launch_fix_small_op(const FixSmallParams& p, hipStream_t s) {
 // finished requests (their descriptors then hold no tiles), or null.
 __global__ void __launch_bounds__(256)
 k_group_step(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, const int* __restrict__ dyn_total) {
-  constexpr int T = 64;
+  constexpr int T = Tile64::B;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   if (dyn_total) total_tiles = min(total_tiles, *dyn_total);
   for (int item = xcd_logical(blockIdx.x, gridDim.x); item < total_tiles; item += gridDim.x) {
@@ -1060,7 +975,7 @@ k_group_step(const GroupDesc* __restrict__ desc, int nreq, int total_tiles, cons
     __syncthreads();  // the previous tile's epilogue is done with LDS
     int tid;  // re-derived per tile: nothing computed from it stays live across tiles
     asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
-    nt_tile<T, T, T / 2, T / 2, 64, OpI8, 2, 1>(p, tm * T, tn * T, g.cnt, smem, tid);
+    nt_tile64(p, tm * T, tn * T, g.cnt, smem, tid);
   }
 }
 
@@ -1535,7 +1450,7 @@ __device__ __forceinline__ bool nt_dma_tile(const NTParams& p, int tm, int tn, u
     // ---- the 0/1 tile through LDS byte by byte
     constexpr int SEG_PER_ROW = BN / 16;
     constexpr int SEGS = BM * SEG_PER_ROW / K::NT;
-    u32x4 addv[SEGS];  // addend segments, requested together as in nt_tile
+    u32x4 addv[SEGS];  // addend segments, requested together (one memory round trip)
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int q = tid + i * K::NT;
@@ -1925,10 +1840,9 @@ hipError_t launch_group_step(int tile, const GroupDesc* desc, int nreq, int tota
   if (nreq <= 0 || total_tiles <= 0) return hipSuccess;
   if (nreq > kMaxGroupRequests) return hipErrorInvalidValue;
   if (tile == 64) {
-    typedef NTKernel<64, 64, 32, 32, 64, OpI8, 2, 1> K;
     const int slots = 4 * g_cus;
-    hipLaunchKernelGGL(k_group_step, dim3(total_tiles < slots ? total_tiles : slots), dim3(K::NT), K::LDS_BYTES, s,
-                       desc, nreq, total_tiles, dyn_total);
+    hipLaunchKernelGGL(k_group_step, dim3(total_tiles < slots ? total_tiles : slots), dim3(Tile64::NT),
+                       Tile64::LDS_BYTES, s, desc, nreq, total_tiles, dyn_total);
     return hipGetLastError();
   }
   if (tile == 128) return launch_group_dma<128>(desc, nreq, total_tiles, s, dyn_total);

@@ -305,7 +305,6 @@ struct LayerLists {
   DenseStart dense;  // the plain closure's (otherwise nothing is written for a row too long)
 };
 constexpr int kLayerWords = 2;
-inline size_t layer_lists_bytes(int64_t n) { return (size_t)(kListMax + 1) * n * 2; }
 hipError_t launch_layer_lists(const LayerLists& p, const int8_t* P, hipStream_t s);
 // The plain closure R = A + A R of a caller's relation the same way (idx, len,
 // words, status_out, n and dense of p are used).
