@@ -60,6 +60,9 @@ def main() -> int:
                          "(profiles then see only the timed workload's launches)")
     ap.add_argument("--serve-requests", type=int, default=10000,
                     help="requests in the Poisson serving stream (0 skips serving)")
+    ap.add_argument("--details", metavar="FILE",
+                    help="write the whole result to FILE as JSON (the printed line leaves tables out that would "
+                         "make it too long)")
     ap.add_argument("--trace-summary", metavar="DB",
                     help="summarise a rocprofv3 --kernel-trace results database and exit")
     ap.add_argument("--eps-only", action="store_true",
@@ -268,8 +271,48 @@ def main() -> int:
         "serving": serving,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(line), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(line, f, indent=1)
+    print(result_line(line), flush=True)
     return 0
+
+
+# What the result line leaves out, in this order, until it has LINE_BYTES or
+# less (--details writes everything): a longer line is cut by whatever keeps
+# only the end of the output, and then cannot be read at all.
+LINE_BYTES = 7000
+LEFT_OUT = [("extras", "autotune"), ("cpu_baseline", "per_graph"), ("serving", "tiles"), ("extras", "programs"),
+            ("extras", "tc_square_variants"), ("extras", "paper_workloads"), ("extras", "tc_plain_fp32"),
+            ("extras", "eps_solve_fp64"), ("per_graph",), ("serving",), ("cpu_baseline",), ("extras",)]
+
+
+def columnar(v):
+    """Lists of dicts with the same keys as one list of names and a list of rows."""
+    if isinstance(v, dict):
+        return {k: columnar(x) for k, x in v.items()}
+    if isinstance(v, list):
+        if len(v) > 1 and all(isinstance(x, dict) and list(x) == list(v[0]) for x in v):
+            return {"columns": list(v[0]), "rows": [[columnar(x) for x in r.values()] for r in v]}
+        return [columnar(x) for x in v]
+    return v
+
+
+def result_line(line: dict) -> str:
+    """The result as one line of JSON of at most LINE_BYTES."""
+    out = columnar(line)
+    gone = []
+    for path in LEFT_OUT:
+        if len(json.dumps(out)) <= LINE_BYTES:
+            break
+        d = out
+        for k in path[:-1]:
+            d = d.get(k) or {}
+        if path[-1] in d:
+            del d[path[-1]]
+            gone.append(".".join(path))
+            out["left_out"] = gone
+    return json.dumps(out)
 
 
 def run_extras(dl, ctx, graphs, outs, np, torch):
