@@ -152,8 +152,8 @@ int dl_tc_noalloc(int64_t n, const uint8_t* A, int64_t lda, uint8_t* R, int64_t 
  * large tiles (n rounded up to 256 at least 4096 by the size rule, or tile
  * configuration 0) only its upper-triangle tiles are computed and then
  * mirrored, and the context's workspace also holds that product's partial
- * tiles (3.4 MB at n = 4096).  With DL_I8, 512 <= n <= 8192, at most 32
- * entries in every row of P, no configuration set for that size
+ * tiles (3.4 MB at n = 4096).  With DL_I8, n <= 8192, at most 32 entries in
+ * every row of P, fewer than 4096 steps, no configuration set for that size
  * (dl_tune_set) and timing off, both products are taken by lists of P's
  * entries on bits instead (the same iterates and sizes, in the same
  * workspace). */
@@ -459,7 +459,8 @@ int dl_batch_info(dl_batch* batch, int32_t* active, int32_t* used_slots, size_t*
  *                      series; fp64 results are thresholded at > 0.
  * Both give the least (perfect) model, the epsilon forms up to fp64
  * underflow of long derivations.  A program handle is used by one thread at
- * a time; its results stay on the device until the next run or destroy. */
+ * a time; its results, of the n of that run, stay on the device until the next
+ * run or destroy, also when a relation is bound at another n in between. */
 typedef struct dl_program dl_program;
 typedef enum { DL_EVAL_ITERATION = 0, DL_EVAL_MATRIX = 1 } dl_eval_method;
 typedef enum {
@@ -485,16 +486,17 @@ int dl_program_bind(dl_program* prog, const char* name, int64_t n, const uint8_t
  * (n rounded up to 256)^2 matrices per predicate plus per-layer temporaries
  * and the fp64 workspace of the epsilon forms.  A context without a budget
  * keeps up to 1 GiB of matrices that its programs gave back for their next
- * runs; they are freed when the context and its programs are destroyed, or
- * when an allocation of the context would fail. */
+ * runs; they are freed when the context, its programs and its batches are
+ * destroyed, or when an allocation of one of them would fail. */
 int dl_program_run(dl_program* prog, int method, void* stream);
 /* Layer `layer` of the last run: its heads (predicate indices, up to cap),
  * form (dl_layer_form), the method used and its count: iterations of the
  * series (including the confirming one), doublings, or 0 for a linear solve. */
 int dl_program_layer(dl_program* prog, int32_t layer, int32_t* n_heads, int32_t* heads, int32_t cap,
                      int32_t* form, int32_t* method_used, int32_t* iters);
-/* Writes the model of a defined predicate into device uint8 [n x ldo] and
- * its number of true entries into *ones (may be NULL). */
+/* Writes the model of a defined predicate of the last run, of n constants,
+ * into device uint8 [n x ldo] (ldo >= that run's n) and its number of true
+ * entries into *ones (may be NULL). */
 int dl_program_fetch(dl_program* prog, const char* name, uint8_t* out, int64_t ldo, int64_t* ones,
                      void* stream);
 

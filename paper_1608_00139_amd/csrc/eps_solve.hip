@@ -57,7 +57,8 @@ constexpr int NB = 128;  // block size of the elimination
 // overlap D.
 //
 // The elimination steps below change single tile rows and columns of a
-// product (ranges in multiples of 128; -1 = none):
+// product (prow, pcol and np multiples of the launched tile's BM and BN; -1 =
+// none):
 //  - pivot rows prow .. prow + np - 1: D takes rows of B (row prow + i = B's
 //    row i) instead of a product;
 //  - pivot columns pcol .. pcol + np - 1: with pmode 1 C counts as zero there,
@@ -542,8 +543,6 @@ static hipError_t dgemm_attrs() {
 //    else 32 x 64 (1024: 46.1 against 16.0; M = N = 512, K = 128: 7.6 against
 //    22.5 us).  A 64 x 64 tile moves 16 KB into LDS for 1024 clocks of
 //    products, so small tiles stay bound by the products.
-// D aliasing B needs one row of tiles (128 rows, each workgroup reads its
-// whole B panel before it writes): 128 x 64.
 //  - with room for partial tiles (g.part), a last pass of 257 to 460 of the 512
 //    slots is split (SPLIT).  M = N = K = 2304, 2560, 2688: 402, 540, 612 us;
 //    whole 128 x 128 tiles 573, 633, 668, 64 x 64 tiles 463, 594, 633.  From
@@ -656,9 +655,9 @@ __device__ inline void inv16_steps(double (&a)[4], int r, int g) {
 
 // NT = 8: blocks of 128, eight column waves and the inverting wave.  NT = 4:
 // blocks of 64 for a panel inverse that runs beside the trailing update: four
-// waves of at most 80 registers and 20 KB of LDS, which fit on a compute unit
-// beside two update workgroups (2 x 216 registers a SIMD lane, 2 x 64 KB); the
-// wave that owns the next pivot block inverts it itself.
+// waves of 72 registers and 24 KB of LDS, which fit on a compute unit beside two
+// update workgroups (2 x 184 registers a SIMD lane, 2 x 64 KB); the wave that
+// owns the next pivot block inverts it itself.
 template <int NT>
 __global__ void __launch_bounds__(NT == 8 ? 576 : 256, NT == 8 ? 1 : 6)
 k_block_inverse(const double* W, int64_t ld, double* Dinv, int64_t ldd) {

@@ -42,9 +42,9 @@ typedef unsigned long long u64;
 
 // Lists of the rows of P: entry k of row j at idx[k n + j], len[j] entries,
 // kListMax + 1 for a row with more.  A wave a row.  Where one of the first
-// rows is too long the host hears of it at once, so that a dense P's products
-// start 10 us earlier; of any other row it hears from k_sg_lists.  (One word
-// that all rows report to took 140 us of stores to one address.)  With ring, the
+// rows is too long the host hears of it at once, and queues the products while
+// their first operands are written; of any other row it hears from the next
+// launch.  (One word that all rows report to took 140 us of stores to one address.)  With ring, the
 // words of the product series start over as well (see DenseStart).
 __global__ void __launch_bounds__(256) k_row_lists(const uint8_t* P, int64_t ldp, int n, unsigned short* idx,
                                                    unsigned short* len, unsigned* status_out,
