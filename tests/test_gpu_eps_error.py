@@ -2,7 +2,7 @@
 
 Every term of the elimination has one sign, so its errors are those of its
 sums.  The reference is the equation X = eps (A + A X) itself, iterated in
-80-bit arithmetic from the computed X until its own error (a factor below 0.7 an
+80-bit arithmetic from the computed X until its own error (a factor below 0.8 an
 iteration) is under that arithmetic's rounding.  The bounds are the errors, by
 the same measure and on the same inputs, of the elimination on the augmented
 matrix [I - eps A | eps A] with divisions and accumulators that start from the
@@ -38,7 +38,7 @@ def _error(a, eps, x):
     z = np.zeros((n + 1, n), dtype=np.longdouble)
     z[:n] = x
     b = (a != 0).astype(np.longdouble)
-    for _ in range(60):
+    for _ in range(40):
         s = b.copy()
         for k in range(idx.shape[1]):
             s += z[idx[:, k]]
