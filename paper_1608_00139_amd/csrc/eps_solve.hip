@@ -589,7 +589,7 @@ static hipError_t dgemm(const GemmArgs& g, hipStream_t s) {
 // while the others finish step k, so the serial chain (16 pivots in a block)
 // runs beside the products.
 // Bound by one compute unit's fp64 matrix cores: 2 NB^3 operations at 128 per
-// clock are 13.7 us.  Measured per 128 x 128 block (MI355X): 29 us, against
+// clock are 13.7 us.  Measured per 128 x 128 block (MI355X): 31 us, against
 // 175 us of the version before it, which took 64 steps of 2 x 2 pivots, each a
 // barrier, two dependent divisions and a rank-2 update on the vector units.
 // Signs: the block is a strictly diagonally dominant M-matrix, so every
